@@ -24,24 +24,34 @@ struct FusedPrune {
     int32_t* kept_idx;
     uint32_t* sample_counters;  // one arrival counter per sample (kept at zero between calls)
 };
-template <bool COHERENT>
-__device__ __forceinline__ void finish_sample(const float* sal_b, const FusedPrune& f, int b,
-                                              uint32_t* keys);
+template <typename Load>
+__device__ __forceinline__ void finish_sample(Load load, float* sal_b, const FusedPrune& f, int b, uint32_t* keys);
 
 constexpr int SAL_THREADS = 256;
-constexpr int SEL_THREADS = 256;    // selection (also the tail of the fused kernel)
 constexpr int SEL_MAX_N = 16384;    // largest segment the selection stages in LDS
-constexpr int SEL_SMALL_N = 64;     // up to here a direct rank count beats the threshold search (measured)
+constexpr int SEL_FOUR_WAVES = 2048;  // longest segment that four waves select; beyond it sixteen
 constexpr int SAL_LPR = 16;                        // lanes per row-group
+// Attention tensors above this are read past the caches.  344 MB (B = 16, 32 heads x 64 queries x 2624
+// columns): 57 us against 87 us with plain loads, which also push the layer output out that the gather
+// reads next.  Below the Infinity Cache's 256 MB the next reader (the per-patch indicators) finds the
+// tensor there: 8.9 MB read non-temporally made that pair 1.6 us slower.
+constexpr size_t SAL_STREAM_BYTES = size_t(256) << 20;
+constexpr int FIN_U = 8;            // columns a thread takes at a time when a sample is finished
+constexpr long SOLO_MAX = 16384;    // most attention values of a sample that one workgroup sums (64 KiB)
+constexpr int SOLO_MAX_ROWS = 128;  // ... most rows (eight a thread)
+constexpr int SOLO_MAX_COLS = 2048; // ... and most columns (their sums of four waves sit in LDS)
 constexpr int SAL_GROUPS = SAL_THREADS / SAL_LPR;  // 16 row-groups per block
 
+typedef float f32v4_t __attribute__((ext_vector_type(4)));
+
+// read_once: non-temporal loads, for a tensor that is larger than the caches (SAL_STREAM_BYTES).
 // FUSED: the workgroup that completes the last column chunk of a sample goes on to split the
 // budget and select that sample's tokens (same arithmetic as budget_kernel / select_kernel).
 template <int VEC, bool FUSED>
 __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
     const float* __restrict__ attn, int R, int S, int n_vis, int rows_per_split, int n_split,
     float inv_rows, float* __restrict__ sal, float* __restrict__ partial,
-    uint32_t* __restrict__ counters, FusedPrune fused) {
+    uint32_t* __restrict__ counters, int read_once, FusedPrune fused) {
     extern __shared__ uint32_t dyn_lds[];  // selection keys (fused variant only)
     constexpr int CW = SAL_LPR * VEC;  // columns per chunk
     const int chunk = blockIdx.x, split = blockIdx.y, b = blockIdx.z;
@@ -59,32 +69,29 @@ __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
 
     if (VEC == 4) {
         if (col0 + 3 < n_vis) {
-            int r = r_begin + group;
-            // four, then two independent loads in flight per lane
-            for (; r + 3 * SAL_GROUPS < r_end; r += 4 * SAL_GROUPS) {
-                const float4 a = *reinterpret_cast<const float4*>(base + (size_t)r * S + col0);
-                const float4 c =
-                    *reinterpret_cast<const float4*>(base + (size_t)(r + SAL_GROUPS) * S + col0);
-                const float4 d =
-                    *reinterpret_cast<const float4*>(base + (size_t)(r + 2 * SAL_GROUPS) * S + col0);
-                const float4 e =
-                    *reinterpret_cast<const float4*>(base + (size_t)(r + 3 * SAL_GROUPS) * S + col0);
-                acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
-                acc[0] += c.x; acc[1] += c.y; acc[2] += c.z; acc[3] += c.w;
-                acc[0] += d.x; acc[1] += d.y; acc[2] += d.z; acc[3] += d.w;
-                acc[0] += e.x; acc[1] += e.y; acc[2] += e.z; acc[3] += e.w;
-            }
-            for (; r + SAL_GROUPS < r_end; r += 2 * SAL_GROUPS) {
-                const float4 a = *reinterpret_cast<const float4*>(base + (size_t)r * S + col0);
-                const float4 c =
-                    *reinterpret_cast<const float4*>(base + (size_t)(r + SAL_GROUPS) * S + col0);
-                acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
-                acc[0] += c.x; acc[1] += c.y; acc[2] += c.z; acc[3] += c.w;
-            }
-            for (; r < r_end; r += SAL_GROUPS) {
-                const float4 a = *reinterpret_cast<const float4*>(base + (size_t)r * S + col0);
-                acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
-            }
+            // eight, then one load in flight per lane
+            auto add_rows = [&](auto load) __attribute__((always_inline)) {
+                constexpr int U = 8;
+                int r = r_begin + group;
+                for (; r + (U - 1) * SAL_GROUPS < r_end; r += U * SAL_GROUPS) {
+                    f32v4_t t[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) t[u] = load(base + (size_t)(r + u * SAL_GROUPS) * S + col0);
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) acc[v] += t[u][v];
+                }
+                for (; r < r_end; r += SAL_GROUPS) {
+                    const f32v4_t t = load(base + (size_t)r * S + col0);
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) acc[v] += t[v];
+                }
+            };
+            if (read_once)
+                add_rows([](const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const f32v4_t*>(p)); });
+            else
+                add_rows([](const float* p) { return *reinterpret_cast<const f32v4_t*>(p); });
         } else {
             for (int r = r_begin + group; r < r_end; r += SAL_GROUPS)
 #pragma unroll
@@ -171,16 +178,92 @@ __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
     }
     __syncthreads();
     if (!is_last) return;
-    finish_sample<true>(sal + (size_t)b * n_vis, fused, b, dyn_lds);
+    // (all loads of a batch in flight together: one by one, each waited a round trip to the level
+    // of memory that all XCDs share)
+    const float* sal_b = sal + (size_t)b * n_vis;
+    finish_sample([&](const int (&col)[FIN_U], float (&v)[FIN_U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < FIN_U; ++u)
+            v[u] = __hip_atomic_load(&sal_b[col[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }, nullptr, fused, b, dyn_lds);
+}
+
+// The fused step of a sample whose rows are few: one workgroup sums all its columns (same order of
+// additions as an unsplit salience_kernel) and goes straight on to budget and selection.  With
+// several workgroups a sample, the store, arrival and load that join them (a memory round trip
+// each) cost more than one compute unit needs to read 64 KiB: 10.4 -> 6.8 us
+// for 64 rows x 128 columns.
+template <int VEC>
+__global__ __launch_bounds__(SAL_THREADS) void prune_solo_kernel(const float* __restrict__ attn, int R, int S,
+                                                                 int n_vis, float inv_rows,
+                                                                 float* __restrict__ sal, FusedPrune fused) {
+    extern __shared__ uint32_t dyn_lds[];   // keys [n_vis], then the four waves' sums [4][chunks * CW]
+    constexpr int CW = SAL_LPR * VEC, CU = 4;
+    const int b = blockIdx.x, tid = threadIdx.x, lane16 = tid % SAL_LPR, group = tid / SAL_LPR;
+    const int wave = tid / 64, lane = tid % 64;
+    const int chunks = (n_vis + CW - 1) / CW;
+    float* part = reinterpret_cast<float*>(dyn_lds + n_vis);
+    const float* base = attn + (size_t)b * R * S;
+    for (int c0 = 0; c0 < chunks; c0 += CU) {
+        float acc[CU][VEC];
+#pragma unroll
+        for (int u = 0; u < CU; ++u)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[u][v] = 0.f;
+#pragma unroll 4
+        for (int r = group; r < R; r += SAL_GROUPS)
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                const int col0 = (c0 + u) * CW + lane16 * VEC;
+                const float* p = base + (size_t)r * S + col0;
+                if (VEC == 4 && col0 + 3 < n_vis) {
+                    const float4 a = *reinterpret_cast<const float4*>(p);
+                    acc[u][0] += a.x; acc[u][1 % VEC] += a.y; acc[u][2 % VEC] += a.z; acc[u][3 % VEC] += a.w;
+                } else {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v)
+                        if (col0 + v < n_vis) acc[u][v] += p[v];
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < CU; ++u)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                acc[u][v] += __shfl_xor(acc[u][v], 16);
+                acc[u][v] += __shfl_xor(acc[u][v], 32);
+            }
+        if (lane < SAL_LPR)
+#pragma unroll
+            for (int u = 0; u < CU; ++u)
+                if (c0 + u < chunks)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v)
+                        part[(wave * chunks + c0 + u) * CW + lane * VEC + v] = acc[u][v];
+    }
+    __syncthreads();
+    finish_sample([&](const int (&col)[FIN_U], float (&v)[FIN_U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < FIN_U; ++u) {
+            v[u] = 0.f;
+#pragma unroll
+            for (int w = 0; w < SAL_THREADS / 64; ++w) v[u] += part[w * chunks * CW + col[u]];
+            v[u] *= inv_rows;
+        }
+    }, sal + (size_t)b * n_vis, fused, b, dyn_lds);
+}
+
+// few enough rows that one workgroup takes a whole sample in the fused step
+static bool salience_solo(int R, int n_vis) {
+    return (long)R * n_vis <= SOLO_MAX && R <= SOLO_MAX_ROWS && n_vis <= SOLO_MAX_COLS;
 }
 
 static void salience_shape(int B, int R, int n_vis, int vec, int* chunks, int* n_split,
                            int* rows_per_split) {
     const int cw = SAL_LPR * vec;
     *chunks = (n_vis + cw - 1) / cw;
-    // aim for ~2048 blocks, at least 2 passes of the 16 row-groups each
+    // aim for ~2048 blocks, at least 2 passes of the 16 row-groups each; few rows are not split at all
     long blocks = (long)B * *chunks;
-    int split = (int)((2048 + blocks - 1) / blocks);
+    int split = salience_solo(R, n_vis) ? 1 : (int)((2048 + blocks - 1) / blocks);
     const int max_split = (R + 2 * SAL_GROUPS - 1) / (2 * SAL_GROUPS);
     if (split > max_split) split = max_split;
     if (split < 1) split = 1;
@@ -207,12 +290,25 @@ static int launch_salience_any(const float* attn, int B, int H, int Nq, int S, i
     if ((long)B * chunks + B > kCounterWords / 2) return MVLA_EUNSUPPORTED;
     dim3 grid(chunks, n_split, B);
     const float inv_rows = 1.0f / (float)(mean_rows > 0 ? mean_rows : R);
+    const int read_once = (size_t)B * R * S * 4 > SAL_STREAM_BYTES;
     FusedPrune f{};
     size_t lds = 0;
     if (fused) {
         f = *fused;
         f.sample_counters = counters + (size_t)B * chunks;
         lds = (size_t)max(f.n2 + f.n3, 1) * 4;   // selection keys of both segments
+        if (salience_solo(R, n_vis)) {           // (at most 8 KiB of keys and 33 KiB of sums)
+            const int cw = SAL_LPR * (vec4 ? 4 : 1);
+            lds += (size_t)(SAL_THREADS / 64) * chunks * cw * 4;
+            if (vec4)
+                hipLaunchKernelGGL(prune_solo_kernel<4>, dim3(B), dim3(SAL_THREADS), lds, st, attn, R, S, n_vis,
+                                   inv_rows, sal, f);
+            else
+                hipLaunchKernelGGL(prune_solo_kernel<1>, dim3(B), dim3(SAL_THREADS), lds, st, attn, R, S, n_vis,
+                                   inv_rows, sal, f);
+            MVLA_HIP_CHECK(hipGetLastError());
+            return MVLA_OK;
+        }
     }
     // (the fused variants keep the keys of both segments in LDS: up to 128 KiB, above the default
     // limit of a kernel, which is raised once per device)
@@ -231,7 +327,7 @@ static int launch_salience_any(const float* attn, int B, int H, int Nq, int S, i
             }                                                                                   \
         }                                                                                       \
         hipLaunchKernelGGL(kern, grid, dim3(SAL_THREADS), lds, st, attn, R, S, n_vis, rps,      \
-                           n_split, inv_rows, sal, partial, counters, f);                       \
+                           n_split, inv_rows, sal, partial, counters, read_once, f);                       \
     } while (0)
     if (vec4) {
         if (fused) MVLA_SAL(4, true); else MVLA_SAL(4, false);
@@ -326,15 +422,24 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-__device__ inline double block_sum_f64(double v, double* sh) {
-    // fixed-shape tree: wave shuffle then 4 partials in LDS
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// two sums over the workgroup, each a fixed-shape tree: wave shuffles, then the waves' partials in LDS
+__device__ inline void block_sum2_f64(double& a, double& b, double* sh /*LDS [2 * waves]*/) {
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+    }
+    constexpr int NW = BUD_THREADS / 64;
+    if ((threadIdx.x & 63) == 0) {
+        sh[threadIdx.x >> 6] = a;
+        sh[NW + (threadIdx.x >> 6)] = b;
+    }
     lds_barrier();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    lds_barrier();
-    double t = 0.0;
-    for (int w = 0; w < BUD_THREADS / 64; ++w) t += sh[w];
-    return t;
+    a = b = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        a += sh[w];
+        b += sh[NW + w];
+    }
 }
 
 __device__ inline void budget_split(double a2, double a3, int n2, int n3, int k_total, int min2,
@@ -353,14 +458,15 @@ __global__ __launch_bounds__(BUD_THREADS) void budget_kernel(const float* __rest
                                                              int n3, int k_total, int min2,
                                                              int min3, int32_t* __restrict__ k2k3,
                                                              float* __restrict__ mass) {
-    __shared__ double sh[BUD_THREADS / 64];
+    __shared__ double sh[2 * (BUD_THREADS / 64)];
     const int b = blockIdx.x;
     const float* s = sal + (size_t)b * (n2 + n3);
     double a2 = 0.0, a3 = 0.0;
+#pragma unroll 8
     for (int i = threadIdx.x; i < n2; i += BUD_THREADS) a2 += (double)s[i];
+#pragma unroll 8
     for (int i = threadIdx.x; i < n3; i += BUD_THREADS) a3 += (double)s[n2 + i];
-    a2 = block_sum_f64(a2, sh);
-    a3 = block_sum_f64(a3, sh);
+    block_sum2_f64(a2, a3, sh);
     if (threadIdx.x == 0) {
         int k2;
         double m2;
@@ -383,12 +489,25 @@ int launch_budget(const float* sal, int B, int n2, int n3, int k_total, int min2
 }
 
 // ---------------------------------------------------------------------------
-// Per-modality top-k.  One workgroup per (sample, segment); the segment's
-// scores sit in LDS as order-preserving 32-bit keys.  Four 8-bit radix passes
-// find the K-th largest key T exactly; tokens with key > T are kept, and of
-// those with key == T the lowest-indexed (K - #greater).  Each thread owns a
-// contiguous index range, so a block prefix sum of its keep counts gives
-// output slots that are already in ascending index order -- no sort.
+// Per-modality top-k.  The scores sit in LDS as order-preserving 32-bit keys; a
+// group of waves works on one segment (one workgroup per segment in
+// select_kernel, half a workgroup each in the tail of the fused kernel, both
+// segments in step).  Exact search for the K-th largest key T: a 1024-bin
+// histogram over [smallest, largest key] -- the keys of a segment share their
+// top bits, so bins over the whole 32-bit range put nearly all of them on a few
+// counters -- narrows the range to the bin that holds T; as soon as at most 64
+// keys are left in it, one wave ranks those directly (at once for short
+// segments), else the bin is split again (four times at most).  Tokens with
+// key > T are kept, and of those with key == T the lowest-indexed ones.  Each
+// wave owns a contiguous run of the indices and places its tokens 64 at a time
+// by ballots behind the counts of the waves before it, so the output is in
+// ascending index order without a sort.
+//
+// Bound by the chain of dependent LDS accesses and barriers, not by bytes.
+// Against four 8-bit radix passes over the whole key range and one segment
+// after the other: 16384 + 16384 tokens
+// (B = 3) 33 -> 15.5 us with the budget call, 768 + 1024 (B = 8) 10.8 -> 9.4 us; fused, two segments of
+// 64 tokens 10.4 -> 6.8 us.
 // ---------------------------------------------------------------------------
 
 __device__ inline uint32_t sal_key(float x) {
@@ -397,193 +516,307 @@ __device__ inline uint32_t sal_key(float x) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// inclusive prefix sum over SEL_THREADS values (one per thread), result per thread
-__device__ inline uint32_t block_scan_incl(uint32_t v, uint32_t* wsum) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(v, o);
-        if (lane >= o) v += t;
-    }
-    lds_barrier();
-    if (lane == 63) wsum[wave] = v;
-    lds_barrier();
-    uint32_t add = 0;
-    for (int w = 0; w < wave; ++w) add += wsum[w];
-    return v + add;
+// one step of a wave-wide combination: the value CTRL fetches for this lane, or `none`
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_get(uint32_t v, uint32_t none) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xf, false);
+}
+// inclusive prefix sum over the 64 lanes: row shifts by 1, 2, 4, 8, then row totals handed on
+__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v) {
+    v += dpp_get<0x111, 0xf>(v, 0u);
+    v += dpp_get<0x112, 0xf>(v, 0u);
+    v += dpp_get<0x114, 0xf>(v, 0u);
+    v += dpp_get<0x118, 0xf>(v, 0u);
+    v += dpp_get<0x142, 0xa>(v, 0u);
+    v += dpp_get<0x143, 0xc>(v, 0u);
+    return v;
+}
+// maximum over the 64 lanes, in every lane
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    v = max(v, dpp_get<0x111, 0xf>(v, 0u));
+    v = max(v, dpp_get<0x112, 0xf>(v, 0u));
+    v = max(v, dpp_get<0x114, 0xf>(v, 0u));
+    v = max(v, dpp_get<0x118, 0xf>(v, 0u));
+    v = max(v, dpp_get<0x142, 0xa>(v, 0u));
+    v = max(v, dpp_get<0x143, 0xc>(v, 0u));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Short segments (at most one token per thread; used up to SEL_SMALL_N): thread i ranks key i
-// directly -- the keys above it plus the equal keys at a lower index -- and keeps it when that
-// rank is below k.  No threshold search: n comparisons per thread instead of four histogram
-// passes with their scans.  Every lane reads the same key in a step (an LDS broadcast).
-// Threads are in index order, so the keep flags' prefix count is the output slot.
-__device__ __forceinline__ void select_small(const uint32_t* keys /*LDS [n]*/, int n, int k, int idx_offset,
-                             int32_t* __restrict__ out, uint32_t* wsum /*LDS [4]*/) {
-    const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
-    lds_barrier();   // the keys are in LDS
-    const uint32_t my = i < n ? keys[i] : 0u;
-    // keys before i count when >= my, keys after i when > my, i.e. >= my + 1 (a key of all ones
-    // is a NaN, invalid input: its threshold wraps and the token is dropped)
-    const uint32_t my1 = my + 1u;
-    const int w0 = min(wave * 64, n), w1 = min(w0 + 64, n);   // the indices this wave's lanes hold
-    int rank = 0;
-    // 32 keys per batch, so that the LDS reads of a batch are in flight together (read one by
-    // one, their latency is all the loop does); batches below or above the wave's own indices
-    // compare against one threshold
-    constexpr int BATCH = 32;
-    for (int j = 0; j < n; j += BATCH) {
-        uint32_t v[BATCH];
-        const bool full = j + BATCH <= n;
-        if (full) {
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) v[u] = keys[j + u];
-        } else {
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) v[u] = j + u < n ? keys[j + u] : 0u;
-        }
-        if (j + BATCH <= w0) {
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) rank += v[u] >= my;
-        } else if (j >= w1 && full) {
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) rank += v[u] >= my1;
-        } else {
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u)
-                rank += (j + u < n) && v[u] >= (j + u < i ? my : my1);
-        }
-    }
-    const bool keep = i < n && rank < k;
-    const unsigned long long bal = __ballot(keep);
-    if (lane == 0) wsum[wave] = (uint32_t)__popcll(bal);
-    lds_barrier();
-    uint32_t slot = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-    for (int w = 0; w < wave; ++w) slot += wsum[w];
-    if (keep) out[slot] = idx_offset + i;
-}
+constexpr int SEL_BINS = 1024;
+constexpr int SEL_CAND = 64;    // keys that one wave ranks directly
 
-// Selection among n keys that already sit in LDS (written by this workgroup; the first barrier
-// below orders those writes before the reads).
-__device__ __forceinline__ void select_from_keys(const uint32_t* keys /*LDS [n]*/, int n, int k, int idx_offset,
-                                 int32_t* __restrict__ out, uint32_t* hist /*LDS [256]*/,
-                                 uint32_t* wsum /*LDS [4]*/, uint32_t* bcast /*LDS [4]*/) {
-    const int tid = threadIdx.x;
-    if (k <= 0) return;
+// LDS of NG groups of GW waves that select side by side
+template <int GW, int NG>
+struct SelShared {
+    uint32_t hist[NG][SEL_BINS];
+    uint32_t cand[NG][SEL_CAND];
+    uint32_t wave[NG][GW][2];
+    uint32_t found[NG][3];      // bin, rank within it, keys in it
+    uint32_t n_cand[NG];
+    uint32_t result[NG][2];     // T, how many keys equal to T are kept
+    uint32_t open;              // groups whose threshold is not found yet
+};
+
+// Every thread of the workgroup calls this with its group's segment (group-uniform arguments;
+// k <= 0 or n <= 0: nothing to do, but the barriers are taken part in; all_short: every group's n is
+// at most 64, the same for the whole workgroup).  The keys were written by
+// this workgroup; the first barrier orders those writes before the reads.
+template <int GW, int NG>
+__device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, int n, int k, int idx_offset,
+                                              int32_t* __restrict__ out, bool all_short,
+                                              SelShared<GW, NG>& sh) {
+    constexpr int GT = GW * 64, BPT = SEL_BINS / GT;
+    static_assert(SEL_BINS % GT == 0, "");
+    const int wave_id = (int)threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int g = wave_id / GW, gw = wave_id % GW, gt = (int)threadIdx.x - g * GT;
     if (k > n) k = n;
-    if (n <= SEL_SMALL_N) {
-        select_small(keys, n, k, idx_offset, out, wsum);
+    const bool work = k > 0;
+    uint32_t lo = 0u, hi = ~0u, remaining = (uint32_t)max(k, 0);   // T has this rank (from the top) in [lo, hi]
+    bool done = !work;                          // threshold known
+    bool rank_now = work && n <= SEL_CAND;      // few enough keys in [lo, hi] to rank directly
+
+    if (gt == 0) sh.n_cand[g] = 0u;
+    if (threadIdx.x == 0) sh.open = 0u;
+    lds_barrier();   // the keys are in LDS
+    if (all_short) {
+        // (no segment of the workgroup is longer than a wave: one wave each ranks and places its
+        // keys, nothing crosses waves)
+        if (work && gw == 0) {
+            const bool in = lane < n;
+            const uint32_t key = in ? keys[lane] : 0u;
+            uint32_t above = 0u, equal = 0u;
+            for (int j = 0; j < n; j += 8)       // (lanes beyond n hold 0, below every valid key)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)key, j + e);
+                    above += v > key;
+                    equal += v == key;
+                }
+            // keys above T all have a rank below k, T itself straddles it
+            const bool is_t = in && above < remaining && remaining <= above + equal;
+            const unsigned long long bt = __ballot(is_t);
+            const unsigned long long below = (1ull << lane) - 1ull;
+            const uint32_t eq_rank = (uint32_t)__popcll(bt & below), need = remaining - min(above, remaining);
+            const bool keep = in && (is_t ? eq_rank < need : above + equal < remaining);
+            const unsigned long long bk = __ballot(keep);
+            if (keep) out[__popcll(bk & below)] = idx_offset + lane;
+        }
         return;
     }
-    uint32_t prefix = 0, prefix_mask = 0;
-    uint32_t remaining = (uint32_t)k;  // rank (1-based, from the top) of T among matching keys
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0;
-        lds_barrier();
-        for (int i = tid; i < n; i += SEL_THREADS) {
+    if (work && !rank_now) {
+        uint32_t mx = 0u, mn_inv = 0u;          // (the minimum as the maximum of the complements)
+        for (int i = gt; i < n; i += GT) {
             const uint32_t key = keys[i];
-            if ((key & prefix_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+            mx = max(mx, key);
+            mn_inv = max(mn_inv, ~key);
+        }
+        mx = wave_max(mx);
+        mn_inv = wave_max(mn_inv);
+        if (lane == 0) {
+            sh.wave[g][gw][0] = mx;
+            sh.wave[g][gw][1] = mn_inv;
+        }
+    }
+    if (gt == 0 && work) atomicAdd(&sh.open, 1u);
+    lds_barrier();
+    if (work && !rank_now) {
+        uint32_t mx = 0u, mn_inv = 0u;
+#pragma unroll
+        for (int w = 0; w < GW; ++w) {
+            mx = max(mx, sh.wave[g][w][0]);
+            mn_inv = max(mn_inv, sh.wave[g][w][1]);
+        }
+        hi = mx;
+        lo = ~mn_inv;
+    }
+    // 32 key bits in steps of 10: a fifth round never has anything left to narrow
+    for (int pass = 0; pass < 5 && sh.open != 0u; ++pass) {
+        const bool narrow = !done && !rank_now;
+        const uint32_t range = hi - lo;
+        const int shift = range < SEL_BINS ? 0 : 22 - __clz((int)range);
+        if (narrow) {
+#pragma unroll
+            for (int j = 0; j < BPT; ++j) sh.hist[g][j * GT + gt] = 0u;
         }
         lds_barrier();
-        // suffix counts from the top digit down: thread t looks at digit 255-t
-        const uint32_t mine = hist[255 - tid];
-        const uint32_t incl = block_scan_incl(mine, wsum);
-        const uint32_t excl = incl - mine;
-        if (excl < remaining && remaining <= incl) {
-            bcast[0] = (uint32_t)(255 - tid);
-            bcast[1] = remaining - excl;
+        if (narrow) {
+#pragma unroll 4
+            for (int i = gt; i < n; i += GT) {
+                const uint32_t d = keys[i] - lo;
+                if (d <= range) atomicAdd(&sh.hist[g][d >> shift], 1u);
+            }
         }
         lds_barrier();
-        prefix |= bcast[0] << shift;
-        prefix_mask |= 255u << shift;
-        remaining = bcast[1];
+        // counts from the top bin down: thread t looks at bins SEL_BINS-1 - t*BPT ...
+        uint32_t c[BPT], mine = 0u, incl = 0u;
+        if (narrow) {
+#pragma unroll
+            for (int j = 0; j < BPT; ++j) {
+                c[j] = sh.hist[g][SEL_BINS - 1 - (gt * BPT + j)];
+                mine += c[j];
+            }
+            incl = wave_scan_incl(mine);
+            if (lane == 63) sh.wave[g][gw][0] = incl;
+        }
+        lds_barrier();
+        if (narrow) {
+            uint32_t before = incl - mine;
+#pragma unroll
+            for (int w = 0; w < GW - 1; ++w) before += w < gw ? sh.wave[g][w][0] : 0u;
+            if (before < remaining && remaining <= before + mine) {
+#pragma unroll
+                for (int j = 0; j < BPT; ++j) {
+                    if (before < remaining && remaining <= before + c[j]) {
+                        sh.found[g][0] = (uint32_t)(SEL_BINS - 1 - (gt * BPT + j));
+                        sh.found[g][1] = remaining - before;
+                        sh.found[g][2] = c[j];
+                    }
+                    before += c[j];
+                }
+            }
+        }
+        lds_barrier();
+        if (narrow) {
+            lo += sh.found[g][0] << shift;
+            remaining = sh.found[g][1];
+            if (shift == 0) {                    // the bin is one key value
+                hi = lo;
+                done = true;
+                if (gt == 0) {
+                    sh.result[g][0] = lo;
+                    sh.result[g][1] = remaining;
+                    atomicSub(&sh.open, 1u);
+                }
+            } else {
+                hi = lo + min(hi - lo, (1u << shift) - 1u);
+                rank_now = sh.found[g][2] <= SEL_CAND;
+            }
+        }
+        const bool rank_pass = !done && rank_now;
+        if (rank_pass) {
+            for (int i = gt; i < n; i += GT) {
+                const uint32_t key = keys[i];
+                if (key >= lo && key <= hi) sh.cand[g][atomicAdd(&sh.n_cand[g], 1u)] = key;
+            }
+        }
+        lds_barrier();
+        if (rank_pass) {
+            done = true;
+            if (gw == 0) {
+                // rank of this lane's key by value among the candidates; every lane whose key is T
+                // writes the same result
+                const int m = (int)sh.n_cand[g];
+                const uint32_t my = lane < m ? sh.cand[g][lane] : 0u;
+                uint32_t above = 0u, equal = 0u;
+                for (int j = 0; j < m; ++j) {
+                    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)my, j);
+                    above += v > my;
+                    equal += v == my;
+                }
+                if (lane < m && above < remaining && remaining <= above + equal) {
+                    sh.result[g][0] = my;
+                    sh.result[g][1] = remaining - above;
+                }
+                if (lane == 0) atomicSub(&sh.open, 1u);
+            }
+        }
         lds_barrier();
     }
-    const uint32_t T = prefix;
-    const uint32_t need_eq = remaining;  // how many keys equal to T are kept
-    const int per = (n + SEL_THREADS - 1) / SEL_THREADS;
-    const int i0 = min(n, tid * per), i1 = min(n, i0 + per);
-    uint32_t gt = 0, eq = 0;
-    for (int i = i0; i < i1; ++i) {
-        const uint32_t key = keys[i];
-        gt += key > T;
-        eq += key == T;
-    }
-    const uint32_t gt_before = block_scan_incl(gt, wsum) - gt;
-    const uint32_t eq_before = block_scan_incl(eq, wsum) - eq;
-    uint32_t eq_rank = eq_before;
-    uint32_t slot = gt_before + min(eq_before, need_eq);
-    for (int i = i0; i < i1; ++i) {
-        const uint32_t key = keys[i];
-        bool keep = key > T;
-        if (key == T) {
-            keep = eq_rank < need_eq;
-            ++eq_rank;
+    // placement: wave gw owns `per` consecutive indices
+    const uint32_t T = sh.result[g][0], need_eq = sh.result[g][1];
+    const int per = (n + GT - 1) / GT * 64, i0 = min(n, gw * per), i1 = min(n, i0 + per);
+    uint32_t n_gt = 0u, n_eq = 0u;
+    if (work) {
+        for (int i = i0; i < i1; i += 64) {
+            const bool in = i + lane < i1;
+            const uint32_t key = in ? keys[i + lane] : 0u;
+            n_gt += (uint32_t)__popcll(__ballot(in && key > T));
+            n_eq += (uint32_t)__popcll(__ballot(in && key == T));
         }
-        if (keep) out[slot++] = idx_offset + i;
+        if (lane == 0) {
+            sh.wave[g][gw][0] = n_gt;
+            sh.wave[g][gw][1] = n_eq;
+        }
+    }
+    lds_barrier();
+    if (work) {
+        uint32_t gt_before = 0u, eq_before = 0u;
+#pragma unroll
+        for (int w = 0; w < GW - 1; ++w) {
+            gt_before += w < gw ? sh.wave[g][w][0] : 0u;
+            eq_before += w < gw ? sh.wave[g][w][1] : 0u;
+        }
+        const unsigned long long below = (1ull << lane) - 1ull;
+        for (int i = i0; i < i1; i += 64) {
+            const bool in = i + lane < i1;
+            const uint32_t key = in ? keys[i + lane] : 0u;
+            const unsigned long long bg = __ballot(in && key > T), be = __ballot(in && key == T);
+            const uint32_t eq_rank = eq_before + (uint32_t)__popcll(be & below);
+            const bool keep = in && (key > T || (key == T && eq_rank < need_eq));
+            const uint32_t slot = gt_before + (uint32_t)__popcll(bg & below) + min(eq_rank, need_eq);
+            if (keep && slot < (uint32_t)k) out[slot] = idx_offset + i + lane;
+            gt_before += (uint32_t)__popcll(bg);
+            eq_before += (uint32_t)__popcll(be);
+        }
     }
 }
 
-__device__ __forceinline__ void select_segment(const float* __restrict__ seg, int n, int k, int idx_offset,
-                               int32_t* __restrict__ out, uint32_t* keys /*LDS [n]*/,
-                               uint32_t* hist, uint32_t* wsum, uint32_t* bcast) {
-    for (int i = threadIdx.x; i < n; i += SEL_THREADS) keys[i] = sal_key(seg[i]);
-    select_from_keys(keys, n, k, idx_offset, out, hist, wsum, bcast);
-}
-
-__global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __restrict__ sal,
-                                                             const int32_t* __restrict__ k2k3,
-                                                             int n2, int n3, int n_text,
-                                                             int k_total,
-                                                             int32_t* __restrict__ kept_idx) {
+// One workgroup of GW waves per (sample, segment).
+template <int GW>
+__global__ __launch_bounds__(GW * 64) void select_kernel(const float* __restrict__ sal,
+                                                         const int32_t* __restrict__ k2k3, int n2,
+                                                         int n3, int n_text, int k_total,
+                                                         int32_t* __restrict__ kept_idx) {
     extern __shared__ uint32_t keys[];
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t wsum[SEL_THREADS / 64];
-    __shared__ uint32_t bcast[4];
+    __shared__ SelShared<GW, 1> sh;
     const int b = blockIdx.y, which = blockIdx.x;
     int32_t* row = kept_idx + (size_t)b * (k_total + n_text);
     // clamp a malformed budget row into the feasible range
     int k2 = k2k3[2 * b];
     k2 = min(max(k2, max(0, k_total - n3)), min(n2, k_total));
-    const int k3 = k_total - k2;
-    if (which == 0) {
-        select_segment(sal + (size_t)b * (n2 + n3), n2, k2, 0, row, keys, hist, wsum, bcast);
-    } else if (which == 1) {
-        select_segment(sal + (size_t)b * (n2 + n3) + n2, n3, k3, n2, row + k2, keys, hist,
-                              wsum, bcast);
-    } else {
-        for (int i = threadIdx.x; i < n_text; i += SEL_THREADS) row[k_total + i] = n2 + n3 + i;
+    if (which == 2) {
+        for (int i = threadIdx.x; i < n_text; i += GW * 64) row[k_total + i] = n2 + n3 + i;
+        return;
     }
+    const float* seg = sal + (size_t)b * (n2 + n3) + (which ? n2 : 0);
+    const int n = which ? n3 : n2;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n; i += GW * 64) keys[i] = sal_key(seg[i]);
+    select_groups<GW, 1>(keys, n, which ? k_total - k2 : k2, which ? n2 : 0, which ? row + k2 : row,
+                         n <= SEL_CAND, sh);
 }
 
-// Budget and selection of one sample by one workgroup (tail of the fused kernel).  Same
-// summation order as budget_kernel, same selection as select_kernel.
-template <bool COHERENT>
-__device__ __forceinline__ void finish_sample(const float* sal_b, const FusedPrune& f, int b,
-                                              uint32_t* keys) {
-    __shared__ double sh_d[BUD_THREADS / 64];
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t wsum[SEL_THREADS / 64];
-    __shared__ uint32_t bcast[4];
+// Budget and selection of one sample by one workgroup (end of the fused kernels).  Same
+// summation order as budget_kernel, same selection as select_kernel; the two segments are
+// selected side by side, half the workgroup's waves each.  load: the salience of FIN_U columns;
+// sal_b: where it is still to be stored, or null.
+template <typename Load>
+__device__ __forceinline__ void finish_sample(Load load, float* sal_b, const FusedPrune& f, int b, uint32_t* keys) {
+    __shared__ double sh_d[2 * (BUD_THREADS / 64)];
+    __shared__ SelShared<SAL_THREADS / 128, 2> sh;
     __shared__ int sh_k2;
-    auto ld = [&](int i) {
-        return COHERENT ? __hip_atomic_load(&sal_b[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                        : sal_b[i];
-    };
     // one pass over the sample's scores feeds both the masses and the selection keys of both
     // segments (keys [0, n2) and [n2, n2 + n3) of the LDS array)
-    double a2 = 0.0, a3 = 0.0;
-    for (int i = threadIdx.x; i < f.n2; i += BUD_THREADS) {
-        const float v = ld(i);
-        a2 += (double)v;
-        keys[i] = sal_key(v);
-    }
-    for (int i = threadIdx.x; i < f.n3; i += BUD_THREADS) {
-        const float v = ld(f.n2 + i);
-        a3 += (double)v;
-        keys[f.n2 + i] = sal_key(v);
-    }
-    a2 = block_sum_f64(a2, sh_d);
-    a3 = block_sum_f64(a3, sh_d);
+    auto feed = [&](int off, int n) __attribute__((always_inline)) {
+        double a = 0.0;
+        for (int i = threadIdx.x; i < n; i += FIN_U * BUD_THREADS) {
+            int col[FIN_U];
+            float v[FIN_U];
+#pragma unroll
+            for (int u = 0; u < FIN_U; ++u) col[u] = off + min(i + u * BUD_THREADS, n - 1);
+            load(col, v);
+#pragma unroll
+            for (int u = 0; u < FIN_U; ++u)
+                if (i + u * BUD_THREADS < n) {
+                    a += (double)v[u];
+                    if (sal_b) sal_b[col[u]] = v[u];
+                    keys[col[u]] = sal_key(v[u]);
+                }
+        }
+        return a;
+    };
+    double a2 = feed(0, f.n2), a3 = feed(f.n2, f.n3);
+    block_sum2_f64(a2, a3, sh_d);
     if (threadIdx.x == 0) {
         int k2;
         double m2;
@@ -592,22 +825,40 @@ __device__ __forceinline__ void finish_sample(const float* sal_b, const FusedPru
         f.k2k3[2 * b + 1] = f.k_total - k2;
         sh_k2 = k2;
     }
+    int32_t* row = f.kept_idx + (size_t)b * (f.k_total + f.n_text);
+    for (int i = threadIdx.x; i < f.n_text; i += SAL_THREADS)
+        row[f.k_total + i] = f.n2 + f.n3 + i;
     lds_barrier();
     const int k2 = sh_k2;
-    int32_t* row = f.kept_idx + (size_t)b * (f.k_total + f.n_text);
-    select_from_keys(keys, f.n2, k2, 0, row, hist, wsum, bcast);
-    lds_barrier();
-    select_from_keys(keys + f.n2, f.n3, f.k_total - k2, f.n2, row + k2, hist, wsum, bcast);
-    for (int i = threadIdx.x; i < f.n_text; i += SEL_THREADS)
-        row[f.k_total + i] = f.n2 + f.n3 + i;
+    const bool second = threadIdx.x >= SAL_THREADS / 2;   // (wave-uniform)
+    select_groups<SAL_THREADS / 128, 2>(second ? keys + f.n2 : keys, second ? f.n3 : f.n2,
+                                        second ? f.k_total - k2 : k2, second ? f.n2 : 0,
+                                        second ? row + k2 : row, max(f.n2, f.n3) <= SEL_CAND, sh);
 }
 
 int launch_select(const float* sal, const int32_t* k2k3, int B, int n2, int n3, int n_text,
                   int k_total, int32_t* kept_idx, hipStream_t st) {
     if (n2 > SEL_MAX_N || n3 > SEL_MAX_N) return MVLA_EUNSUPPORTED;
     const size_t lds = (size_t)max(max(n2, n3), 1) * 4;
-    hipLaunchKernelGGL(select_kernel, dim3(3, B), dim3(SEL_THREADS), lds, st, sal, k2k3, n2, n3,
-                       n_text, k_total, kept_idx);
+    // (up to 64 KiB of keys and 5 KiB beside them: above the default limit for the longest segments)
+#define MVLA_SELECT(GW)                                                                         \
+    do {                                                                                        \
+        auto kern = select_kernel<GW>;                                                          \
+        static bool lds_set[kMaxDevices] = {};                                                  \
+        int dev = 0;                                                                            \
+        MVLA_HIP_CHECK(hipGetDevice(&dev));                                                     \
+        if (dev < 0 || dev >= kMaxDevices || !lds_set[dev]) {                                   \
+            MVLA_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),             \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,      \
+                                               SEL_MAX_N * 4));                                 \
+            if (dev >= 0 && dev < kMaxDevices) lds_set[dev] = true;                             \
+        }                                                                                       \
+        hipLaunchKernelGGL(kern, dim3(3, B), dim3(GW * 64), lds, st, sal, k2k3, n2, n3, n_text, \
+                           k_total, kept_idx);                                                  \
+    } while (0)
+    if (max(n2, n3) <= SEL_FOUR_WAVES) MVLA_SELECT(4);
+    else MVLA_SELECT(16);
+#undef MVLA_SELECT
     MVLA_HIP_CHECK(hipGetLastError());
     return MVLA_OK;
 }

@@ -1,0 +1,69 @@
+"""Selection and fused pruning at the sizes where their kernels change path: segments of one wave
+(ranked directly), segments around the four- / sixteen-wave limit, keys that agree in all but their
+last bits (the narrowing goes through every round), samples around the limits up to which one
+workgroup sums all columns.  Selection is compared with the oracle exactly; the fused step with the
+four single calls exactly (same order of additions, same selection)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2604_09244_amd import binding as mv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = mv.Context(4, 32768 + 8, 64, 4, 64, 160)
+    yield c
+    c.close()
+
+
+def _scores(kind, shape, r):
+    if kind == "lognormal":
+        return r.lognormal(size=shape).astype(np.float32)
+    if kind == "last bits":        # 1 + i * 2^-23 for few i: thousands of equal keys per value
+        return (1.0 + r.integers(0, 5, size=shape) * 2.0 ** -23).astype(np.float32)
+    if kind == "all equal":
+        return np.full(shape, 0.25, np.float32)
+    # both signs over the whole exponent range, and both zeros
+    s = (np.sign(r.normal(size=shape)) * np.exp(r.uniform(-80, 80, size=shape))).astype(np.float32)
+    return np.where(r.uniform(size=shape) < 0.2, np.float32(-0.0), s).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["lognormal", "last bits", "all equal", "wide"])
+@pytest.mark.parametrize("n2,n3", [(1, 0), (64, 64), (64, 65), (65, 1), (2048, 2047), (2049, 63), (16384, 16384)])
+def test_select_paths(ctx, n2, n3, kind):
+    r = np.random.default_rng(n2 * 31 + n3)
+    B, n = 2, n2 + n3
+    s = _scores(kind, (B, n), r)
+    for K in sorted({0, 1, n // 7, n // 2, n - 1, n}):
+        k2 = r.integers(max(0, K - n3), min(n2, K) + 1, size=B)
+        k2k3 = np.stack([k2, K - k2], 1).astype(np.int32)
+        got = ctx.select_topk(torch.from_numpy(s).cuda(), torch.from_numpy(k2k3).cuda(), n2, n3, 3, K)
+        assert np.array_equal(got.cpu().numpy(), O.select_topk(s, k2k3, n2, n3, 3)), (n2, n3, kind, K)
+
+
+# H * Nq rows x columns: 16384 values is the most one workgroup takes, 128 rows and 2048 columns
+@pytest.mark.parametrize("H,Nq,n2,n3,nt", [(4, 16, 64, 64, 16), (4, 32, 64, 64, 32), (4, 33, 50, 50, 33),
+                                           (4, 32, 64, 65, 32), (1, 8, 1024, 1024, 8), (1, 8, 1025, 1024, 7),
+                                           (4, 8, 256, 256, 32), (2, 8, 3, 700, 9), (4, 160, 300, 700, 160)])
+def test_fused_step_equals_single_calls(ctx, H, Nq, n2, n3, nt):
+    B, D, S = 3, 64, n2 + n3 + nt
+    g = torch.Generator().manual_seed(H * 1000 + S)
+    p = torch.rand(B, H, Nq, S, generator=g) ** 4
+    p = (p / p.sum(-1, keepdim=True)).cuda()
+    h = torch.randn(B, S, D, generator=g).to(torch.bfloat16).cuda()
+    pos = torch.arange(S, dtype=torch.int32).repeat(B, 1).cuda()
+    K = (n2 + n3) * 2 // 5
+    o = ctx.prune_step(p, h, pos, n2, n3, nt, K)
+    sal = ctx.salience(p, n2 + n3)
+    k2k3 = ctx.modality_budget(sal, n2, n3, K)
+    kept = ctx.select_topk(sal, k2k3, n2, n3, nt, K)
+    hk, pk = ctx.compact(h, pos, kept)
+    ref = O.salience(p.cpu().numpy().astype(np.float64), n2 + n3)
+    # a column sum of H*Nq fp32 values: at most (H*Nq) * 2^-24 relative, far less in groups of 16
+    assert np.max(np.abs(sal.cpu().numpy() - ref) / ref) < H * Nq * 2.0 ** -24
+    for a, b in ((o["sal"], sal), (o["k2k3"], k2k3), (o["kept_idx"], kept), (o["h"], hk), (o["pos"], pk)):
+        assert torch.equal(a, b)
