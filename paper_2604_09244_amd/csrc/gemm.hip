@@ -21,6 +21,7 @@
 // partial buffer and whichever piece arrives last (integer arrival counter)
 // adds them up in fixed piece order and runs the epilogue, so results do not
 // depend on timing.
+// The four-wave 256x256 shape runs as a persistent kernel of its own (persistent_body).
 //
 // Epilogues: the q/k/v projection (q and k columns rotated by the row's position
 // on the fp32 accumulators and stored as bf16, v columns stored transposed for
@@ -132,11 +133,469 @@ struct EpiGeom {
     static_assert(TM * WM == BM || PASSES == WM, "overlapping wave rows go one per pass");
 };
 
+// ---------------------------------------------------------------------------------------------
+// The four-wave 256x256 shape (128x128 per wave, its 256 accumulator registers in the second register
+// file) as a persistent kernel: one workgroup per CU walks through its tiles, and the stream of slab
+// loads runs on across tile borders -- the last two slabs of a tile are followed by the first two of
+// the next one, into the same two stages, so the epilogue starts with the next tile's operands in
+// flight and no tile but the first waits for its first slab.  The epilogue needs no workgroup
+// barrier and none of the stages: every wave turns its accumulator blocks through 4.5 KiB of LDS of
+// its own (LDS accesses of a wave are in order) into whole 128-byte lines of the output.
+//
+// Bound by the matrix core, and that by the part's power: the main loop takes about 2280 clocks a slab of
+// which 2048 are products, at 1.6 GHz instead of 2.4; the epilogue (9 k clocks of a gate/up tile's 155 k,
+// 11 k q/k/v, 20 k with a residual) is what nothing overlaps.  Hence the 16x16x32 products (see mfma16).
+// Against one workgroup per tile with 32x32x16 products, M = 21504: gate/up 2832 -> 2546 us
+// (1.50 PFLOP/s), q/k/v 1701 -> 1543, down 1375 -> 1292, output 555 -> 525; of that the persistent form
+// alone, with 32x32x16 products, gave 3 %, 6 %, 1 % and 4 %.
+//
+// Main loop, per 64-deep slab: the fragments of k-steps 2 and 3 are read during k-step 0, those of the
+// next slab's k-steps 0 and 1 during k-step 3, one LDS read after each MFMA, so the stage is free after
+// k-step 0; the direct loads of the slab after next go out a third each over k-steps 1 to 3 (the load
+// unit takes one 64-lane load per 16 clocks: 64 loads are two k-steps of it).
+// ---------------------------------------------------------------------------------------------
+constexpr int PT_BK = 64, PT_STAGE = 512 * 8, PT_LD = 8, PT_P = 2 * PT_LD;   // 16-byte slots of a stage; loads per thread
+constexpr int PT_TLD = 36;                                   // floats per row of a wave's turning area
+constexpr int PT_TURN = 32 * PT_TLD;                         // floats of it
+constexpr int PT_LDS_BYTES = 2 * PT_STAGE * 16 + 4 * PT_TURN * 4;
+
+// direct global -> LDS copy with a wave-uniform base and a 32-bit per-lane byte offset
+// (LDS address: lds_base + the immediate OFF)
+template <int OFF>
+__device__ __forceinline__ void dma16_at(const void* base, uint32_t off, uint32_t lds_base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base),
+                 "v"(off), "s"(base), "i"(OFF)
+                 : "memory", "m0", "scc");
+}
+// Workgroup barrier for LDS traffic: this wave's LDS reads have returned; its global stores (of the
+// epilogue before) may be on their way, which __syncthreads() would wait for.
+__device__ __forceinline__ void lds_only_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int EPI>
+__device__ __forceinline__ void persistent_body(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W,
+                                                int M, int N, int K, void* __restrict__ Cv, int ldc,
+                                                const void* __restrict__ Rv, int ldr, const GemmPlan& plan,
+                                                const RopeEpilogue& rope) {
+    extern __shared__ uint4 lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int fr = lane & 31, fg = lane >> 5;
+    const int k_tiles = plan.k_tiles;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+    float* turn = reinterpret_cast<float*>(lds + 2 * PT_STAGE) + wave * PT_TURN;
+
+    // tile r of this workgroup: launch id blockIdx.x + r * gridDim.x, as if every tile were a workgroup
+    // (the ids of a launch of whole tiles; see xcd_chunked); -1 when there is none
+    auto next_tile = [&](int& id) __attribute__((always_inline)) {
+        while (id < plan.dp_grid) {
+            const int lin = xcd_chunked(id, plan.dp_tiles);
+            id += (int)gridDim.x;
+            if (lin < plan.dp_tiles) return lin;
+        }
+        return -1;
+    };
+
+    // ---- stream of slab loads: where the next slab comes from ------------------------------------
+    // (v tiles of the q/k/v projection are computed transposed -- weight rows take the place of the
+    // activation rows and the other way round -- so that a lane's registers run along the tokens)
+    const char *dma_a, *dma_b;           // wave-uniform: first row of the tile, current slab
+    uint32_t off_a[PT_LD], off_b[PT_LD]; // per lane, from there
+    int dma_left;                        // slabs of the stream's tile not issued yet
+    auto aim = [&](int lin) __attribute__((always_inline)) {
+        int tm, tn;
+        tile_of(lin, plan.tiles_m, plan.tiles_n, &tm, &tn);
+        const bool turned = EPI == EPI_QKV_ROPE && tn * 256 >= 2 * rope.D;
+        const bf16_t* act = A + (size_t)tm * 256 * lda;
+        const bf16_t* wgt = W + (size_t)tn * 256 * K;
+        dma_a = reinterpret_cast<const char*>(turned ? wgt : act);
+        dma_b = reinterpret_cast<const char*>(turned ? act : wgt);
+        const int lim_m = M - 1 - tm * 256, lim_n = N - 1 - tn * 256;
+        const int lim_a = turned ? lim_n : lim_m, lim_b = turned ? lim_m : lim_n;
+        const int ld_a = turned ? K : lda, ld_b = turned ? lda : K;
+#pragma unroll
+        for (int i = 0; i < PT_LD; ++i) {
+            const int sl = i * 256 + tid, row = sl >> 3, ch = (sl & 7) ^ swz<8>(row);
+            off_a[i] = ((uint32_t)min(row, lim_a) * (uint32_t)ld_a + (uint32_t)ch * 8u) * 2u;
+            off_b[i] = ((uint32_t)min(row, lim_b) * (uint32_t)ld_b + (uint32_t)ch * 8u) * 2u;
+        }
+        dma_left = k_tiles;
+    };
+    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds_base + (uint32_t)wave * 1024u);
+    // load l of the stream's current slab into stage STG
+    // (the index is a constant once the loops are unrolled; "n"-type operands need it before that)
+    auto load_one = [&](int l, uint32_t to) __attribute__((always_inline)) {
+        switch (l) {
+#define PT_CASE(L) \
+    case L: dma16_at<L * 4096>(L < PT_LD ? dma_a : dma_b, L < PT_LD ? off_a[L % PT_LD] : off_b[L % PT_LD], to); break;
+            PT_CASE(0) PT_CASE(1) PT_CASE(2) PT_CASE(3) PT_CASE(4) PT_CASE(5) PT_CASE(6) PT_CASE(7)
+            PT_CASE(8) PT_CASE(9) PT_CASE(10) PT_CASE(11) PT_CASE(12) PT_CASE(13) PT_CASE(14) PT_CASE(15)
+#undef PT_CASE
+        }
+    };
+#define PT_LOAD(L, STG) load_one(L, lds_wave + (uint32_t)(STG) * (PT_STAGE * 16u));
+    int ahead_id = blockIdx.x;           // launch id the stream looks at next
+    int tile = next_tile(ahead_id);      // tile being computed
+    if (tile < 0) return;
+    int ahead = tile;                    // tile the stream loads (-1: none left, the last one is loaded again)
+    aim(tile);
+    // after a slab: on to the next one, or to the next tile's first
+    auto advance = [&]() __attribute__((always_inline)) {
+        dma_a += PT_BK * 2;
+        dma_b += PT_BK * 2;
+        if (--dma_left == 0) {
+            if (ahead >= 0) ahead = next_tile(ahead_id);
+            if (ahead >= 0) {
+                aim(ahead);
+            } else {                     // (keeps the count of loads in flight; never read)
+                dma_a -= (size_t)PT_BK * 2;
+                dma_b -= (size_t)PT_BK * 2;
+                dma_left = 1;
+            }
+        }
+    };
+
+    // fragments: lane -> row lane % 16 of a 16-row block, chunk lane / 16 of the k-step's four
+    const int fr16 = lane & 15, fq = lane >> 4;
+    const int a_row = (wm * 128 + fr16) * 8, b_row = 2048 + (wn * 128 + fr16) * 8;
+    const int sw = swz<8>(fr16);         // (rows of a lane differ by multiples of 16: one pattern)
+    // fragment read R of the sixteen of k-step KS, in the order the products need them
+#define PT_READ(DST_A, DST_B, STG, KS, R)                                                        \
+    {                                                                                            \
+        const uint4* st_ = lds + (STG) * PT_STAGE + (((KS) * 4 + fq) ^ sw);                      \
+        if ((R) == 0 || (R) > 8) DST_A[(R) > 8 ? (R) - 8 : 0] = st_[a_row + ((R) > 8 ? (R) - 8 : 0) * 128]; \
+        else DST_B[((R) - 1) & 7] = st_[b_row + (((R) - 1) & 7) * 128];                          \
+    }
+    // 32 of the 64 MFMAs of a k-step: block rows I0 .. I0+3.  After every other MFMA a fragment read of
+    // k-step RKS of stage RSTG (when READS), and the loads [L0, L1) of the stream's slab into stage
+    // LSTG spread out
+#define PT_HALF(AF, BF, I0, READS, DA, DB, RSTG, RKS, LSTG, L0, L1)                              \
+    {                                                                                            \
+        constexpr int EVERY_ = (L1) > (L0) ? 32 / ((L1) - (L0)) : 99;                            \
+        int l_ = (L0);                                                                           \
+        _Pragma("unroll") for (int n_ = 0; n_ < 32; ++n_) {                                      \
+            const int i_ = (I0) + (n_ >> 3), j_ = n_ & 7;                                        \
+            acc[i_][j_] = mfma16(BF[j_], AF[i_], acc[i_][j_]);                                   \
+            if ((READS) && (n_ & 1) == 0) PT_READ(DA, DB, RSTG, RKS, (n_ >> 1))                  \
+            if (n_ % EVERY_ == EVERY_ - 1 && l_ < (L1)) {                                        \
+                PT_LOAD(l_, LSTG)                                                                \
+                ++l_;                                                                            \
+            }                                                                                    \
+            __builtin_amdgcn_sched_barrier(0);                                                   \
+        }                                                                                        \
+    }
+
+    uint4 af0[8], bf0[8], af1[8], bf1[8];
+    f32x4_t acc[8][8];                   // block (i, j): 16 rows x 16 columns
+#pragma unroll
+    for (int l = 0; l < PT_P; ++l) PT_LOAD(l, 0)
+    advance();
+#pragma unroll
+    for (int l = 0; l < PT_P; ++l) PT_LOAD(l, 1)
+    advance();
+    wait_vm<PT_P>();
+    lds_only_barrier();
+    int stage = 0;
+    int tile_id = blockIdx.x;            // launch ids of the tiles computed
+    (void)next_tile(tile_id);
+    constexpr int L1_ = PT_P / 3, L2_ = 2 * PT_P / 3;
+
+    while (tile >= 0) {
+        // (the first fragments are read again here rather than carried across the epilogue before,
+        // which needs their registers)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) PT_READ(af0, bf0, stage, 0, r)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int kt = 0; kt < k_tiles; ++kt) {
+            // first k-step, reading the fragments of the second: after it this slab is in registers
+            PT_HALF(af0, bf0, 0, true, af1, bf1, stage, 1, 0, 0, 0)
+            lds_only_barrier();   // ... for every wave: the stage is free for the slab after next
+            PT_HALF(af0, bf0, 4, false, af1, bf1, 0, 0, stage, 0, L1_)
+            PT_HALF(af1, bf1, 0, false, af1, bf1, 0, 0, stage, L1_, L2_)
+            // the next slab has landed for every wave (two thirds of the one after may be in flight)
+            wait_vm<L2_>();
+            lds_only_barrier();
+            PT_HALF(af1, bf1, 4, true, af0, bf0, stage ^ 1, 0, stage, L2_, PT_P)
+            advance();
+            stage ^= 1;
+        }
+
+        // ---- epilogue, wave by wave: rows r0w .. r0w+127, columns c0w .. c0w+127 of the tile ----
+        int tile_m, tile_n;
+        tile_of(tile, plan.tiles_m, plan.tiles_n, &tile_m, &tile_n);
+        const int m0 = tile_m * 256, n0 = tile_n * 256;
+        tile = next_tile(tile_id);
+        int el = lane, ew = wave;        // (the epilogue's indices are computed here, not held across the loop)
+        asm volatile("" : "+v"(el), "+s"(ew));
+        const int efr = el & 15, efq = (el >> 4) * 4;    // a lane's row and first column in a 16x16 block
+        const int trow = el >> 3, tcol = (el & 7) * 4;   // turned: row (of 8 a read) and first of 4 floats
+        const int r0w = (ew >> 1) * 128, c0w = (ew & 1) * 128;
+        // 32x32 accumulators (blocks 2i, 2i+1 by 2j, 2j+1) into the turning area as fp32 rows
+        auto lay = [&](int i, int j) __attribute__((always_inline)) {
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                *reinterpret_cast<f32x4_t*>(turn + ((h >> 1) * 16 + efr) * PT_TLD + (h & 1) * 16 + efq) =
+                    acc[2 * i + (h >> 1)][2 * j + (h & 1)];
+            asm volatile("" ::: "memory");   // (the reads stay behind the writes; the LDS keeps a wave's order)
+        };
+        auto turned4 = [&](int t) __attribute__((always_inline)) {
+            return *reinterpret_cast<const f32x4_t*>(turn + (t * 8 + trow) * PT_TLD + tcol);
+        };
+        // a quad of packed bf16 pairs into the area as rows of 64 bf16 (same row pitch)
+        auto lay_bf16 = [&](int row, int col, uint32_t x, uint32_t y) __attribute__((always_inline)) {
+            *reinterpret_cast<u32x2_t*>(reinterpret_cast<bf16_t*>(turn) + row * (PT_TLD * 2) + col) = u32x2_t{x, y};
+            asm volatile("" ::: "memory");
+        };
+        auto turned8 = [&](int t) __attribute__((always_inline)) {
+            return *reinterpret_cast<const u32x4_t*>(turn + (t * 8 + trow) * PT_TLD + tcol);
+        };
+        // (the compiler fetched all 256 accumulators from the second register file at once otherwise)
+        auto pin_rows = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) asm volatile("" : "+a"(acc[2 * i][j]), "+a"(acc[2 * i + 1][j]));
+        };
+        const int rows_here = min(256, M - m0);
+        if constexpr (EPI == EPI_SILU_MUL) {
+            const int out_n0 = n0 / 2, cols_here = min(128, N / 2 - out_n0);
+            const __amdgpu_buffer_rsrc_t c_buf = buffer_of(static_cast<bf16_t*>(Cv) + (size_t)m0 * ldc + out_n0,
+                                                           ((rows_here - 1) * ldc + cols_here) * 2);
+            const int col = c0w / 2 + tcol * 2;          // 8 output columns of a lane
+            int off[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                off[t] = col < cols_here ? ((r0w + t * 8 + trow) * ldc + col) * 2 : OOB_OFFSET;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                pin_rows(i);
+                // gate and up columns alternate in blocks of 32: block columns 4p, 4p+1 and 4p+2, 4p+3
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        const f32x4_t g = acc[2 * i + (h >> 1)][4 * p + (h & 1)];
+                        const f32x4_t u = acc[2 * i + (h >> 1)][4 * p + 2 + (h & 1)];
+                        float x[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            x[e] = g[e] * u[e] * __builtin_amdgcn_rcpf(1.f + __expf(-g[e]));
+                        lay_bf16((h >> 1) * 16 + efr, p * 32 + (h & 1) * 16 + efq, pack_bf16x2(x[0], x[1]),
+                                 pack_bf16x2(x[2], x[3]));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    __builtin_amdgcn_raw_buffer_store_b128(turned8(t), c_buf,
+                                                           off[t] == OOB_OFFSET ? OOB_OFFSET : off[t] + i * 64 * ldc, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if constexpr (EPI == EPI_RES_BF16_TO_F32 || EPI == EPI_RES_F32_TO_BF16) {
+            constexpr int ES = EPI == EPI_RES_BF16_TO_F32 ? 4 : 2, RS = 6 - ES;   // bytes per output / residual value
+            const int cols_here = min(256, N - n0);
+            const __amdgpu_buffer_rsrc_t c_buf = buffer_of(static_cast<char*>(Cv) + ((size_t)m0 * ldc + n0) * ES,
+                                                           ((rows_here - 1) * ldc + cols_here) * ES);
+            const __amdgpu_buffer_rsrc_t r_buf = buffer_of(static_cast<const char*>(Rv) + ((size_t)m0 * ldr + n0) * RS,
+                                                           ((rows_here - 1) * ldr + cols_here) * RS);
+            const int row = r0w + trow, col = c0w + tcol;
+            // residual of the 32 rows i: 16 loads, one set of 32 rows ahead of its use
+            constexpr int RW = RS == 2 ? 2 : 4;
+            uint32_t res[2][16][RW];
+            auto request = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int o = ((row + i * 32 + t * 8) * ldr + col + j * 32) * RS;
+                        if constexpr (RW == 2) {
+                            const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r_buf, o, 0, 0);
+                            res[i & 1][j * 4 + t][0] = v.x;
+                            res[i & 1][j * 4 + t][1] = v.y;
+                        } else {
+                            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r_buf, o, 0, 0);
+                            res[i & 1][j * 4 + t][0] = v.x;
+                            res[i & 1][j * 4 + t][1] = v.y;
+                            res[i & 1][j * 4 + t][RW - 2] = v.z;
+                            res[i & 1][j * 4 + t][RW - 1] = v.w;
+                        }
+                    }
+            };
+            request(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (i < 3) request(i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                pin_rows(i);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    lay(i, j);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const f32x4_t a = turned4(t);
+                        const uint32_t* r = res[i & 1][j * 4 + t];
+                        const int o = col + j * 32 < cols_here
+                                          ? ((row + i * 32 + t * 8) * ldc + col + j * 32) * ES : OOB_OFFSET;
+                        if constexpr (RW == 2) {
+                            const u32x4_t v = {__float_as_uint(a.x + __uint_as_float(r[0] << 16)),
+                                               __float_as_uint(a.y + __uint_as_float(r[0] & 0xFFFF0000u)),
+                                               __float_as_uint(a.z + __uint_as_float(r[1] << 16)),
+                                               __float_as_uint(a.w + __uint_as_float(r[1] & 0xFFFF0000u))};
+                            __builtin_amdgcn_raw_buffer_store_b128(v, c_buf, o, 0, 0);
+                        } else {
+                            const u32x2_t v = {pack_bf16x2(a.x + __uint_as_float(r[0]), a.y + __uint_as_float(r[1])),
+                                               pack_bf16x2(a.z + __uint_as_float(r[RW - 2]), a.w + __uint_as_float(r[RW - 1]))};
+                            __builtin_amdgcn_raw_buffer_store_b64(v, c_buf, o, 0, 0);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else if (n0 < 2 * rope.D) {
+            // q and k columns: a head's first half sits in one block (dh = 64) or two (dh = 128), its
+            // second half in the block(s) after; both are turned together, rotated in fp32 and packed
+            const int cols_here = min(256, N - n0), half = rope.dh >> 1;
+            const __amdgpu_buffer_rsrc_t c_buf = buffer_of(static_cast<bf16_t*>(Cv) + (size_t)m0 * ldc + n0,
+                                                           ((rows_here - 1) * ldc + cols_here) * 2);
+            const int row = r0w + trow;
+            auto rotate = [&](int j1, int j2, const float4 (&c)[4], const float4 (&s)[4], int i,
+                              int colb) __attribute__((always_inline)) {
+                f32x4_t a[4];
+                lay(i, j1);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) a[t] = turned4(t);
+                lay(i, j2);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const f32x4_t b = turned4(t);
+                    const int col = colb + tcol;
+                    const int o = col < cols_here ? ((row + i * 32 + t * 8) * ldc + col) * 2 : OOB_OFFSET;
+                    const u32x2_t x = {pack_bf16x2(a[t].x * c[t].x - b.x * s[t].x, a[t].y * c[t].y - b.y * s[t].y),
+                                       pack_bf16x2(a[t].z * c[t].z - b.z * s[t].z, a[t].w * c[t].w - b.w * s[t].w)};
+                    const u32x2_t y = {pack_bf16x2(b.x * c[t].x + a[t].x * s[t].x, b.y * c[t].y + a[t].y * s[t].y),
+                                       pack_bf16x2(b.z * c[t].z + a[t].z * s[t].z, b.w * c[t].w + a[t].w * s[t].w)};
+                    __builtin_amdgcn_raw_buffer_store_b64(x, c_buf, o, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(y, c_buf, o + half * 2, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // (the position ids of 32 rows are asked for one step, their table rows another step ahead)
+            auto place = [&](int i, int (&pos)[4]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) pos[t] = rope.pos[min(m0 + row + i * 32 + t * 8, M - 1)];
+            };
+            auto table = [&](const int (&pos)[4], int c0, float4 (&c)[4], float4 (&s)[4]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const size_t at = (size_t)min(max(pos[t], 0), rope.rope_len - 1) * half + c0 + tcol;
+                    c[t] = *reinterpret_cast<const float4*>(rope.rc + at);
+                    s[t] = *reinterpret_cast<const float4*>(rope.rs + at);
+                }
+            };
+            int pos[2][4];
+            float4 c[2][4], s[2][4];
+            place(0, pos[0]);
+            place(1, pos[1]);
+            table(pos[0], 0, c[0], s[0]);
+            if (rope.dh == 128) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {            // (rows k/2, half a half head k%2)
+                    const int i = k >> 1, n = (k + 1) & 1;
+                    if (k < 7) table(pos[((k + 1) >> 1) & 1], n * 32, c[n], s[n]);
+                    if (n == 0 && i < 2) place(i + 2, pos[i & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    pin_rows(i);
+                    rotate(k & 1, (k & 1) + 2, c[k & 1], s[k & 1], i, c0w + (k & 1) * 32);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (i < 3) table(pos[(i + 1) & 1], 0, c[(i + 1) & 1], s[(i + 1) & 1]);
+                    if (i < 2) place(i + 2, pos[i & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    pin_rows(i);
+                    rotate(0, 1, c[i & 1], s[i & 1], i, c0w);
+                    rotate(2, 3, c[i & 1], s[i & 1], i, c0w + 64);
+                }
+            }
+        } else {
+            // v columns: rows of the turned tile are columns of V (n0 ..), columns are tokens (m0 ..);
+            // vt [B, H, dh, S_pad] is [B*D, S_pad] by (sample, V column), addressed from the row of the
+            // tile's first sample and V column (offsets below 2^31: see launch_gemm)
+            const int S = rope.S, S_pad = rope.S_pad, D = rope.D, v0 = n0 - 2 * D, b0 = m0 / S;
+            const int v_here = min(256, N - n0);
+            const __amdgpu_buffer_rsrc_t v_buf = buffer_of(rope.vt + ((size_t)b0 * D + v0) * S_pad, OOB_OFFSET - 65536);
+            auto lay_tokens = [&](int i, int jp) __attribute__((always_inline)) {   // 32 V columns x 64 tokens
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4_t a = acc[2 * i + h][jp * 4 + q];
+                        lay_bf16(h * 16 + efr, q * 16 + efq, pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
+                    }
+            };
+            // byte offset of a token's entry in the first V column, or out of range
+            auto token_at = [&](int tok) __attribute__((always_inline)) {
+                const int bs = tok / S;
+                return tok < M ? ((bs - b0) * D * S_pad + tok - bs * S) * 2 : OOB_OFFSET;
+            };
+            if ((S & 7) == 0) {          // every 8 tokens from a tile's start are of one sample
+                const int off[2] = {token_at(m0 + c0w + (el & 7) * 8), token_at(m0 + c0w + 64 + (el & 7) * 8)};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    pin_rows(i);
+#pragma unroll
+                    for (int jp = 0; jp < 2; ++jp) {
+                        lay_tokens(i, jp);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const int r = r0w + i * 32 + t * 8 + trow;
+                            __builtin_amdgcn_raw_buffer_store_b128(
+                                turned8(t), v_buf, off[jp] != OOB_OFFSET && r < v_here ? off[jp] + r * S_pad * 2 : OOB_OFFSET,
+                                0, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            } else {                     // one token a lane: 64 consecutive ones of a V column per store
+                const int off[2] = {token_at(m0 + c0w + el), token_at(m0 + c0w + 64 + el)};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    pin_rows(i);
+#pragma unroll
+                    for (int jp = 0; jp < 2; ++jp) {
+                        lay_tokens(i, jp);
+#pragma unroll 8
+                        for (int r = 0; r < 32; ++r) {
+                            const bf16_t v = reinterpret_cast<const bf16_t*>(turn)[r * (PT_TLD * 2) + el];
+                            const int vr = r0w + i * 32 + r;
+                            __builtin_amdgcn_raw_buffer_store_b16(
+                                v, v_buf, off[jp] != OOB_OFFSET && vr < v_here ? off[jp] + vr * S_pad * 2 : OOB_OFFSET, 0, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            // padding behind every sample whose last token is in this tile
+            const int z = S + el;
+            for (int b = b0; (b + 1) * S - 1 < m0 + rows_here; ++b)
+                for (int r = ew; r < v_here; r += 4)
+                    if (z < S_pad) rope.vt[((size_t)b * D + v0 + r) * S_pad + z] = 0;
+        }
+    }
+    wait_vm<0>();   // (the last loads into the stages have landed before the workgroup's LDS is given back)
+#undef PT_LOAD
+#undef PT_READ
+#undef PT_HALF
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
+__device__ __forceinline__ void tile_body(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
-    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
-    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope) {
+    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, const GemmPlan& plan,
+    float* __restrict__ partial, uint32_t* __restrict__ counters, const RopeEpilogue& rope) {
     constexpr int NT = WM * WN * 64;
     constexpr int CPR = BK / 8;             // 16-byte chunks per LDS row
     constexpr int KS = BK / 16;             // MFMA k-steps per slab
@@ -878,6 +1337,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     }
 }
 
+// The four-wave 256x256 shape is the persistent kernel, every other one takes a workgroup per tile.
+constexpr bool is_persistent(int BM, int BN, int WM, int WN) { return BM == 256 && BN == 256 && WM * WN == 4; }
+
+template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
+    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
+    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope) {
+    if constexpr (is_persistent(BM, BN, WM, WN))
+        persistent_body<EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, rope);
+    else
+        tile_body<BM, BN, BK, WM, WN, NS, EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope);
+}
+
 // ---- host side ------------------------------------------------------------------------------
 // Compute units of the current device: sets how many workgroups are resident at once (the round
 // size of the tile plan) and the size of the K-split partial buffer.  Asked once; 256 (MI355X)
@@ -958,11 +1431,16 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
         plan.dp_grid = 0;                           // workgroup ids start at the K-split workgroups
     }
     if (!has_sk && plan.sk_blocks > 0) return MVLA_EINVAL;
-    const int grid = plan.dp_grid + plan.sk_blocks;
+    int grid = plan.dp_grid + plan.sk_blocks;
     if (grid == 0) return MVLA_OK;
     const size_t stage_bytes = (size_t)NS * (BM + BN) * (BK / 8) * sizeof(uint4);
     const size_t epi_bytes = EpiGeom<BM, BN, WM, NS>::BYTES;
-    const size_t lds = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
+    size_t lds = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
+    if (is_persistent(BM, BN, WM, WN)) {   // one workgroup per CU, a multiple of 8 (see xcd_chunked)
+        const int cus = device_cu_count() & ~7;
+        if (cus > 0 && grid > cus) grid = cus;
+        lds = PT_LDS_BYTES;
+    }
     dim3 block(WM * WN * 64);
     // the dynamic-LDS limit of a kernel is raised once per device (the size is a constant of the
     // instantiation), not on every launch
@@ -1092,6 +1570,11 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         case 2: return launch_cfg<128, 128, 64, 2, 2, 2>(MVLA_ARGS);
         case 3: return launch_cfg<128, 128, 64, 4, 2, 3>(MVLA_ARGS);
         case 4: {
+            // (the persistent kernel addresses V^T with 32-bit offsets from a tile's first sample: at most
+            // 256 / S + 2 samples of D * S_pad values; beyond that the eight-wave kernel takes the call)
+            if (epilogue == EPI_QKV_ROPE && N == 3 * rope->D &&
+                (size_t)(256 / rope->S + 2) * rope->D * rope->S_pad * 2 >= (size_t)OOB_OFFSET - 65536)
+                return launch_cfg<256, 256, 64, 2, 4, 2>(MVLA_ARGS);
             // four waves of 128x128 have no registers for the K-split exchange: when the last round
             // is to be cut, its tiles go to the eight-wave kernel of the same tile size in a second
             // launch (same plan, same tile numbering)
