@@ -1473,42 +1473,67 @@ size_t gemm_partial_bytes() {
     return (size_t)2 * device_cu_count() * 256 * 256 * sizeof(float);
 }
 
-// Tile configurations and the time one round of them takes at K = 4096 on this chip (measured
-// once, microseconds; only their ratios matter for the choice below).
+// Tile configurations, and what predicts their time (see estimate_us; microseconds, fitted to the
+// measured times of all of them on 108 projections of this package's models, 64 to 21504 rows).
 struct TileCfg {
     int BM, BN, slots_per_cu;
-    float round_us;
-    bool can_split;   // has the K-split path
+    bool can_split;      // has the K-split path
+    float slab_us;       // a 64-deep slab with every workgroup slot of the chip busy
+    float alone;         // ... and the share of it that remains with one workgroup alone
+    float tile_us[4];    // start and epilogue of a tile, by epilogue
+    float piece_us;      // K-split: summing one piece of a tile
+    float straddle_us;   // K-split: when workgroups' ranges straddle two tiles (two starts, two parts put out)
+    float mb_per_us;     // operand bytes beyond the caches
 };
 constexpr int kNumCfgs = 7;
 static const TileCfg kCfgs[kNumCfgs] = {
-    {256, 256, 1, 105.f, true},   // K-slab 64, eight waves of 128x64, two stages
-    {256, 128, 1, 62.f, true},    // K-slab 64, eight waves of 64x64, three stages
-    {128, 128, 2, 67.f, true},    // K-slab 64, four waves of 64x64, two stages, two workgroups per CU
-    {128, 128, 1, 35.f, true},    // K-slab 64, eight waves of 32x64, three stages
-    {256, 256, 1, 98.f, true},    // K-slab 64, four waves of 128x128 (accumulators fill the second
-                                  // register file, a third less LDS traffic per MFMA); a K-split last
-                                  // round runs on the eight-wave kernel of the same tile size
-    {192, 128, 1, 50.f, true},    // K-slab 64, eight waves of 96x32, three stages (row counts just over
-                                  // 2x256 with few column tiles: three row tiles, K-split over all CUs)
-    {288, 192, 1, 92.f, false},   // K-slab 64, four waves of 160x96 (the two wave rows overlap by one
-                                  // 32-row block), accumulators in the second register file, whole
-                                  // tiles only
+    // K-slab 64, eight waves of 128x64, two stages
+    {256, 256, 1, true, 1.69f, .604f, {8.6f, 10.7f, 11.6f, 5.5f}, 2.5f, 23.8f, 4.2f},
+    // K-slab 64, eight waves of 64x64, three stages
+    {256, 128, 1, true, .889f, .505f, {7.1f, 7.1f, 8.4f, 4.9f}, 2.1f, 13.4f, 4.4f},
+    // K-slab 64, four waves of 64x64, two stages, two workgroups per CU
+    {128, 128, 2, true, 1.01f, .381f, {4.9f, 4.5f, 5.1f, 3.4f}, 1.8f, 15.3f, 3.0f},
+    // K-slab 64, eight waves of 32x64, three stages
+    {128, 128, 1, true, .567f, .686f, {5.2f, 4.3f, 4.1f, 3.0f}, 1.7f, 6.5f, 3.9f},
+    // K-slab 64, four waves of 128x128, persistent (accumulators fill the second register file, a third
+    // less LDS traffic per MFMA); a K-split last round runs on the eight-wave kernel of the same tile size
+    {256, 256, 1, true, 1.39f, .694f, {9.2f, 10.8f, 9.0f, 6.0f}, 0.f, 0.f, 5.2f},
+    // K-slab 64, eight waves of 96x32, three stages (row counts just over 2x256 with few column tiles:
+    // three row tiles, K-split over all CUs)
+    {192, 128, 1, true, .759f, .601f, {6.1f, 6.2f, 5.6f, 4.2f}, 1.8f, 10.2f, 4.6f},
+    // K-slab 64, four waves of 160x96 (the two wave rows overlap by one 32-row block), accumulators in the
+    // second register file, whole tiles only
+    {288, 192, 1, false, 1.40f, .702f, {5.0f, 13.4f, 8.6f, 8.1f}, 0.f, 0.f, 5.8f},
 };
-constexpr int kSplitPct = 50;        // cut the last round along K only when it is under half full
-constexpr float kSplitOverhead = 0.3f;  // cost of the partial-sum exchange, in rounds
+constexpr float kLaunchUs = 3.f;
 
-// Estimated rounds of work for a tile configuration: whole rounds, plus the last partial
-// round either as a full round or, when K-split, as its fill fraction plus the exchange cost.
-static float estimate_us(const TileCfg& c, int M, int N, int K) {
-    const long tiles = (long)((M + c.BM - 1) / c.BM) * ((N + c.BN - 1) / c.BN);
-    const int slots = device_cu_count() * c.slots_per_cu;
+// Predicted time of a configuration: whole rounds of its tiles, then the last partial round either as it
+// is or cut along K over all compute units.  A slab takes longer the more of the chip is busy, and no
+// less than its share of the operands takes from memory (weights once for all row tiles in flight).
+// Over those 108 projections the configuration this picks is 1.2 % slower than the best one (a
+// round-count model with one constant per configuration and a fixed threshold for the cut: 7.4 %).
+static float estimate_us(int cfg, int M, int N, int K, int epi, bool split) {
+    const TileCfg& c = kCfgs[cfg];
+    const int slots = device_cu_count() * c.slots_per_cu, kt = K / 64;
+    const GemmPlan p = make_plan(M, N, K, c.BM, c.BN, 64, slots, split ? 101 : 0);
+    const long tiles = (long)p.tiles_m * p.tiles_n;
     const long full = tiles / slots, rem = tiles % slots;
-    float rounds = (float)full;
-    if (rem)
-        rounds += (c.can_split && rem * 100 < (long)slots * kSplitPct)
-                      ? (float)rem / slots + kSplitOverhead : 1.f;
-    return rounds * c.round_us * (float)K / 4096.f;
+    auto slab = [&](float n) {
+        const float work = c.slab_us * (c.alone + (1.f - c.alone) * n / slots);
+        const float cols = fminf((float)p.tiles_n, fmaxf(1.f, n / p.tiles_m)), rows = fminf((float)p.tiles_m, n);
+        const float mem = (cols * c.BN + .2f * rows * c.BM) * 128.f * 1e-6f / c.mb_per_us;
+        const float w2 = work * work, m2 = mem * mem;
+        return sqrtf(sqrtf(w2 * w2 + m2 * m2));
+    };
+    float t = kLaunchUs + full * (c.tile_us[epi] + kt * slab((float)slots));
+    if (rem == 0) return t;
+    if (p.sk_blocks == 0) return t + c.tile_us[epi] + kt * slab((float)rem);
+    const bool second = cfg == 4;            // (the cut round is the eight-wave kernel's, a launch of its own)
+    const TileCfg& s = second ? kCfgs[0] : c;
+    const float its = (float)((rem * kt + p.sk_blocks - 1) / p.sk_blocks), pieces = (float)p.sk_blocks / rem;
+    const float per_slab = second ? s.slab_us * (s.alone + (1.f - s.alone) * p.sk_blocks / slots) : slab((float)p.sk_blocks);
+    return t + (second ? kLaunchUs : 0.f) + s.tile_us[epi] + its * per_slab + s.piece_us * pieces +
+           (p.sk_blocks % rem ? s.straddle_us : 0.f);
 }
 
 int gemm_num_configs() { return kNumCfgs; }
@@ -1545,7 +1570,7 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         if ((N == 3 * rope->D) != (rope->vt != nullptr)) return MVLA_EINVAL;
         if (M % rope->S != 0 || rope->S_pad < rope->S || rope->S_pad % 8 != 0) return MVLA_EINVAL;
     }
-    int best = -1, split_pct = kSplitPct;
+    int best = -1, split_pct = 0;
     if (force_cfg >= 0 && force_cfg < kNumCfgs && cfg_runs(kCfgs[force_cfg], epilogue, rope)) {
         best = force_cfg;
         split_pct = force_split_pct;
@@ -1553,10 +1578,13 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         float best_us = 0.f;
         for (int i = 0; i < kNumCfgs; ++i) {
             if (!cfg_runs(kCfgs[i], epilogue, rope)) continue;
-            const float t = estimate_us(kCfgs[i], M, N, K);
-            if (best < 0 || t < best_us) {
-                best_us = t;
-                best = i;
+            for (int split = 0; split <= (kCfgs[i].can_split ? 1 : 0); ++split) {
+                const float t = estimate_us(i, M, N, K, epilogue, split != 0);
+                if (best < 0 || t < best_us) {
+                    best_us = t;
+                    best = i;
+                    split_pct = split ? 101 : 0;
+                }
             }
         }
         if (best < 0) return MVLA_EUNSUPPORTED;
