@@ -284,13 +284,27 @@ __global__ __launch_bounds__(SC_THREADS) void score_probs_kernel(
     }
 }
 
-// Single-pass variant for S <= 8 waves * KBW key blocks * 32 keys: every wave keeps the logits
-// of its KBW key blocks in registers, so Q*K^T is computed once.
-constexpr int SCR_THREADS = 512;
-constexpr int SCR_WAVES = SCR_THREADS / 64;
+// Combination over the 32 lanes of a half-wave, result in all of them: rotations within 16 lanes, then
+// the two 16-lane rows of the half (vector-ALU only; the general shuffle goes through the LDS unit)
+template <typename Op>
+__device__ __forceinline__ float half_wave_all(float x, Op op) {
+    x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, false)));   // row_ror:8
+    x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false)));
+    x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, false)));
+    x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false)));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
-template <int DH, int KBW, bool COLSUM>
-__global__ __launch_bounds__(SCR_THREADS) void score_probs_reg_kernel(
+// Single-pass variant for S <= NW waves * KBW key blocks * 32 keys: every wave keeps the logits
+// of its KBW key blocks in registers, so Q*K^T is computed once and the keys are read once.  AHEAD key
+// blocks are in flight (all of them for short rows: one memory round trip).
+// Bound by latency at batch 1 (one workgroup per head), by the key reads at large batches.  With two key
+// blocks in flight and row reductions through the LDS unit: S = 144 10.5 us, S = 544 17.1 us; now
+// 6.4 and 13.1 us.  (Eleven blocks a wave, for S up to 2816, spill: 868 us at B = 16, S = 2624
+// against 279 us of the two-pass kernel.)
+template <int DH, int NW, int KBW, int AHEAD, bool COLSUM>
+__global__ __launch_bounds__(NW * 64) void score_probs_reg_kernel(
     const bf16_t* __restrict__ q, int ldq, int q_rows /* per sample */, const bf16_t* __restrict__ k,
     int ldk, const float* __restrict__ key_bias, int S, int H, int nq, float scale,
     float* __restrict__ probs, int n_out) {
@@ -299,6 +313,16 @@ __global__ __launch_bounds__(SCR_THREADS) void score_probs_reg_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fr = lane & 31, fg = lane >> 5;
     const int row0 = S - nq, qi0 = qt * 32;
+    const int n_kb = (S + 31) / 32;
+    const bf16_t* kbase = k + (size_t)b * S * ldk + h * DH + fg * 8;
+    const float* bias = key_bias ? key_bias + (size_t)b * S : nullptr;
+    // (rows past the end are clamped: loaded, never used)
+    uint4 kf[AHEAD][STEPS];
+    auto fetch = [&](int i) __attribute__((always_inline)) {
+        const bf16_t* src = kbase + (size_t)min((wave + NW * i) * 32 + fr, S - 1) * ldk;
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) kf[i % AHEAD][st] = *reinterpret_cast<const uint4*>(src + st * 16);
+    };
     uint4 qf[STEPS];
     {
         const int qi = min(qi0 + fr, nq - 1);
@@ -307,57 +331,58 @@ __global__ __launch_bounds__(SCR_THREADS) void score_probs_reg_kernel(
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) qf[st] = *reinterpret_cast<const uint4*>(src + st * 16);
     }
-    const int n_kb = (S + 31) / 32;
-    const bf16_t* kbase = k + (size_t)b * S * ldk + h * DH + fg * 8;
-    const float* bias = key_bias ? key_bias + (size_t)b * S : nullptr;
+#pragma unroll
+    for (int i = 0; i < AHEAD && i < KBW; ++i) fetch(i);
+    // (asked for here where the rows are short, else where it is used: registers)
+    constexpr bool EARLY_BIAS = KBW <= 3;
+    auto key_bias_of = [&](int i) __attribute__((always_inline)) {
+        return bias ? bias[min((wave + NW * i) * 32 + fr, S - 1)] : 0.f;
+    };
+    float kbias[EARLY_BIAS ? KBW : 1];
+    if (EARLY_BIAS)
+#pragma unroll
+        for (int i = 0; i < KBW; ++i) kbias[i] = key_bias_of(i);
 
     f32x16_t lg[KBW];
-    // key fragments of block i+1 are requested before the products of block i are issued
-    // (rows past the end are clamped: loaded, never used)
-    uint4 kf[2][STEPS];
-    {
-        const bf16_t* ksrc = kbase + (size_t)min(wave * 32 + fr, S - 1) * ldk;
-#pragma unroll
-        for (int st = 0; st < STEPS; ++st) kf[0][st] = *reinterpret_cast<const uint4*>(ksrc + st * 16);
-    }
 #pragma unroll
     for (int i = 0; i < KBW; ++i) {
-        const int kb = wave + SCR_WAVES * i;
-        const int key = kb * 32 + fr;
+        const int kb = wave + NW * i;
 #pragma unroll
         for (int v = 0; v < 16; ++v) lg[i][v] = 0.f;
-        if (i + 1 < KBW) {
-            const bf16_t* nsrc = kbase + (size_t)min(key + SCR_WAVES * 32, S - 1) * ldk;
-#pragma unroll
-            for (int st = 0; st < STEPS; ++st)
-                kf[(i + 1) & 1][st] = *reinterpret_cast<const uint4*>(nsrc + st * 16);
-        }
         if (kb < n_kb) {   // wave-uniform
 #pragma unroll
-            for (int st = 0; st < STEPS; ++st) lg[i] = mfma32(qf[st], kf[i & 1][st], lg[i]);
+            for (int st = 0; st < STEPS; ++st) lg[i] = mfma32(qf[st], kf[i % AHEAD][st], lg[i]);
         }
+        if (i + AHEAD < KBW) fetch(i + AHEAD);
     }
     float run_m[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) run_m[v] = -INFINITY;
 #pragma unroll
     for (int i = 0; i < KBW; ++i) {
-        const int kb = wave + SCR_WAVES * i;
-        const int key = kb * 32 + fr;
-        const float kbias = (bias && key < S) ? bias[key] : 0.f;
+        const int kb = wave + NW * i, key = kb * 32 + fr;
+        const float kbv = EARLY_BIAS ? kbias[EARLY_BIAS ? i : 0] : key_bias_of(i);
+        // a key up to the first scoring row is seen by every query (wave-uniform test)
+        if (kb * 32 + 31 <= row0 + qi0) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int qi = qi0 + mfma32_row(v, lane);
-            const bool valid = kb < n_kb && key < S && key <= row0 + qi;
-            lg[i][v] = valid ? lg[i][v] * scale + kbias : -INFINITY;
-            run_m[v] = fmaxf(run_m[v], lg[i][v]);
+            for (int v = 0; v < 16; ++v) {
+                lg[i][v] = lg[i][v] * scale + kbv;
+                run_m[v] = fmaxf(run_m[v], lg[i][v]);
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int qi = qi0 + mfma32_row(v, lane);
+                const bool valid = key < S && key <= row0 + qi;
+                lg[i][v] = valid ? lg[i][v] * scale + kbv : -INFINITY;
+                run_m[v] = fmaxf(run_m[v], lg[i][v]);
+            }
         }
     }
-    __shared__ float sh_m[SCR_WAVES][32], sh_l[SCR_WAVES][32];
+    __shared__ float sh_m[NW][32], sh_l[NW][32];
     // row maxima: over the 32 lanes of a half-wave, then over the waves
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-        for (int o = 16; o > 0; o >>= 1) run_m[v] = fmaxf(run_m[v], __shfl_xor(run_m[v], o));
+    for (int v = 0; v < 16; ++v) run_m[v] = half_wave_all(run_m[v], [](float a, float c) { return fmaxf(a, c); });
     if (fr == 0) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) sh_m[wave][mfma32_row(v, lane)] = run_m[v];
@@ -369,7 +394,7 @@ __global__ __launch_bounds__(SCR_THREADS) void score_probs_reg_kernel(
         const int r = mfma32_row(v, lane);
         float gm = sh_m[0][r];
 #pragma unroll
-        for (int w = 1; w < SCR_WAVES; ++w) gm = fmaxf(gm, sh_m[w][r]);
+        for (int w = 1; w < NW; ++w) gm = fmaxf(gm, sh_m[w][r]);
         run_m[v] = gm;     // finite: key 0 is visible to every query
         run_l[v] = 0.f;
     }
@@ -381,8 +406,7 @@ __global__ __launch_bounds__(SCR_THREADS) void score_probs_reg_kernel(
             run_l[v] += lg[i][v];
         }
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-        for (int o = 16; o > 0; o >>= 1) run_l[v] += __shfl_xor(run_l[v], o);
+    for (int v = 0; v < 16; ++v) run_l[v] = half_wave_all(run_l[v], [](float a, float c) { return a + c; });
     if (fr == 0) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) sh_l[wave][mfma32_row(v, lane)] = run_l[v];
@@ -393,12 +417,12 @@ __global__ __launch_bounds__(SCR_THREADS) void score_probs_reg_kernel(
         const int r = mfma32_row(v, lane);
         float gl = 0.f;
 #pragma unroll
-        for (int w = 0; w < SCR_WAVES; ++w) gl += sh_l[w][r];
+        for (int w = 0; w < NW; ++w) gl += sh_l[w][r];
         run_l[v] = 1.0f / gl;
     }
 #pragma unroll
     for (int i = 0; i < KBW; ++i) {
-        const int kb = wave + SCR_WAVES * i;
+        const int kb = wave + NW * i;
         const int key = kb * 32 + fr;
         if (COLSUM) {
             float csum = 0.f;   // masked entries hold exp(-inf) = 0
@@ -409,10 +433,11 @@ __global__ __launch_bounds__(SCR_THREADS) void score_probs_reg_kernel(
             if (fg == 0 && kb < n_kb && key < n_out)
                 probs[(((size_t)b * H + h) * gridDim.x + qt) * n_out + key] = csum;
         } else if (kb < n_kb && key < S) {
+            float* out = probs + (((size_t)b * H + h) * nq + qi0) * S + key;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int qi = qi0 + mfma32_row(v, lane);
-                if (qi < nq) probs[(((size_t)b * H + h) * nq + qi) * S + key] = lg[i][v] * run_l[v];
+                const int r = mfma32_row(v, lane);
+                if (qi0 + r < nq) out[(size_t)r * S] = lg[i][v] * run_l[v];
             }
         }
     }
@@ -423,13 +448,14 @@ static bool launch_score_reg(const bf16_t* q, int ldq, int q_rows, const bf16_t*
                              const float* key_bias, int B, int S, int H, int nq, float scale,
                              float* out, int n_out, hipStream_t st) {
     dim3 grid((nq + 31) / 32, H, B);
-    const int need = ((S + 31) / 32 + SCR_WAVES - 1) / SCR_WAVES;  // key blocks per wave
-#define MVLA_SCR(KBW)                                                                       \
-    hipLaunchKernelGGL((score_probs_reg_kernel<DH, KBW, COLSUM>), grid, dim3(SCR_THREADS), 0, st, \
+    const int blocks = (S + 31) / 32;
+#define MVLA_SCR(NW, KBW, AHEAD)                                                            \
+    hipLaunchKernelGGL((score_probs_reg_kernel<DH, NW, KBW, AHEAD, COLSUM>), grid, dim3(NW * 64), 0, st, \
                        q, ldq, q_rows, k, ldk, key_bias, S, H, nq, scale, out, n_out)
-    if (need <= 3) MVLA_SCR(3);
-    else if (need <= 6) MVLA_SCR(6);
-    else if (need <= 8) MVLA_SCR(8);
+    if (blocks <= 8 * 1) MVLA_SCR(8, 1, 1);
+    else if (blocks <= 8 * 3) MVLA_SCR(8, 3, 3);
+    else if (blocks <= 8 * 6) MVLA_SCR(8, 6, 2);
+    else if (blocks <= 8 * 8) MVLA_SCR(8, 8, 2);
     else return false;
 #undef MVLA_SCR
     return true;
