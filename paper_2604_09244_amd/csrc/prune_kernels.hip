@@ -37,9 +37,11 @@ constexpr int SAL_LPR = 16;                        // lanes per row-group
 // tensor there: 8.9 MB read non-temporally made that pair 1.6 us slower.
 constexpr size_t SAL_STREAM_BYTES = size_t(256) << 20;
 constexpr int FIN_U = 8;            // columns a thread takes at a time when a sample is finished
-constexpr long SOLO_MAX = 16384;    // most attention values of a sample that one workgroup sums (64 KiB)
+// Most attention values of a sample that one workgroup sums (32 KiB).  64 rows x 128 columns: 6.8 us, 10.4
+// with the columns spread over four workgroups; 32 rows x 512 columns: 15.1 us against 9.7 with eight.
+constexpr long SOLO_MAX = 8192;
 constexpr int SOLO_MAX_ROWS = 128;  // ... most rows (eight a thread)
-constexpr int SOLO_MAX_COLS = 2048; // ... and most columns (their sums of four waves sit in LDS)
+constexpr int SOLO_MAX_COLS = 1024; // ... and most columns (their sums of four waves sit in LDS)
 constexpr int SAL_GROUPS = SAL_THREADS / SAL_LPR;  // 16 row-groups per block
 
 typedef float f32v4_t __attribute__((ext_vector_type(4)));
@@ -191,8 +193,7 @@ __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
 // The fused step of a sample whose rows are few: one workgroup sums all its columns (same order of
 // additions as an unsplit salience_kernel) and goes straight on to budget and selection.  With
 // several workgroups a sample, the store, arrival and load that join them (a memory round trip
-// each) cost more than one compute unit needs to read 64 KiB: 10.4 -> 6.8 us
-// for 64 rows x 128 columns.
+// each) cost more than one compute unit needs to read 32 KiB (see SOLO_MAX).
 template <int VEC>
 __global__ __launch_bounds__(SAL_THREADS) void prune_solo_kernel(const float* __restrict__ attn, int R, int S,
                                                                  int n_vis, float inv_rows,
@@ -297,7 +298,7 @@ static int launch_salience_any(const float* attn, int B, int H, int Nq, int S, i
         f = *fused;
         f.sample_counters = counters + (size_t)B * chunks;
         lds = (size_t)max(f.n2 + f.n3, 1) * 4;   // selection keys of both segments
-        if (salience_solo(R, n_vis)) {           // (at most 8 KiB of keys and 33 KiB of sums)
+        if (salience_solo(R, n_vis)) {           // (at most 4 KiB of keys and 17 KiB of sums)
             const int cw = SAL_LPR * (vec4 ? 4 : 1);
             lds += (size_t)(SAL_THREADS / 64) * chunks * cw * 4;
             if (vec4)

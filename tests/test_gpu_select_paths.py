@@ -45,9 +45,9 @@ def test_select_paths(ctx, n2, n3, kind):
         assert np.array_equal(got.cpu().numpy(), O.select_topk(s, k2k3, n2, n3, 3)), (n2, n3, kind, K)
 
 
-# H * Nq rows x columns: 16384 values is the most one workgroup takes, 128 rows and 2048 columns
-@pytest.mark.parametrize("H,Nq,n2,n3,nt", [(4, 16, 64, 64, 16), (4, 32, 64, 64, 32), (4, 33, 50, 50, 33),
-                                           (4, 32, 64, 65, 32), (1, 8, 1024, 1024, 8), (1, 8, 1025, 1024, 7),
+# H * Nq rows x columns: 8192 values is the most one workgroup takes, 128 rows and 1024 columns
+@pytest.mark.parametrize("H,Nq,n2,n3,nt", [(4, 16, 64, 64, 16), (4, 16, 64, 65, 16), (4, 32, 32, 32, 32), (4, 33, 30, 30, 33),
+                                           (4, 32, 64, 65, 32), (1, 8, 512, 512, 8), (1, 7, 513, 512, 7),
                                            (4, 8, 256, 256, 32), (2, 8, 3, 700, 9), (4, 160, 300, 700, 160)])
 def test_fused_step_equals_single_calls(ctx, H, Nq, n2, n3, nt):
     B, D, S = 3, 64, n2 + n3 + nt
