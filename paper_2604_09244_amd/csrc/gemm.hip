@@ -38,13 +38,15 @@
 
 namespace mvla {
 
-// direct global -> LDS copy of 16 bytes per lane: the wave's 64 lanes land on 1 KiB starting
-// at the wave-uniform LDS byte address lds_addr.  Not tracked by the compiler's wait-count
-// insertion; every consumer is ordered behind wait_vm<>() and a workgroup barrier.
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr),
-                 "v"(g)
-                 : "memory", "m0");
+// Direct global -> LDS copy of 16 bytes per lane, from a wave-uniform base and a 32-bit per-lane byte
+// offset: the wave's 64 lanes land on 1 KiB starting at the wave-uniform LDS byte address lds_base + OFF.
+// Not tracked by the compiler's wait-count insertion; every consumer is ordered behind wait_vm<>() and a
+// workgroup barrier.
+template <int OFF>
+__device__ __forceinline__ void dma16_at(const void* base, uint32_t off, uint32_t lds_base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base),
+                 "v"(off), "s"(base), "i"(OFF)
+                 : "memory", "m0", "scc");
 }
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -57,13 +59,15 @@ __device__ __forceinline__ void wait_vm() {
 typedef float f32q_t __attribute__((ext_vector_type(4)));
 // The wait states after the store keep the next VALU write away from the data registers
 // (a store of more than 64 bits reads them late; the compiler cannot see that inside asm).
-__device__ __forceinline__ void st16_coherent(float* p, f32q_t v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 2" ::"v"(p), "v"(v) : "memory");
+// (wave-uniform base and a 32-bit per-lane byte offset: with whole addresses per access the compiler keeps
+// a table of 64-bit constants in scalar registers, more than there are)
+__device__ __forceinline__ void st16_coherent(float* base, uint32_t off, f32q_t v) {
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 2" ::"v"(off), "v"(v), "s"(base) : "memory");
 }
 // Issues the load; the value may be used only after settle() has been applied to it.
-__device__ __forceinline__ f32q_t ld16_coherent(const float* p) {
+__device__ __forceinline__ f32q_t ld16_coherent(const float* base, uint32_t off) {
     f32q_t v;
-    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
+    asm volatile("global_load_dwordx4 %0, %1, %2 sc1" : "=v"(v) : "v"(off), "s"(base) : "memory");
     return v;
 }
 // Output (and residual) of the epilogues as a bounds-checked buffer: a lane whose byte offset lies
@@ -102,6 +106,7 @@ struct GemmPlan {
     int dp_grid;      // dp_tiles rounded up to a multiple of 8 (workgroup ids 0 .. dp_grid-1)
     int sk_tiles;     // tiles of the last partial round, split along K
     int sk_blocks;    // workgroups sharing the sk_tiles * k_tiles iterations
+    int quarter_of;   // >= 0: the dp_tiles are quarters (128x128) of the 256x256 tiles from this one on
 };
 
 // Workgroup ids are dealt round-robin to the 8 XCDs (each has its own L2).  Give every XCD a
@@ -128,7 +133,8 @@ struct EpiGeom {
     static constexpr int TM = (BM / 32 + WM - 1) / WM * 32;   // rows of a wave row
     static constexpr int PASSES = BM * LDT * 4 <= CAP ? 1 : WM;
     static constexpr int RP = PASSES == 1 ? BM : TM;
-    static constexpr int BYTES = RP * LDT * 4;
+    // (where waves hold 15 or more blocks, a spare strip of 16 rows: see the lay-down)
+    static constexpr int BYTES = (RP + (TM / 32 * (BN / 64) >= 15 ? 16 : 0)) * LDT * 4;
     static_assert(BYTES <= CAP, "epilogue tile does not fit the LDS");
     static_assert(TM * WM == BM || PASSES == WM, "overlapping wave rows go one per pass");
 };
@@ -159,14 +165,6 @@ constexpr int PT_TLD = 36;                                   // floats per row o
 constexpr int PT_TURN = 32 * PT_TLD;                         // floats of it
 constexpr int PT_LDS_BYTES = 2 * PT_STAGE * 16 + 4 * PT_TURN * 4;
 
-// direct global -> LDS copy with a wave-uniform base and a 32-bit per-lane byte offset
-// (LDS address: lds_base + the immediate OFF)
-template <int OFF>
-__device__ __forceinline__ void dma16_at(const void* base, uint32_t off, uint32_t lds_base) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base),
-                 "v"(off), "s"(base), "i"(OFF)
-                 : "memory", "m0", "scc");
-}
 // Workgroup barrier for LDS traffic: this wave's LDS reads have returned; its global stores (of the
 // epilogue before) may be on their way, which __syncthreads() would wait for.
 __device__ __forceinline__ void lds_only_barrier() {
@@ -181,7 +179,7 @@ __device__ __forceinline__ void persistent_body(const bf16_t* __restrict__ A, in
     extern __shared__ uint4 lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int fr = lane & 31, fg = lane >> 5;
+
     const int k_tiles = plan.k_tiles;
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
     float* turn = reinterpret_cast<float*>(lds + 2 * PT_STAGE) + wave * PT_TURN;
@@ -598,8 +596,7 @@ __device__ __forceinline__ void tile_body(
     float* __restrict__ partial, uint32_t* __restrict__ counters, const RopeEpilogue& rope) {
     constexpr int NT = WM * WN * 64;
     constexpr int CPR = BK / 8;             // 16-byte chunks per LDS row
-    constexpr int KS = BK / 16;             // MFMA k-steps per slab
-    // A wave owns FM x FN accumulator blocks of 32x32.  When the tile's 32-row blocks do not
+    // A wave owns FM x FN blocks of 32x32, four 16x16 accumulators each.  When the tile's 32-row blocks do not
     // divide among the WM wave rows (288 rows on two wave rows), every wave row still takes
     // FM = ceil blocks and the last one starts early: the rows both cover are computed twice
     // (identical values) so that the main loop stays free of branches.
@@ -610,15 +607,15 @@ __device__ __forceinline__ void tile_body(
     constexpr int A_LD = A_SLOTS / NT, B_LD = B_SLOTS / NT;
     constexpr int P = A_LD + B_LD;          // direct loads per thread per slab
     static_assert(A_SLOTS % NT == 0 && B_SLOTS % NT == 0, "tile/thread mismatch");
-    static_assert(KS % 2 == 0 && NS >= 2, "");
+    static_assert(BK == 64 && CPR == 8 && NS >= 2, "two k-steps of 32 a slab");
+    constexpr int GM = 2 * FM, GN = 2 * FN; // 16-row and 16-column blocks of a wave
 
     extern __shared__ uint4 lds[];
     __shared__ int sh_last;
     __shared__ int sh_slot[SK_MAX_PIECES];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int wrow0 = min(wm * TM, BM - TM);   // first tile row of this wave's blocks
-    const int fr = lane & 31, fg = lane >> 5;
     const int k_tiles = plan.k_tiles;
 
     // ---- which part of which tile is ours --------------------------------------------------
@@ -639,6 +636,9 @@ __device__ __forceinline__ void tile_body(
     }
 
     for (int seg = 0; seg < n_seg_work; ++seg) {
+        int stid = tid;   // (per-lane indices of the main loop are made per segment, not held across epilogues)
+        asm volatile("" : "+v"(stid));
+        const int fr = stid & 15, fq = (stid & 63) >> 4;   // row in a 16-row block; 16-byte chunk of a k-step's four
         int lin, k0, k1, sk_tile = -1, first_blk = 0, last_blk = 0;
         if (is_dp) {
             lin = xcd_chunked(blockIdx.x, plan.dp_tiles);
@@ -657,95 +657,101 @@ __device__ __forceinline__ void tile_body(
             last_blk = (int)((((long)(sk_tile + 1) * k_tiles) * plan.sk_blocks - 1) / total);
         }
         int tile_m, tile_n;
-        tile_of(lin, plan.tiles_m, plan.tiles_n, &tile_m, &tile_n);
-        const int m0 = tile_m * BM, n0 = tile_n * BN;
+        int m0, n0;
+        if (BM == 128 && BN == 128 && WM * WN == 8 && plan.quarter_of >= 0) {
+            tile_of(plan.quarter_of + (lin >> 2), plan.tiles_m, plan.tiles_n, &tile_m, &tile_n);
+            m0 = tile_m * 256 + ((lin >> 1) & 1) * 128;
+            n0 = tile_n * 256 + (lin & 1) * 128;
+            if (m0 >= M || n0 >= N) continue;
+        } else {
+            tile_of(lin, plan.tiles_m, plan.tiles_n, &tile_m, &tile_n);
+            m0 = tile_m * BM;
+            n0 = tile_n * BN;
+        }
 
         // ---- direct-load mapping: op i covers slot i*NT + tid of the A (or W) tile ----------
-        const bf16_t* a_src[A_LD];
-        const bf16_t* b_src[B_LD];
-        uint32_t a_lds[A_LD], b_lds[B_LD];
-        const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+        // (wave-uniform base of the tile's rows, per-lane 32-bit byte offsets from there)
+        const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * lda);
+        const char* b_base = reinterpret_cast<const char*>(W + (size_t)n0 * K);
+        uint32_t a_off[A_LD], b_off[B_LD];
+        const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds + (uint32_t)wave * 1024u);
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
-            const int sl = i * NT + tid, row = sl / CPR, ch = (sl % CPR) ^ swz<CPR>(row);
-            a_src[i] = A + (size_t)min(m0 + row, M - 1) * lda + ch * 8;
-            a_lds[i] = __builtin_amdgcn_readfirstlane(
-                lds_base + (uint32_t)(i * NT + wave * 64) * 16u);
+            const int sl = i * NT + stid, row = sl / CPR, ch = (sl % CPR) ^ swz<CPR>(row);
+            a_off[i] = ((uint32_t)min(row, M - 1 - m0) * (uint32_t)lda + (uint32_t)ch * 8u) * 2u;
         }
 #pragma unroll
         for (int i = 0; i < B_LD; ++i) {
-            const int sl = i * NT + tid, row = sl / CPR, ch = (sl % CPR) ^ swz<CPR>(row);
-            b_src[i] = W + (size_t)min(n0 + row, N - 1) * K + ch * 8;
-            b_lds[i] = __builtin_amdgcn_readfirstlane(
-                lds_base + (uint32_t)(A_SLOTS + i * NT + wave * 64) * 16u);
+            const int sl = i * NT + stid, row = sl / CPR, ch = (sl % CPR) ^ swz<CPR>(row);
+            b_off[i] = ((uint32_t)min(row, N - 1 - n0) * (uint32_t)K + (uint32_t)ch * 8u) * 2u;
         }
-        int a_row[FM], b_row[FN];
-#pragma unroll
-        for (int i = 0; i < FM; ++i) a_row[i] = wrow0 + i * 32 + fr;
-#pragma unroll
-        for (int j = 0; j < FN; ++j) b_row[j] = wn * TN + j * 32 + fr;
+        // load l (of P) of the slab at byte offset koff into the stage at lds_wave + soff
+        auto load_one = [&](int l, size_t koff, uint32_t soff) __attribute__((always_inline)) {
+            switch (l) {
+#define MVLA_CASE(L) \
+    case L: \
+        dma16_at<L * NT * 16>(L < A_LD ? a_base + koff : b_base + koff, \
+                              L < A_LD ? a_off[L < A_LD ? L : 0] : b_off[L >= A_LD && L < P ? L - A_LD : 0], \
+                              lds_wave + soff); \
+        break;
+                MVLA_CASE(0) MVLA_CASE(1) MVLA_CASE(2) MVLA_CASE(3) MVLA_CASE(4) MVLA_CASE(5) MVLA_CASE(6) MVLA_CASE(7)
+                MVLA_CASE(8) MVLA_CASE(9) MVLA_CASE(10) MVLA_CASE(11) MVLA_CASE(12) MVLA_CASE(13) MVLA_CASE(14)
+                MVLA_CASE(15)
+#undef MVLA_CASE
+            }
+        };
+        static_assert(P <= 16, "load_one has sixteen cases");
+        const int a_row = (wrow0 + fr) * CPR, b_row = (BM + wn * TN + fr) * CPR;
+        const int sw = swz<CPR>(fr);   // (rows of a lane differ by multiples of 16: one pattern)
 
-        f32x16_t acc[FM][FN];
+        f32x4_t acc[GM][GN];
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < GM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int j = 0; j < GN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
 #define MVLA_ISSUE(KT, STG)                                                                    \
     {                                                                                          \
-        const int koff = min((KT), k1 - 1) * BK;                                               \
+        const size_t koff = (size_t)min((KT), k1 - 1) * (BK * 2);                              \
         const uint32_t soff = (uint32_t)(STG) * STAGE * 16u;                                   \
-        _Pragma("unroll") for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + koff, a_lds[i] + soff); \
-        _Pragma("unroll") for (int i = 0; i < B_LD; ++i) dma16(b_src[i] + koff, b_lds[i] + soff); \
+        _Pragma("unroll") for (int i = 0; i < P; ++i) load_one(i, koff, soff);                 \
     }
-#define MVLA_READ_FRAGS(AF, BF, STG, S)                                                        \
+// fragment read R of the GM + GN of k-step KS of stage STG, in the order the products need them
+#define MVLA_READ_ONE(AF, BF, STG, KS, R)                                                      \
     {                                                                                          \
-        const uint4* As_ = lds + (STG) * STAGE;                                                \
-        const uint4* Bs_ = As_ + BM * CPR;                                                     \
-        _Pragma("unroll") for (int i = 0; i < FM; ++i) AF[i] =                                 \
-            As_[a_row[i] * CPR + (((S) * 2 + fg) ^ swz<CPR>(a_row[i]))];                            \
-        _Pragma("unroll") for (int j = 0; j < FN; ++j) BF[j] =                                 \
-            Bs_[b_row[j] * CPR + (((S) * 2 + fg) ^ swz<CPR>(b_row[j]))];                            \
+        const uint4* st_ = lds + (STG) * STAGE + (((KS) * 4 + fq) ^ sw);                       \
+        if ((R) == 0 || (R) > GN) AF[(R) > GN ? (R) - GN : 0] = st_[a_row + ((R) > GN ? (R) - GN : 0) * 16 * CPR]; \
+        else BF[(R) > 0 && (R) <= GN ? (R) - 1 : 0] = st_[b_row + ((R) > 0 ? (R) - 1 : 0) * 16 * CPR]; \
     }
-#define MVLA_MFMA(AF, BF)                                                                      \
+#define MVLA_READ_FRAGS(AF, BF, STG, KS)                                                       \
+    _Pragma("unroll") for (int r_ = 0; r_ < GM + GN; ++r_) MVLA_READ_ONE(AF, BF, STG, KS, r_)
+// block rows [I0, I1) of a k-step's MFMAs; between them the NRD fragment reads of k-step RKS of stage
+// RSTG and the direct loads [L0, L1) of slab KT into stage STG, dealt out evenly
+#define MVLA_STEP(AF, BF, I0, I1, NRD, RA, RB, RSTG, RKS, KT, STG, L0, L1)                     \
     {                                                                                          \
-        _Pragma("unroll") for (int i = 0; i < FM; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j) \
-            acc[i][j] = mfma32(BF[j], AF[i], acc[i][j]);                                       \
-    }
-
-// Scheduling of one k-step: the fragment reads of the next step are dealt out between this
-// step's MFMAs (MPR MFMAs, then one read, ...) instead of going out in one burst.
-#define MVLA_SPREAD_READS                                                                      \
-    {                                                                                          \
-        constexpr int MPR = (FM * FN) / (FM + FN) > 0 ? (FM * FN) / (FM + FN) : 1;             \
-        _Pragma("unroll") for (int r = 0; r < FM + FN; ++r) {                                  \
-            __builtin_amdgcn_sched_group_barrier(0x008, MPR, 0);                               \
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                 \
-        }                                                                                      \
-        __builtin_amdgcn_sched_group_barrier(0x008, FM * FN, 0);                               \
-        __builtin_amdgcn_sched_barrier(0);                                                     \
-    }
-// the MFMAs of one k-step with the direct loads of slab KT dealt out between them, one per MFMA
-// (a wave that is alone on its SIMD would otherwise issue nothing to the matrix core while it
-// sets up the loads)
-#define MVLA_MFMA_ISSUE(AF, BF, KT, STG)                                                       \
-    {                                                                                          \
-        const int koff = min((KT), k1 - 1) * BK;                                               \
+        const size_t koff = (size_t)min((KT), k1 - 1) * (BK * 2);                              \
         const uint32_t soff = (uint32_t)(STG) * STAGE * 16u;                                   \
-        int n_ = 0;                                                                            \
-        _Pragma("unroll") for (int i = 0; i < FM; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j) { \
-            acc[i][j] = mfma32(BF[j], AF[i], acc[i][j]);                                       \
-            if (n_ < A_LD) dma16(a_src[n_ < A_LD ? n_ : 0] + koff, a_lds[n_ < A_LD ? n_ : 0] + soff); \
-            else if (n_ < P) dma16(b_src[n_ < P ? n_ - A_LD : 0] + koff, b_lds[n_ < P ? n_ - A_LD : 0] + soff); \
+        constexpr int NM_ = ((I1) - (I0)) * GN, NL_ = (L1) - (L0);                             \
+        constexpr int EVERY_L = NL_ > 0 && NM_ / (NL_ > 0 ? NL_ : 1) > 0 ? NM_ / (NL_ > 0 ? NL_ : 1) : 1; \
+        constexpr int EVERY_R = (NRD) > 0 && NM_ / ((NRD) > 0 ? (NRD) : 1) > 0 ? NM_ / ((NRD) > 0 ? (NRD) : 1) : 1; \
+        int l_ = (L0), r_ = 0;                                                                 \
+        _Pragma("unroll") for (int n_ = 0; n_ < NM_; ++n_) {                                   \
+            const int i_ = (I0) + n_ / GN, j_ = n_ % GN;                                       \
+            acc[i_][j_] = mfma16(BF[j_], AF[i_], acc[i_][j_]);                                 \
+            if (n_ % EVERY_R == 0 && r_ < (NRD)) {                                             \
+                MVLA_READ_ONE(RA, RB, RSTG, RKS, r_)                                           \
+                ++r_;                                                                          \
+            }                                                                                  \
+            if (n_ % EVERY_L == EVERY_L - 1 && l_ < (L1)) {                                    \
+                load_one(l_, koff, soff);                                                      \
+                ++l_;                                                                          \
+            }                                                                                  \
             __builtin_amdgcn_sched_barrier(0);                                                 \
-            ++n_;                                                                              \
         }                                                                                      \
-        _Pragma("unroll") for (int r = FM * FN; r < P; ++r) {                                  \
-            if (r < A_LD) dma16(a_src[r < A_LD ? r : 0] + koff, a_lds[r < A_LD ? r : 0] + soff);     \
-            else dma16(b_src[r - A_LD] + koff, b_lds[r - A_LD] + soff);                        \
-        }                                                                                      \
+        _Pragma("unroll") for (int q_ = 0; q_ < GM + GN; ++q_)                                 \
+            if (q_ >= r_ && q_ < (NRD)) MVLA_READ_ONE(RA, RB, RSTG, RKS, q_)                   \
+        _Pragma("unroll") for (int q_ = 0; q_ < P; ++q_)                                       \
+            if (q_ >= l_ && q_ < (L1)) load_one(q_, koff, soff);                               \
     }
 
         // every thread of the workgroup has left the previous segment's LDS reads behind
@@ -757,144 +763,66 @@ __device__ __forceinline__ void tile_body(
         // ---- prologue: NS-1 slabs in flight, then one more behind the first barrier ---------
 #pragma unroll
         for (int s = 0; s < NS - 1; ++s) MVLA_ISSUE(k0 + s, s)
-        uint4 af0[FM], bf0[FN], af1[FM], bf1[FN];
+        uint4 af0[GM], bf0[GN], af1[GM], bf1[GN];   // the two k-steps of a slab
         wait_vm<(NS - 2) * P>();
         __syncthreads();
-        if constexpr (NS >= 3 && KS == 4 && P >= 4) {   // (the loop's first three k-steps issue the rest)
-            const int koff = min(k0 + NS - 1, k1 - 1) * BK;
+        // Three or more stages: there is always a free one, and the loads of a slab go out half in the
+        // last k-step of one iteration and half in the first of the next (all in one, they kept the
+        // waves standing at load issue: the load unit of a CU takes one 64-lane load per 16 clocks).
+        constexpr bool SPREAD = NS >= 3;
+        // Four-wave shapes with two stages and registers to spare: a slab's second k-step is read during
+        // the first half of its first one, so the stage is free from there on and the loads go out
+        // a third each over the remaining halves.
+        constexpr bool DEEP = WM * WN == 4 && NS == 2;
+        if constexpr (SPREAD) {   // (the loop's first k-step issues the rest)
+            const size_t koff = (size_t)min(k0 + NS - 1, k1 - 1) * (BK * 2);
             const uint32_t soff = (uint32_t)(NS - 1) * STAGE * 16u;
 #pragma unroll
-            for (int r = 0; r < P / 4; ++r) {
-                if (r < A_LD) dma16(a_src[r < A_LD ? r : 0] + koff, a_lds[r < A_LD ? r : 0] + soff);
-                else dma16(b_src[r < P ? r - A_LD : 0] + koff, b_lds[r < P ? r - A_LD : 0] + soff);
-            }
+            for (int r = 0; r < P / 2; ++r) load_one(r, koff, soff);
         } else {
             MVLA_ISSUE(k0 + NS - 1, NS - 1)
         }
         MVLA_READ_FRAGS(af0, bf0, 0, 0)
         int stage = 0;
-        // Four-wave shapes (registers to spare).  The load unit of a CU takes one 64-lane direct
-        // load per 16 clocks, so the 64 loads of a 256x256x64 slab need 1024 clocks of it -- two
-        // k-steps.  Issued all in the last k-step (as the other shapes do), they kept the waves
-        // standing at load issue instead of feeding the matrix core: 1100 - 1800 clocks for that
-        // k-step instead of 512 (cycle counters in a working copy).  Here a slab's fragments are
-        // read two k-steps ahead -- those of k-steps 2 and 3 during k-step 0, those of the next
-        // slab's k-steps 0 and 1 during k-step 3, one LDS read after each MFMA -- so the stage is
-        // free after k-step 0 and the loads of slab kt+2 go out a third each over k-steps 1, 2
-        // and 3, with the wait for slab kt+1 before the last.
-        constexpr bool DEEP = WM * WN == 4 && NS == 2 && KS == 4 && P >= 3;
-        // Shapes with three stages always have a free one: the loads of a slab go out a quarter
-        // per k-step (the last k-step of one iteration and the first three of the next) instead
-        // of all in one, for the same reason.
-        constexpr bool SPREAD4 = NS >= 3 && KS == 4 && P >= 4;
-        constexpr int NR = 2 * (FM + FN);   // fragment reads of two k-steps
-// read number R of the fragments of k-steps SA (first FM + FN reads, into AFA/BFA) and
-// SB (the rest, into AFB/BFB) of stage STG
-#define MVLA_READ_ONE(AFA, BFA, AFB, BFB, STG, SA, SB, R)                                      \
-    {                                                                                          \
-        const uint4* As_ = lds + (STG) * STAGE;                                                \
-        const uint4* Bs_ = As_ + BM * CPR;                                                     \
-        const int set_ = (R) / (FM + FN), idx_ = (R) % (FM + FN);                              \
-        const int ks_ = set_ == 0 ? (SA) : (SB);                                               \
-        if (idx_ < FM) {                                                                       \
-            const int ii_ = idx_ < FM ? idx_ : 0;                                              \
-            const uint4 v_ = As_[a_row[ii_] * CPR + ((ks_ * 2 + fg) ^ swz<CPR>(a_row[ii_]))];  \
-            if (set_ == 0) AFA[ii_] = v_; else AFB[ii_] = v_;                                  \
-        } else {                                                                               \
-            const int jj_ = idx_ >= FM ? idx_ - FM : 0;                                        \
-            const uint4 v_ = Bs_[b_row[jj_] * CPR + ((ks_ * 2 + fg) ^ swz<CPR>(b_row[jj_]))];  \
-            if (set_ == 0) BFA[jj_] = v_; else BFB[jj_] = v_;                                  \
-        }                                                                                      \
-    }
-// the MFMAs of one k-step; after MFMA n comes fragment read n (of NRD) of (RSTG; SA, SB), and
-// the direct loads [L0, L1) of slab KT into stage STG are dealt out evenly
-#define MVLA_STEP(AF, BF, NRD, AFA, BFA, AFB, BFB, RSTG, SA, SB, KT, STG, L0, L1)            \
-    {                                                                                          \
-        const int koff = min((KT), k1 - 1) * BK;                                               \
-        const uint32_t soff = (uint32_t)(STG) * STAGE * 16u;                                   \
-        constexpr int NL_ = (L1) - (L0);                                                       \
-        constexpr int EVERY_ = NL_ > 0 && (FM * FN) / (NL_ > 0 ? NL_ : 1) > 0 ? (FM * FN) / (NL_ > 0 ? NL_ : 1) : 1; \
-        int n_ = 0, l_ = (L0);                                                                 \
-        _Pragma("unroll") for (int i = 0; i < FM; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j) { \
-            acc[i][j] = mfma32(BF[j], AF[i], acc[i][j]);                                       \
-            if (n_ < (NRD)) MVLA_READ_ONE(AFA, BFA, AFB, BFB, RSTG, SA, SB, n_)                \
-            if (n_ % EVERY_ == EVERY_ - 1 && l_ < (L1)) {                                      \
-                if (l_ < A_LD) dma16(a_src[l_ < A_LD ? l_ : 0] + koff, a_lds[l_ < A_LD ? l_ : 0] + soff); \
-                else dma16(b_src[l_ < P ? l_ - A_LD : 0] + koff, b_lds[l_ < P ? l_ - A_LD : 0] + soff);   \
-                ++l_;                                                                          \
-            }                                                                                  \
-            __builtin_amdgcn_sched_barrier(0);                                                 \
-            ++n_;                                                                              \
-        }                                                                                      \
-        _Pragma("unroll") for (int r = FM * FN; r < (NRD); ++r)                                \
-            MVLA_READ_ONE(AFA, BFA, AFB, BFB, RSTG, SA, SB, r)                                 \
-        _Pragma("unroll") for (int r = 0; r < P; ++r)                                          \
-            if (r >= l_ && r < (L1)) {                                                         \
-                if (r < A_LD) dma16(a_src[r < A_LD ? r : 0] + koff, a_lds[r < A_LD ? r : 0] + soff); \
-                else dma16(b_src[r - A_LD] + koff, b_lds[r - A_LD] + soff);                    \
-            }                                                                                  \
-    }
         if constexpr (DEEP) {
-            uint4 af2[FM], bf2[FN], af3[FM], bf3[FN];
-            constexpr int L1_ = P / 3, L2_ = 2 * P / 3;
-            MVLA_READ_FRAGS(af1, bf1, 0, 1)
+            constexpr int L1_ = P / 3, L2_ = 2 * P / 3, GH = GM / 2;
             for (int kt = k0; kt < k1; ++kt) {
                 const int nstage = stage ^ 1;
-                // k-step 0, reading the fragments of k-steps 2 and 3: after it this slab is in registers
-                MVLA_STEP(af0, bf0, NR, af2, bf2, af3, bf3, stage, 2, 3, kt + 2, stage, 0, 0)
-                __syncthreads();   // ... for every wave: the stage is free for slab kt+2
-                MVLA_STEP(af1, bf1, 0, af2, bf2, af3, bf3, stage, 2, 3, kt + 2, stage, 0, L1_)
-                MVLA_STEP(af2, bf2, 0, af2, bf2, af3, bf3, stage, 2, 3, kt + 2, stage, L1_, L2_)
+                MVLA_STEP(af0, bf0, 0, GH, GM + GN, af1, bf1, stage, 1, kt + 2, stage, 0, 0)
+                __syncthreads();   // this slab is in every wave's registers: the stage is free for slab kt+2
+                MVLA_STEP(af0, bf0, GH, GM, 0, af1, bf1, stage, 1, kt + 2, stage, 0, L1_)
+                MVLA_STEP(af1, bf1, 0, GH, 0, af1, bf1, stage, 1, kt + 2, stage, L1_, L2_)
                 // slab kt+1 has landed for every wave (the two thirds of slab kt+2 may be in flight)
                 wait_vm<L2_>();
                 __syncthreads();
-                // k-step 3, reading the fragments of k-steps 0 and 1 of the next slab
-                MVLA_STEP(af3, bf3, NR, af0, bf0, af1, bf1, nstage, 0, 1, kt + 2, stage, L2_, P)
+                MVLA_STEP(af1, bf1, GH, GM, GM + GN, af0, bf0, nstage, 0, kt + 2, stage, L2_, P)
                 stage = nstage;
             }
-        } else if constexpr (SPREAD4) {
-            constexpr int Q1 = P / 4, Q2 = P / 2, Q3 = 3 * P / 4;
+        } else if constexpr (SPREAD) {
             for (int kt = k0; kt < k1; ++kt) {
                 const int nstage = stage + 1 == NS ? 0 : stage + 1;
                 const int pstage = stage == 0 ? NS - 1 : stage - 1;   // freed one iteration ago
-                MVLA_STEP(af0, bf0, FM + FN, af1, bf1, af1, bf1, stage, 1, 1, kt + NS - 1, pstage, Q1, Q2)
-                MVLA_STEP(af1, bf1, FM + FN, af0, bf0, af0, bf0, stage, 2, 2, kt + NS - 1, pstage, Q2, Q3)
-                MVLA_STEP(af0, bf0, FM + FN, af1, bf1, af1, bf1, stage, 3, 3, kt + NS - 1, pstage, Q3, P)
+                MVLA_STEP(af0, bf0, 0, GM, GM + GN, af1, bf1, stage, 1, kt + NS - 1, pstage, P / 2, P)
                 // slab kt+1 has landed for every wave; slab kt's stage is free for slab kt+NS
                 wait_vm<(NS - 2) * P>();
                 __syncthreads();
-                MVLA_STEP(af1, bf1, FM + FN, af0, bf0, af0, bf0, nstage, 0, 0, kt + NS, stage, 0, Q1)
+                MVLA_STEP(af1, bf1, 0, GM, GM + GN, af0, bf0, nstage, 0, kt + NS, stage, 0, P / 2)
                 stage = nstage;
             }
-        } else
-        for (int kt = k0; kt < k1; ++kt) {
-            const int nstage = stage + 1 == NS ? 0 : stage + 1;
-#pragma unroll
-            for (int s = 0; s < KS - 2; s += 2) {
-                MVLA_READ_FRAGS(af1, bf1, stage, s + 1)
-                MVLA_MFMA(af0, bf0)
-                MVLA_SPREAD_READS
-                MVLA_READ_FRAGS(af0, bf0, stage, s + 2)
-                MVLA_MFMA(af1, bf1)
-                MVLA_SPREAD_READS
+        } else {
+            for (int kt = k0; kt < k1; ++kt) {
+                const int nstage = stage ^ 1;
+                MVLA_STEP(af0, bf0, 0, GM, GM + GN, af1, bf1, stage, 1, kt, stage, 0, 0)
+                // slab kt+1 has landed for every wave; slab kt's stage is free for slab kt+2
+                wait_vm<0>();
+                __syncthreads();
+                MVLA_STEP(af1, bf1, 0, GM, GM + GN, af0, bf0, nstage, 0, kt + NS, stage, 0, P)
+                stage = nstage;
             }
-            MVLA_READ_FRAGS(af1, bf1, stage, KS - 1)
-            MVLA_MFMA(af0, bf0)
-            MVLA_SPREAD_READS
-            // slab kt+1 has landed for every wave; slab kt's stage is free for slab kt+NS
-            wait_vm<(NS - 2) * P>();
-            __syncthreads();
-            MVLA_READ_FRAGS(af0, bf0, nstage, 0)
-            __builtin_amdgcn_sched_barrier(0);
-            MVLA_MFMA_ISSUE(af1, bf1, kt + NS, stage)
-            stage = nstage;
         }
         wait_vm<0>();
 #undef MVLA_ISSUE
 #undef MVLA_READ_FRAGS
-#undef MVLA_MFMA
-#undef MVLA_MFMA_ISSUE
-#undef MVLA_SPREAD_READS
 #undef MVLA_READ_ONE
 #undef MVLA_STEP
 
@@ -907,18 +835,14 @@ __device__ __forceinline__ void tile_body(
             // slot 0 of a workgroup holds the piece of the tile its range starts in, slot 1 the next
             const int my_slot = 2 * sk_id + (seg == 0 ? 0 : 1);
             float* mine = partial + (size_t)my_slot * (BM * BN);
-            // 16 bytes per lane: register quad c of block (i,j) goes to float offset
-            // (((i*FN + j)*4 + c)*NT + tid)*4 of the slot
+            uint32_t so = (uint32_t)tid * 16u;
+            asm volatile("" : "+v"(so));
+            // 16 bytes per lane: block (i,j) goes to float offset ((i*GN + j)*NT + tid)*4 of the slot
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
+            for (int i = 0; i < GM; ++i)
 #pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        f32q_t q = {acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2],
-                                    acc[i][j][4 * c + 3]};
-                        st16_coherent(&mine[(((i * FN + j) * 4 + c) * NT + tid) * 4], q);
-                    }
+                for (int j = 0; j < GN; ++j)
+                    st16_coherent(mine, so + (uint32_t)((i * GN + j) * NT * 16), acc[i][j]);
             wait_vm<0>();     // this thread's partial sums have reached the coherent level
             __syncthreads();  // ... and so have everyone else's in the workgroup
             if (tid == 0) {
@@ -951,15 +875,14 @@ __device__ __forceinline__ void tile_body(
                                : (NQ % 8 == 0) ? 8 : 4;
             static_assert(NQ % CH == 0 && CH % 4 == 0, "");
             constexpr int PPR = (KEEP_OWN && 2 * NQ <= 16) ? 2 : 1;   // pieces per round trip
-            f32x16_t own[KEEP_OWN ? FM : 1][KEEP_OWN ? FN : 1];
+            f32x4_t own[KEEP_OWN ? GM : 1][KEEP_OWN ? GN : 1];
             const int my_piece = KEEP_OWN ? sk_id - first_blk : -1;
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
+            for (int i = 0; i < GM; ++i)
 #pragma unroll
-                for (int j = 0; j < FN; ++j) {
+                for (int j = 0; j < GN; ++j) {
                     if (KEEP_OWN) own[i][j] = acc[i][j];
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+                    acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
                 }
 #pragma unroll 1
             for (int pc = 0; pc < n_pieces; pc += PPR) {
@@ -967,14 +890,16 @@ __device__ __forceinline__ void tile_body(
                     // both pieces of the pair in flight together (own piece: no load)
                     f32q_t t[2][NQ];
                     const int p1 = min(pc + 1, n_pieces - 1);
-                    const float* s0 = partial + (size_t)sh_slot[pc] * (BM * BN) + tid * 4;
-                    const float* s1 = partial + (size_t)sh_slot[p1] * (BM * BN) + tid * 4;
+                    uint32_t po = (uint32_t)tid * 16u;
+                    asm volatile("" : "+v"(po));
+                    const float* s0 = partial + (size_t)__builtin_amdgcn_readfirstlane(sh_slot[pc]) * (BM * BN);
+                    const float* s1 = partial + (size_t)__builtin_amdgcn_readfirstlane(sh_slot[p1]) * (BM * BN);
                     if (pc != my_piece)
 #pragma unroll
-                        for (int q = 0; q < NQ; ++q) t[0][q] = ld16_coherent(&s0[(size_t)q * NT * 4]);
+                        for (int q = 0; q < NQ; ++q) t[0][q] = ld16_coherent(s0, po + (uint32_t)(q * NT * 16));
                     if (pc + 1 < n_pieces && pc + 1 != my_piece)
 #pragma unroll
-                        for (int q = 0; q < NQ; ++q) t[1][q] = ld16_coherent(&s1[(size_t)q * NT * 4]);
+                        for (int q = 0; q < NQ; ++q) t[1][q] = ld16_coherent(s1, po + (uint32_t)(q * NT * 16));
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -985,35 +910,34 @@ __device__ __forceinline__ void tile_body(
                         const bool mine = (pc + h == my_piece);
 #pragma unroll
                         for (int q = 0; q < NQ; ++q) {
-                            const int blk = q / 4, c = q % 4;
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
-                                acc[blk / FN][blk % FN][4 * c + e] +=
-                                    mine ? own[KEEP_OWN ? blk / FN : 0][KEEP_OWN ? blk % FN : 0][4 * c + e]
-                                         : t[h][q][e];
+                                acc[q / GN][q % GN][e] +=
+                                    mine ? own[KEEP_OWN ? q / GN : 0][KEEP_OWN ? q % GN : 0][e] : t[h][q][e];
                         }
                     }
                 } else {
                     const bool mine = (pc == my_piece);
-                    const float* src = partial + (size_t)sh_slot[pc] * (BM * BN) + tid * 4;
+                    uint32_t po = (uint32_t)tid * 16u;   // (offsets are made here, not held for every access)
+                    asm volatile("" : "+v"(po));
+                    const float* src = partial + (size_t)__builtin_amdgcn_readfirstlane(sh_slot[pc]) * (BM * BN);
 #pragma unroll
                     for (int q0 = 0; q0 < NQ; q0 += CH) {
                         f32q_t t[CH];
                         if (!mine) {
 #pragma unroll
                             for (int q = 0; q < CH; ++q)
-                                t[q] = ld16_coherent(&src[(size_t)(q0 + q) * NT * 4]);
+                                t[q] = ld16_coherent(src, po + (uint32_t)((q0 + q) * NT * 16));
                         }
 #pragma unroll
                         for (int q = 0; q < CH; q += 4) settle(t[q], t[q + 1], t[q + 2], t[q + 3]);
 #pragma unroll
                         for (int q = 0; q < CH; ++q) {
-                            const int blk = (q0 + q) / 4, c = (q0 + q) % 4;
+                            const int blk = q0 + q;
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
-                                acc[blk / FN][blk % FN][4 * c + e] +=
-                                    mine ? own[KEEP_OWN ? blk / FN : 0][KEEP_OWN ? blk % FN : 0][4 * c + e]
-                                         : t[q][e];
+                                acc[blk / GN][blk % GN][e] +=
+                                    mine ? own[KEEP_OWN ? blk / GN : 0][KEEP_OWN ? blk % GN : 0][e] : t[q][e];
                         }
                     }
                 }
@@ -1039,8 +963,7 @@ __device__ __forceinline__ void tile_body(
         asm volatile("" : "+v"(etid));
         const int out_n0 = EPI == EPI_SILU_MUL ? n0 / 2 : n0;
         const int out_N = EPI == EPI_SILU_MUL ? N / 2 : N;
-#pragma unroll 1
-        for (int pass = 0; pass < PASSES; ++pass) {
+        auto epilogue_pass = [&](int pass) __attribute__((always_inline)) {
             // first tile row of the pass (with overlapping wave rows the last pass starts early)
             const int prow0 = PASSES == 1 ? 0 : min(pass * TM, BM - TM);
             // q/k rotation: the position ids of this thread's items of the pass, fetched while
@@ -1075,17 +998,14 @@ __device__ __forceinline__ void tile_body(
             // read wait for the one before it -- a memory round trip per item -- and behind
             // conditional stores for the stores before it).
             constexpr bool RES = EPI == EPI_RES_BF16_TO_F32 || EPI == EPI_RES_F32_TO_BF16;
-            // (register room: the four-wave 256x256 shape has its accumulators in the second
-            // register file and takes 16 items per batch; the others 16 registers' worth; shapes
-            // with no registers to spare request after the lay-down)
-            constexpr bool BIG = WM * WN == 4 && BM == 256 && BN == 256;
+            // (register room: shapes with none to spare request after the lay-down, and fewer at a time)
             constexpr bool TIGHT = (WM * WN == 8 && BM == 256 && BN == 256) || BM == 288 ||
                                    (WM * WN == 4 && BM == 128);
             constexpr int IPR = OUT_COLS / 4;                                 // items per tile row
             constexpr int RPT = (RP * IPR + NT - 1) / NT;                     // items per thread and pass
             constexpr int RREG = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;          // registers per item
             constexpr int RES_ES = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;        // bytes per residual element
-            constexpr int RU_MAX = BIG ? 16 : 16 / RREG;
+            constexpr int RU_MAX = (WM * WN == 8 && BM == 256 && BN == 256 ? 8 : 16) / RREG;
             constexpr int RU = RPT < RU_MAX ? RPT : RU_MAX, RNB = (RPT + RU - 1) / RU;
             // item k of this thread: row r of the pass and first column c4 of the tile.  Where the
             // threads of the workgroup cover whole rows, the column is the same for every item
@@ -1148,19 +1068,28 @@ __device__ __forceinline__ void tile_body(
             };
             if constexpr (RES && !TIGHT) res_request(0);
             __syncthreads();   // previous readers of the LDS (fragments or the last pass) are done
-            if (PASSES == 1 || wm == pass) {
+            if constexpr (WM * WN == 4 && FM * FN >= 15) {
+                // Accumulators in the second register file: fetched one by one (pinned there until then),
+                // and without a branch, which would make the compiler copy them: 16-row blocks that are
+                // not of this pass go to a spare strip behind the tile.
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+                for (int i = 0; i < GM; ++i) {
+                    const int r0 = wrow0 - prow0 + i * 16;
+                    float* strip = tile + (r0 >= 0 && r0 < RP ? r0 : RP) * LDT;
 #pragma unroll
-                    for (int j = 0; j < FN; ++j)
+                    for (int j = 0; j < GN; ++j) {
+                        asm volatile("" : "+a"(acc[i][j]));
+                        *reinterpret_cast<f32x4_t*>(strip + fr * LDT + wn * TN + j * 16 + 4 * fq) = acc[i][j];
+                    }
+                }
+            } else if (PASSES == 1 || wm == pass) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int r = wrow0 - prow0 + i * 32 + fr;
-                            const int c = wn * TN + j * 32 + 8 * q + 4 * fg;
-                            *reinterpret_cast<float4*>(tile + r * LDT + c) =
-                                make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1],
-                                            acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                        }
+                for (int i = 0; i < GM; ++i)
+#pragma unroll
+                    for (int j = 0; j < GN; ++j) {
+                        const int r = wrow0 - prow0 + i * 16 + fr, c = wn * TN + j * 16 + 4 * fq;
+                        *reinterpret_cast<f32x4_t*>(tile + r * LDT + c) = acc[i][j];
+                    }
             }
             __syncthreads();
             // (what the items need beyond their residual is computed from here on, not before
@@ -1293,7 +1222,7 @@ __device__ __forceinline__ void tile_body(
                         g_a = g_e;
                     }
                 }
-                continue;
+                return;
             }
             if constexpr (RES) {
                 if constexpr (TIGHT) res_request(0);
@@ -1302,7 +1231,7 @@ __device__ __forceinline__ void tile_body(
                     res_finish(b);
                     if (b + 1 < RNB) res_request(b + 1);
                 }
-                continue;
+                return;
             }
             // SiLU(gate) * up: 8 output columns per item (16 bytes of bf16), two items at a time
             constexpr int U = 2;
@@ -1333,7 +1262,16 @@ __device__ __forceinline__ void tile_body(
                     __builtin_amdgcn_raw_buffer_store_b128(o, c_buf, ok ? (r * ldc + oc) * 2 : OOB_OFFSET, 0, 0);
                 }
             }
+        };
+        if constexpr (WM * WN == 4 && FM * FN >= 15 && PASSES == 2) {
+            // (not a loop: pinned accumulators would be carried round it, and copied)
+            epilogue_pass(0);
+            epilogue_pass(1);
+        } else {
+#pragma unroll 1
+            for (int pass = 0; pass < PASSES; ++pass) epilogue_pass(pass);
         }
+
     }
 }
 
@@ -1375,6 +1313,7 @@ static GemmPlan make_plan(int M, int N, int K, int BM, int BN, int BK, int slots
     p.tiles_m = (M + BM - 1) / BM;
     p.tiles_n = (N + BN - 1) / BN;
     p.k_tiles = K / BK;
+    p.quarter_of = -1;
     const int tiles = p.tiles_m * p.tiles_n;
     const int rem = tiles % slots;
     // a last round that is at least sk_pct % full is not worth cutting up
@@ -1399,7 +1338,8 @@ static GemmPlan make_plan(int M, int N, int K, int BM, int BN, int BK, int slots
 
 // Which part of the tile plan a launch covers: all of it, or -- when two kernels of the same tile
 // size share one plan -- the whole tiles only, or the K-split tiles of the last round only.
-enum PlanPart { PLAN_ALL = 0, PLAN_WHOLE_TILES = 1, PLAN_SPLIT_TILES = 2 };
+// (cut along K, or in quarters).
+enum PlanPart { PLAN_ALL = 0, PLAN_WHOLE_TILES = 1, PLAN_SPLIT_TILES = 2, PLAN_QUARTERS = 3 };
 
 // The plan for a tile shape, with the K-split dropped when the workspace has no room for it.
 static GemmPlan plan_for(int M, int N, int K, int BM, int BN, int BK, int slots, int sk_pct,
@@ -1422,13 +1362,19 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
                       float* partial, size_t partial_bytes, uint32_t* counters, int n_counters,
                       const RopeEpilogue& rope, hipStream_t st, PlanPart part = PLAN_ALL) {
     constexpr bool has_sk = !(WM * WN == 4 && ((BM / 32 + WM - 1) / WM) * (BN / WN / 32) >= 15);
-    GemmPlan plan = plan_for(M, N, K, BM, BN, BK, device_cu_count() * slots_per_cu,
+    const int pb = part == PLAN_QUARTERS ? 2 : 1;   // (planned on the tiles that are quartered)
+    GemmPlan plan = plan_for(M, N, K, BM * pb, BN * pb, BK, device_cu_count() * slots_per_cu,
                              (has_sk || part != PLAN_ALL) ? sk_pct : 0, partial_bytes, n_counters);
     if (part == PLAN_WHOLE_TILES) {
         plan.sk_tiles = plan.sk_blocks = 0;         // (their tiles are left to the other launch)
     } else if (part == PLAN_SPLIT_TILES) {
         if (plan.sk_blocks == 0) return MVLA_OK;
         plan.dp_grid = 0;                           // workgroup ids start at the K-split workgroups
+    } else if (part == PLAN_QUARTERS) {
+        plan.quarter_of = plan.dp_tiles;
+        plan.dp_tiles = 4 * plan.sk_tiles;
+        plan.dp_grid = (plan.dp_tiles + 7) / 8 * 8;
+        plan.sk_tiles = plan.sk_blocks = 0;
     }
     if (!has_sk && plan.sk_blocks > 0) return MVLA_EINVAL;
     int grid = plan.dp_grid + plan.sk_blocks;
@@ -1474,7 +1420,7 @@ size_t gemm_partial_bytes() {
 }
 
 // Tile configurations, and what predicts their time (see estimate_us; microseconds, fitted to the
-// measured times of all of them on 108 projections of this package's models, 64 to 21504 rows).
+// measured times of all of them on 124 projections of this package's models, 64 to 14720 rows).
 struct TileCfg {
     int BM, BN, slots_per_cu;
     bool can_split;      // has the K-split path
@@ -1488,52 +1434,70 @@ struct TileCfg {
 constexpr int kNumCfgs = 7;
 static const TileCfg kCfgs[kNumCfgs] = {
     // K-slab 64, eight waves of 128x64, two stages
-    {256, 256, 1, true, 1.69f, .604f, {8.6f, 10.7f, 11.6f, 5.5f}, 2.5f, 23.8f, 4.2f},
+    {256, 256, 1, true, 1.56f, .659f, {7.8f, 9.8f, 14.8f, 4.4f}, 2.4f, 23.4f, 2.6f},
     // K-slab 64, eight waves of 64x64, three stages
-    {256, 128, 1, true, .889f, .505f, {7.1f, 7.1f, 8.4f, 4.9f}, 2.1f, 13.4f, 4.4f},
+    {256, 128, 1, true, .801f, .594f, {6.4f, 6.5f, 7.9f, 4.4f}, 2.0f, 11.2f, 4.1f},
     // K-slab 64, four waves of 64x64, two stages, two workgroups per CU
-    {128, 128, 2, true, 1.01f, .381f, {4.9f, 4.5f, 5.1f, 3.4f}, 1.8f, 15.3f, 3.0f},
+    {128, 128, 2, true, .943f, .434f, {4.4f, 4.3f, 4.2f, 2.9f}, 2.1f, 18.0f, 3.0f},
     // K-slab 64, eight waves of 32x64, three stages
-    {128, 128, 1, true, .567f, .686f, {5.2f, 4.3f, 4.1f, 3.0f}, 1.7f, 6.5f, 3.9f},
+    {128, 128, 1, true, .516f, .653f, {4.9f, 4.0f, 3.5f, 2.9f}, 1.7f, 6.3f, 3.5f},
     // K-slab 64, four waves of 128x128, persistent (accumulators fill the second register file, a third
     // less LDS traffic per MFMA); a K-split last round runs on the eight-wave kernel of the same tile size
-    {256, 256, 1, true, 1.39f, .694f, {9.2f, 10.8f, 9.0f, 6.0f}, 0.f, 0.f, 5.2f},
+    {256, 256, 1, true, 1.32f, .642f, {9.3f, 11.3f, 10.0f, 5.8f}, 0.f, 0.f, 6.1f},
     // K-slab 64, eight waves of 96x32, three stages (row counts just over 2x256 with few column tiles:
     // three row tiles, K-split over all CUs)
-    {192, 128, 1, true, .759f, .601f, {6.1f, 6.2f, 5.6f, 4.2f}, 1.8f, 10.2f, 4.6f},
+    {192, 128, 1, true, .654f, .665f, {5.3f, 5.3f, 5.4f, 3.6f}, 1.9f, 9.2f, 4.2f},
     // K-slab 64, four waves of 160x96 (the two wave rows overlap by one 32-row block), accumulators in the
     // second register file, whole tiles only
-    {288, 192, 1, false, 1.40f, .702f, {5.0f, 13.4f, 8.6f, 8.1f}, 0.f, 0.f, 5.8f},
+    {288, 192, 1, false, 1.21f, .727f, {5.0f, 14.1f, 8.7f, 8.8f}, 0.f, 0.f, 6.3f},
 };
 constexpr float kLaunchUs = 3.f;
+// The exchange of a K-split behind a full-chip kernel takes longer than the fit says (117 us measured, 92
+// predicted, for 64 tiles at K = 11008; quarters 98 and 92): the quarters are taken unless it is well ahead.
+constexpr float kSplitRisk = 1.2f;
+
+// A 64-deep slab with n workgroups busy: longer the more of the chip is, and no less than its share of the
+// operands takes from memory (weights once for all row tiles in flight).
+static float slab_us(const TileCfg& c, float n, float tiles_m, float tiles_n) {
+    const float work = c.slab_us * (c.alone + (1.f - c.alone) * n / (device_cu_count() * c.slots_per_cu));
+    const float cols = fminf(tiles_n, fmaxf(1.f, n / tiles_m)), rows = fminf(tiles_m, n);
+    const float mem = (cols * c.BN + .2f * rows * c.BM) * 128.f * 1e-6f / c.mb_per_us;
+    const float w2 = work * work, m2 = mem * mem;
+    return sqrtf(sqrtf(w2 * w2 + m2 * m2));
+}
+// The cut last round of configuration cfg: its tiles split along K over all compute units.
+static float split_us(int cfg, const GemmPlan& p, int epi) {
+    const TileCfg& c = kCfgs[cfg];
+    const float its = (float)(((long)p.sk_tiles * p.k_tiles + p.sk_blocks - 1) / p.sk_blocks);
+    return c.tile_us[epi] + its * slab_us(c, (float)p.sk_blocks, (float)p.tiles_m, (float)p.tiles_n) +
+           c.piece_us * p.sk_blocks / p.sk_tiles + (p.sk_blocks % p.sk_tiles ? c.straddle_us : 0.f);
+}
+// The cut last round of 256x256 tiles in quarters of 128x128 (configuration 3), whole along K.
+static float quarters_us(const GemmPlan& p, int epi) {
+    const TileCfg& c = kCfgs[3];
+    const int n = 4 * p.sk_tiles, cus = device_cu_count();
+    const float tm = 2.f * p.tiles_m, tn = 2.f * p.tiles_n;
+    return (float)(n / cus) * (c.tile_us[epi] + p.k_tiles * slab_us(c, (float)cus, tm, tn)) +
+           (n % cus ? c.tile_us[epi] + p.k_tiles * slab_us(c, (float)(n % cus), tm, tn) : 0.f);
+}
 
 // Predicted time of a configuration: whole rounds of its tiles, then the last partial round either as it
-// is or cut along K over all compute units.  A slab takes longer the more of the chip is busy, and no
-// less than its share of the operands takes from memory (weights once for all row tiles in flight).
-// Over those 108 projections the configuration this picks is 1.2 % slower than the best one (a
+// is or cut (split) along K over all compute units or, the persistent kernel's, into quarters.
+// Over those 124 projections the configuration this picks is 1.6 % slower than the best one (a
 // round-count model with one constant per configuration and a fixed threshold for the cut: 7.4 %).
 static float estimate_us(int cfg, int M, int N, int K, int epi, bool split) {
     const TileCfg& c = kCfgs[cfg];
-    const int slots = device_cu_count() * c.slots_per_cu, kt = K / 64;
+    const int slots = device_cu_count() * c.slots_per_cu;
     const GemmPlan p = make_plan(M, N, K, c.BM, c.BN, 64, slots, split ? 101 : 0);
     const long tiles = (long)p.tiles_m * p.tiles_n;
     const long full = tiles / slots, rem = tiles % slots;
-    auto slab = [&](float n) {
-        const float work = c.slab_us * (c.alone + (1.f - c.alone) * n / slots);
-        const float cols = fminf((float)p.tiles_n, fmaxf(1.f, n / p.tiles_m)), rows = fminf((float)p.tiles_m, n);
-        const float mem = (cols * c.BN + .2f * rows * c.BM) * 128.f * 1e-6f / c.mb_per_us;
-        const float w2 = work * work, m2 = mem * mem;
-        return sqrtf(sqrtf(w2 * w2 + m2 * m2));
-    };
-    float t = kLaunchUs + full * (c.tile_us[epi] + kt * slab((float)slots));
+    const float tm = (float)p.tiles_m, tn = (float)p.tiles_n;
+    float t = kLaunchUs + full * (c.tile_us[epi] + p.k_tiles * slab_us(c, (float)slots, tm, tn));
     if (rem == 0) return t;
-    if (p.sk_blocks == 0) return t + c.tile_us[epi] + kt * slab((float)rem);
-    const bool second = cfg == 4;            // (the cut round is the eight-wave kernel's, a launch of its own)
-    const TileCfg& s = second ? kCfgs[0] : c;
-    const float its = (float)((rem * kt + p.sk_blocks - 1) / p.sk_blocks), pieces = (float)p.sk_blocks / rem;
-    const float per_slab = second ? s.slab_us * (s.alone + (1.f - s.alone) * p.sk_blocks / slots) : slab((float)p.sk_blocks);
-    return t + (second ? kLaunchUs : 0.f) + s.tile_us[epi] + its * per_slab + s.piece_us * pieces +
-           (p.sk_blocks % rem ? s.straddle_us : 0.f);
+    if (p.sk_blocks == 0) return t + c.tile_us[epi] + p.k_tiles * slab_us(c, (float)rem, tm, tn);
+    if (cfg == 4)            // (a launch of its own)
+        return t + (full ? kLaunchUs : 0.f) + fminf(kSplitRisk * split_us(0, p, epi), quarters_us(p, epi));
+    return t + split_us(cfg, p, epi);
 }
 
 int gemm_num_configs() { return kNumCfgs; }
@@ -1603,14 +1567,18 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
             if (epilogue == EPI_QKV_ROPE && N == 3 * rope->D &&
                 (size_t)(256 / rope->S + 2) * rope->D * rope->S_pad * 2 >= (size_t)OOB_OFFSET - 65536)
                 return launch_cfg<256, 256, 64, 2, 4, 2>(MVLA_ARGS);
-            // four waves of 128x128 have no registers for the K-split exchange: when the last round
-            // is to be cut, its tiles go to the eight-wave kernel of the same tile size in a second
-            // launch (same plan, same tile numbering)
+            // four waves of 128x128 have no registers for the K-split exchange: when the last round is to be
+            // cut, its tiles go to the eight-wave kernel of the same tile size in a second launch (same
+            // plan, same tile numbering), or in quarters to the 128x128 kernel where that is predicted
+            // to be faster: nothing is exchanged then (K = 4096: 64 tiles 66 -> 45 us, 48 tiles 71 -> 35 us)
             const GemmPlan pl = plan_for(M, N, K, 256, 256, 64, device_cu_count(), split_pct,
                                          partial_bytes, n_counters);
             if (pl.sk_blocks == 0) return launch_cfg<256, 256, 64, 2, 2, 2>(MVLA_ARGS);
             const int rc = launch_cfg<256, 256, 64, 2, 2, 2>(MVLA_ARGS, PLAN_WHOLE_TILES);
             if (rc) return rc;
+            // (the quarter tiles hold whole heads only of 128 and, as every tile, lie in one q, k, v section)
+            if (cfg_runs(kCfgs[3], epilogue, rope) && quarters_us(pl, epilogue) < kSplitRisk * split_us(0, pl, epilogue))
+                return launch_cfg<128, 128, 64, 4, 2, 3>(MVLA_ARGS, PLAN_QUARTERS);
             return launch_cfg<256, 256, 64, 2, 4, 2>(MVLA_ARGS, PLAN_SPLIT_TILES);
         }
         case 5: return launch_cfg<192, 128, 64, 2, 4, 3>(MVLA_ARGS);
