@@ -3,6 +3,7 @@
 // latency-bound; none uses floating-point atomics, so every result is
 // reproducible bit for bit.
 #include "common.h"
+#include "wave.h"
 
 namespace mvla {
 
@@ -262,10 +263,12 @@ static void salience_shape(int B, int R, int n_vis, int vec, int* chunks, int* n
                            int* rows_per_split) {
     const int cw = SAL_LPR * vec;
     *chunks = (n_vis + cw - 1) / cw;
-    // aim for ~2048 blocks, at least 2 passes of the 16 row-groups each; few rows are not split at all
+    // Aim for ~2048 blocks, at least 8 passes of the 16 row-groups each (a thread's eight loads then fly
+    // together, and the last block to arrive has fewer partial sums to fetch: 1024 rows x 512 columns
+    // (B = 4) 14.2 -> 5.8 us against 2 passes); few rows are not split at all.
     long blocks = (long)B * *chunks;
     int split = salience_solo(R, n_vis) ? 1 : (int)((2048 + blocks - 1) / blocks);
-    const int max_split = (R + 2 * SAL_GROUPS - 1) / (2 * SAL_GROUPS);
+    const int max_split = (R + 8 * SAL_GROUPS - 1) / (8 * SAL_GROUPS);
     if (split > max_split) split = max_split;
     if (split < 1) split = 1;
     *rows_per_split = (R + split - 1) / split;
@@ -423,12 +426,10 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// two sums over the workgroup, each a fixed-shape tree: wave shuffles, then the waves' partials in LDS
+// two sums over the workgroup, each a fixed-shape tree: over the wave, then the waves' partials in LDS
 __device__ inline void block_sum2_f64(double& a, double& b, double* sh /*LDS [2 * waves]*/) {
-    for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o);
-        b += __shfl_xor(b, o);
-    }
+    a = wave_sum_f64(a);
+    b = wave_sum_f64(b);
     constexpr int NW = BUD_THREADS / 64;
     if ((threadIdx.x & 63) == 0) {
         sh[threadIdx.x >> 6] = a;
@@ -905,77 +906,137 @@ int launch_compact(const bf16_t* h, const int32_t* pos, const int32_t* kept_idx,
 // Eqs. 4-6): the 3D attention vector of a patch (over the head x query rows)
 // is split into its projection on the 2D vector and the orthogonal rest; the
 // outputs are the L1 shares |a2| / (|a2|+|a3|) and |a3_ortho| / (|a2|+|a3|).
-// One workgroup handles 8 patches of one sample with 32 row-groups (a thread
-// owns a patch and every 32nd row; small patch groups keep the launch wide at
-// batch 1); pass 1 accumulates <a2,a2>, <a2,a3>, |a2|, |a3|, pass 2 the L1 norm
-// of the residual (second read served by the L2).
+// One workgroup of 16 waves handles 16 patches of one sample; a thread owns VEC patches and every
+// (64 * VEC)-th row.  Up to RPT rows a thread (16 * VEC * 64 ... rows in all) stay in registers between the
+// two sums -- <a2,a2>, <a2,a3>, |a2|, |a3|, then the L1 norm of the residual --, so the rows are read once,
+// all requests in flight together; longer ones are read a second time (served by the caches).
+// Bound by latency: 1024 rows x 2 x 256 patches (B = 4) 12.6 -> 7.4 us against 8 patches a
+// workgroup of four waves, read twice in 32-byte pieces.
 // ---------------------------------------------------------------------------
-constexpr int DEC_THREADS = 256;
-constexpr int DEC_PP = 8;                       // patches per workgroup
-constexpr int DEC_RG = DEC_THREADS / DEC_PP;    // row groups
+constexpr int DEC_THREADS = 1024;
+constexpr int DEC_PP = 16;                      // patches per workgroup
 
+// Sum over the lanes of a wave that hold the same patches (every LP-th lane), in all of them: rotations
+// within 16 lanes, then the 16-lane rows, then the halves.
+template <int LP>
+__device__ __forceinline__ float same_patch_sum(float x) {
+    if (LP <= 4) x += __uint_as_float(dpp_get<0x124, 0xf>(__float_as_uint(x), 0u));   // row_ror:4
+    if (LP <= 8) x += __uint_as_float(dpp_get<0x128, 0xf>(__float_as_uint(x), 0u));   // row_ror:8
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
+template <int VEC, int RPT /* rows a thread keeps; 0: read twice */>
 __global__ __launch_bounds__(DEC_THREADS) void decompose_kernel(const float* __restrict__ attn,
                                                                 int R, int S, int n_patch,
                                                                 float* __restrict__ m2d,
                                                                 float* __restrict__ m3d) {
-    __shared__ float red[4][DEC_RG][DEC_PP];
-    __shared__ float coef[DEC_PP];
-    const int lp = threadIdx.x % DEC_PP, g = threadIdx.x / DEC_PP;
-    const int b = blockIdx.y, p = blockIdx.x * DEC_PP + lp;
-    const bool live = p < n_patch;
-    const float* base = attn + (size_t)b * R * S;
-    float s22 = 0.f, s23 = 0.f, l2 = 0.f, l3 = 0.f;
-    if (live) {
-#pragma unroll 4
-        for (int r = g; r < R; r += DEC_RG) {
-            const float a2 = base[(size_t)r * S + p], a3 = base[(size_t)r * S + n_patch + p];
-            s22 += a2 * a2;
-            s23 += a2 * a3;
-            l2 += fabsf(a2);
-            l3 += fabsf(a3);
-        }
-    }
-    red[0][g][lp] = s22;
-    red[1][g][lp] = s23;
-    red[2][g][lp] = l2;
-    red[3][g][lp] = l3;
-    __syncthreads();
-    float den = 0.f, n2 = 0.f;
-    if (g == 0) {
-        float t[4];
+    constexpr int LP = DEC_PP / VEC, RG = DEC_THREADS / LP;   // lanes across the patches; row groups
+    __shared__ float red[4][DEC_THREADS / 64][DEC_PP], tot[4][DEC_PP];
+    const int tid = threadIdx.x, l = tid % LP, g = tid / LP, wave = tid >> 6;
+    const int b = blockIdx.y, p0 = blockIdx.x * DEC_PP + l * VEC;
+    const float* base = attn + (size_t)b * R * S + p0;
+    typedef float vec_t __attribute__((ext_vector_type(VEC)));
+    // (VEC == 4: n_patch % 4 == 0, so a lane's patches exist all or none)
+    const bool live = p0 < n_patch;
+    auto load = [&](int r, int col) __attribute__((always_inline)) {
+        return *reinterpret_cast<const vec_t*>(base + (size_t)r * S + col);
+    };
+    vec_t s22 = 0.f, s23 = 0.f, l2 = 0.f, l3 = 0.f;
+    auto add = [&](vec_t a2, vec_t a3) __attribute__((always_inline)) {
+        s22 += a2 * a2;
+        s23 += a2 * a3;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            t[q] = 0.f;
-            for (int w = 0; w < DEC_RG; ++w) t[q] += red[q][w][lp];
+        for (int v = 0; v < VEC; ++v) {
+            l2[v] += fabsf(a2[v]);
+            l3[v] += fabsf(a3[v]);
         }
-        coef[lp] = t[0] > 0.f ? t[1] / t[0] : 0.f;
-        n2 = t[2];
-        den = t[2] + t[3];
-    }
-    __syncthreads();
-    const float c = coef[lp];
-    float lo = 0.f;
-    if (live) {
+    };
+    vec_t k2[RPT > 0 ? RPT : 1], k3[RPT > 0 ? RPT : 1];
+    if (RPT > 0) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int r = g + i * RG;
+            k2[i] = k3[i] = 0.f;
+            if (live && r < R) {
+                k2[i] = load(r, 0);
+                k3[i] = load(r, n_patch);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) add(k2[i], k3[i]);     // (rows that are not there add zeros)
+    } else if (live) {
 #pragma unroll 4
-        for (int r = g; r < R; r += DEC_RG) {
-            const float a2 = base[(size_t)r * S + p], a3 = base[(size_t)r * S + n_patch + p];
-            lo += fabsf(a3 - c * a2);
-        }
+        for (int r = g; r < R; r += RG) add(load(r, 0), load(r, n_patch));
     }
-    red[0][g][lp] = lo;
+    const vec_t sums[4] = {s22, s23, l2, l3};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            const float t = same_patch_sum<LP>(sums[q][v]);
+            if ((tid & 63) < LP) red[q][wave][l * VEC + v] = t;
+        }
     __syncthreads();
-    if (g == 0 && live) {
+    if (tid < 4 * DEC_PP) {              // one wave folds the waves' sums: 4 quantities x 16 patches
         float t = 0.f;
-        for (int w = 0; w < DEC_RG; ++w) t += red[0][w][lp];
-        m2d[(size_t)b * n_patch + p] = den > 0.f ? n2 / den : 0.f;
+#pragma unroll
+        for (int w = 0; w < DEC_THREADS / 64; ++w) t += red[tid / DEC_PP][w][tid % DEC_PP];
+        tot[tid / DEC_PP][tid % DEC_PP] = t;
+    }
+    __syncthreads();
+    vec_t c;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        const float a = tot[0][l * VEC + v];
+        c[v] = a > 0.f ? tot[1][l * VEC + v] / a : 0.f;
+    }
+    vec_t lo = 0.f;
+    auto rest = [&](vec_t a2, vec_t a3) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) lo[v] += fabsf(a3[v] - c[v] * a2[v]);
+    };
+    if (RPT > 0) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) rest(k2[i], k3[i]);
+    } else if (live) {
+#pragma unroll 4
+        for (int r = g; r < R; r += RG) rest(load(r, 0), load(r, n_patch));
+    }
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        const float t = same_patch_sum<LP>(lo[v]);
+        if ((tid & 63) < LP) red[0][wave][l * VEC + v] = t;   // (read by the first wave before the last barrier)
+    }
+    __syncthreads();
+    const int p = blockIdx.x * DEC_PP + tid;
+    if (tid < DEC_PP && p < n_patch) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < DEC_THREADS / 64; ++w) t += red[0][w][tid];
+        const float den = tot[2][tid] + tot[3][tid];
+        m2d[(size_t)b * n_patch + p] = den > 0.f ? tot[2][tid] / den : 0.f;
         m3d[(size_t)b * n_patch + p] = den > 0.f ? t / den : 0.f;
     }
 }
 
 int launch_decompose(const float* attn, int B, int H, int Nq, int S, int n_patch, float* m2d,
                      float* m3d, hipStream_t st) {
-    hipLaunchKernelGGL(decompose_kernel, dim3((n_patch + DEC_PP - 1) / DEC_PP, B), dim3(DEC_THREADS),
-                       0, st, attn, H * Nq, S, n_patch, m2d, m3d);
+    const int R = H * Nq;
+    const dim3 grid((n_patch + DEC_PP - 1) / DEC_PP, B);
+#define MVLA_DEC(V, T)                                                                              \
+    hipLaunchKernelGGL((decompose_kernel<V, T>), grid, dim3(DEC_THREADS), 0, st, attn, R, S, n_patch, m2d, m3d)
+    // 16 bytes a lane where every row of both halves is aligned for it: 256 row groups, else 64
+    if (S % 4 == 0 && n_patch % 4 == 0 && (reinterpret_cast<uintptr_t>(attn) & 15) == 0) {
+        if (R <= 256 * 4) MVLA_DEC(4, 4);
+        else MVLA_DEC(4, 0);
+    } else {
+        if (R <= 64 * 16) MVLA_DEC(1, 16);
+        else MVLA_DEC(1, 0);
+    }
+#undef MVLA_DEC
     MVLA_HIP_CHECK(hipGetLastError());
     return MVLA_OK;
 }

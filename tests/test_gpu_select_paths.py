@@ -67,3 +67,19 @@ def test_fused_step_equals_single_calls(ctx, H, Nq, n2, n3, nt):
     assert np.max(np.abs(sal.cpu().numpy() - ref) / ref) < H * Nq * 2.0 ** -24
     for a, b in ((o["sal"], sal), (o["k2k3"], k2k3), (o["kept_idx"], kept), (o["h"], hk), (o["pos"], pk)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,H,Nq,P,nt", [(4, 32, 32, 256, 32), (2, 32, 33, 20, 4), (1, 4, 256, 17, 3), (3, 4, 257, 16, 0),
+                                         (2, 4, 260, 18, 2), (1, 1, 1, 1, 0), (2, 3, 5, 50, 1)])
+def test_decompose_paths(ctx, B, H, Nq, P, nt):
+    """Per-patch indicators with rows kept in registers (up to 1024) and read twice, aligned and not,
+    patches that end inside a workgroup."""
+    S = 2 * P + nt
+    g = torch.Generator().manual_seed(B * 1000 + P)
+    p = torch.rand(B, H, Nq, S, generator=g) ** 4
+    p = (p / p.sum(-1, keepdim=True)).contiguous()
+    m2, m3 = ctx.modality_decompose(p.cuda(), P)
+    r2, r3 = O.modality_decompose(p.numpy().astype(np.float64), P)
+    # sums of H*Nq fp32 values in groups of at most 16 a thread: well inside 1e-5 relative
+    for got, ref in ((m2, r2), (m3, r3)):
+        assert np.max(np.abs(got.cpu().numpy() - ref)) <= 1e-5 * max(1.0, float(np.max(ref)))
