@@ -589,7 +589,7 @@ __device__ __forceinline__ void persistent_body(const bf16_t* __restrict__ A, in
 #undef PT_HALF
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
+template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI, bool SPLITS = true>
 __device__ __forceinline__ void tile_body(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
     void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, const GemmPlan& plan,
@@ -829,7 +829,7 @@ __device__ __forceinline__ void tile_body(
         // ---- K-split tiles: park the partial sums; the last piece to arrive finishes --------
         // (the four-wave 128x128-per-wave shape keeps its register budget for the main loop:
         // whole tiles only, the host never plans a K-split for it)
-        constexpr bool HAS_SK = !(WM * WN == 4 && FM * FN >= 15);
+        constexpr bool HAS_SK = SPLITS && !(WM * WN == 4 && FM * FN >= 15);
         const int n_pieces = (!HAS_SK || is_dp) ? 1 : last_blk - first_blk + 1;
         if (HAS_SK && n_pieces > 1) {
             // slot 0 of a workgroup holds the piece of the tile its range starts in, slot 1 the next
@@ -1289,6 +1289,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
         tile_body<BM, BN, BK, WM, WN, NS, EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope);
 }
 
+// Shapes that only the choice by size uses (whole tiles, no K-split): the same body under another name.
+// (two waves a SIMD in the bounds keep the accumulators in the ordinary registers; given more room, the
+// compiler moves them to the second file and back in every slab)
+template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
+__global__ __launch_bounds__(WM * WN * 64, 2) void small_tile_kernel(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
+    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
+    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope) {
+    tile_body<BM, BN, BK, WM, WN, NS, EPI, false>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope);
+}
+
 // ---- host side ------------------------------------------------------------------------------
 // Compute units of the current device: sets how many workgroups are resident at once (the round
 // size of the tile plan) and the size of the K-split partial buffer.  Asked once; 256 (MI355X)
@@ -1356,12 +1367,18 @@ static GemmPlan plan_for(int M, int N, int K, int BM, int BN, int BK, int slots,
     return plan;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS>
+template <int BM, int BN, int BK, int WM, int WN, int NS, int E, bool SMALL>
+static constexpr auto kernel_of() {
+    if constexpr (SMALL) return small_tile_kernel<BM, BN, BK, WM, WN, NS, E>;
+    else return gemm_kernel<BM, BN, BK, WM, WN, NS, E>;
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool SMALL = false>
 static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, void* C,
                       int ldc, const void* R, int ldr, int epi, int slots_per_cu, int sk_pct,
                       float* partial, size_t partial_bytes, uint32_t* counters, int n_counters,
                       const RopeEpilogue& rope, hipStream_t st, PlanPart part = PLAN_ALL) {
-    constexpr bool has_sk = !(WM * WN == 4 && ((BM / 32 + WM - 1) / WM) * (BN / WN / 32) >= 15);
+    constexpr bool has_sk = !SMALL && !(WM * WN == 4 && ((BM / 32 + WM - 1) / WM) * (BN / WN / 32) >= 15);
     const int pb = part == PLAN_QUARTERS ? 2 : 1;   // (planned on the tiles that are quartered)
     GemmPlan plan = plan_for(M, N, K, BM * pb, BN * pb, BK, device_cu_count() * slots_per_cu,
                              (has_sk || part != PLAN_ALL) ? sk_pct : 0, partial_bytes, n_counters);
@@ -1392,7 +1409,7 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
     // instantiation), not on every launch
 #define MVLA_GEMM_LAUNCH(E)                                                                   \
     do {                                                                                      \
-        auto kern = gemm_kernel<BM, BN, BK, WM, WN, NS, E>;                                       \
+        auto kern = kernel_of<BM, BN, BK, WM, WN, NS, E, SMALL>();                                \
         static bool lds_set[kMaxDevices] = {};                                                \
         int dev = 0;                                                                          \
         MVLA_HIP_CHECK(hipGetDevice(&dev));                                                   \
@@ -1420,7 +1437,7 @@ size_t gemm_partial_bytes() {
 }
 
 // Tile configurations, and what predicts their time (see estimate_us; microseconds, fitted to the
-// measured times of all of them on 124 projections of this package's models, 64 to 14720 rows).
+// measured times of all of them on 200 projections of this package's models, 32 to 14720 rows).
 struct TileCfg {
     int BM, BN, slots_per_cu;
     bool can_split;      // has the K-split path
@@ -1431,25 +1448,37 @@ struct TileCfg {
     float straddle_us;   // K-split: when workgroups' ranges straddle two tiles (two starts, two parts put out)
     float mb_per_us;     // operand bytes beyond the caches
 };
-constexpr int kNumCfgs = 7;
-static const TileCfg kCfgs[kNumCfgs] = {
+constexpr int kNumCfgs = 7;      // configurations a caller can record (mvla_set_gemm_choice)
+constexpr int kAllCfgs = 12;     // ... and those that only the choice by size uses
+static const TileCfg kCfgs[kAllCfgs] = {
     // K-slab 64, eight waves of 128x64, two stages
-    {256, 256, 1, true, 1.56f, .659f, {7.8f, 9.8f, 14.8f, 4.4f}, 2.4f, 23.4f, 2.6f},
+    {256, 256, 1, true, 1.55f, 0.697f, {8.5f, 9.3f, 13.7f, 5.2f}, 2.4f, 27.7f, 3.f},
     // K-slab 64, eight waves of 64x64, three stages
-    {256, 128, 1, true, .801f, .594f, {6.4f, 6.5f, 7.9f, 4.4f}, 2.0f, 11.2f, 4.1f},
+    {256, 128, 1, true, 0.806f, 0.587f, {6.6f, 6.3f, 7.6f, 4.5f}, 1.9f, 11.3f, 4.f},
     // K-slab 64, four waves of 64x64, two stages, two workgroups per CU
-    {128, 128, 2, true, .943f, .434f, {4.4f, 4.3f, 4.2f, 2.9f}, 2.1f, 18.0f, 3.0f},
+    {128, 128, 2, true, 0.95f, 0.449f, {4.4f, 4.1f, 3.6f, 2.9f}, 2.1f, 18.2f, 3.4f},
     // K-slab 64, eight waves of 32x64, three stages
-    {128, 128, 1, true, .516f, .653f, {4.9f, 4.0f, 3.5f, 2.9f}, 1.7f, 6.3f, 3.5f},
+    {128, 128, 1, true, 0.516f, 0.689f, {4.9f, 3.8f, 3.2f, 2.9f}, 1.8f, 6.9f, 3.5f},
     // K-slab 64, four waves of 128x128, persistent (accumulators fill the second register file, a third
     // less LDS traffic per MFMA); a K-split last round runs on the eight-wave kernel of the same tile size
-    {256, 256, 1, true, 1.32f, .642f, {9.3f, 11.3f, 10.0f, 5.8f}, 0.f, 0.f, 6.1f},
+    {256, 256, 1, true, 1.3f, 0.686f, {10.5f, 10.5f, 9.f, 6.4f}, 0.f, 0.f, 6.2f},
     // K-slab 64, eight waves of 96x32, three stages (row counts just over 2x256 with few column tiles:
     // three row tiles, K-split over all CUs)
-    {192, 128, 1, true, .654f, .665f, {5.3f, 5.3f, 5.4f, 3.6f}, 1.9f, 9.2f, 4.2f},
+    {192, 128, 1, true, 0.659f, 0.662f, {5.5f, 5.4f, 5.2f, 3.8f}, 1.8f, 9.5f, 4.1f},
     // K-slab 64, four waves of 160x96 (the two wave rows overlap by one 32-row block), accumulators in the
     // second register file, whole tiles only
-    {288, 192, 1, false, 1.21f, .727f, {5.0f, 14.1f, 8.7f, 8.8f}, 0.f, 0.f, 6.3f},
+    {288, 192, 1, false, 1.2f, 0.722f, {5.f, 14.6f, 9.6f, 9.4f}, 0.f, 0.f, 6.9f},
+    // The rest: four waves, whole tiles only, for few rows and columns, where the larger tiles leave most
+    // of the chip without work.  64x96 per wave, three stages (M = 237, N = 22016: 63 -> 60 us)
+    {128, 192, 1, false, 0.601f, 0.953f, {5.f, 5.3f, 3.6f, 3.6f}, 0.f, 0.f, 3.75f},
+    // 32x32 per wave, six stages (M = 100, N = K = 1024: 12.0 -> 8.3 us; M = 80, N = 256, K = 1024: 11 -> 7.9)
+    {64, 64, 1, false, 0.21f, 0.922f, {3.4f, 2.4f, 1.7f, 2.2f}, 0.f, 0.f, 2.7f},
+    // 64x64 per wave, four stages (M = 948, N = K = 4096: 41 -> 37 us)
+    {128, 128, 1, false, 0.454f, 0.87f, {4.6f, 4.f, 2.7f, 3.1f}, 0.f, 0.f, 3.7f},
+    // 32x64 per wave, five stages (M = 237, N = 3072, K = 1024, heads of 128: 14 -> 11 us)
+    {64, 128, 1, false, 0.346f, 1.f, {3.6f, 2.6f, 1.f, 2.3f}, 0.f, 0.f, 3.4f},
+    // 64x32 per wave, five stages (M = 400, N = K = 4096: 29 -> 26 us)
+    {128, 64, 1, false, 0.302f, 0.974f, {4.1f, 2.9f, 2.1f, 2.6f}, 0.f, 0.f, 4.f},
 };
 constexpr float kLaunchUs = 3.f;
 // The exchange of a K-split behind a full-chip kernel takes longer than the fit says (117 us measured, 92
@@ -1483,7 +1512,7 @@ static float quarters_us(const GemmPlan& p, int epi) {
 
 // Predicted time of a configuration: whole rounds of its tiles, then the last partial round either as it
 // is or cut (split) along K over all compute units or, the persistent kernel's, into quarters.
-// Over those 124 projections the configuration this picks is 1.6 % slower than the best one (a
+// Over those 200 projections the configuration this picks is 1.2 % slower than the best one (a
 // round-count model with one constant per configuration and a fixed threshold for the cut: 7.4 %).
 static float estimate_us(int cfg, int M, int N, int K, int epi, bool split) {
     const TileCfg& c = kCfgs[cfg];
@@ -1540,7 +1569,7 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         split_pct = force_split_pct;
     } else {
         float best_us = 0.f;
-        for (int i = 0; i < kNumCfgs; ++i) {
+        for (int i = 0; i < kAllCfgs; ++i) {
             if (!cfg_runs(kCfgs[i], epilogue, rope)) continue;
             for (int split = 0; split <= (kCfgs[i].can_split ? 1 : 0); ++split) {
                 const float t = estimate_us(i, M, N, K, epilogue, split != 0);
@@ -1582,7 +1611,12 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
             return launch_cfg<256, 256, 64, 2, 4, 2>(MVLA_ARGS, PLAN_SPLIT_TILES);
         }
         case 5: return launch_cfg<192, 128, 64, 2, 4, 3>(MVLA_ARGS);
-        default: return launch_cfg<288, 192, 64, 2, 2, 2>(MVLA_ARGS);
+        case 6: return launch_cfg<288, 192, 64, 2, 2, 2>(MVLA_ARGS);
+        case 7: return launch_cfg<128, 192, 64, 2, 2, 3, true>(MVLA_ARGS);
+        case 8: return launch_cfg<64, 64, 64, 2, 2, 6, true>(MVLA_ARGS);
+        case 9: return launch_cfg<128, 128, 64, 2, 2, 4, true>(MVLA_ARGS);
+        case 10: return launch_cfg<64, 128, 64, 2, 2, 5, true>(MVLA_ARGS);
+        default: return launch_cfg<128, 64, 64, 2, 2, 5, true>(MVLA_ARGS);
     }
 #undef MVLA_ARGS
 }

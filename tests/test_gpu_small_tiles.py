@@ -1,0 +1,34 @@
+"""Layers at sizes for which the choice by size takes the small whole-tile projection kernels (64x64,
+64x128, 128x64, 128x128 on four waves, 128x192): rows and columns that end inside a tile, one to 44 slabs,
+heads of 64 and 128, V^T stored in whole groups of eight tokens and token by token.  Every sample against
+the oracle layer at the stated bar."""
+from dataclasses import replace
+
+import pytest
+import torch
+
+import oracle as O
+from helpers import assert_layer_close, device_layer, layer_cfg, oracle_weights, to64
+from paper_2604_09244_amd import binding as mv
+from paper_2604_09244_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,H,F", [(256, 4, 1024), (256, 2, 192), (192, 3, 64), (1024, 8, 2816), (1024, 16, 704)])
+@pytest.mark.parametrize("B,S", [(1, 1), (1, 65), (3, 79), (2, 136), (4, 435)])
+def test_small_tiles(D, H, F, B, S):
+    wl = replace(W.WORKLOADS["tiny"], D=D, H=H, dh=D // H, F=F, n2=S // 2, n3=S - S // 2, nt=0, B=B, seed=D + S)
+    ctx = mv.Context(B, S, D, H, F, 0)
+    w_cpu = W.layer_weights(wl, 0)
+    packed, struct = device_layer(ctx, wl, w_cpu)
+    ow = oracle_weights(w_cpu)
+    x, pos = W.hidden_states(wl, device="cuda")
+    y = ctx.prefill_layer(layer_cfg(wl), struct, x, pos)
+    again = ctx.prefill_layer(layer_cfg(wl), struct, x, pos)
+    torch.cuda.synchronize()
+    for b in range(B):
+        ref = O.decoder_layer(to64(x[b]), pos[b].cpu().numpy(), ow, H, wl.rms_eps, wl.rope_base)[0]
+        assert_layer_close(y[b], ref, f"D={D} F={F} B={B} S={S} sample {b}", D)
+    assert torch.equal(y, again)
+    ctx.close()
