@@ -134,6 +134,12 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
                 const void* R, int ldr, int epilogue, float* partial, size_t partial_bytes,
                 uint32_t* counters, int n_counters, int force_cfg, int force_split_pct,
                 const RopeEpilogue* rope, hipStream_t st);
+// Two projections onto D columns of the rotating kind (no V), K = D, in one launch: the configuration that does so
+// where it is predicted to be faster than one launch after the other (-1: it is not), and the launch.
+int rope_pair_config(int M1, const RopeEpilogue& rope1, int M2, const RopeEpilogue& rope2, int D);
+int launch_rope_pair(int cfg, const bf16_t* A1, const bf16_t* W1, int M1, void* C1, const RopeEpilogue& rope1,
+                     const bf16_t* A2, const bf16_t* W2, int M2, void* C2, const RopeEpilogue& rope2, int D,
+                     hipStream_t st);
 int gemm_num_configs();
 // whether tile configuration cfg can run this epilogue (the rotating one needs whole heads per tile)
 bool gemm_config_runs(int cfg, int epilogue, const RopeEpilogue* rope);

@@ -109,6 +109,16 @@ struct GemmPlan {
     int quarter_of;   // >= 0: the dp_tiles are quarters (128x128) of the 256x256 tiles from this one on
 };
 
+// A second q/k/v-type projection in the same launch, with the same N, K and row pitches: the workgroups from
+// first_block on are its (0: there is none).  Two projections that would each leave compute units idle
+// run side by side.
+struct PairedGemm {
+    const bf16_t *A, *W;
+    void* C;
+    const int32_t* pos;
+    int M, tiles_m, first_block;
+};
+
 // Workgroup ids are dealt round-robin to the 8 XCDs (each has its own L2).  Give every XCD a
 // contiguous range of the sequence, and run the sequence through groups of GROUP_M row-tiles
 // column by column, so the tiles an XCD has in flight share activation rows and weight panels.
@@ -592,8 +602,20 @@ __device__ __forceinline__ void persistent_body(const bf16_t* __restrict__ A, in
 template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI, bool SPLITS = true>
 __device__ __forceinline__ void tile_body(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
-    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, const GemmPlan& plan,
-    float* __restrict__ partial, uint32_t* __restrict__ counters, const RopeEpilogue& rope) {
+    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
+    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, const PairedGemm& pair) {
+    int bid = blockIdx.x;
+    if (EPI == EPI_QKV_ROPE && pair.first_block > 0 && bid >= pair.first_block) {
+        bid -= pair.first_block;
+        A = pair.A;
+        W = pair.W;
+        Cv = pair.C;
+        M = pair.M;
+        rope.pos = pair.pos;
+        plan.tiles_m = pair.tiles_m;
+        plan.dp_tiles = pair.tiles_m * plan.tiles_n;
+        plan.dp_grid = (plan.dp_tiles + 7) / 8 * 8;
+    }
     constexpr int NT = WM * WN * 64;
     constexpr int CPR = BK / 8;             // 16-byte chunks per LDS row
     // A wave owns FM x FN blocks of 32x32, four 16x16 accumulators each.  When the tile's 32-row blocks do not
@@ -621,13 +643,13 @@ __device__ __forceinline__ void tile_body(
     // ---- which part of which tile is ours --------------------------------------------------
     int n_seg_work;   // 1 for a whole tile, up to 2 for a K-range that straddles two tiles
     int it_begin = 0, it_end = 0, sk_id = 0;
-    const bool is_dp = (int)blockIdx.x < plan.dp_grid;
+    const bool is_dp = bid < plan.dp_grid;
     if (is_dp) {
-        n_seg_work = xcd_chunked(blockIdx.x, plan.dp_tiles) < plan.dp_tiles ? 1 : 0;
+        n_seg_work = xcd_chunked(bid, plan.dp_tiles) < plan.dp_tiles ? 1 : 0;
     } else {
         // K-split workgroups in XCD-contiguous order too: the pieces of a tile, and the tiles that
         // share a weight panel, then run on one XCD at the same time and share its L2
-        const int id = blockIdx.x - plan.dp_grid, x = id & 7;   // dp_grid is a multiple of 8
+        const int id = bid - plan.dp_grid, x = id & 7;   // dp_grid is a multiple of 8
         sk_id = x * (plan.sk_blocks >> 3) + min(x, plan.sk_blocks & 7) + (id >> 3);
         const long total = (long)plan.sk_tiles * k_tiles;
         it_begin = (int)(total * sk_id / plan.sk_blocks);
@@ -641,7 +663,7 @@ __device__ __forceinline__ void tile_body(
         const int fr = stid & 15, fq = (stid & 63) >> 4;   // row in a 16-row block; 16-byte chunk of a k-step's four
         int lin, k0, k1, sk_tile = -1, first_blk = 0, last_blk = 0;
         if (is_dp) {
-            lin = xcd_chunked(blockIdx.x, plan.dp_tiles);
+            lin = xcd_chunked(bid, plan.dp_tiles);
             k0 = 0;
             k1 = k_tiles;
         } else {
@@ -1282,11 +1304,12 @@ template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
     void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
-    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope) {
+    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, PairedGemm pair) {
     if constexpr (is_persistent(BM, BN, WM, WN))
         persistent_body<EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, rope);
     else
-        tile_body<BM, BN, BK, WM, WN, NS, EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope);
+        tile_body<BM, BN, BK, WM, WN, NS, EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
+                                             pair);
 }
 
 // Shapes that only the choice by size uses (whole tiles, no K-split): the same body under another name.
@@ -1296,8 +1319,9 @@ template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(WM * WN * 64, 2) void small_tile_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
     void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
-    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope) {
-    tile_body<BM, BN, BK, WM, WN, NS, EPI, false>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope);
+    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, PairedGemm pair) {
+    tile_body<BM, BN, BK, WM, WN, NS, EPI, false>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
+                                                  pair);
 }
 
 // ---- host side ------------------------------------------------------------------------------
@@ -1377,7 +1401,8 @@ template <int BM, int BN, int BK, int WM, int WN, int NS, bool SMALL = false>
 static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, void* C,
                       int ldc, const void* R, int ldr, int epi, int slots_per_cu, int sk_pct,
                       float* partial, size_t partial_bytes, uint32_t* counters, int n_counters,
-                      const RopeEpilogue& rope, hipStream_t st, PlanPart part = PLAN_ALL) {
+                      const RopeEpilogue& rope, hipStream_t st, PlanPart part = PLAN_ALL,
+                      const PairedGemm* second = nullptr) {
     constexpr bool has_sk = !SMALL && !(WM * WN == 4 && ((BM / 32 + WM - 1) / WM) * (BN / WN / 32) >= 15);
     const int pb = part == PLAN_QUARTERS ? 2 : 1;   // (planned on the tiles that are quartered)
     GemmPlan plan = plan_for(M, N, K, BM * pb, BN * pb, BK, device_cu_count() * slots_per_cu,
@@ -1395,6 +1420,14 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
     }
     if (!has_sk && plan.sk_blocks > 0) return MVLA_EINVAL;
     int grid = plan.dp_grid + plan.sk_blocks;
+    PairedGemm pair{};
+    if (second) {
+        if (plan.sk_blocks > 0) return MVLA_EINVAL;     // (whole tiles only)
+        pair = *second;
+        pair.tiles_m = (pair.M + BM - 1) / BM;
+        pair.first_block = grid;
+        grid += (pair.tiles_m * plan.tiles_n + 7) / 8 * 8;
+    }
     if (grid == 0) return MVLA_OK;
     const size_t stage_bytes = (size_t)NS * (BM + BN) * (BK / 8) * sizeof(uint4);
     const size_t epi_bytes = EpiGeom<BM, BN, WM, NS>::BYTES;
@@ -1420,7 +1453,7 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
             if (dev >= 0 && dev < kMaxDevices) lds_set[dev] = true;                           \
         }                                                                                     \
         hipLaunchKernelGGL(kern, dim3(grid), block, lds, st, A, lda, W, M, N, K, C, ldc, R,   \
-                           ldr, plan, partial, counters, rope);                               \
+                           ldr, plan, partial, counters, rope, pair);                         \
     } while (0)
     if (epi == EPI_QKV_ROPE) MVLA_GEMM_LAUNCH(EPI_QKV_ROPE);
     else if (epi == EPI_RES_BF16_TO_F32) MVLA_GEMM_LAUNCH(EPI_RES_BF16_TO_F32);
@@ -1529,6 +1562,16 @@ static float estimate_us(int cfg, int M, int N, int K, int epi, bool split) {
     return t + split_us(cfg, p, epi);
 }
 
+// Whole tiles of two row counts in one launch.
+static float estimate_pair_us(int cfg, int M1, int M2, int N, int K, int epi) {
+    const TileCfg& c = kCfgs[cfg];
+    const int tm = (M1 + c.BM - 1) / c.BM + (M2 + c.BM - 1) / c.BM, tn = (N + c.BN - 1) / c.BN;
+    const int slots = device_cu_count() * c.slots_per_cu;
+    const long full = (long)tm * tn / slots, rem = (long)tm * tn % slots;
+    return kLaunchUs + full * (c.tile_us[epi] + K / 64 * slab_us(c, (float)slots, (float)tm, (float)tn)) +
+           (rem ? c.tile_us[epi] + K / 64 * slab_us(c, (float)rem, (float)tm, (float)tn) : 0.f);
+}
+
 int gemm_num_configs() { return kNumCfgs; }
 
 // The rotating q/k/v epilogue works on tiles that hold whole heads and lie inside one of the
@@ -1540,6 +1583,24 @@ static bool cfg_runs(const TileCfg& c, int epilogue, const RopeEpilogue* rope) {
 bool gemm_config_runs(int cfg, int epilogue, const RopeEpilogue* rope) {
     return cfg >= 0 && cfg < kNumCfgs && (epilogue != EPI_QKV_ROPE || rope) &&
            cfg_runs(kCfgs[cfg], epilogue, rope);
+}
+
+// Fastest configuration for a shape by the prediction (-1: none runs it).
+static int predict(int M, int N, int K, int epilogue, const RopeEpilogue* rope, int* split_pct, float* us) {
+    int best = -1;
+    *us = 0.f;
+    for (int i = 0; i < kAllCfgs; ++i) {
+        if (!cfg_runs(kCfgs[i], epilogue, rope)) continue;
+        for (int split = 0; split <= (kCfgs[i].can_split ? 1 : 0); ++split) {
+            const float t = estimate_us(i, M, N, K, epilogue, split != 0);
+            if (best < 0 || t < *us) {
+                *us = t;
+                best = i;
+                *split_pct = split ? 101 : 0;
+            }
+        }
+    }
+    return best;
 }
 
 // force_cfg >= 0 picks that tile configuration and force_split_pct the K-split threshold
@@ -1568,18 +1629,8 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         best = force_cfg;
         split_pct = force_split_pct;
     } else {
-        float best_us = 0.f;
-        for (int i = 0; i < kAllCfgs; ++i) {
-            if (!cfg_runs(kCfgs[i], epilogue, rope)) continue;
-            for (int split = 0; split <= (kCfgs[i].can_split ? 1 : 0); ++split) {
-                const float t = estimate_us(i, M, N, K, epilogue, split != 0);
-                if (best < 0 || t < best_us) {
-                    best_us = t;
-                    best = i;
-                    split_pct = split ? 101 : 0;
-                }
-            }
-        }
+        float us = 0.f;
+        best = predict(M, N, K, epilogue, rope, &split_pct, &us);
         if (best < 0) return MVLA_EUNSUPPORTED;
     }
     const RopeEpilogue rope_args = rope ? *rope : RopeEpilogue{};
@@ -1619,6 +1670,49 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         default: return launch_cfg<128, 64, 64, 2, 2, 5, true>(MVLA_ARGS);
     }
 #undef MVLA_ARGS
+}
+
+int rope_pair_config(int M1, const RopeEpilogue& rope1, int M2, const RopeEpilogue& rope2, int D) {
+    // what launch_gemm would refuse is left to it
+    if (M1 <= 0 || M2 <= 0 || D < 64 || D % 64 != 0 || D > (1 << 20)) return -1;
+    for (const RopeEpilogue* r : {&rope1, &rope2})
+        if (!r->pos || !r->rc || !r->rs || r->vt || r->rope_len <= 0 || r->D != D || (r->dh != 64 && r->dh != 128))
+            return -1;
+    if (rope1.dh != rope2.dh || D % rope1.dh != 0 || rope1.rope_len != rope2.rope_len) return -1;
+    int split = 0, best = -1;
+    float t1 = 0.f, t2 = 0.f, best_us = 0.f;
+    if (predict(M1, D, D, EPI_QKV_ROPE, &rope1, &split, &t1) < 0 ||
+        predict(M2, D, D, EPI_QKV_ROPE, &rope2, &split, &t2) < 0)
+        return -1;
+    for (int i : {1, 3, 5, 8, 9, 10, 11}) {   // (the larger ones are for shapes that fill the chip by themselves)
+        if (!cfg_runs(kCfgs[i], EPI_QKV_ROPE, &rope1)) continue;
+        const float t = estimate_pair_us(i, M1, M2, D, D, EPI_QKV_ROPE);
+        if (best < 0 || t < best_us) {
+            best_us = t;
+            best = i;
+        }
+    }
+    return best_us < t1 + t2 ? best : -1;
+}
+
+int launch_rope_pair(int cfg, const bf16_t* A1, const bf16_t* W1, int M1, void* C1, const RopeEpilogue& rope1,
+                     const bf16_t* A2, const bf16_t* W2, int M2, void* C2, const RopeEpilogue& rope2, int D,
+                     hipStream_t st) {
+    const PairedGemm second = {A2, W2, C2, rope2.pos, M2, 0, 0};
+#define MVLA_PAIR(BM, BN, WM, WN, NS, SMALL)                                                       \
+    launch_cfg<BM, BN, 64, WM, WN, NS, SMALL>(A1, D, W1, M1, D, D, C1, D, nullptr, 0, EPI_QKV_ROPE, 1, 0, nullptr, 0, \
+                                              nullptr, 0, rope1, st, PLAN_ALL, &second)
+    switch (cfg) {
+        case 1: return MVLA_PAIR(256, 128, 4, 2, 3, false);
+        case 3: return MVLA_PAIR(128, 128, 4, 2, 3, false);
+        case 5: return MVLA_PAIR(192, 128, 2, 4, 3, false);
+        case 8: return MVLA_PAIR(64, 64, 2, 2, 6, true);
+        case 9: return MVLA_PAIR(128, 128, 2, 2, 4, true);
+        case 10: return MVLA_PAIR(64, 128, 2, 2, 5, true);
+        case 11: return MVLA_PAIR(128, 64, 2, 2, 5, true);
+        default: return MVLA_EINVAL;
+    }
+#undef MVLA_PAIR
 }
 
 }  // namespace mvla

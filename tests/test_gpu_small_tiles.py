@@ -11,8 +11,10 @@ import oracle as O
 from helpers import assert_layer_close, device_layer, layer_cfg, oracle_weights, to64
 from paper_2604_09244_amd import binding as mv
 from paper_2604_09244_amd import workloads as W
+from test_gpu_layer import PROBS_ATOL, PROBS_RTOL
 
 pytestmark = pytest.mark.gpu
+EPI_QKV_ROPE = 0
 
 
 @pytest.mark.parametrize("D,H,F", [(256, 4, 1024), (256, 2, 192), (192, 3, 64), (1024, 8, 2816), (1024, 16, 704)])
@@ -32,3 +34,32 @@ def test_small_tiles(D, H, F, B, S):
         assert_layer_close(y[b], ref, f"D={D} F={F} B={B} S={S} sample {b}", D)
     assert torch.equal(y, again)
     ctx.close()
+
+
+@pytest.mark.parametrize("D,H", [(256, 4), (192, 3), (1024, 8)])
+@pytest.mark.parametrize("B,S,nt", [(1, 9, 1), (1, 66, 33), (3, 201, 7), (2, 520, 65)])
+def test_paired_projections(D, H, B, S, nt):
+    """Scoring pass with the key and the query projection in one launch, and (a choice recorded) in two:
+    both against the oracle at the bar of the layer's own scoring rows."""
+    wl = replace(W.WORKLOADS["tiny"], D=D, H=H, dh=D // H, F=64, n2=(S - nt) // 2, n3=S - nt - (S - nt) // 2,
+                 nt=nt, B=B, seed=D + S)
+    w_cpu = W.layer_weights(wl, 0)
+    ow = oracle_weights(w_cpu)
+    x, pos = W.hidden_states(wl, device="cuda")
+    for paired in (True, False):
+        ctx = mv.Context(B, S, D, H, 64, nt)
+        packed, struct = device_layer(ctx, wl, w_cpu)
+        if not paired:
+            ctx.set_gemm_choice(B * S, D, D, EPI_QKV_ROPE, 3, 0)
+        ctx.profile_enable(None)
+        probs = ctx.score_only(layer_cfg(wl), struct, x, pos, nt)
+        launches = [name for name, _, _ in ctx.profile_read()]
+        ctx.profile_enable([])
+        again = ctx.score_only(layer_cfg(wl), struct, x, pos, nt)
+        torch.cuda.synchronize()
+        assert launches.count("gemm_qkv") == (1 if paired else 2), launches
+        assert torch.equal(probs, again)
+        for b in range(B):
+            ref = O.score_only(to64(x[b]), pos[b].cpu().numpy(), ow, H, nt, wl.rms_eps, wl.rope_base)
+            assert (abs(to64(probs[b]) - ref) <= PROBS_RTOL * abs(ref) + PROBS_ATOL).all(), f"sample {b}"
+        ctx.close()
