@@ -318,7 +318,8 @@ int mvla_prefill_layer_prune(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvl
  * the four projections of a layer at M = B*S rows on this device, cycling
  * through the n_layers weight sets so that weights come from HBM as in real
  * use, and records the fastest per shape in the context; later layer calls at
- * that shape use it instead of the built-in cost model.  Results of the layer
+ * that shape use it instead of the built-in cost model (which also has a few smaller
+ * tiles that are not recorded).  Results of the layer
  * calls change only in fp32 summation order.  Uses the context's workspace,
  * runs on and SYNCHRONISES the context's stream (not for use under graph
  * capture); takes a few tens of milliseconds.
@@ -329,8 +330,9 @@ int mvla_tune_layers(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_
  * summation order across runs): configuration index 0 .. 6 (256x256 on eight waves,
  * 256x128, 128x128 two per CU, 128x128 on eight waves, 256x256 on four waves, 192x128,
  * 288x192 on four waves; the 288x192 shape runs whole tiles only and ignores the K-split
- * threshold, the four-wave 256x256 shape hands a K-split last round to the eight-wave
- * kernel of the same tile size in a second launch; a shape whose tiles do not hold whole heads is not used for the
+ * threshold, the four-wave 256x256 shape hands a last round that is to be cut to a second
+ * launch: in quarters to the 128x128 eight-wave kernel or along K to the 256x256 eight-wave
+ * one, whichever is predicted faster; a shape whose tiles do not hold whole heads is not used for the
  * q/k/v projection, whatever is recorded) and the K-split
  * threshold in percent (0 never, 101 whenever the last round of tiles is not
  * full); cfg < 0 removes the record.  Host-side only, nothing is launched. */

@@ -4,9 +4,11 @@
 //   S^T = K * Q^T   (MFMA rows = keys, columns = queries)
 //   O^T = V^T * P^T (MFMA rows = head-dim, columns = queries)
 // The S^T accumulator layout (lane = query column, registers = key rows) is
-// exactly the B-operand layout P^T needs, up to a fixed permutation of the 16
-// keys of a step which the V^T fragments follow, so probabilities go from one
-// product to the next without leaving registers.  Softmax statistics are
+// exactly the B-operand layout P^T needs when the K rows are laid down in LDS
+// with the two middle runs of four keys of every 16 swapped (att_key): a lane's
+// eight probabilities of a step are then eight consecutive keys, one 16-byte
+// V^T fragment, and go from one product to the next without leaving registers.
+// Softmax statistics are
 // per-lane scalars; the two lanes that share a query exchange one value per
 // tile.  K tiles [64 keys x dh] and V^T tiles [dh x 64 keys] travel from global
 // memory straight into a ring of LDS stages (global_load_lds, 16 bytes per
@@ -41,6 +43,11 @@ template <int CPR>
 __device__ __forceinline__ int att_swz(int row) {
     return CPR == 16 ? (row & 15) : ((row >> 1) & 7);
 }
+
+// Key of a tile that LDS row r holds: bits 2 and 3 swapped.  (In key order a lane needs two 8-byte pieces of two
+// V^T chunks, 32 reads a tile with two lanes on every bank; 16 whole chunks instead take the LDS's busy cycles from
+// 46 to 31 million at B = 16, S = 1344, 383 -> 366 us, and 1161 -> 1109 us at S = 2624.)
+__device__ __forceinline__ int att_key(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
 template <int DH, int NS>
 __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
@@ -90,13 +97,12 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
     // or one head's V^T: fewer address registers than one pointer per op)
     const bf16_t* k_base = k + (size_t)b * S * ld + h * DH;
     const bf16_t* v_base = vt + (size_t)(b * H + h) * DH * S_pad;
-    int k_row[K_LD];
     uint32_t k_off[K_LD], k_lds[K_LD];
+    const uint32_t k_pitch = (uint32_t)ld * 2u;
 #pragma unroll
     for (int i = 0; i < K_LD; ++i) {
         const int sl = i * ATT_THREADS + tid, row = sl / CPR, ch = (sl % CPR) ^ att_swz<CPR>(row);
-        k_row[i] = row;
-        k_off[i] = (uint32_t)ch * 16u;
+        k_off[i] = (uint32_t)att_key(row) * k_pitch + (uint32_t)ch * 16u;
         k_lds[i] = __builtin_amdgcn_readfirstlane(lds_base + (uint32_t)(i * ATT_THREADS + wave * 64) * 16u);
     }
     uint32_t v_off[V_LD], v_lds[V_LD];
@@ -107,14 +113,15 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
         v_lds[i] = __builtin_amdgcn_readfirstlane(
             lds_base + (uint32_t)(K_SLOTS + i * ATT_THREADS + wave * 64) * 16u);
     }
+    // (a key beyond the sequence: the last 16 bytes of its last row instead, which the mask leaves out)
 #define ATT_ISSUE(KT, STG)                                                                  \
     {                                                                                       \
         const int kt_ = min((KT), n_kt - 1);                                                \
         const uint32_t soff = (uint32_t)(STG) * STAGE * 16u;                                \
-        _Pragma("unroll") for (int i = 0; i < K_LD; ++i) {                                  \
-            const int key = min(kt_ * ATT_KT + k_row[i], S - 1);                            \
-            att_dma16(k_base, k_off[i] + (uint32_t)key * (uint32_t)ld * 2u, k_lds[i] + soff); \
-        }                                                                                   \
+        const size_t k_tile = (size_t)(kt_ * ATT_KT) * k_pitch;                             \
+        const uint32_t k_last = (uint32_t)(S - 1 - kt_ * ATT_KT) * k_pitch + (uint32_t)(DH - 8) * 2u; \
+        _Pragma("unroll") for (int i = 0; i < K_LD; ++i)                                    \
+            att_dma16(reinterpret_cast<const char*>(k_base) + k_tile, min(k_off[i], k_last), k_lds[i] + soff); \
         _Pragma("unroll") for (int i = 0; i < V_LD; ++i)                                    \
             att_dma16(v_base + kt_ * ATT_KT, v_off[i], v_lds[i] + soff);                    \
     }
@@ -143,7 +150,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
         // a wave whose queries all precede this tile has nothing to add
         if (key0 <= qw0 + 31 && qw0 < S) {
             const uint4* Kc = lds + stage * STAGE;
-            const uint2* Vc = reinterpret_cast<const uint2*>(Kc + K_SLOTS);
+            const uint4* Vc = Kc + K_SLOTS;
             // ---- S^T for the two 32-key halves of the tile
             // (the two independent accumulator chains alternate, so the matrix core does not
             // wait on its own results)
@@ -171,11 +178,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
                 const int row = min(d, DB - 1) * 32 + fr;
                 const int sw = att_swz<8>(row);
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    const uint2 lo = Vc[(row * 8 + ((ks * 2) ^ sw)) * 2 + fg];
-                    const uint2 hi = Vc[(row * 8 + ((ks * 2 + 1) ^ sw)) * 2 + fg];
-                    vfrag[d][ks] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                }
+                for (int ks = 0; ks < 4; ++ks) vfrag[d][ks] = Vc[row * 8 + ((ks * 2 + fg) ^ sw)];
             }
             // ---- (mask,) row max on the raw logits; only tiles that reach the diagonal or the end
             // of the sequence need the mask (wave-uniform test).  The softmax scale is positive, so
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int key = key0 + t * 32 + mfma32_row(v, lane);
+                        const int key = key0 + t * 32 + 16 * (v >> 3) + 8 * fg + (v & 7);   // att_key of the row
                         const float x = (key <= my_q && key < S) ? s_acc[t][v] : -INFINITY;
                         s_acc[t][v] = x;
                         tile_m = fmaxf(tile_m, x);
@@ -216,8 +219,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
                     pf[t * 2 + hh] = make_uint4(pack_bf16x2(e[0], e[1]), pack_bf16x2(e[2], e[3]),
                                                 pack_bf16x2(e[4], e[5]), pack_bf16x2(e[6], e[7]));
                 }
-            // the running max rarely moves after the first tiles: rescale only when it did for
-            // some query of the wave (a factor of exactly 1 otherwise)
+            // rescale only when the running max moved for some query of the wave (a factor of exactly 1 otherwise)
             if (__any(new_m != run_m)) {
                 const float corr = __builtin_amdgcn_exp2f((run_m - new_m) * scale_log2e);
                 run_l *= corr;
@@ -228,8 +230,8 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
                 run_m = new_m;
             }
             run_l += psum;
-            // ---- O^T += V^T * P^T ; the A fragment takes keys {4g..4g+3, 8+4g..8+4g+3} of each
-            // 16-key step, matching the key order of the P^T registers.  The fragments of a pair
+            // ---- O^T += V^T * P^T ; the A fragment takes keys 8g..8g+7 of each 16-key step,
+            // matching the key order of the P^T registers (see att_key).  The fragments of a pair
             // of head-dim blocks are read ahead of their MFMAs (the first pair before the softmax
             // arithmetic above, see vfrag), so the matrix core does not wait on LDS latency.
 #pragma unroll
@@ -241,11 +243,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
                         const int row = (dp + 2 + d) * 32 + fr;
                         const int sw = att_swz<8>(row);
 #pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const uint2 lo = Vc[(row * 8 + ((ks * 2) ^ sw)) * 2 + fg];
-                            const uint2 hi = Vc[(row * 8 + ((ks * 2 + 1) ^ sw)) * 2 + fg];
-                            vnext[d][ks] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                        }
+                        for (int ks = 0; ks < 4; ++ks) vnext[d][ks] = Vc[row * 8 + ((ks * 2 + fg) ^ sw)];
                     }
                 }
 #pragma unroll

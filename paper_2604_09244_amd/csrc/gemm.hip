@@ -9,19 +9,20 @@
 // always lands its 64 lanes on 1 KiB of consecutive LDS, the swizzle is applied
 // on the global side: lane l fetches the chunk that belongs at its slot.
 // MFMA fragments are double-buffered in registers: the ds_reads of k-step s+1
-// (and, across the stage barrier, of the next slab) are issued before the MFMAs
-// of step s.
+// (and, across the stage barrier, of the next slab) are dealt out between the
+// MFMAs of step s, and so are the next slabs' direct loads.
 //
 // Work split.  A workgroup owns a BM x BN tile; its waves own (BM/WM) x (BN/WN)
-// sub-tiles of 32x32 MFMA blocks (wave rows overlap by a block where the 32-row
-// blocks do not divide).  Tiles that fill whole rounds of the chip
+// sub-tiles of 32x32 blocks, four 16x16x32 products each (wave rows overlap by a block
+// where the 32-row blocks do not divide).  Tiles that fill whole rounds of the chip
 // are computed start to finish by one workgroup.  The tiles of the last,
 // partial round are cut along K into equal ranges of k-iterations handed out
 // contiguously to the otherwise idle CUs; the pieces of a tile meet in an fp32
 // partial buffer and whichever piece arrives last (integer arrival counter)
 // adds them up in fixed piece order and runs the epilogue, so results do not
 // depend on timing.
-// The four-wave 256x256 shape runs as a persistent kernel of its own (persistent_body).
+// The four-wave 256x256 shape runs as a persistent kernel of its own (persistent_body), its cut last
+// round in quarters on another shape where that is predicted faster.
 //
 // Epilogues: the q/k/v projection (q and k columns rotated by the row's position
 // on the fp32 accumulators and stored as bf16, v columns stored transposed for
