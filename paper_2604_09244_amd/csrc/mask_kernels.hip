@@ -66,40 +66,37 @@ constexpr int CM_WAVES = CM_THREADS / 64;
 
 struct CmShared {
     double d[2][3][CM_WAVES];
-    int n[2][3][CM_WAVES], any[2][CM_WAVES];
+    uint32_t n[2][CM_WAVES];
+    int any[2][CM_WAVES];
     float f[2][CM_WAVES];
 };
 
-// Sums three doubles and three counts over the workgroup, same order every time; returns whether any
-// thread's flag was set.  Counts and flag are kept per wave (n: this wave's, in every lane).  The LDS
-// areas alternate from call to call, so one barrier is enough.
-__device__ inline bool block_sum3(double s[3], int n[3], bool flag, CmShared& sh, int parity) {
+// Sums three doubles and a count (or two, 16 bits each) over the workgroup, same order every time; returns
+// whether any thread's flag was set.  The LDS areas alternate from call to call, so one barrier is enough.
+__device__ inline bool block_sum3(double s[3], uint32_t& n, bool flag, CmShared& sh, int parity) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) s[j] = wave_sum_f64(s[j]);
+    n = wave_sum_u32(n);
     const bool any = __ballot(flag) != 0ull;
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            sh.d[parity][j][threadIdx.x >> 6] = s[j];
-            sh.n[parity][j][threadIdx.x >> 6] = n[j];
-        }
+        for (int j = 0; j < 3; ++j) sh.d[parity][j][threadIdx.x >> 6] = s[j];
+        sh.n[parity][threadIdx.x >> 6] = n;
         sh.any[parity][threadIdx.x >> 6] = any;
     }
     __syncthreads();
     int f = 0;
+    n = 0u;
 #pragma unroll
-    for (int w = 0; w < CM_WAVES; ++w) f |= sh.any[parity][w];
+    for (int w = 0; w < CM_WAVES; ++w) {
+        f |= sh.any[parity][w];
+        n += sh.n[parity][w];
+    }
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        double a = 0.0;
-        int c = 0;
+        s[j] = 0.0;
 #pragma unroll
-        for (int w = 0; w < CM_WAVES; ++w) {
-            a += sh.d[parity][j][w];
-            c += sh.n[parity][j][w];
-        }
-        s[j] = a;
-        n[j] = c;
+        for (int w = 0; w < CM_WAVES; ++w) s[j] += sh.d[parity][j][w];
     }
     return f != 0;
 }
@@ -144,17 +141,18 @@ __global__ __launch_bounds__(CM_THREADS) void candidate_kernel(
     // Lloyd iterations (Sec. 4.2): centres start at min, mid-range, max; nearest centre, the
     // lower-numbered one on equal distance; a centre without points stays; stop when an
     // assignment repeats the previous one or after kmeans_max_iter assignments.
-    // (One barrier an iteration; counts by ballots.  An iteration is a chain of one fp64 tree and one
-    // LDS exchange: 256 patches 18.6 -> 15.3 us against shuffles and four barriers.)
+    // (One barrier an iteration.  A patch costs one LDS round trip: its score and label are asked for
+    // together, nothing in the loop is conditional, and the counts stay with the thread.  256 patches
+    // 15.0 us, 1024 28, 4096 88, 16384 253; with ballots for the counts and a branch around the label in
+    // here 18.6, 42, 158 and 490; with shuffles and four barriers an iteration 22.9, 39, 106 and 270.)
     double c0 = (double)lo, c2 = (double)hi, c1 = 0.5 * (c0 + c2);
-    const int P_up = (P + CM_THREADS - 1) / CM_THREADS * CM_THREADS;   // (whole waves in the loops: ballots)
     for (int it = 0; it < rules.kmeans_max_iter; ++it) {
         double s[3] = {0.0, 0.0, 0.0};
-        int n[3] = {0, 0, 0};
+        uint32_t n01 = 0u;      // patches of labels 0 and 1, 16 bits each (P <= 16384)
         bool changed = false;
-        for (int p = tid; p < P_up; p += CM_THREADS) {
-            const bool in = p < P;
-            const double x = (double)score[min(p, P - 1)];
+        for (int p = tid; p < P; p += CM_THREADS) {
+            const int was = label[p];
+            const double x = (double)score[p];
             const double d0 = fabs(x - c0), d1 = fabs(x - c1), d2 = fabs(x - c2);
             int l = 0;
             double best = d0;
@@ -163,21 +161,17 @@ __global__ __launch_bounds__(CM_THREADS) void candidate_kernel(
                 l = 1;
             }
             if (d2 < best) l = 2;
-            if (in) {
-                changed |= (l != (int)label[p]);
-                label[p] = (uint8_t)l;
-            }
+            changed |= l != was;
+            label[p] = (uint8_t)l;
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const bool mine = in && l == j;
-                s[j] += mine ? x : 0.0;
-                n[j] += (int)__popcll(__ballot(mine));
-            }
+            for (int j = 0; j < 3; ++j) s[j] += l == j ? x : 0.0;
+            n01 += l == 0 ? 1u : (l == 1 ? 0x10000u : 0u);
         }
-        if (!block_sum3(s, n, changed, sh, it & 1)) break;
-        if (n[0] > 0) c0 = s[0] / (double)n[0];
-        if (n[1] > 0) c1 = s[1] / (double)n[1];
-        if (n[2] > 0) c2 = s[2] / (double)n[2];
+        if (!block_sum3(s, n01, changed, sh, it & 1)) break;
+        const int n0 = (int)(n01 & 0xFFFFu), n1 = (int)(n01 >> 16), n2 = P - n0 - n1;
+        if (n0 > 0) c0 = s[0] / (double)n0;
+        if (n1 > 0) c1 = s[1] / (double)n1;
+        if (n2 > 0) c2 = s[2] / (double)n2;
     }
     __syncthreads();
 
@@ -186,7 +180,7 @@ __global__ __launch_bounds__(CM_THREADS) void candidate_kernel(
     const float* m2_s2 = x_hat + ((size_t)2 * B + b) * P;
     const float* m3_s2 = x_hat + ((size_t)3 * B + b) * P;
     double mu[3] = {0.0, 0.0, 0.0};
-    int unused[3] = {0, 0, 0};
+    uint32_t unused = 0u;
     for (int p = tid; p < P; p += CM_THREADS) {
         mu[0] += (double)m2_s2[p];
         mu[1] += (double)m3_s2[p];
@@ -194,7 +188,7 @@ __global__ __launch_bounds__(CM_THREADS) void candidate_kernel(
     block_sum3(mu, unused, false, sh, 0);
     const double mu2 = mu[0] / (double)P, mu3 = mu[1] / (double)P;
 
-    int kept = 0;
+    uint32_t kept = 0u;
     for (int p = tid; p < P; p += CM_THREADS) {
         // data-preprocessing stage (Sec. 4.1): dual threshold on the 3D feature share
         const float share3 = m3_s1[p];
@@ -216,13 +210,11 @@ __global__ __launch_bounds__(CM_THREADS) void candidate_kernel(
         mask2d[(size_t)b * P + p] = (uint8_t)(fin & C_2D ? 1 : 0);
         mask3d[(size_t)b * P + p] = (uint8_t)(fin & C_3D ? 1 : 0);
         if (sem) sem[(size_t)b * P + p] = (uint8_t)l;
-        kept += (int)(fin & 1u) + (int)(fin >> 1);
+        kept += (fin & 1u) + (fin >> 1);
     }
-    for (int o = 32; o > 0; o >>= 1) kept += __shfl_xor(kept, o);
     double z[3] = {0.0, 0.0, 0.0};
-    int cnt[3] = {kept, 0, 0};
-    block_sum3(z, cnt, false, sh, 1);
-    if (tid == 0) kept_len[b] = cnt[0] + n_text;
+    block_sum3(z, kept, false, sh, 1);
+    if (tid == 0) kept_len[b] = (int)kept + n_text;
 }
 
 int launch_candidate_masks(const float* x_hat, const float* sal, const float* u, int B, int P,

@@ -38,4 +38,17 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
     return x;
 }
 
+// Sum over the 64 lanes, in all of them.
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+    const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    x = h[0] + h[1];
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = r[0] + r[1];
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false);   // row_ror:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false);
+    return x;
+}
+
 }  // namespace mvla

@@ -153,3 +153,25 @@ def test_no_compiler_wait_catches_the_direct_loads(src, prefix, n_kernels, tmp_p
     assert len(found) == n_kernels, sorted(found)
     for name, waits in found.items():
         assert not waits, (name, waits)
+
+
+def test_clustering_loop_takes_one_lds_round_trip_a_patch(tmp_path):
+    """The Lloyd loop of the candidate masks runs once per patch of a thread and iteration: a patch's
+    score and label are read together (nothing waits in between) and nothing in the loop branches, so a
+    sample of many patches is bound by one LDS round trip a patch, not by two and a branch."""
+    lines = _device_assembly("mask_kernels.hip", tmp_path)
+    start = next(i for i, l in enumerate(lines) if re.match(r"^_ZN4mvla16candidate_kernel.*:", l))
+    k = lines[start:]
+    k = k[:next(i for i, l in enumerate(k) if "s_endpgm" in l)]
+    labels = {m.group(1): i for i, l in enumerate(k) for m in [re.match(r"^(\.LBB\d+_\d+):", l)] if m}
+    loops = [(labels[m.group(1)], i) for i, l in enumerate(k)
+             for m in [re.search(r"s_c?branch\w* (\.LBB\d+_\d+)", l)] if m and labels.get(m.group(1), i) < i]
+    inner = [(a, b) for a, b in loops if not any(a2 >= a and b2 <= b and (a2, b2) != (a, b) for a2, b2 in loops)]
+    bodies = [k[a:b + 1] for a, b in inner]
+    lloyd = [b for b in bodies if any("ds_read_u8" in x for x in b) and any("ds_write_b8" in x for x in b)]
+    assert len(lloyd) == 1
+    body = lloyd[0]
+    first_wait = next(i for i, x in enumerate(body) if "s_waitcnt" in x)
+    reads = [i for i, x in enumerate(body) if "ds_read" in x]
+    assert len(reads) == 2 and max(reads) < first_wait, body
+    assert sum("branch" in x for x in body) == 1, body
