@@ -4,6 +4,7 @@
 // reproducible bit for bit.
 #include "common.h"
 #include "wave.h"
+#include <type_traits>
 
 namespace mvla {
 
@@ -43,6 +44,7 @@ constexpr int FIN_U = 8;            // columns a thread takes at a time when a s
 constexpr long SOLO_MAX = 8192;
 constexpr int SOLO_MAX_ROWS = 128;  // ... most rows (eight a thread)
 constexpr int SOLO_MAX_COLS = 1024; // ... and most columns (their sums of four waves sit in LDS)
+constexpr long SAL_FEW = 96 * 1024;                // values up to which more splits pay (see salience_shape)
 constexpr int SAL_GROUPS = SAL_THREADS / SAL_LPR;  // 16 row-groups per block
 
 typedef float f32v4_t __attribute__((ext_vector_type(4)));
@@ -72,11 +74,12 @@ __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
 
     if (VEC == 4) {
         if (col0 + 3 < n_vis) {
-            // eight, then one load in flight per lane
+            // eight loads in flight per lane, the rows left over in batches of four, two and one (one by one,
+            // every one of up to seven was a memory round trip)
             auto add_rows = [&](auto load) __attribute__((always_inline)) {
-                constexpr int U = 8;
                 int r = r_begin + group;
-                for (; r + (U - 1) * SAL_GROUPS < r_end; r += U * SAL_GROUPS) {
+                auto batch = [&](auto rows) __attribute__((always_inline)) {
+                    constexpr int U = decltype(rows)::value;
                     f32v4_t t[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) t[u] = load(base + (size_t)(r + u * SAL_GROUPS) * S + col0);
@@ -84,12 +87,12 @@ __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
                     for (int u = 0; u < U; ++u)
 #pragma unroll
                         for (int v = 0; v < VEC; ++v) acc[v] += t[u][v];
-                }
-                for (; r < r_end; r += SAL_GROUPS) {
-                    const f32v4_t t = load(base + (size_t)r * S + col0);
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[v] += t[v];
-                }
+                    r += U * SAL_GROUPS;
+                };
+                while (r + 7 * SAL_GROUPS < r_end) batch(std::integral_constant<int, 8>{});
+                if (r + 3 * SAL_GROUPS < r_end) batch(std::integral_constant<int, 4>{});
+                if (r + SAL_GROUPS < r_end) batch(std::integral_constant<int, 2>{});
+                if (r < r_end) batch(std::integral_constant<int, 1>{});
             };
             if (read_once)
                 add_rows([](const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const f32v4_t*>(p)); });
@@ -159,11 +162,27 @@ __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
         __syncthreads();
         if (!is_last) return;
         if (tid < CW && c < n_vis) {
+            // (eight in flight together; a last batch of fewer loads the last one again and leaves it out)
             float s = 0.f;
-#pragma unroll 8
-            for (int i = 0; i < n_split; ++i)
-                s += __hip_atomic_load(&pslot[(size_t)i * CW + tid], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+            int i = 0;
+            auto part = [&](int j) __attribute__((always_inline)) {
+                return __hip_atomic_load(&pslot[(size_t)j * CW + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            for (; i + 8 <= n_split; i += 8) {
+                float t[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t[u] = part(i + u);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += t[u];
+            }
+            if (i < n_split) {
+                float t[7];
+#pragma unroll
+                for (int u = 0; u < 7; ++u) t[u] = part(min(i + u, n_split - 1));
+#pragma unroll
+                for (int u = 0; u < 7; ++u)
+                    if (i + u < n_split) s += t[u];
+            }
             put(s * inv_rows);
         }
         if (!FUSED) return;
@@ -265,10 +284,14 @@ static void salience_shape(int B, int R, int n_vis, int vec, int* chunks, int* n
     *chunks = (n_vis + cw - 1) / cw;
     // Aim for ~2048 blocks, at least 8 passes of the 16 row-groups each (a thread's eight loads then fly
     // together, and the last block to arrive has fewer partial sums to fetch: 1024 rows x 512 columns
-    // (B = 4) 14.2 -> 5.8 us against 2 passes); few rows are not split at all.
+    // (B = 4) 14.4 -> 5.3 us against 2 passes); few rows are not split at all.
     long blocks = (long)B * *chunks;
     int split = salience_solo(R, n_vis) ? 1 : (int)((2048 + blocks - 1) / blocks);
-    const int max_split = (R + 8 * SAL_GROUPS - 1) / (8 * SAL_GROUPS);
+    int max_split = (R + 8 * SAL_GROUPS - 1) / (8 * SAL_GROUPS);
+    // Where all of it is little, a compute unit's reads of its rows take longer than the exchange: down to two
+    // passes in up to eight splits, whose partial sums are still one batch of loads (512 rows x 160 columns
+    // 4.1 -> 3.7 us; 256 rows x 512 columns 3.7 with two splits, 3.8 with eight).
+    if (max_split > 1 && (long)B * R * n_vis < SAL_FEW) max_split = max(max_split, min(8, R / (2 * SAL_GROUPS)));
     if (split > max_split) split = max_split;
     if (split < 1) split = 1;
     *rows_per_split = (R + split - 1) / split;

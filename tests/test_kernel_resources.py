@@ -155,19 +155,26 @@ def test_no_compiler_wait_catches_the_direct_loads(src, prefix, n_kernels, tmp_p
         assert not waits, (name, waits)
 
 
+def _innermost_loops(lines, kernel_prefix):
+    """Per kernel: the instructions of its innermost loops (label ... backward branch)."""
+    starts = [i for i, l in enumerate(lines) if re.match(r"^%s.*:" % kernel_prefix, l)]
+    found = {}
+    for a0, b0 in zip(starts, starts[1:] + [len(lines)]):
+        k = lines[a0:b0]
+        k = k[:next((i for i, l in enumerate(k) if "s_endpgm" in l), len(k))]
+        labels = {m.group(1): i for i, l in enumerate(k) for m in [re.match(r"^(\.LBB\d+_\d+):", l)] if m}
+        loops = [(labels[m.group(1)], i) for i, l in enumerate(k)
+                 for m in [re.search(r"s_c?branch\w* (\.LBB\d+_\d+)", l)] if m and labels.get(m.group(1), i) < i]
+        inner = [(a, b) for a, b in loops if not any(a2 >= a and b2 <= b and (a2, b2) != (a, b) for a2, b2 in loops)]
+        found[lines[a0].split(":")[0]] = [k[a:b + 1] for a, b in inner]
+    return found
+
+
 def test_clustering_loop_takes_one_lds_round_trip_a_patch(tmp_path):
     """The Lloyd loop of the candidate masks runs once per patch of a thread and iteration: a patch's
     score and label are read together (nothing waits in between) and nothing in the loop branches, so a
     sample of many patches is bound by one LDS round trip a patch, not by two and a branch."""
-    lines = _device_assembly("mask_kernels.hip", tmp_path)
-    start = next(i for i, l in enumerate(lines) if re.match(r"^_ZN4mvla16candidate_kernel.*:", l))
-    k = lines[start:]
-    k = k[:next(i for i, l in enumerate(k) if "s_endpgm" in l)]
-    labels = {m.group(1): i for i, l in enumerate(k) for m in [re.match(r"^(\.LBB\d+_\d+):", l)] if m}
-    loops = [(labels[m.group(1)], i) for i, l in enumerate(k)
-             for m in [re.search(r"s_c?branch\w* (\.LBB\d+_\d+)", l)] if m and labels.get(m.group(1), i) < i]
-    inner = [(a, b) for a, b in loops if not any(a2 >= a and b2 <= b and (a2, b2) != (a, b) for a2, b2 in loops)]
-    bodies = [k[a:b + 1] for a, b in inner]
+    (bodies,) = _innermost_loops(_device_assembly("mask_kernels.hip", tmp_path), "_ZN4mvla16candidate_kernel").values()
     lloyd = [b for b in bodies if any("ds_read_u8" in x for x in b) and any("ds_write_b8" in x for x in b)]
     assert len(lloyd) == 1
     body = lloyd[0]
@@ -175,3 +182,14 @@ def test_clustering_loop_takes_one_lds_round_trip_a_patch(tmp_path):
     reads = [i for i, x in enumerate(body) if "ds_read" in x]
     assert len(reads) == 2 and max(reads) < first_wait, body
     assert sum("branch" in x for x in body) == 1, body
+
+
+def test_salience_loops_load_in_batches(tmp_path):
+    """Rows and partial sums of the salience kernels go out eight loads at a time; what is left over is a
+    shorter batch behind the loop.  A loop that takes one load a turn waits a memory round trip for each."""
+    kernels = _innermost_loops(_device_assembly("prune_kernels.hip", tmp_path), "_ZN4mvla15salience_kernelILi4E")
+    assert len(kernels) == 2                                  # plain and fused
+    for name, loops in kernels.items():
+        for what in (r"global_load_dwordx4", r"global_load_dword .* sc1"):
+            counts = [n for n in (sum(bool(re.search(what, x)) for x in b) for b in loops) if n]
+            assert counts and min(counts) >= 8, (name, what, counts)
