@@ -929,14 +929,14 @@ int launch_compact(const bf16_t* h, const int32_t* pos, const int32_t* kept_idx,
 // Eqs. 4-6): the 3D attention vector of a patch (over the head x query rows)
 // is split into its projection on the 2D vector and the orthogonal rest; the
 // outputs are the L1 shares |a2| / (|a2|+|a3|) and |a3_ortho| / (|a2|+|a3|).
-// One workgroup of 16 waves handles 16 patches of one sample; a thread owns VEC patches and every
-// (64 * VEC)-th row.  Up to RPT rows a thread (16 * VEC * 64 ... rows in all) stay in registers between the
-// two sums -- <a2,a2>, <a2,a3>, |a2|, |a3|, then the L1 norm of the residual --, so the rows are read once,
+// One workgroup handles 16 patches of one sample; a thread owns VEC patches and every RG-th row.  Up to RPT
+// rows a thread (1024 rows at sixteen waves) stay in registers between the two
+// sums -- <a2,a2>, <a2,a3>, |a2|, |a3|, then the L1 norm of the residual --, so the rows are read once,
 // all requests in flight together; longer ones are read a second time (served by the caches).
-// Bound by latency: 1024 rows x 2 x 256 patches (B = 4) 12.6 -> 7.4 us against 8 patches a
-// workgroup of four waves, read twice in 32-byte pieces.
+// Bound by latency: 1024 rows x 2 x 256 patches (B = 4) 11.0 -> 5.5 us against 8 patches a
+// workgroup of four waves, read twice in 32-byte pieces.  Few rows take four or eight waves: a wave's
+// reductions cost the same however few rows it has, and the waves of a SIMD take turns at them.
 // ---------------------------------------------------------------------------
-constexpr int DEC_THREADS = 1024;
 constexpr int DEC_PP = 16;                      // patches per workgroup
 
 // Sum over the lanes of a wave that hold the same patches (every LP-th lane), in all of them: rotations
@@ -951,13 +951,13 @@ __device__ __forceinline__ float same_patch_sum(float x) {
     return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
-template <int VEC, int RPT /* rows a thread keeps; 0: read twice */>
-__global__ __launch_bounds__(DEC_THREADS) void decompose_kernel(const float* __restrict__ attn,
+template <int THREADS, int VEC, int RPT /* rows a thread keeps; 0: read twice */>
+__global__ __launch_bounds__(THREADS) void decompose_kernel(const float* __restrict__ attn,
                                                                 int R, int S, int n_patch,
                                                                 float* __restrict__ m2d,
                                                                 float* __restrict__ m3d) {
-    constexpr int LP = DEC_PP / VEC, RG = DEC_THREADS / LP;   // lanes across the patches; row groups
-    __shared__ float red[4][DEC_THREADS / 64][DEC_PP], tot[4][DEC_PP];
+    constexpr int LP = DEC_PP / VEC, RG = THREADS / LP;   // lanes across the patches; row groups
+    __shared__ float red[4][THREADS / 64][DEC_PP], tot[4][DEC_PP];
     const int tid = threadIdx.x, l = tid % LP, g = tid / LP, wave = tid >> 6;
     const int b = blockIdx.y, p0 = blockIdx.x * DEC_PP + l * VEC;
     const float* base = attn + (size_t)b * R * S + p0;
@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decompose_kernel(const float* __r
     if (tid < 4 * DEC_PP) {              // one wave folds the waves' sums: 4 quantities x 16 patches
         float t = 0.f;
 #pragma unroll
-        for (int w = 0; w < DEC_THREADS / 64; ++w) t += red[tid / DEC_PP][w][tid % DEC_PP];
+        for (int w = 0; w < THREADS / 64; ++w) t += red[tid / DEC_PP][w][tid % DEC_PP];
         tot[tid / DEC_PP][tid % DEC_PP] = t;
     }
     __syncthreads();
@@ -1038,7 +1038,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decompose_kernel(const float* __r
     if (tid < DEC_PP && p < n_patch) {
         float t = 0.f;
 #pragma unroll
-        for (int w = 0; w < DEC_THREADS / 64; ++w) t += red[0][w][tid];
+        for (int w = 0; w < THREADS / 64; ++w) t += red[0][w][tid];
         const float den = tot[2][tid] + tot[3][tid];
         m2d[(size_t)b * n_patch + p] = den > 0.f ? tot[2][tid] / den : 0.f;
         m3d[(size_t)b * n_patch + p] = den > 0.f ? t / den : 0.f;
@@ -1049,15 +1049,22 @@ int launch_decompose(const float* attn, int B, int H, int Nq, int S, int n_patch
                      float* m3d, hipStream_t st) {
     const int R = H * Nq;
     const dim3 grid((n_patch + DEC_PP - 1) / DEC_PP, B);
-#define MVLA_DEC(V, T)                                                                              \
-    hipLaunchKernelGGL((decompose_kernel<V, T>), grid, dim3(DEC_THREADS), 0, st, attn, R, S, n_patch, m2d, m3d)
-    // 16 bytes a lane where every row of both halves is aligned for it: 256 row groups, else 64
-    if (S % 4 == 0 && n_patch % 4 == 0 && (reinterpret_cast<uintptr_t>(attn) & 15) == 0) {
-        if (R <= 256 * 4) MVLA_DEC(4, 4);
-        else MVLA_DEC(4, 0);
+#define MVLA_DEC(T, V, N)                                                                              \
+    hipLaunchKernelGGL((decompose_kernel<T, V, N>), grid, dim3(T), 0, st, attn, R, S, n_patch, m2d, m3d)
+    // As few threads as hold all rows in registers.  16 bytes a lane where every row of both halves is
+    // aligned for it, T / 4 row groups of four rows each; else, and for up to 256 rows, 4 bytes, T / 16 row groups of
+    // sixteen (a quarter of the reductions).  64 rows x 2 x 256 patches (B = 4) 3.0 us, with 256 threads and
+    // 16 bytes 3.6, with 1024 threads 4.7; 256 rows 3.4, 4.0 and 4.8; 512 rows with 512 threads 4.2, with 1024 5.0.
+    if (R <= 256) {
+        MVLA_DEC(256, 1, 16);
+    } else if (S % 4 == 0 && n_patch % 4 == 0 && (reinterpret_cast<uintptr_t>(attn) & 15) == 0) {
+        if (R <= 512) MVLA_DEC(512, 4, 4);
+        else if (R <= 1024) MVLA_DEC(1024, 4, 4);
+        else MVLA_DEC(1024, 4, 0);
     } else {
-        if (R <= 64 * 16) MVLA_DEC(1, 16);
-        else MVLA_DEC(1, 0);
+        if (R <= 512) MVLA_DEC(512, 1, 16);
+        else if (R <= 1024) MVLA_DEC(1024, 1, 16);
+        else MVLA_DEC(1024, 1, 0);
     }
 #undef MVLA_DEC
     MVLA_HIP_CHECK(hipGetLastError());

@@ -83,3 +83,20 @@ def test_decompose_paths(ctx, B, H, Nq, P, nt):
     # sums of H*Nq fp32 values in groups of at most 16 a thread: well inside 1e-5 relative
     for got, ref in ((m2, r2), (m3, r3)):
         assert np.max(np.abs(got.cpu().numpy() - ref)) <= 1e-5 * max(1.0, float(np.max(ref)))
+
+
+@pytest.mark.parametrize("P,nt", [(20, 4), (21, 2)])       # 16 bytes a lane, and 4
+@pytest.mark.parametrize("R", [1, 15, 16, 17, 255, 256, 257, 511, 512, 513, 1023, 1025])
+def test_decompose_row_limits(R, P, nt):
+    """Row counts around the limits of the workgroup sizes, a row of one value among them."""
+    B, S = 2, 2 * P + nt
+    g = torch.Generator().manual_seed(R * 100 + P)
+    p = torch.rand(B, 1, R, S, generator=g) ** 4
+    p = (p / p.sum(-1, keepdim=True)).contiguous()
+    ctx = mv.Context(B, S, 64, 1, 64, R)
+    m2, m3 = ctx.modality_decompose(p.cuda(), P)
+    r2, r3 = O.modality_decompose(p.numpy().astype(np.float64), P)
+    # sums of R fp32 values, at most 64 a thread: inside 1e-5 relative
+    for got, ref in ((m2, r2), (m3, r3)):
+        assert np.max(np.abs(got.cpu().numpy() - ref)) <= 1e-5 * max(1.0, float(np.max(ref)))
+    ctx.close()

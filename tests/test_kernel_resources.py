@@ -193,3 +193,12 @@ def test_salience_loops_load_in_batches(tmp_path):
         for what in (r"global_load_dwordx4", r"global_load_dword .* sc1"):
             counts = [n for n in (sum(bool(re.search(what, x)) for x in b) for b in loops) if n]
             assert counts and min(counts) >= 8, (name, what, counts)
+
+
+def test_decomposition_workgroups_fit_their_rows(tmp_path):
+    """Per-patch decomposition: four, eight and sixteen waves for up to 256, 512 and more rows (sixteen for
+    a handful of rows spend their time on reductions of nothing), none of them spilling."""
+    k = {n: v for n, v in _resource_usage("prune_kernels.hip").items() if "decompose_kernel" in n}
+    assert {int(re.search(r"decompose_kernelILi(\d+)E", n).group(1)) for n in k} == {256, 512, 1024}
+    for name, v in k.items():
+        assert v["ScratchSize"] == 0, (name, v)
