@@ -1023,7 +1023,8 @@ __global__ __launch_bounds__(THREADS) void decompose_kernel(const float* __restr
     };
     if (RPT > 0) {
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) rest(k2[i], k3[i]);
+        for (int i = 0; i < RPT; ++i)
+            if (g + i * RG < R) rest(k2[i], k3[i]);   // (0 - c * 0 is no zero where c has overflowed)
     } else if (live) {
 #pragma unroll 4
         for (int r = g; r < R; r += RG) rest(load(r, 0), load(r, n_patch));

@@ -100,3 +100,15 @@ def test_decompose_row_limits(R, P, nt):
     for got, ref in ((m2, r2), (m3, r3)):
         assert np.max(np.abs(got.cpu().numpy() - ref)) <= 1e-5 * max(1.0, float(np.max(ref)))
     ctx.close()
+
+
+@pytest.mark.parametrize("R,P", [(5, 20), (300, 20), (300, 21), (900, 20), (900, 21)])
+def test_decompose_overflowed_coefficient(R, P):
+    """<a2,a3>/<a2,a2> beyond fp32: every row's rest is infinite and so is the share.  Rows that a thread
+    keeps room for and that do not exist must not turn it into NaN."""
+    ctx = mv.Context(1, 2 * P, 64, 1, 64, R)
+    p = torch.empty(1, 1, R, 2 * P, device="cuda")
+    p[..., :P], p[..., P:] = 1e-19, 1e21               # squares 1e-38, coefficient 1e40, products finite
+    m2, m3 = ctx.modality_decompose(p, P)
+    assert (m2 < 1e-30).all() and torch.isposinf(m3).all(), (m2, m3)
+    ctx.close()
