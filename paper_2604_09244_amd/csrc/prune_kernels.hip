@@ -27,7 +27,7 @@ struct FusedPrune {
     uint32_t* sample_counters;  // one arrival counter per sample (kept at zero between calls)
 };
 template <typename Load>
-__device__ __forceinline__ void finish_sample(Load load, float* sal_b, const FusedPrune& f, int b, uint32_t* keys);
+__device__ __forceinline__ void finish_sample(Load load, const FusedPrune& f, int b, uint32_t* keys);
 
 constexpr int SAL_THREADS = 256;
 constexpr int SEL_MAX_N = 16384;    // largest segment the selection stages in LDS
@@ -39,11 +39,6 @@ constexpr int SAL_LPR = 16;                        // lanes per row-group
 // tensor there: 8.9 MB read non-temporally made that pair 1.6 us slower.
 constexpr size_t SAL_STREAM_BYTES = size_t(256) << 20;
 constexpr int FIN_U = 8;            // columns a thread takes at a time when a sample is finished
-// Most attention values of a sample that one workgroup sums (32 KiB).  64 rows x 128 columns: 6.8 us, 10.4
-// with the columns spread over four workgroups; 32 rows x 512 columns: 15.1 us against 9.7 with eight.
-constexpr long SOLO_MAX = 8192;
-constexpr int SOLO_MAX_ROWS = 128;  // ... most rows (eight a thread)
-constexpr int SOLO_MAX_COLS = 1024; // ... and most columns (their sums of four waves sit in LDS)
 constexpr long SAL_FEW = 96 * 1024;                // values up to which more splits pay (see salience_shape)
 constexpr int SAL_GROUPS = SAL_THREADS / SAL_LPR;  // 16 row-groups per block
 
@@ -207,75 +202,7 @@ __global__ __launch_bounds__(SAL_THREADS) void salience_kernel(
 #pragma unroll
         for (int u = 0; u < FIN_U; ++u)
             v[u] = __hip_atomic_load(&sal_b[col[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }, nullptr, fused, b, dyn_lds);
-}
-
-// The fused step of a sample whose rows are few: one workgroup sums all its columns (same order of
-// additions as an unsplit salience_kernel) and goes straight on to budget and selection.  With
-// several workgroups a sample, the store, arrival and load that join them (a memory round trip
-// each) cost more than one compute unit needs to read 32 KiB (see SOLO_MAX).
-template <int VEC>
-__global__ __launch_bounds__(SAL_THREADS) void prune_solo_kernel(const float* __restrict__ attn, int R, int S,
-                                                                 int n_vis, float inv_rows,
-                                                                 float* __restrict__ sal, FusedPrune fused) {
-    extern __shared__ uint32_t dyn_lds[];   // keys [n_vis], then the four waves' sums [4][chunks * CW]
-    constexpr int CW = SAL_LPR * VEC, CU = 4;
-    const int b = blockIdx.x, tid = threadIdx.x, lane16 = tid % SAL_LPR, group = tid / SAL_LPR;
-    const int wave = tid / 64, lane = tid % 64;
-    const int chunks = (n_vis + CW - 1) / CW;
-    float* part = reinterpret_cast<float*>(dyn_lds + n_vis);
-    const float* base = attn + (size_t)b * R * S;
-    for (int c0 = 0; c0 < chunks; c0 += CU) {
-        float acc[CU][VEC];
-#pragma unroll
-        for (int u = 0; u < CU; ++u)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[u][v] = 0.f;
-#pragma unroll 4
-        for (int r = group; r < R; r += SAL_GROUPS)
-#pragma unroll
-            for (int u = 0; u < CU; ++u) {
-                const int col0 = (c0 + u) * CW + lane16 * VEC;
-                const float* p = base + (size_t)r * S + col0;
-                if (VEC == 4 && col0 + 3 < n_vis) {
-                    const float4 a = *reinterpret_cast<const float4*>(p);
-                    acc[u][0] += a.x; acc[u][1 % VEC] += a.y; acc[u][2 % VEC] += a.z; acc[u][3 % VEC] += a.w;
-                } else {
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v)
-                        if (col0 + v < n_vis) acc[u][v] += p[v];
-                }
-            }
-#pragma unroll
-        for (int u = 0; u < CU; ++u)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                acc[u][v] += __shfl_xor(acc[u][v], 16);
-                acc[u][v] += __shfl_xor(acc[u][v], 32);
-            }
-        if (lane < SAL_LPR)
-#pragma unroll
-            for (int u = 0; u < CU; ++u)
-                if (c0 + u < chunks)
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v)
-                        part[(wave * chunks + c0 + u) * CW + lane * VEC + v] = acc[u][v];
-    }
-    __syncthreads();
-    finish_sample([&](const int (&col)[FIN_U], float (&v)[FIN_U]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < FIN_U; ++u) {
-            v[u] = 0.f;
-#pragma unroll
-            for (int w = 0; w < SAL_THREADS / 64; ++w) v[u] += part[w * chunks * CW + col[u]];
-            v[u] *= inv_rows;
-        }
-    }, sal + (size_t)b * n_vis, fused, b, dyn_lds);
-}
-
-// few enough rows that one workgroup takes a whole sample in the fused step
-static bool salience_solo(int R, int n_vis) {
-    return (long)R * n_vis <= SOLO_MAX && R <= SOLO_MAX_ROWS && n_vis <= SOLO_MAX_COLS;
+    }, fused, b, dyn_lds);
 }
 
 static void salience_shape(int B, int R, int n_vis, int vec, int* chunks, int* n_split,
@@ -286,7 +213,7 @@ static void salience_shape(int B, int R, int n_vis, int vec, int* chunks, int* n
     // together, and the last block to arrive has fewer partial sums to fetch: 1024 rows x 512 columns
     // (B = 4) 14.4 -> 5.3 us against 2 passes); few rows are not split at all.
     long blocks = (long)B * *chunks;
-    int split = salience_solo(R, n_vis) ? 1 : (int)((2048 + blocks - 1) / blocks);
+    int split = (int)((2048 + blocks - 1) / blocks);
     int max_split = (R + 8 * SAL_GROUPS - 1) / (8 * SAL_GROUPS);
     // Where all of it is little, a compute unit's reads of its rows take longer than the exchange: down to two
     // passes in up to eight splits, whose partial sums are still one batch of loads (512 rows x 160 columns
@@ -324,18 +251,6 @@ static int launch_salience_any(const float* attn, int B, int H, int Nq, int S, i
         f = *fused;
         f.sample_counters = counters + (size_t)B * chunks;
         lds = (size_t)max(f.n2 + f.n3, 1) * 4;   // selection keys of both segments
-        if (salience_solo(R, n_vis)) {           // (at most 4 KiB of keys and 17 KiB of sums)
-            const int cw = SAL_LPR * (vec4 ? 4 : 1);
-            lds += (size_t)(SAL_THREADS / 64) * chunks * cw * 4;
-            if (vec4)
-                hipLaunchKernelGGL(prune_solo_kernel<4>, dim3(B), dim3(SAL_THREADS), lds, st, attn, R, S, n_vis,
-                                   inv_rows, sal, f);
-            else
-                hipLaunchKernelGGL(prune_solo_kernel<1>, dim3(B), dim3(SAL_THREADS), lds, st, attn, R, S, n_vis,
-                                   inv_rows, sal, f);
-            MVLA_HIP_CHECK(hipGetLastError());
-            return MVLA_OK;
-        }
     }
     // (the fused variants keep the keys of both segments in LDS: up to 128 KiB, above the default
     // limit of a kernel, which is raised once per device)
@@ -531,8 +446,8 @@ int launch_budget(const float* sal, int B, int n2, int n3, int k_total, int min2
 // Bound by the chain of dependent LDS accesses and barriers, not by bytes.
 // Against four 8-bit radix passes over the whole key range and one segment
 // after the other: 16384 + 16384 tokens
-// (B = 3) 33 -> 15.5 us with the budget call, 768 + 1024 (B = 8) 10.8 -> 9.4 us; fused, two segments of
-// 64 tokens 10.4 -> 6.8 us.
+// (B = 1) 52 -> 17 us, 768 + 1024 (B = 8) 7.8 -> 6.4; the fused step and its gather, 64 rows of two segments of
+// 64 tokens, 13.1 -> 8.0.
 // ---------------------------------------------------------------------------
 
 __device__ inline uint32_t sal_key(float x) {
@@ -813,10 +728,9 @@ __global__ __launch_bounds__(GW * 64) void select_kernel(const float* __restrict
 
 // Budget and selection of one sample by one workgroup (end of the fused kernels).  Same
 // summation order as budget_kernel, same selection as select_kernel; the two segments are
-// selected side by side, half the workgroup's waves each.  load: the salience of FIN_U columns;
-// sal_b: where it is still to be stored, or null.
+// selected side by side, half the workgroup's waves each.  load: the salience of FIN_U columns.
 template <typename Load>
-__device__ __forceinline__ void finish_sample(Load load, float* sal_b, const FusedPrune& f, int b, uint32_t* keys) {
+__device__ __forceinline__ void finish_sample(Load load, const FusedPrune& f, int b, uint32_t* keys) {
     __shared__ double sh_d[2 * (BUD_THREADS / 64)];
     __shared__ SelShared<SAL_THREADS / 128, 2> sh;
     __shared__ int sh_k2;
@@ -834,7 +748,6 @@ __device__ __forceinline__ void finish_sample(Load load, float* sal_b, const Fus
             for (int u = 0; u < FIN_U; ++u)
                 if (i + u * BUD_THREADS < n) {
                     a += (double)v[u];
-                    if (sal_b) sal_b[col[u]] = v[u];
                     keys[col[u]] = sal_key(v[u]);
                 }
         }

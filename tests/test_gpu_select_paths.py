@@ -1,7 +1,6 @@
 """Selection and fused pruning at the sizes where their kernels change path: segments of one wave
 (ranked directly), segments around the four- / sixteen-wave limit, keys that agree in all but their
-last bits (the narrowing goes through every round), samples around the limits up to which one
-workgroup sums all columns.  Selection is compared with the oracle exactly; the fused step with the
+last bits (the narrowing goes through every round), the fused step with few and many rows and columns.  Selection is compared with the oracle exactly; the fused step with the
 four single calls exactly (same order of additions, same selection)."""
 import numpy as np
 import pytest
@@ -45,7 +44,7 @@ def test_select_paths(ctx, n2, n3, kind):
         assert np.array_equal(got.cpu().numpy(), O.select_topk(s, k2k3, n2, n3, 3)), (n2, n3, kind, K)
 
 
-# H * Nq rows x columns: 8192 values is the most one workgroup takes, 128 rows and 1024 columns
+# H * Nq rows x columns: up to 128 rows are one split, more are several
 @pytest.mark.parametrize("H,Nq,n2,n3,nt", [(4, 16, 64, 64, 16), (4, 16, 64, 65, 16), (4, 32, 32, 32, 32), (4, 33, 30, 30, 33),
                                            (4, 32, 64, 65, 32), (1, 8, 512, 512, 8), (1, 7, 513, 512, 7),
                                            (4, 8, 256, 256, 32), (2, 8, 3, 700, 9), (4, 160, 300, 700, 160)])
