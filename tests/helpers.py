@@ -1,4 +1,6 @@
 """Shared plumbing of the GPU parity tests (no method arithmetic of the HIP path)."""
+import re
+
 import numpy as np
 import torch
 
@@ -23,6 +25,30 @@ def device_layer(ctx, wl, w_cpu, rope_len=None):
 
 def layer_cfg(wl):
     return mv.LayerCfg(wl.D, wl.H, wl.dh, wl.F, wl.rms_eps)
+
+
+# Template arguments of the projection kernels' tile configurations (rows, columns, waves along
+# each, stages), by index; those from 7 on are used by the choice by size only.
+TILE_CONFIGS = [(256, 256, 2, 4, 2), (256, 128, 4, 2, 3), (128, 128, 2, 2, 2), (128, 128, 4, 2, 3),
+                (256, 256, 2, 2, 2), (192, 128, 2, 4, 3), (288, 192, 2, 2, 2), (128, 192, 2, 2, 3),
+                (64, 64, 2, 2, 6), (128, 128, 2, 2, 4), (64, 128, 2, 2, 5), (128, 64, 2, 2, 5)]
+EPI_QKV, EPI_OUT, EPI_DOWN, EPI_GATEUP = range(4)
+
+
+def projection_launches(fn):
+    """Runs fn under the profiler: [(epilogue, tile configuration), ...] of the projection kernels that
+    it launched, by the names of the kernels that ran."""
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    found = []
+    for e in prof.events():
+        m = re.search(r"mvla::(?:gemm|small_tile)_kernel<(\d+), (\d+), 64, (\d+), (\d+), (\d+), (\d+)>", e.name)
+        if m:
+            v = [int(g) for g in m.groups()]
+            found.append((v[5], TILE_CONFIGS.index(tuple(v[:5]))))
+    return found
 
 
 def rms(a):
