@@ -1,6 +1,6 @@
 """Selection and fused pruning at the sizes where their kernels change path: segments of one wave
 (ranked directly), segments around the four- / sixteen-wave limit, keys that agree in all but their
-last bits (the narrowing goes through every round), the fused step with few and many rows and columns.  Selection is compared with the oracle exactly; the fused step with the
+last bits (one histogram of single key values), thresholds that take one to four histograms, the fused step with few and many rows and columns.  Selection is compared with the oracle exactly; the fused step with the
 four single calls exactly (same order of additions, same selection)."""
 import numpy as np
 import pytest
@@ -42,6 +42,39 @@ def test_select_paths(ctx, n2, n3, kind):
         k2k3 = np.stack([k2, K - k2], 1).astype(np.int32)
         got = ctx.select_topk(torch.from_numpy(s).cuda(), torch.from_numpy(k2k3).cuda(), n2, n3, 3, K)
         assert np.array_equal(got.cpu().numpy(), O.select_topk(s, k2k3, n2, n3, 3)), (n2, n3, kind, K)
+
+
+def _rounds(s, k):
+    """Histograms that the search for the k-th largest score takes: 1024 bins over the keys' range, then over
+    the bin that holds the threshold, until it holds at most 64 keys or is one key value."""
+    u = s.view(np.uint32).astype(np.int64)
+    keys = np.where(u >> 31, 0xFFFFFFFF - u, u + 0x80000000)
+    lo, hi, n = int(keys.min()), int(keys.max()), 0
+    t = int(np.sort(keys)[len(keys) - k])
+    while True:
+        n += 1
+        shift = max(0, (hi - lo).bit_length() - 10)
+        b = (t - lo) >> shift
+        lo, hi = lo + (b << shift), min(hi, lo + ((b + 1) << shift) - 1)
+        if shift == 0 or np.sum((keys >= lo) & (keys <= hi)) <= 64:
+            return n
+
+
+@pytest.mark.parametrize("n", [1200, 5000])          # four waves, sixteen
+def test_select_takes_every_number_of_histograms(ctx, n):
+    """Scores between two outliers, crowded around 1 in ever narrower bands: most of a bin's keys lie in
+    one bin of the next histogram."""
+    r = np.random.default_rng(n)
+    bands = np.concatenate([r.integers(0, w, size=n // 6) for w in (4, 4, 1 << 9, 1 << 17)]).astype(np.uint32)
+    s = np.concatenate([[-3e38, 3e38], r.uniform(2, 1e30, size=n - 2 - len(bands))]).astype(np.float32)
+    s = r.permutation(np.concatenate([s, (bands + np.uint32(0x3F800000)).view(np.float32)]))
+    took = set()
+    for k in [1, 2, n // 6, n // 3, n // 2, *range(n // 3 + 20, n, n // 37), n - 1]:
+        took.add(_rounds(s, k))
+        k2k3 = np.array([[k, 0]], np.int32)
+        got = ctx.select_topk(torch.from_numpy(s[None]).cuda(), torch.from_numpy(k2k3).cuda(), n, 0, 0, k)
+        assert np.array_equal(got.cpu().numpy(), O.select_topk(s[None], k2k3, n, 0, 0)), k
+    assert took == {1, 2, 3, 4}, took
 
 
 # H * Nq rows x columns: up to 128 rows are one split, more are several

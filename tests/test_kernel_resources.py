@@ -10,6 +10,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2604_09244_amd", "csrc")
+PROJECTION_KERNEL = "_ZN4mvla(?:11gemm|17small_tile)_kernelI"
 
 
 def _resource_usage(src):
@@ -35,8 +36,8 @@ def _resource_usage(src):
 
 def test_projection_kernels_fit_their_launch_shapes():
     k = _resource_usage("gemm.hip")
-    gemm = {n: v for n, v in k.items() if "gemm_kernel" in n}
-    assert len(gemm) == 28                                   # 7 tile shapes x 4 epilogues
+    gemm = {n: v for n, v in k.items() if "gemm_kernel" in n or "small_tile_kernel" in n}
+    assert len(gemm) == 48                                   # 12 tile shapes x 4 epilogues
     for name, v in gemm.items():
         assert v["ScratchSize"] == 0, (name, v)              # (a spill reload in the main loop
         four_wave_big = ("ILi256ELi256ELi64ELi2ELi2ELi2E" in name    # would also wait on the loads)
@@ -137,12 +138,12 @@ def test_no_compiler_vmcnt_wait_inside_the_projection_main_loops(tmp_path):
     runs every iteration and waits for the direct loads just issued.  The kernel clears the
     compiler's count once per tile; no main loop of any configuration may hold such a wait."""
     found, n_loops = _waits_in_innermost_mfma_loops(_device_assembly("gemm.hip", tmp_path),
-                                                    "_ZN4mvla11gemm_kernelI")
-    assert n_loops == 28
+                                                    PROJECTION_KERNEL)
+    assert n_loops == 48
     assert not found, found
 
 
-@pytest.mark.parametrize("src,prefix,n_kernels", [("gemm.hip", "_ZN4mvla11gemm_kernelI", 28),
+@pytest.mark.parametrize("src,prefix,n_kernels", [("gemm.hip", PROJECTION_KERNEL, 48),
                                                   ("attention.hip", "_ZN4mvla16attention_kernelI", 2)])
 def test_no_compiler_wait_catches_the_direct_loads(src, prefix, n_kernels, tmp_path):
     """The global->LDS loads are issued from inline asm and waited for explicitly.  A wait the
