@@ -183,11 +183,11 @@ def main():
         measured = dict(
             read_gbs=ctx.peak_probe(mv.PROBE_READ, big, 10),
             copy_gbs=ctx.peak_probe(mv.PROBE_COPY, big, 10),
-            mfma_tflops_zeros=ctx.peak_probe(mv.PROBE_MFMA, zeros, 5),
-            mfma_tflops_random=ctx.peak_probe(mv.PROBE_MFMA, rnd, 5),
+            mfma_tflops_zeros=ctx.peak_probe(mv.PROBE_MFMA, zeros, 20),
+            mfma_tflops_random=ctx.peak_probe(mv.PROBE_MFMA, rnd, 20),
             empty_launch_us=ctx.peak_probe(mv.PROBE_LAUNCH, None, 200),
             note="stream read of 2 GiB; copy of 1 GiB to 1 GiB (bytes read + written); loop of "
-                 "32x32x16 bf16 matrix-core products on register operands, four waves per "
+                 "16x16x32 bf16 matrix-core products on register operands, four waves per "
                  "compute unit, all-zero and N(0, 0.25) operands; empty kernels back to back")
         del big
 

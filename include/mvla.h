@@ -491,11 +491,11 @@ const char* mvla_kernel_name(int id);
  * stream between two HIP events and SYNCHRONISES the stream.
  *   MVLA_PROBE_READ   streams `bytes` of buf once per launch        -> GB/s
  *   MVLA_PROBE_COPY   copies the first half of buf to the second    -> GB/s (bytes read + written)
- *   MVLA_PROBE_MFMA   every wave (four per compute unit) runs a loop of the sixteen
- *                     independent 32x32x16 bf16 products of a 128x128 register tile on
- *                     operands taken from the first 8 KiB of buf (all zeros, or random
- *                     values: the part's clock under matrix load depends on the data)
- *                                                                   -> TFLOP/s
+ *   MVLA_PROBE_MFMA   every wave (four per compute unit) runs a loop of the 32
+ *                     independent 16x16x32 bf16 products of a 64x128 register tile (the
+ *                     form the projection kernels use) on operands taken from the first
+ *                     8 KiB of buf (all zeros, or random values: the part's clock under
+ *                     matrix load depends on the data)             -> TFLOP/s
  *   MVLA_PROBE_LAUNCH empty kernels back to back (buf unused)       -> microseconds per launch
  * buf: device, 16-byte aligned; bytes >= 1 MiB for READ/COPY, >= 8 KiB for MFMA.
  * result: HOST. */

@@ -866,8 +866,8 @@ int mvla_peak_probe(mvla_ctx* ctx, int kind, void* buf, size_t bytes, int reps, 
         case MVLA_PROBE_READ: *result = (double)(bytes & ~(size_t)15) / sec * 1e-9; break;
         case MVLA_PROBE_COPY: *result = 2.0 * (double)half / sec * 1e-9; break;
         case MVLA_PROBE_MFMA:
-            // per wave and iteration: 16 products of 32 x 32 x 16, two flops per multiply-add
-            *result = (double)n_cu * 4 * mfma_iters * 16 * (2.0 * 32 * 32 * 16) / sec * 1e-12;
+            // per wave and iteration: 32 products of 16 x 16 x 32, two flops per multiply-add
+            *result = (double)n_cu * 4 * mfma_iters * 32 * (2.0 * 16 * 16 * 32) / sec * 1e-12;
             break;
         default: *result = sec * 1e6; break;
     }

@@ -53,38 +53,35 @@ __global__ __launch_bounds__(PROBE_THREADS) void probe_copy_kernel(const u32x4_t
     for (; i < hi; i += PROBE_THREADS) dst[i] = src[i];
 }
 
-// Every wave takes 4 + 4 operand fragments from `operands` (whatever values lie there: zeros,
-// or random bf16) and runs `iters` rounds of the 16 independent 32x32x16 products of a 128x128
-// register tile, the shape of the projection kernel's inner loop without any memory traffic.
-__global__ __launch_bounds__(PROBE_THREADS) void probe_mfma_kernel(const uint4* __restrict__ operands,
-                                                                   int iters, float* sink) {
+// Every wave takes 4 + 8 operand fragments from the first 8 KiB of `operands` (whatever values lie there:
+// zeros, or random bf16; neighbouring fragments start 512 bytes apart) and runs `iters` rounds of the 32
+// independent 16x16x32 products of a 64x128 register tile, the projection kernels' product without any
+// memory traffic.  (Two waves a SIMD in the bounds keep the accumulators in the ordinary registers; given
+// more room the compiler moves them to the second file and back in every round.)
+__global__ __launch_bounds__(PROBE_THREADS, 2) void probe_mfma_kernel(const uint4* __restrict__ operands,
+                                                                      int iters, float* sink) {
     const int lane = threadIdx.x & 63;
-    uint4 a[4], b[4];
+    uint4 a[4], b[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        a[i] = operands[(size_t)(i * 64 + lane)];
-        b[i] = operands[(size_t)((4 + i) * 64 + lane)];
-    }
-    f32x16_t acc[4][4];
+    for (int i = 0; i < 4; ++i) a[i] = operands[i * 32 + lane];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = operands[(256 + j * 32 + lane) & 511];
+    f32x4_t acc[4][8];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = mfma32(b[j], a[i], acc[i][j]);
+            for (int j = 0; j < 8; ++j) acc[i][j] = mfma16(b[j], a[i], acc[i][j]);
     }
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) s += acc[i][j][v];
+        for (int j = 0; j < 8; ++j) s += acc[i][j][0] + acc[i][j][1] + acc[i][j][2] + acc[i][j][3];
     if (s == 1.2345e30f && sink) *sink = s;
 }
 
