@@ -314,12 +314,12 @@ int mvla_prefill_layer_prune(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvl
                              float* sal, int32_t* k2k3, int32_t* kept_idx, void* h_out,
                              int32_t* pos_out);
 
-/* Optional set-up step: times every tile configuration / K-split policy of
+/* Optional set-up step: times every recordable tile configuration / K-split policy of
  * the four projections of a layer at M = B*S rows on this device, cycling
  * through the n_layers weight sets so that weights come from HBM as in real
  * use, and records the fastest per shape in the context; later layer calls at
  * that shape use it instead of the built-in cost model (which also has a few smaller
- * tiles that are not recorded).  Results of the layer
+ * tiles that are not recorded: at a few hundred rows it can be the faster of the two).  Results of the layer
  * calls change only in fp32 summation order.  Uses the context's workspace,
  * runs on and SYNCHRONISES the context's stream (not for use under graph
  * capture); takes a few tens of milliseconds.

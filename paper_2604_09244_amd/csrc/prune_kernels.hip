@@ -969,6 +969,7 @@ int launch_decompose(const float* attn, int B, int H, int Nq, int S, int n_patch
     // aligned for it, T / 4 row groups of four rows each; else, and for up to 256 rows, 4 bytes, T / 16 row groups of
     // sixteen (a quarter of the reductions).  64 rows x 2 x 256 patches (B = 4) 3.0 us, with 256 threads and
     // 16 bytes 3.6, with 1024 threads 4.7; 256 rows 3.4, 4.0 and 4.8; 512 rows with 512 threads 4.2, with 1024 5.0.
+    // Beyond 1024 rows they are read twice (1024 rows 5.5 us, 1056 10.2).
     if (R <= 256) {
         MVLA_DEC(256, 1, 16);
     } else if (S % 4 == 0 && n_patch % 4 == 0 && (reinterpret_cast<uintptr_t>(attn) & 15) == 0) {
