@@ -13,16 +13,16 @@
 // MFMAs of step s, and so are the next slabs' direct loads.
 //
 // Work split.  A workgroup owns a BM x BN tile; its waves own (BM/WM) x (BN/WN)
-// sub-tiles of 32x32 blocks, four 16x16x32 products each (wave rows overlap by a block
-// where the 32-row blocks do not divide).  Tiles that fill whole rounds of the chip
-// are computed start to finish by one workgroup.  The tiles of the last,
+// sub-tiles in 16x16x32 products (the wave rows of the recordable 288x192 shape overlap by 32 rows).
+// Tiles that fill whole rounds of the chip are computed start to finish by one workgroup.  The tiles of the last,
 // partial round are cut along K into equal ranges of k-iterations handed out
 // contiguously to the otherwise idle CUs; the pieces of a tile meet in an fp32
 // partial buffer and whichever piece arrives last (integer arrival counter)
 // adds them up in fixed piece order and runs the epilogue, so results do not
 // depend on timing.
 // The four-wave 256x256 shape runs as a persistent kernel of its own (persistent_body), its cut last
-// round in quarters on another shape where that is predicted faster.
+// round in quarters on another shape where that is predicted faster.  Row counts in between take whole tiles of
+// a height and width that fit them (fitted_tile_kernel).
 //
 // Epilogues: the q/k/v projection (q and k columns rotated by the row's position
 // on the fp32 accumulators and stored as bf16, v columns stored transposed for
@@ -134,18 +134,23 @@ __device__ __forceinline__ void tile_of(int lin, int tiles_m, int tiles_n, int* 
     *tn = r / gm;
 }
 
+// The three families of tile kernels: shapes with the K-split path (recordable choices), small whole tiles, and
+// whole tiles whose height is fitted to the row count.
+enum KernelKind { SPLITTING, SMALL, FITTED };
+constexpr int rows_unit(KernelKind kind) { return kind == FITTED ? 16 : 32; }
+
 // Epilogue staging: the output tile goes through LDS as fp32 rows of BN + 4 floats (the 4 keep
 // 16-byte accesses of 32 consecutive rows on different banks), RP rows per pass.  The whole tile
 // in one pass if the LDS a workgroup may use holds it, else one wave row per pass.
-template <int BM, int BN, int WM, int NS>
+template <int BM, int BN, int WM, int NS, int RU = 32 /* rows a wave's blocks come in */>
 struct EpiGeom {
     static constexpr int LDT = BN + 4;
     static constexpr int CAP = (NS == 2 && BM == 128 && BN == 128) ? 76 * 1024 : 156 * 1024;
-    static constexpr int TM = (BM / 32 + WM - 1) / WM * 32;   // rows of a wave row
+    static constexpr int TM = (BM / RU + WM - 1) / WM * RU;   // rows of a wave row
     static constexpr int PASSES = BM * LDT * 4 <= CAP ? 1 : WM;
     static constexpr int RP = PASSES == 1 ? BM : TM;
-    // (where waves hold 15 or more blocks, a spare strip of 16 rows: see the lay-down)
-    static constexpr int BYTES = (RP + (TM / 32 * (BN / 64) >= 15 ? 16 : 0)) * LDT * 4;
+    // (where the accumulators are in the second register file, a spare strip of 16 rows: see the lay-down)
+    static constexpr int BYTES = (RP + (TM / 16 * (BN / 32) >= 54 ? 16 : 0)) * LDT * 4;
     static_assert(BYTES <= CAP, "epilogue tile does not fit the LDS");
     static_assert(TM * WM == BM || PASSES == WM, "overlapping wave rows go one per pass");
 };
@@ -600,7 +605,7 @@ __device__ __forceinline__ void persistent_body(const bf16_t* __restrict__ A, in
 #undef PT_HALF
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI, bool SPLITS = true>
+template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI, KernelKind KIND>
 __device__ __forceinline__ void tile_body(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
     void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
@@ -617,21 +622,21 @@ __device__ __forceinline__ void tile_body(
         plan.dp_tiles = pair.tiles_m * plan.tiles_n;
         plan.dp_grid = (plan.dp_tiles + 7) / 8 * 8;
     }
+    constexpr int RU = rows_unit(KIND);
     constexpr int NT = WM * WN * 64;
     constexpr int CPR = BK / 8;             // 16-byte chunks per LDS row
-    // A wave owns FM x FN blocks of 32x32, four 16x16 accumulators each.  When the tile's 32-row blocks do not
-    // divide among the WM wave rows (288 rows on two wave rows), every wave row still takes
-    // FM = ceil blocks and the last one starts early: the rows both cover are computed twice
+    // A wave owns GM x GN blocks of 16x16.  Where its rows come in blocks of 32 and the tile's do not divide among the WM
+    // wave rows (288 rows on two wave rows), every wave row still takes the larger share
+    // and the last one starts early: the rows both cover are computed twice
     // (identical values) so that the main loop stays free of branches.
-    constexpr int FM = (BM / 32 + WM - 1) / WM, TM = FM * 32, TN = BN / WN, FN = TN / 32;
-    static_assert(BM % 32 == 0 && BN % (32 * WN) == 0 && TM <= BM, "");
+    constexpr int TM = (BM / RU + WM - 1) / WM * RU, TN = BN / WN, GM = TM / 16, GN = TN / 16;
+    static_assert(BM % RU == 0 && BN % (16 * WN) == 0 && TM <= BM, "");
     constexpr int STAGE = (BM + BN) * CPR;  // 16-byte slots per stage
     constexpr int A_SLOTS = BM * CPR, B_SLOTS = BN * CPR;   // 16-byte slots of the A and W tiles
     constexpr int A_LD = A_SLOTS / NT, B_LD = B_SLOTS / NT;
     constexpr int P = A_LD + B_LD;          // direct loads per thread per slab
     static_assert(A_SLOTS % NT == 0 && B_SLOTS % NT == 0, "tile/thread mismatch");
     static_assert(BK == 64 && CPR == 8 && NS >= 2, "two k-steps of 32 a slab");
-    constexpr int GM = 2 * FM, GN = 2 * FN; // 16-row and 16-column blocks of a wave
 
     extern __shared__ uint4 lds[];
     __shared__ int sh_last;
@@ -807,6 +812,16 @@ __device__ __forceinline__ void tile_body(
         }
         MVLA_READ_FRAGS(af0, bf0, 0, 0)
         int stage = 0;
+        // (accumulators of the fitted shapes live in the second register file; left to itself the compiler moves them
+        // to the first and back in every slab)
+        auto pin = [&]() __attribute__((always_inline)) {
+            if constexpr (KIND == FITTED)
+#pragma unroll
+                for (int i = 0; i < GM; ++i)
+#pragma unroll
+                    for (int j = 0; j < GN; ++j) asm volatile("" : "+a"(acc[i][j]));
+        };
+        pin();
         if constexpr (DEEP) {
             constexpr int L1_ = P / 3, L2_ = 2 * P / 3, GH = GM / 2;
             for (int kt = k0; kt < k1; ++kt) {
@@ -820,6 +835,7 @@ __device__ __forceinline__ void tile_body(
                 __syncthreads();
                 MVLA_STEP(af1, bf1, GH, GM, GM + GN, af0, bf0, nstage, 0, kt + 2, stage, L2_, P)
                 stage = nstage;
+                pin();
             }
         } else if constexpr (SPREAD) {
             for (int kt = k0; kt < k1; ++kt) {
@@ -831,6 +847,7 @@ __device__ __forceinline__ void tile_body(
                 __syncthreads();
                 MVLA_STEP(af1, bf1, 0, GM, GM + GN, af0, bf0, nstage, 0, kt + NS, stage, 0, P / 2)
                 stage = nstage;
+                pin();
             }
         } else {
             for (int kt = k0; kt < k1; ++kt) {
@@ -852,9 +869,9 @@ __device__ __forceinline__ void tile_body(
         // ---- K-split tiles: park the partial sums; the last piece to arrive finishes --------
         // (the four-wave 128x128-per-wave shape keeps its register budget for the main loop:
         // whole tiles only, the host never plans a K-split for it)
-        constexpr bool HAS_SK = SPLITS && !(WM * WN == 4 && FM * FN >= 15);
+        constexpr bool HAS_SK = KIND == SPLITTING && !(WM * WN == 4 && GM * GN >= 54);
         const int n_pieces = (!HAS_SK || is_dp) ? 1 : last_blk - first_blk + 1;
-        if (HAS_SK && n_pieces > 1) {
+        if constexpr (HAS_SK) if (n_pieces > 1) {
             // slot 0 of a workgroup holds the piece of the tile its range starts in, slot 1 the next
             const int my_slot = 2 * sk_id + (seg == 0 ? 0 : 1);
             float* mine = partial + (size_t)my_slot * (BM * BN);
@@ -889,7 +906,7 @@ __device__ __forceinline__ void tile_body(
             // last), several 16-byte loads in flight at a time; then the common epilogue below.
             // With few accumulator registers the own piece is taken from a register copy instead
             // of being read back, and two pieces are fetched per round trip.
-            constexpr int NQ = FM * FN * 4;                       // quads per thread per piece
+            constexpr int NQ = GM * GN;                           // quads per thread per piece
             // (not for the shape that runs two workgroups per CU: the copy would cost it that)
             constexpr bool KEEP_OWN = NQ <= 16 && !(NS == 2 && BM == 128 && BN == 128);
             constexpr int CH_MAX = (NQ <= 16) ? 16 : 8;           // quads in flight
@@ -974,7 +991,7 @@ __device__ __forceinline__ void tile_body(
         // written), so the residual is read and the result written with one access per lane on
         // whole consecutive cache lines.  A pass covers as many tile rows as the LDS holds (a whole
         // number of wave rows); only the waves owning them write.
-        using EG = EpiGeom<BM, BN, WM, NS>;
+        using EG = EpiGeom<BM, BN, WM, NS, RU>;
         constexpr int LDT = EG::LDT, PASSES = EG::PASSES, RP = EG::RP;
         constexpr int OUT_COLS = EPI == EPI_SILU_MUL ? BN / 2 : BN;   // output columns per tile
         static_assert(RP % 16 == 0, "row groups of 8 come in pairs");
@@ -992,7 +1009,7 @@ __device__ __forceinline__ void tile_body(
             // q/k rotation: the position ids of this thread's items of the pass, fetched while
             // the tile is laid down (items: 8 columns of a half head, BN/16 per row)
             constexpr int PER_ROW = BN / 16;
-            constexpr int QB = (FM * FN >= 8 && WM * WN >= 8) ? 2 : 4;   // items whose table rows fly together
+            constexpr int QB = (GM * GN >= 32 && WM * WN >= 8) ? 2 : 4;   // items whose table rows fly together
             constexpr int NB = (RP * PER_ROW + QB * NT - 1) / (QB * NT);
             constexpr bool PREFETCH = EPI == EPI_QKV_ROPE && QB == 4;   // (registers to spare)
             int pos_pre[PREFETCH ? NB * QB : 1];
@@ -1015,7 +1032,7 @@ __device__ __forceinline__ void tile_body(
             // Residual epilogues: an item is 4 columns of a row (16 bytes of fp32: a wave's load
             // or store covers consecutive whole cache lines; with 8-column items a lane's two
             // 16-byte fp32 accesses lay 32 bytes apart and a store burst of that form takes 1.4-1.8
-            // times as long).  Items go in batches of RU whose residual reads are in flight
+            // times as long).  Items go in batches of RB whose residual reads are in flight
             // together, the first batch requested before the tile is laid down; reads and stores
             // are unconditional buffer accesses (behind a per-item branch the compiler made each
             // read wait for the one before it -- a memory round trip per item -- and behind
@@ -1028,8 +1045,8 @@ __device__ __forceinline__ void tile_body(
             constexpr int RPT = (RP * IPR + NT - 1) / NT;                     // items per thread and pass
             constexpr int RREG = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;          // registers per item
             constexpr int RES_ES = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;        // bytes per residual element
-            constexpr int RU_MAX = (WM * WN == 8 && BM == 256 && BN == 256 ? 8 : 16) / RREG;
-            constexpr int RU = RPT < RU_MAX ? RPT : RU_MAX, RNB = (RPT + RU - 1) / RU;
+            constexpr int RES_MAX = (WM * WN == 8 && BM == 256 && BN == 256 ? 8 : 16) / RREG;
+            constexpr int RB = RPT < RES_MAX ? RPT : RES_MAX, RNB = (RPT + RB - 1) / RB;
             // item k of this thread: row r of the pass and first column c4 of the tile.  Where the
             // threads of the workgroup cover whole rows, the column is the same for every item
             // and the row advances by a constant: no divisions, offsets by one addition.
@@ -1049,13 +1066,13 @@ __device__ __forceinline__ void tile_body(
             const __amdgpu_buffer_rsrc_t r_buf = buffer_of(
                 RES ? static_cast<const char*>(Rv) + ((size_t)(m0 + prow0) * ldr + out_n0) * RES_ES : nullptr,
                 RES && rows_here > 0 ? ((rows_here - 1) * ldr + cols_here) * RES_ES : 0);
-            u32x2_t rh_[RES ? RU : 1];    // bf16 residual (4 values)
-            u32x4_t rf_[RES ? RU : 1];    // fp32 residual
+            u32x2_t rh_[RES ? RB : 1];    // bf16 residual (4 values)
+            u32x4_t rf_[RES ? RB : 1];    // fp32 residual
             auto res_request = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < RU; ++u) {
+                for (int u = 0; u < RB; ++u) {
                     int r, c4;
-                    item_rc(etid, b * RU + u, r, c4);
+                    item_rc(etid, b * RB + u, r, c4);
                     const int off = (min(r, RP - 1) * ldr + c4) * RES_ES;   // (beyond the records: zeros)
                     if (EPI == EPI_RES_BF16_TO_F32)
                         rh_[u] = __builtin_amdgcn_raw_buffer_load_b64(r_buf, off, 0, 0);
@@ -1065,9 +1082,9 @@ __device__ __forceinline__ void tile_body(
             };
             auto res_finish = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < RU; ++u) {
+                for (int u = 0; u < RB; ++u) {
                     int r, c4;
-                    item_rc(ftid, b * RU + u, r, c4);
+                    item_rc(ftid, b * RB + u, r, c4);
                     const bool ok = r >= r_lo && r < rows_here && c4 < cols_here;
                     const int off = ok ? (r * ldc + c4) * ES : OOB_OFFSET;
                     const float4 t = *reinterpret_cast<const float4*>(tile + min(r, RP - 1) * LDT + c4);
@@ -1091,7 +1108,7 @@ __device__ __forceinline__ void tile_body(
             };
             if constexpr (RES && !TIGHT) res_request(0);
             __syncthreads();   // previous readers of the LDS (fragments or the last pass) are done
-            if constexpr (WM * WN == 4 && FM * FN >= 15) {
+            if constexpr (WM * WN == 4 && GM * GN >= 54) {
                 // Accumulators in the second register file: fetched one by one (pinned there until then),
                 // and without a branch, which would make the compiler copy them: 16-row blocks that are
                 // not of this pass go to a spare strip behind the tile.
@@ -1286,7 +1303,7 @@ __device__ __forceinline__ void tile_body(
                 }
             }
         };
-        if constexpr (WM * WN == 4 && FM * FN >= 15 && PASSES == 2) {
+        if constexpr (WM * WN == 4 && GM * GN >= 54 && PASSES == 2) {
             // (not a loop: pinned accumulators would be carried round it, and copied)
             epilogue_pass(0);
             epilogue_pass(1);
@@ -1309,8 +1326,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
     if constexpr (is_persistent(BM, BN, WM, WN))
         persistent_body<EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, rope);
     else
-        tile_body<BM, BN, BK, WM, WN, NS, EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
-                                             pair);
+        tile_body<BM, BN, BK, WM, WN, NS, EPI, SPLITTING>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
+                                                        pair);
 }
 
 // Shapes that only the choice by size uses (whole tiles, no K-split): the same body under another name.
@@ -1321,7 +1338,18 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void small_tile_kernel(
     const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
     void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
     float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, PairedGemm pair) {
-    tile_body<BM, BN, BK, WM, WN, NS, EPI, false>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
+    tile_body<BM, BN, BK, WM, WN, NS, EPI, SMALL>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
+                                                  pair);
+}
+
+// Tiles fitted to the row count (whole tiles as well), large enough that the accumulators may go to the second
+// register file.
+template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
+__global__ __launch_bounds__(WM * WN * 64) void fitted_tile_kernel(
+    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
+    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
+    float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, PairedGemm pair) {
+    tile_body<BM, BN, BK, WM, WN, NS, EPI, FITTED>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
                                                   pair);
 }
 
@@ -1392,19 +1420,20 @@ static GemmPlan plan_for(int M, int N, int K, int BM, int BN, int BK, int slots,
     return plan;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, int E, bool SMALL>
+template <int BM, int BN, int BK, int WM, int WN, int NS, int E, KernelKind KIND>
 static constexpr auto kernel_of() {
-    if constexpr (SMALL) return small_tile_kernel<BM, BN, BK, WM, WN, NS, E>;
+    if constexpr (KIND == SMALL) return small_tile_kernel<BM, BN, BK, WM, WN, NS, E>;
+    else if constexpr (KIND == FITTED) return fitted_tile_kernel<BM, BN, BK, WM, WN, NS, E>;
     else return gemm_kernel<BM, BN, BK, WM, WN, NS, E>;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool SMALL = false>
+template <int BM, int BN, int BK, int WM, int WN, int NS, KernelKind KIND = SPLITTING>
 static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, void* C,
                       int ldc, const void* R, int ldr, int epi, int slots_per_cu, int sk_pct,
                       float* partial, size_t partial_bytes, uint32_t* counters, int n_counters,
                       const RopeEpilogue& rope, hipStream_t st, PlanPart part = PLAN_ALL,
                       const PairedGemm* second = nullptr) {
-    constexpr bool has_sk = !SMALL && !(WM * WN == 4 && ((BM / 32 + WM - 1) / WM) * (BN / WN / 32) >= 15);
+    constexpr bool has_sk = KIND == SPLITTING && !(WM * WN == 4 && ((BM / 32 + WM - 1) / WM) * (BN / WN / 32) >= 15);
     const int pb = part == PLAN_QUARTERS ? 2 : 1;   // (planned on the tiles that are quartered)
     GemmPlan plan = plan_for(M, N, K, BM * pb, BN * pb, BK, device_cu_count() * slots_per_cu,
                              (has_sk || part != PLAN_ALL) ? sk_pct : 0, partial_bytes, n_counters);
@@ -1431,7 +1460,7 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
     }
     if (grid == 0) return MVLA_OK;
     const size_t stage_bytes = (size_t)NS * (BM + BN) * (BK / 8) * sizeof(uint4);
-    const size_t epi_bytes = EpiGeom<BM, BN, WM, NS>::BYTES;
+    const size_t epi_bytes = EpiGeom<BM, BN, WM, NS, rows_unit(KIND)>::BYTES;
     size_t lds = stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
     if (is_persistent(BM, BN, WM, WN)) {   // one workgroup per CU, a multiple of 8 (see xcd_chunked)
         const int cus = device_cu_count() & ~7;
@@ -1443,7 +1472,7 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
     // instantiation), not on every launch
 #define MVLA_GEMM_LAUNCH(E)                                                                   \
     do {                                                                                      \
-        auto kern = kernel_of<BM, BN, BK, WM, WN, NS, E, SMALL>();                                \
+        auto kern = kernel_of<BM, BN, BK, WM, WN, NS, E, KIND>();                                 \
         static bool lds_set[kMaxDevices] = {};                                                \
         int dev = 0;                                                                          \
         MVLA_HIP_CHECK(hipGetDevice(&dev));                                                   \
@@ -1483,7 +1512,8 @@ struct TileCfg {
     float mb_per_us;     // operand bytes beyond the caches
 };
 constexpr int kNumCfgs = 7;      // configurations a caller can record (mvla_set_gemm_choice)
-constexpr int kAllCfgs = 12;     // ... and those that only the choice by size uses
+constexpr int kFitted = 12;      // from here on the tiles fitted to the row count
+constexpr int kAllCfgs = 24;     // ... both only used by the choice by size
 static const TileCfg kCfgs[kAllCfgs] = {
     // K-slab 64, eight waves of 128x64, two stages
     {256, 256, 1, true, 1.55f, 0.697f, {8.5f, 9.3f, 13.7f, 5.2f}, 2.4f, 27.7f, 3.f},
@@ -1513,8 +1543,34 @@ static const TileCfg kCfgs[kAllCfgs] = {
     {64, 128, 1, false, 0.346f, 1.f, {3.6f, 2.6f, 1.f, 2.3f}, 0.f, 0.f, 3.4f},
     // 64x32 per wave, five stages (M = 400, N = K = 4096: 29 -> 26 us)
     {128, 64, 1, false, 0.302f, 0.974f, {4.1f, 2.9f, 2.1f, 2.6f}, 0.f, 0.f, 4.f},
+    // Fitted tiles: four waves of half the rows and half the columns each, whole tiles only, in heights and widths
+    // between those above.  What a projection of a few hundred to a few thousand rows loses is the last round of tiles
+    // that do not fit its row count, and what bounds a slab of it is the load path (a compute unit has 256 cache lines
+    // on their way at most: some 55 bytes per ns where the weights come from memory), so the tile should be as large as
+    // fills the chip in whole rounds.  One or two steps of height either way are 10 to 30 % there.
+    // M = 288, N = 22016: 288x192 on 115 units 76 -> 160x192 on 230 58 us; M = 948, N = 12288: 256x256 on 192 91 ->
+    // 192x256 on 240 77; M = 948, N = 22016 158 -> 136 (192x256); M = 2176, N = K = 4096: 79 -> 64 (160x256); M = 2176,
+    // N = 4096, K = 11008: 192 -> 164.  (27 row counts of 32 to 7000 at the 7B widths: 5 % on average.)
+    // (their times: fitted to 15 row counts at D = 1024, F = 2816 and 27 at D = 4096, F = 11008)
+    {160, 128, 1, false, 0.586f, 0.713f, {3.8f, 2.9f, 1.0f, 1.4f}, 0.f, 0.f, 4.8f},
+    {192, 128, 1, false, 0.664f, 0.721f, {3.8f, 3.1f, 1.0f, 1.5f}, 0.f, 0.f, 4.9f},
+    {160, 192, 1, false, 0.755f, 0.701f, {5.1f, 5.1f, 3.6f, 2.6f}, 0.f, 0.f, 4.3f},
+    {256, 128, 1, false, 0.759f, 0.608f, {5.4f, 6.0f, 5.2f, 3.6f}, 0.f, 0.f, 4.9f},
+    {128, 256, 1, false, 0.784f, 0.676f, {4.3f, 3.7f, 3.4f, 2.5f}, 0.f, 0.f, 3.9f},
+    {192, 192, 1, false, 0.838f, 0.675f, {7.4f, 7.4f, 5.9f, 4.3f}, 0.f, 0.f, 4.5f},
+    {160, 256, 1, false, 0.906f, 0.724f, {8.0f, 6.6f, 4.3f, 4.4f}, 0.f, 0.f, 4.4f},
+    {224, 192, 1, false, 0.932f, 0.650f, {8.8f, 8.8f, 8.6f, 5.5f}, 0.f, 0.f, 4.6f},
+    {192, 256, 1, false, 1.029f, 0.701f, {9.6f, 7.4f, 5.6f, 5.1f}, 0.f, 0.f, 4.2f},
+    {288, 192, 1, false, 1.133f, 0.602f, {13.1f, 13.1f, 12.7f, 8.1f}, 0.f, 0.f, 4.2f},
+    {224, 256, 1, false, 1.168f, 0.634f, {11.6f, 11.3f, 10.5f, 7.7f}, 0.f, 0.f, 4.8f},
+    {320, 192, 1, false, 1.264f, 0.528f, {14.1f, 14.1f, 15.8f, 8.6f}, 0.f, 0.f, 4.7f},
 };
 constexpr float kLaunchUs = 3.f;
+// Where the fitted tiles are considered.  Shorter projections are mostly start and epilogue, and there the small tiles are
+// the faster ones (of 15 row counts from 130 to 7000 at D = 1024, F = 2816 none below 20 us has a faster
+// fitted tile); shorter contractions are outside of what their times were fitted to.
+constexpr float kFittedFromUs = 20.f;
+constexpr int kFittedFromK = 1024;
 // The exchange of a K-split behind a full-chip kernel takes longer than the fit says (117 us measured, 92
 // predicted, for 64 tiles at K = 11008; quarters 98 and 92): the quarters are taken unless it is well ahead.
 constexpr float kSplitRisk = 1.2f;
@@ -1588,9 +1644,9 @@ bool gemm_config_runs(int cfg, int epilogue, const RopeEpilogue* rope) {
 static int predict(int M, int N, int K, int epilogue, const RopeEpilogue* rope, int* split_pct, float* us) {
     int best = -1;
     *us = INFINITY;
-    for (int i = kAllCfgs - 1; i >= 0; --i) {
+    auto consider = [&](int i) {
         const TileCfg& c = kCfgs[i];
-        if (!cfg_runs(c, epilogue, rope)) continue;
+        if (!cfg_runs(c, epilogue, rope)) return;
         const int tiles_m = (M + c.BM - 1) / c.BM, tiles_n = (N + c.BN - 1) / c.BN, k_tiles = K / 64;
         const int slots = device_cu_count() * c.slots_per_cu;
         const long tiles = (long)tiles_m * tiles_n, full = tiles < slots ? 0 : tiles / slots;
@@ -1607,13 +1663,16 @@ static int predict(int M, int N, int K, int epilogue, const RopeEpilogue* rope, 
         };
         if (rem == 0) {
             take(t, 0);
-            continue;
+            return;
         }
         const float slab = c.slab_us * c.alone;      // (no slab takes less)
         const float least = i == 4 ? t : t + last + (float)((long)rem * k_tiles / slots) * slab;   // (4: cut on others)
         if (c.can_split && least <= *us) take(cut_us(i, M, N, K, epilogue, t, full > 0), 101);
         if (t + last + k_tiles * slab <= *us) take(t + last + k_tiles * slab_us(c, (float)rem, tm, tn), 0);
-    }
+    };
+    for (int i = kFitted - 1; i >= 0; --i) consider(i);
+    if (*us >= kFittedFromUs && K >= kFittedFromK)
+        for (int i = kFitted; i < kAllCfgs; ++i) consider(i);
     return best;
 }
 
@@ -1677,11 +1736,24 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         }
         case 5: return launch_cfg<192, 128, 64, 2, 4, 3>(MVLA_ARGS);
         case 6: return launch_cfg<288, 192, 64, 2, 2, 2>(MVLA_ARGS);
-        case 7: return launch_cfg<128, 192, 64, 2, 2, 3, true>(MVLA_ARGS);
-        case 8: return launch_cfg<64, 64, 64, 2, 2, 6, true>(MVLA_ARGS);
-        case 9: return launch_cfg<128, 128, 64, 2, 2, 4, true>(MVLA_ARGS);
-        case 10: return launch_cfg<64, 128, 64, 2, 2, 5, true>(MVLA_ARGS);
-        default: return launch_cfg<128, 64, 64, 2, 2, 5, true>(MVLA_ARGS);
+        case 7: return launch_cfg<128, 192, 64, 2, 2, 3, SMALL>(MVLA_ARGS);
+        case 8: return launch_cfg<64, 64, 64, 2, 2, 6, SMALL>(MVLA_ARGS);
+        case 9: return launch_cfg<128, 128, 64, 2, 2, 4, SMALL>(MVLA_ARGS);
+        case 10: return launch_cfg<64, 128, 64, 2, 2, 5, SMALL>(MVLA_ARGS);
+        case 11: return launch_cfg<128, 64, 64, 2, 2, 5, SMALL>(MVLA_ARGS);
+        case 12: return launch_cfg<160, 128, 64, 2, 2, 4, FITTED>(MVLA_ARGS);
+        case 13: return launch_cfg<192, 128, 64, 2, 2, 3, FITTED>(MVLA_ARGS);
+        case 14: return launch_cfg<160, 192, 64, 2, 2, 3, FITTED>(MVLA_ARGS);
+        case 15: return launch_cfg<256, 128, 64, 2, 2, 3, FITTED>(MVLA_ARGS);
+        case 16: return launch_cfg<128, 256, 64, 2, 2, 3, FITTED>(MVLA_ARGS);
+        case 17: return launch_cfg<192, 192, 64, 2, 2, 3, FITTED>(MVLA_ARGS);
+        case 18: return launch_cfg<160, 256, 64, 2, 2, 3, FITTED>(MVLA_ARGS);
+        case 19: return launch_cfg<224, 192, 64, 2, 2, 3, FITTED>(MVLA_ARGS);
+        case 20: return launch_cfg<192, 256, 64, 2, 2, 2, FITTED>(MVLA_ARGS);
+        case 21: return launch_cfg<288, 192, 64, 2, 2, 2, FITTED>(MVLA_ARGS);
+        case 22: return launch_cfg<224, 256, 64, 2, 2, 2, FITTED>(MVLA_ARGS);
+        case 23: return launch_cfg<320, 192, 64, 2, 2, 2, FITTED>(MVLA_ARGS);
+        default: return MVLA_EINVAL;
     }
 #undef MVLA_ARGS
 }
@@ -1714,16 +1786,16 @@ int launch_rope_pair(int cfg, const bf16_t* A1, const bf16_t* W1, int M1, void* 
                      const bf16_t* A2, const bf16_t* W2, int M2, void* C2, const RopeEpilogue& rope2, int D,
                      hipStream_t st) {
     const PairedGemm second = {A2, W2, C2, rope2.pos, M2, 0, 0};
-#define MVLA_PAIR(BM, BN, WM, WN, NS, SMALL)                                                       \
-    launch_cfg<BM, BN, 64, WM, WN, NS, SMALL>(A1, D, W1, M1, D, D, C1, D, nullptr, 0, EPI_QKV_ROPE, 1, 0, nullptr, 0, \
+#define MVLA_PAIR(BM, BN, WM, WN, NS, KIND)                                                        \
+    launch_cfg<BM, BN, 64, WM, WN, NS, KIND>(A1, D, W1, M1, D, D, C1, D, nullptr, 0, EPI_QKV_ROPE, 1, 0, nullptr, 0, \
                                               nullptr, 0, rope1, st, PLAN_ALL, &second)
     switch (cfg) {
-        case 1: return MVLA_PAIR(256, 128, 4, 2, 3, false);
-        case 5: return MVLA_PAIR(192, 128, 2, 4, 3, false);
-        case 8: return MVLA_PAIR(64, 64, 2, 2, 6, true);
-        case 9: return MVLA_PAIR(128, 128, 2, 2, 4, true);
-        case 10: return MVLA_PAIR(64, 128, 2, 2, 5, true);
-        case 11: return MVLA_PAIR(128, 64, 2, 2, 5, true);
+        case 1: return MVLA_PAIR(256, 128, 4, 2, 3, SPLITTING);
+        case 5: return MVLA_PAIR(192, 128, 2, 4, 3, SPLITTING);
+        case 8: return MVLA_PAIR(64, 64, 2, 2, 6, SMALL);
+        case 9: return MVLA_PAIR(128, 128, 2, 2, 4, SMALL);
+        case 10: return MVLA_PAIR(64, 128, 2, 2, 5, SMALL);
+        case 11: return MVLA_PAIR(128, 64, 2, 2, 5, SMALL);
         default: return MVLA_EINVAL;
     }
 #undef MVLA_PAIR
