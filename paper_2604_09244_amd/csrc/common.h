@@ -101,6 +101,9 @@ int launch_rmsnorm_f32(const float* x, const bf16_t* gain, int M, int D, float e
 int launch_rmsnorm_tail(const bf16_t* x, const int32_t* pos, const bf16_t* gain, int B, int S,
                         int tail, int D, float eps, bf16_t* out, bf16_t* out_tail, int32_t* pos_out,
                         hipStream_t st);
+// gather-compaction (as launch_compact) with the gathered rows' norm written as well
+int launch_compact_norm(const bf16_t* h, const int32_t* pos, const int32_t* kept_idx, int B, int S, int S_out, int D,
+                        bf16_t* h_out, int32_t* pos_out, const bf16_t* gain, float eps, bf16_t* u, hipStream_t st);
 int launch_rope_table(double base, int rope_len, int dh, float* c, float* s, hipStream_t st);
 // scoring probabilities of the last nq rows: probs [B,H,nq,S] fp32.  q_tail_only: q holds just
 // those rows, nq per sample ([B*nq, q_row_stride]); otherwise all S rows of every sample.

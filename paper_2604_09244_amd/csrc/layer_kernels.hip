@@ -4,6 +4,7 @@
 // probabilities (paper Sec. 3.2: the attention rows that salience is read from).
 #include "common.h"
 #include "mfma.h"
+#include "wave.h"
 
 namespace mvla {
 
@@ -11,123 +12,145 @@ namespace mvla {
 // RMSNorm: out = x * gain / sqrt(mean(x^2) + eps), fp32 maths, bf16 out.  One
 // workgroup per row; a thread keeps its 16-byte chunks in registers between the
 // sum of squares and the scaling, so the row is read once.
+// Bound by memory at large batches, by latency at small ones: the gain is asked for with the row, the sum goes
+// over the vector unit, and a row of up to 512 or 1024 values takes one or two waves (NT threads) instead of four that
+// meet at a barrier.
 // ---------------------------------------------------------------------------
-constexpr int NORM_THREADS = 256;
-constexpr int NORM_MAX_CHUNKS = 4;  // per thread: D <= 256 * 4 * 8 = 8192
+constexpr int NORM_MAX_CHUNKS = 4;  // per thread of 256: D <= 256 * 4 * 8 = 8192
 
+template <int NT>
 __device__ __forceinline__ float block_sum(float v, float* sh) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = wave_sum_f32(v);
+    if (NT == 64) return v;
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
     float t = 0.f;
 #pragma unroll
-    for (int w = 0; w < NORM_THREADS / 64; ++w) t += sh[w];
+    for (int w = 0; w < NT / 64; ++w) t += sh[w];
     return t;
 }
 
-// IN_F32: the row is fp32 (the mid-layer residual stream), else bf16.
-// tail > 0: the last `tail` rows of every sample of S rows are written a second time, packed
-// into out_tail [B*tail, D], and their position ids are copied to pos_out [B*tail] (the scoring
-// pass projects queries for those rows only).
-template <bool IN_F32>
-__global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(const void* __restrict__ xv,
-                                                               const uint4* __restrict__ gain,
-                                                               int row_vec /* D/8 */, float inv_d,
-                                                               float eps, uint4* __restrict__ out,
-                                                               int S, int tail,
-                                                               uint4* __restrict__ out_tail,
-                                                               const int32_t* __restrict__ pos,
-                                                               int32_t* __restrict__ pos_out) {
-    __shared__ float sh[NORM_THREADS / 64];
+// The rows a norm kernel works on.
+enum NormRows {
+    NORM_BF16,      // all rows of x (bf16)
+    NORM_F32,       // ... of the mid-layer residual stream (fp32)
+    NORM_GATHER     // rows of x that `index` names, copied to x_out as well, their position ids to pos_out
+};
+struct NormSide {   // what else a norm kernel reads and writes
+    int S, tail;                 // tail > 0: the last `tail` rows of every sample of S rows are written a second time,
+    uint4* out2;                 // packed into out2 [B*tail, D] (the scoring pass projects queries for those rows only);
+    const int32_t* pos;          // NORM_GATHER: the copied rows
+    int32_t* pos_out;
+    const int32_t* index;        // NORM_GATHER: [B, S_out] rows of each sample
+    int S_out;
+};
+
+template <NormRows ROWS, int NT, int CHUNKS>
+__global__ __launch_bounds__(NT) void rmsnorm_kernel(const void* __restrict__ xv, const uint4* __restrict__ gain,
+                                                     int row_vec /* D/8 */, float inv_d, float eps,
+                                                     uint4* __restrict__ out, NormSide side) {
+    __shared__ float sh[NT / 64];
     const int row = blockIdx.x, tid = threadIdx.x;
-    int trow = -1;                       // row of the packed tail matrix, if this is a tail row
-    if (tail > 0) {
-        const int b = row / S, s_ = row - b * S;
-        if (s_ >= S - tail) trow = b * tail + s_ - (S - tail);
+    int from = row;                      // row of x
+    int row2 = -1;                       // row of out2, if this row has one
+    if (ROWS == NORM_GATHER) {
+        const int b = row / side.S_out;
+        from = b * side.S + min(max(side.index[row], 0), side.S - 1);
+        row2 = row;
+    } else if (ROWS == NORM_BF16 && side.tail > 0) {
+        const int b = row / side.S, s_ = row - b * side.S;
+        if (s_ >= side.S - side.tail) row2 = b * side.tail + s_ - (side.S - side.tail);
     }
-    if (trow >= 0 && tid == 0) pos_out[trow] = pos[row];
-    float vals[NORM_MAX_CHUNKS][8];
+    uint4 in[CHUNKS], in_hi[ROWS == NORM_F32 ? CHUNKS : 1], g[CHUNKS];
+#pragma unroll
+    for (int k = 0; k < CHUNKS; ++k) {
+        const int c = min(tid + k * NT, row_vec - 1);   // (chunks beyond the row: its last one, left out of the sum)
+        if (ROWS == NORM_F32) {
+            const uint4* xr = static_cast<const uint4*>(xv) + (size_t)from * row_vec * 2;
+            in[k] = xr[2 * c];
+            in_hi[ROWS == NORM_F32 ? k : 0] = xr[2 * c + 1];
+        } else {
+            in[k] = (static_cast<const uint4*>(xv) + (size_t)from * row_vec)[c];
+        }
+        g[k] = gain[c];
+    }
+    if (row2 >= 0 && tid == 0) side.pos_out[row2] = side.pos[from];
+    auto value = [&](int k, int i) __attribute__((always_inline)) {
+        if (ROWS == NORM_F32) {
+            const uint4& v = i < 4 ? in[k] : in_hi[ROWS == NORM_F32 ? k : 0];
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            return __uint_as_float(w[i & 3]);
+        }
+        const uint32_t w[4] = {in[k].x, in[k].y, in[k].z, in[k].w};
+        return __uint_as_float((i & 1) ? w[i >> 1] & 0xFFFF0000u : w[i >> 1] << 16);
+    };
     float ss = 0.f;
 #pragma unroll
-    for (int k = 0; k < NORM_MAX_CHUNKS; ++k) {
-        const int c = tid + k * NORM_THREADS;
-        if (c < row_vec) {
-            if (IN_F32) {
-                const float4* xr = static_cast<const float4*>(xv) + (size_t)row * row_vec * 2;
-                const float4 a = xr[2 * c], b = xr[2 * c + 1];
-                vals[k][0] = a.x; vals[k][1] = a.y; vals[k][2] = a.z; vals[k][3] = a.w;
-                vals[k][4] = b.x; vals[k][5] = b.y; vals[k][6] = b.z; vals[k][7] = b.w;
-            } else {
-                const uint4 v = (static_cast<const uint4*>(xv) + (size_t)row * row_vec)[c];
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    for (int k = 0; k < CHUNKS; ++k)
+        if (tid + k * NT < row_vec)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    vals[k][2 * i] = __uint_as_float(w[i] << 16);
-                    vals[k][2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ss += vals[k][i] * vals[k][i];
-        }
-    }
-    ss = block_sum(ss, sh);
+            for (int i = 0; i < 8; ++i) ss += value(k, i) * value(k, i);
+    ss = block_sum<NT>(ss, sh);
     const float scale = 1.0f / sqrtf(ss * inv_d + eps);
     uint4* optr = out + (size_t)row * row_vec;
-    uint4* tptr = out_tail + (size_t)(trow >= 0 ? trow : 0) * row_vec;
+    uint4* ptr2 = side.out2 + (size_t)(row2 >= 0 ? row2 : 0) * row_vec;
 #pragma unroll
-    for (int k = 0; k < NORM_MAX_CHUNKS; ++k) {
-        const int c = tid + k * NORM_THREADS;
+    for (int k = 0; k < CHUNKS; ++k) {
+        const int c = tid + k * NT;
         if (c < row_vec) {
-            const uint4 g = gain[c];
-            const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
+            const uint32_t gw[4] = {g[k].x, g[k].y, g[k].z, g[k].w};
             uint32_t r[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                r[i] = pack_bf16x2(vals[k][2 * i] * scale * __uint_as_float(gw[i] << 16),
-                                   vals[k][2 * i + 1] * scale * __uint_as_float(gw[i] & 0xFFFF0000u));
+                r[i] = pack_bf16x2(value(k, 2 * i) * scale * __uint_as_float(gw[i] << 16),
+                                   value(k, 2 * i + 1) * scale * __uint_as_float(gw[i] & 0xFFFF0000u));
             optr[c] = make_uint4(r[0], r[1], r[2], r[3]);
-            if (trow >= 0) tptr[c] = make_uint4(r[0], r[1], r[2], r[3]);
+            if (row2 >= 0) ptr2[c] = ROWS == NORM_GATHER ? in[k] : make_uint4(r[0], r[1], r[2], r[3]);
         }
     }
 }
 
-static int launch_rmsnorm_any(const void* x, bool f32, const bf16_t* gain, int M, int D, float eps,
-                              bf16_t* out, hipStream_t st) {
+template <NormRows ROWS>
+static int launch_rmsnorm_any(const void* x, const bf16_t* gain, int M, int D, float eps, bf16_t* out,
+                              const NormSide& side, hipStream_t st) {
     if (M <= 0) return MVLA_OK;
-    if (D % 8 != 0 || D / 8 > NORM_THREADS * NORM_MAX_CHUNKS) return MVLA_EUNSUPPORTED;
-    if (f32)
-        hipLaunchKernelGGL(rmsnorm_kernel<true>, dim3(M), dim3(NORM_THREADS), 0, st, x,
-                           reinterpret_cast<const uint4*>(gain), D / 8, 1.0f / (float)D, eps,
-                           reinterpret_cast<uint4*>(out), 0, 0, nullptr, nullptr, nullptr);
-    else
-        hipLaunchKernelGGL(rmsnorm_kernel<false>, dim3(M), dim3(NORM_THREADS), 0, st, x,
-                           reinterpret_cast<const uint4*>(gain), D / 8, 1.0f / (float)D, eps,
-                           reinterpret_cast<uint4*>(out), 0, 0, nullptr, nullptr, nullptr);
+    if (D % 8 != 0 || D / 8 > 256 * NORM_MAX_CHUNKS) return MVLA_EUNSUPPORTED;
+#define MVLA_NORM(NT, CHUNKS)                                                                          \
+    hipLaunchKernelGGL((rmsnorm_kernel<ROWS, NT, CHUNKS>), dim3(M), dim3(NT), 0, st, x,                \
+                       reinterpret_cast<const uint4*>(gain), D / 8, 1.0f / (float)D, eps,              \
+                       reinterpret_cast<uint4*>(out), side)
+    if (D <= 512) MVLA_NORM(64, 1);
+    else if (D <= 1024) MVLA_NORM(128, 1);
+    else if (D <= 2048) MVLA_NORM(256, 1);
+    else if (D <= 4096) MVLA_NORM(256, 2);
+    else MVLA_NORM(256, NORM_MAX_CHUNKS);
+#undef MVLA_NORM
     MVLA_HIP_CHECK(hipGetLastError());
     return MVLA_OK;
 }
 
 int launch_rmsnorm(const bf16_t* x, const bf16_t* gain, int M, int D, float eps, bf16_t* out,
                    hipStream_t st) {
-    return launch_rmsnorm_any(x, false, gain, M, D, eps, out, st);
+    return launch_rmsnorm_any<NORM_BF16>(x, gain, M, D, eps, out, NormSide{}, st);
 }
 int launch_rmsnorm_f32(const float* x, const bf16_t* gain, int M, int D, float eps, bf16_t* out,
                        hipStream_t st) {
-    return launch_rmsnorm_any(x, true, gain, M, D, eps, out, st);
+    return launch_rmsnorm_any<NORM_F32>(x, gain, M, D, eps, out, NormSide{}, st);
 }
 
 int launch_rmsnorm_tail(const bf16_t* x, const int32_t* pos, const bf16_t* gain, int B, int S,
                         int tail, int D, float eps, bf16_t* out, bf16_t* out_tail, int32_t* pos_out,
                         hipStream_t st) {
     if (B <= 0 || S <= 0) return MVLA_OK;
-    if (D % 8 != 0 || D / 8 > NORM_THREADS * NORM_MAX_CHUNKS) return MVLA_EUNSUPPORTED;
     if (tail <= 0 || tail > S || !pos || !pos_out || !out_tail) return MVLA_EINVAL;
-    hipLaunchKernelGGL(rmsnorm_kernel<false>, dim3(B * S), dim3(NORM_THREADS), 0, st, x,
-                       reinterpret_cast<const uint4*>(gain), D / 8, 1.0f / (float)D, eps,
-                       reinterpret_cast<uint4*>(out), S, tail, reinterpret_cast<uint4*>(out_tail), pos,
-                       pos_out);
-    MVLA_HIP_CHECK(hipGetLastError());
-    return MVLA_OK;
+    return launch_rmsnorm_any<NORM_BF16>(x, gain, B * S, D, eps, out,
+                                         {S, tail, reinterpret_cast<uint4*>(out_tail), pos, pos_out, nullptr, 0}, st);
+}
+
+int launch_compact_norm(const bf16_t* h, const int32_t* pos, const int32_t* kept_idx, int B, int S, int S_out, int D,
+                        bf16_t* h_out, int32_t* pos_out, const bf16_t* gain, float eps, bf16_t* u, hipStream_t st) {
+    return launch_rmsnorm_any<NORM_GATHER>(h, gain, B * S_out, D, eps, u,
+                                           {S, 0, reinterpret_cast<uint4*>(h_out), pos, pos_out, kept_idx, S_out}, st);
 }
 
 // ---------------------------------------------------------------------------
