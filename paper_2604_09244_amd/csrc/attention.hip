@@ -280,25 +280,256 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
     }
 }
 
-template <int DH, int NS>
-static int launch_att(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad,
-                      int B, int S, int H, bf16_t* out, int ldo, hipStream_t st) {
-    dim3 grid(H, (S + ATT_QT - 1) / ATT_QT, B);
-    const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
-    const size_t lds = (size_t)NS * (ATT_KT * (DH / 8) + DH * 8) * sizeof(uint4);
-    auto kern = attention_kernel<DH, NS>;
-    static bool lds_set[kMaxDevices] = {};   // the dynamic-LDS limit is raised once per device
-    int dev = 0;
+// The same product for grids that leave the chip idle: one workgroup per 32 queries, whose waves deal the key
+// tiles (32 keys each) out among themselves and add up their parts at the end.
+//
+// Such a launch is bound by its longest chain of dependent tiles, not by any rate: in the kernel above a wave
+// walks every 64-key tile up to its queries (0.9 us each).  Here a wave takes one of NW 32-key tiles.  Every
+// wave stages its own tiles in its own part of LDS, so nothing in the loop waits for another wave; one stage is
+// enough, because the next K tile is asked for as soon as the fragments of this one are in registers (behind
+// the softmax and O^T), and the next V^T tile the same (behind the next S^T).  A wave's O^T takes the
+// place of its tiles in LDS (16 KiB each at dh = 128), the waves add up the parts of all, in wave order, a share of
+// the head dimension each.
+// Launches of 32 heads of 128: S = 237 9.3 -> 6.6 us, S = 544 15.0 -> 12.2; 4 heads of 64: S = 144 5.1 -> 4.3,
+// S = 1344 19.3 -> 9.6.  Once the chip is full it is the slower one (every 32 queries fetch their keys for
+// themselves: B = 4, S = 544 28 against 38 us), see short_limit.  Eight waves: slower wherever a second round of
+// workgroups is needed (128 KiB of LDS leave one per CU), 5-15 % faster only with few heads and S > 1000.
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void short_attention_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int ld, const bf16_t* __restrict__ vt,
+    int S_pad, int S, int H, float scale_log2e, bf16_t* __restrict__ out, int ldo) {
+    constexpr int CPR = DH / 8;            // 16-byte chunks per K row
+    constexpr int STEPS = DH / 16;         // MFMA k-steps over the head dim
+    constexpr int DB = DH / 32;            // 32-row blocks of O^T
+    constexpr int KT = 32;                 // keys per tile
+    constexpr int K_SLOTS = KT * CPR, V_SLOTS = DH * (KT / 8), STAGE = K_SLOTS + V_SLOTS;
+    constexpr int K_LD = K_SLOTS / 64, V_LD = V_SLOTS / 64;   // direct loads per lane per tile
+    constexpr int GROUPS = DB * 4;         // a lane's accumulators in fours
+    static_assert(GROUPS % NW == 0 && GROUPS * 64 == STAGE, "");
+
+    extern __shared__ uint4 lds[];
+    __shared__ float sh_m[NW][32], sh_l[NW][32];
+
+    // (heads along x, heavier query blocks first: as above)
+    const int qblock = gridDim.y - 1 - blockIdx.y, h = blockIdx.x, b = blockIdx.z;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int fr = lane & 31, fg = lane >> 5;
+    const int q0 = qblock * 32, my_q = q0 + fr;
+    const int n_kt = qblock + 1;           // key tiles up to these queries; only the last needs the mask
+
+    const bf16_t* k_base = k + (size_t)b * S * ld + h * DH;
+    const bf16_t* v_base = vt + (size_t)(b * H + h) * DH * S_pad;
+    const uint32_t lds_wave = (uint32_t)(uintptr_t)lds + (uint32_t)(wave * STAGE) * 16u;
+    const uint32_t k_pitch = (uint32_t)ld * 2u;
+    uint32_t k_off[K_LD], v_off[V_LD];
+#pragma unroll
+    for (int i = 0; i < K_LD; ++i) {
+        const int sl = i * 64 + lane, row = sl / CPR, ch = (sl % CPR) ^ att_swz<CPR>(row);
+        k_off[i] = (uint32_t)att_key(row) * k_pitch + (uint32_t)ch * 16u;
+    }
+#pragma unroll
+    for (int i = 0; i < V_LD; ++i) {
+        const int sl = i * 64 + lane, row = sl >> 2, ch = (sl & 3) ^ ((row >> 2) & 3);
+        v_off[i] = ((uint32_t)row * (uint32_t)S_pad + (uint32_t)ch * 8u) * 2u;
+    }
+    // (a key beyond the sequence: the last 16 bytes of its last row instead, which the mask leaves out)
+    auto issue_k = [&](int kt) __attribute__((always_inline)) {
+        const char* base = reinterpret_cast<const char*>(k_base) + (size_t)(kt * KT) * k_pitch;
+        const uint32_t k_last = (uint32_t)(S - 1 - kt * KT) * k_pitch + (uint32_t)(DH - 8) * 2u;
+#pragma unroll
+        for (int i = 0; i < K_LD; ++i) att_dma16(base, min(k_off[i], k_last), lds_wave + (uint32_t)(i * 64) * 16u);
+    };
+    auto issue_v = [&](int kt) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < V_LD; ++i)
+            att_dma16(v_base + kt * KT, v_off[i], lds_wave + (uint32_t)(K_SLOTS + i * 64) * 16u);
+    };
+
+    if (wave < n_kt) {
+        issue_k(wave);
+        issue_v(wave);
+    }
+    // B operand of S^T: this lane's query row, one memory round trip with the first tiles (pinned: the compiler's
+    // wait for it stands here and not in the loop)
+    uint4 qf[STEPS];
+    {
+        const bf16_t* src = q + ((size_t)b * S + min(my_q, S - 1)) * ld + h * DH + fg * 8;
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) qf[st] = *reinterpret_cast<const uint4*>(src + st * 16);
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st)
+            asm volatile("" : "+v"(qf[st].x), "+v"(qf[st].y), "+v"(qf[st].z), "+v"(qf[st].w));
+    }
+
+    f32x16_t o_acc[DB];
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o_acc[d][v] = 0.f;
+    float run_m = -INFINITY, run_l = 0.f;   // run_l: this lane's share of the row sum
+
+    const uint4* Kc = lds + wave * STAGE;
+    const uint4* Vc = Kc + K_SLOTS;
+    for (int kt = wave; kt < n_kt; kt += NW) {
+        const bool more = kt + NW < n_kt;
+        att_wait_vm<V_LD>();               // K landed (V^T of the tile behind it)
+        uint4 kf[STEPS];
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) kf[st] = Kc[fr * CPR + ((st * 2 + fg) ^ att_swz<CPR>(fr))];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read: its place is free
+        if (more) issue_k(kt + NW);
+        f32x16_t s_acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s_acc[v] = 0.f;
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) s_acc = mfma32(kf[st], qf[st], s_acc);
+        if (more) att_wait_vm<K_LD>();     // V^T landed (the next K behind it)
+        else att_wait_vm<0>();
+        uint4 vf[DB][2];
+#pragma unroll
+        for (int d = 0; d < DB; ++d) {
+            const int row = d * 32 + fr;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) vf[d][ks] = Vc[row * 4 + ((ks * 2 + fg) ^ ((row >> 2) & 3))];
+        }
+        // ---- softmax of the tile against the wave's own running maximum
+        float tile_m = -INFINITY;
+        if (kt == n_kt - 1) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int key = kt * KT + 16 * (v >> 3) + 8 * fg + (v & 7);   // att_key of the row
+                s_acc[v] = (key <= my_q && key < S) ? s_acc[v] : -INFINITY;
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) tile_m = fmaxf(tile_m, s_acc[v]);
+        tile_m = fmaxf(tile_m, __shfl_xor(tile_m, 32));
+        const float new_m = fmaxf(run_m, tile_m);
+        // (a wave's tiles may hold nothing but logits of -inf, where another wave's do not: they weigh 0)
+        const float neg_m = new_m == -INFINITY ? 0.f : -new_m * scale_log2e;
+        float psum = 0.f;
+        uint4 pf[2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            float e[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                e[i] = __builtin_amdgcn_exp2f(fmaf(s_acc[hh * 8 + i], scale_log2e, neg_m));
+                psum += e[i];
+            }
+            pf[hh] = make_uint4(pack_bf16x2(e[0], e[1]), pack_bf16x2(e[2], e[3]), pack_bf16x2(e[4], e[5]),
+                                pack_bf16x2(e[6], e[7]));
+        }
+        if (__any(new_m != run_m)) {
+            const float corr = new_m == run_m ? 1.f : __builtin_amdgcn_exp2f((run_m - new_m) * scale_log2e);
+            run_l *= corr;
+#pragma unroll
+            for (int d = 0; d < DB; ++d)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o_acc[d][v] *= corr;
+            run_m = new_m;
+        }
+        run_l += psum;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // V^T read: its place is free
+        if (more) issue_v(kt + NW);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int d = 0; d < DB; ++d) o_acc[d] = mfma32(vf[d][ks], pf[ks], o_acc[d]);
+    }
+
+    // ---- parts of all waves: O^T in fours per lane, one after the other, maximum and sum per query
+    // (a wave's tiles have all been read, and no load is in flight)
+    run_l += __shfl_xor(run_l, 32);
+    float4* part = reinterpret_cast<float4*>(lds);
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+        part[wave * STAGE + g * 64 + lane] =
+            make_float4(o_acc[g >> 2][(g & 3) * 4], o_acc[g >> 2][(g & 3) * 4 + 1], o_acc[g >> 2][(g & 3) * 4 + 2],
+                        o_acc[g >> 2][(g & 3) * 4 + 3]);
+    if (fg == 0) {
+        sh_m[wave][fr] = run_m;
+        sh_l[wave][fr] = run_l;
+    }
+    __syncthreads();
+    float top = sh_m[0][fr];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) top = fmaxf(top, sh_m[w][fr]);
+    float f[NW], tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float m = sh_m[w][fr];
+        f[w] = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - top) * scale_log2e);
+        tot += sh_l[w][fr] * f[w];
+    }
+    if (my_q < S) {
+        const float inv = 1.0f / tot;
+        bf16_t* orow = out + ((size_t)b * S + my_q) * ldo + h * DH;
+#pragma unroll
+        for (int j = 0; j < GROUPS / NW; ++j) {
+            const int g = wave * (GROUPS / NW) + j;
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float4 t = part[w * STAGE + g * 64 + lane];
+                a.x = fmaf(t.x, f[w], a.x);
+                a.y = fmaf(t.y, f[w], a.y);
+                a.z = fmaf(t.z, f[w], a.z);
+                a.w = fmaf(t.w, f[w], a.w);
+            }
+            uint2 o;
+            o.x = pack_bf16x2(a.x * inv, a.y * inv);
+            o.y = pack_bf16x2(a.z * inv, a.w * inv);
+            *reinterpret_cast<uint2*>(orow + (g >> 2) * 32 + 8 * (g & 3) + 4 * fg) = o;
+        }
+    }
+}
+
+template <typename Kernel>
+static int start_attention(Kernel kern, bool* lds_set, dim3 grid, int threads, size_t lds, const bf16_t* q,
+                           const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad, int S, int H, int dh, bf16_t* out,
+                           int ldo, hipStream_t st) {
+    int dev = 0;   // (the dynamic-LDS limit is raised once per device)
     MVLA_HIP_CHECK(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices || !lds_set[dev]) {
         MVLA_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         if (dev >= 0 && dev < kMaxDevices) lds_set[dev] = true;
     }
-    hipLaunchKernelGGL(kern, grid, dim3(ATT_THREADS), lds, st, q, k, ldqkv, vt, S_pad, S, H,
-                       scale_log2e, out, ldo);
+    const float scale_log2e = 1.4426950408889634f / sqrtf((float)dh);
+    hipLaunchKernelGGL(kern, grid, dim3(threads), lds, st, q, k, ldqkv, vt, S_pad, S, H, scale_log2e, out, ldo);
     MVLA_HIP_CHECK(hipGetLastError());
     return MVLA_OK;
+}
+
+template <int DH, int NS>
+static int launch_att(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad,
+                      int B, int S, int H, bf16_t* out, int ldo, hipStream_t st) {
+    static bool lds_set[kMaxDevices] = {};
+    const size_t lds = (size_t)NS * (ATT_KT * (DH / 8) + DH * 8) * sizeof(uint4);
+    return start_attention(attention_kernel<DH, NS>, lds_set, dim3(H, (S + ATT_QT - 1) / ATT_QT, B), ATT_THREADS, lds,
+                           q, k, ldqkv, vt, S_pad, S, H, DH, out, ldo, st);
+}
+
+template <int DH, int NW>
+static int launch_short(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad,
+                        int B, int S, int H, bf16_t* out, int ldo, hipStream_t st) {
+    static bool lds_set[kMaxDevices] = {};
+    const size_t lds = (size_t)NW * (32 * (DH / 8) + DH * 4) * sizeof(uint4);
+    return start_attention(short_attention_kernel<DH, NW>, lds_set, dim3(H, (S + 31) / 32, B), NW * 64, lds, q, k,
+                           ldqkv, vt, S_pad, S, H, DH, out, ldo, st);
+}
+
+// Workgroups of 32 queries up to which short_attention_kernel is the faster one, measured on both sides of each line
+// (us, long chain / short chains): one per compute unit for a few tiles (S = 80: 240
+// 6.3 / 5.5, 288 6.4 / 6.9; up to 64 keys there is no chain to cut, 5.0 / 5.2), two from four long tiles on (S = 237:
+// 512 9.7 / 9.1, 640 10.1 / 11.6), and where the chain is long a partial third round still pays, twice that at dh =
+// 64, whose workgroups take half the LDS (dh = 128: S = 700, 704 17.9 / 16.8, 880 equal; dh = 64: 1408 16.0 / 13.9).
+static int short_limit(int S, int dh) {
+    if (S <= ATT_KT) return 0;
+    if (S <= 3 * ATT_KT) return 256;
+    if (S < 512) return 512;
+    return dh == 64 ? 1408 : 704;
 }
 
 int launch_attention(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad,
@@ -308,6 +539,10 @@ int launch_attention(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* 
     // per-lane byte offsets inside one sample's keys / one head's V^T are 32-bit (kept below 2^31)
     if ((size_t)S * ldqkv * 2 >= ((size_t)1 << 31) || (size_t)dh * S_pad * 2 >= ((size_t)1 << 31))
         return MVLA_EUNSUPPORTED;
+    if ((size_t)B * H * ((S + 31) / 32) <= (size_t)short_limit(S, dh)) {
+        if (dh == 128) return launch_short<128, 4>(q, k, ldqkv, vt, S_pad, B, S, H, out, ldo, st);
+        if (dh == 64) return launch_short<64, 4>(q, k, ldqkv, vt, S_pad, B, S, H, out, ldo, st);
+    }
     // two stages of 32 KiB each: two workgroups per CU, whose waves overlap softmax and MFMA
     if (dh == 128) return launch_att<128, 2>(q, k, ldqkv, vt, S_pad, B, S, H, out, ldo, st);
     if (dh == 64) return launch_att<64, 2>(q, k, ldqkv, vt, S_pad, B, S, H, out, ldo, st);

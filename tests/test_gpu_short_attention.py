@@ -1,0 +1,55 @@
+"""Attention of short launches (32 queries a workgroup, key tiles dealt out to its waves): a layer against the
+oracle at sequence lengths around the edges of the tiles, of the number of waves and of the two lengths at which the
+dispatch's limit changes, and at batches on both sides of that limit, for both head dimensions."""
+from dataclasses import replace
+
+import pytest
+import torch
+
+from helpers import check_layer, device_layer, layer_cfg, oracle_weights, to64
+from paper_2604_09244_amd import binding as mv
+from paper_2604_09244_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _attention_kernels(fn):
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if "attention_kernel" in e.name]
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("S,limit", [(65, 256), (96, 256), (127, 256), (129, 256), (161, 256), (192, 256), (193, 512),
+                                     (257, 512), (511, 512), (512, 0), (545, 0)])
+def test_layer_with_short_attention(dh, S, limit):
+    limit = limit or (1408 if dh == 64 else 704)
+    H = 4
+    most = limit // (H * ((S + 31) // 32))       # samples up to which the launch is a short one
+    wl = replace(W.WORKLOADS["tiny"], D=H * dh, H=H, dh=dh, F=256, n2=S // 2, n3=S - S // 2, nt=0, B=most + 1, L=1, p=0,
+                 seed=S + dh)
+    ctx = mv.Context(wl.B, S, wl.D, H, wl.F, 1)
+    w_cpu = W.layer_weights(wl, 0)
+    packed, ws = device_layer(ctx, wl, w_cpu)
+    x, pos = W.hidden_states(wl)
+    wo, cfg = oracle_weights(w_cpu), layer_cfg(wl)
+    for B in (most, most + 1):
+        xb, pb = x[:B].contiguous().cuda(), pos[:B].contiguous().cuda()
+        y = ctx.prefill_layer(cfg, ws, xb, pb)
+        names = _attention_kernels(lambda: ctx.prefill_layer(cfg, ws, xb, pb, y))
+        assert len(names) == 1 and ("short_attention" in names[0]) == (B <= most), names
+        for b in {0, B - 1}:
+            check_layer(y[b], to64(x[b]), pos[b].numpy(), wo, wl, f"dh={dh} B={B} b={b} S={S}")
+    ctx.close()
+
+
+def test_up_to_one_tile_stays_with_the_long_kernel():
+    wl = replace(W.WORKLOADS["tiny"], n2=32, n3=32, nt=0, seed=5)
+    ctx = mv.Context(1, 64, wl.D, wl.H, wl.F, 1)
+    packed, ws = device_layer(ctx, wl, W.layer_weights(wl, 0))
+    x, pos = (t.cuda() for t in W.hidden_states(wl))
+    names = _attention_kernels(lambda: ctx.prefill_layer(layer_cfg(wl), ws, x, pos))
+    assert len(names) == 1 and "short_attention" not in names[0], names
+    ctx.close()
