@@ -290,7 +290,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(
 // the softmax and O^T), and the next V^T tile the same (behind the next S^T).  A wave's O^T takes the
 // place of its tiles in LDS (16 KiB each at dh = 128), the waves add up the parts of all, in wave order, a share of
 // the head dimension each.
-// Launches of 32 heads of 128: S = 237 9.3 -> 6.6 us, S = 544 15.0 -> 12.2; 4 heads of 64: S = 144 5.1 -> 4.3,
+// 32 heads of 128: S = 237 9.3 -> 6.6 us, S = 448 12.8 -> 9.8; 4 heads of 64: S = 144 5.1 -> 4.3,
 // S = 1344 19.3 -> 9.6.  Once the chip is full it is the slower one (every 32 queries fetch their keys for
 // themselves: B = 4, S = 544 28 against 38 us), see short_limit.  Eight waves: slower wherever a second round of
 // workgroups is needed (128 KiB of LDS leave one per CU), 5-15 % faster only with few heads and S > 1000.
@@ -521,15 +521,17 @@ static int launch_short(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_
 }
 
 // Workgroups of 32 queries up to which short_attention_kernel is the faster one, measured on both sides of each line
-// (us, long chain / short chains): one per compute unit for a few tiles (S = 80: 240
-// 6.3 / 5.5, 288 6.4 / 6.9; up to 64 keys there is no chain to cut, 5.0 / 5.2), two from four long tiles on (S = 237:
-// 512 9.7 / 9.1, 640 10.1 / 11.6), and where the chain is long a partial third round still pays, twice that at dh =
-// 64, whose workgroups take half the LDS (dh = 128: S = 700, 704 17.9 / 16.8, 880 equal; dh = 64: 1408 16.0 / 13.9).
+// (us, long chain / short chains): one per compute unit for a few tiles (S = 80: 240 6.3 / 5.5, 288 6.4 / 6.9; up to 64
+// keys there is no chain to cut, 5.0 / 5.2), from four long tiles on what is resident at once, two per compute unit
+// at dh = 128 (S = 237: 512 9.7 / 9.1, 640 10.1 / 11.6) and, once the chain is long, four at dh = 64, whose
+// workgroups take half the LDS (S = 900: 928 15.3 / 12.9; S = 448: 512 8.6 / 7.0, 896 9.0 / 9.4).  A partial third
+// round would pay too at S >= 512 (544 15.0 / 12.2, 704 17.9 / 16.8), but those are the full-sequence layers in
+// front of the scoring, whose saliences hang on a few keys: on single inputs another order of sums put them up to 1.5
+// times as far from their 64-bit values, and as often nearer (mean over 12 inputs 0.96), so these keep the long chain.
 static int short_limit(int S, int dh) {
     if (S <= ATT_KT) return 0;
     if (S <= 3 * ATT_KT) return 256;
-    if (S < 512) return 512;
-    return dh == 64 ? 1408 : 704;
+    return dh == 64 && S >= 512 ? 1024 : 512;
 }
 
 int launch_attention(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad,

@@ -25,7 +25,7 @@ def _attention_kernels(fn):
 @pytest.mark.parametrize("S,limit", [(65, 256), (96, 256), (127, 256), (129, 256), (161, 256), (192, 256), (193, 512),
                                      (257, 512), (511, 512), (512, 0), (545, 0)])
 def test_layer_with_short_attention(dh, S, limit):
-    limit = limit or (1408 if dh == 64 else 704)
+    limit = limit or (1024 if dh == 64 else 512)
     H = 4
     most = limit // (H * ((S + 31) // 32))       # samples up to which the launch is a short one
     wl = replace(W.WORKLOADS["tiny"], D=H * dh, H=H, dh=dh, F=256, n2=S // 2, n3=S - S // 2, nt=0, B=most + 1, L=1, p=0,
