@@ -442,18 +442,23 @@ static int run_layer(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_
     if (n_query_tail > 0 && !red) {
         TIMED(ctx, KID_SCORE_PROBS, M,
               launch_score_probs(lb.qkv, 3 * D, false, lb.qkv + D, 3 * D, key_bias, B, S, H, dh,
-                                 n_query_tail, probs_out, 0, st));
+                                 n_query_tail, probs_out, 0, score_tile_queries(B, H, S, n_query_tail, false), st));
     } else if (n_query_tail > 0) {
-        // Column sums per 32-query tile go to the (still unused) MLP activation buffer, the
+        // Column sums per tile of queries go to the (still unused) MLP activation buffer, the
         // row-split partials of their reduction to the attention output buffer.
-        const int n_vis = red->n2 + red->n3, tiles = (n_query_tail + 31) / 32;
+        const int n_vis = red->n2 + red->n3;
         float* colsum = reinterpret_cast<float*>(lb.act);
-        if ((size_t)B * H * tiles * n_vis * 4 > (size_t)M * F * 2 ||
-            salience_scratch_bytes(B, H, tiles, n_vis) > (size_t)M * D * 2)
-            return MVLA_ENOMEM;
+        const auto fits = [&](int tiles) {
+            return (size_t)B * H * tiles * n_vis * 4 <= (size_t)M * F * 2 &&
+                   salience_scratch_bytes(B, H, tiles, n_vis) <= (size_t)M * D * 2;
+        };
+        int tile = score_tile_queries(B, H, S, n_query_tail, true);
+        if (!fits((n_query_tail + tile - 1) / tile)) tile = 32;   // (fewer column sums)
+        const int tiles = (n_query_tail + tile - 1) / tile;
+        if (!fits(tiles)) return MVLA_ENOMEM;
         TIMED(ctx, KID_SCORE_PROBS, M,
               launch_score_probs(lb.qkv, 3 * D, false, lb.qkv + D, 3 * D, key_bias, B, S, H, dh,
-                                 n_query_tail, colsum, n_vis, st));
+                                 n_query_tail, colsum, n_vis, tile, st));
         if (red->kept_idx) {
             TIMED(ctx, KID_PRUNE_FUSED, B,
                   launch_prune_fused(colsum, B, H, tiles, n_vis, red->n2, red->n3, red->n_text,
@@ -980,7 +985,7 @@ int mvla_score_only(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_w
     }
     TIMED(ctx, KID_SCORE_PROBS, M,
           launch_score_probs(q_buf, D, true, k_buf, D, key_bias, B, S, H, dh, n_query_tail,
-                             probs_out, 0, st));
+                             probs_out, 0, score_tile_queries(B, H, S, n_query_tail, false), st));
     return MVLA_OK;
 }
 

@@ -105,11 +105,13 @@ int launch_rmsnorm_tail(const bf16_t* x, const int32_t* pos, const bf16_t* gain,
 int launch_compact_norm(const bf16_t* h, const int32_t* pos, const int32_t* kept_idx, int B, int S, int S_out, int D,
                         bf16_t* h_out, int32_t* pos_out, const bf16_t* gain, float eps, bf16_t* u, hipStream_t st);
 int launch_rope_table(double base, int rope_len, int dh, float* c, float* s, hipStream_t st);
+// queries a workgroup with which launch_score_probs is fastest (16 or 32); sums: it writes column sums
+int score_tile_queries(int B, int H, int S, int nq, bool sums);
 // scoring probabilities of the last nq rows: probs [B,H,nq,S] fp32.  q_tail_only: q holds just
 // those rows, nq per sample ([B*nq, q_row_stride]); otherwise all S rows of every sample.
 int launch_score_probs(const bf16_t* q, int q_row_stride, bool q_tail_only, const bf16_t* k,
                        int k_row_stride, const float* key_bias, int B, int S, int H, int dh, int nq,
-                       float* out, int colsum_n, hipStream_t st);
+                       float* out, int colsum_n, int tile, hipStream_t st);
 
 // gemm.hip:  C[M,N] = A[M,K] * W[N,K]^T  (bf16 in, fp32 accumulate)
 // EPI_QKV_ROPE: the q/k/v projection (N = 3D, or 2D for q and k alone).  Columns [0, 2D) are

@@ -307,14 +307,19 @@ __global__ __launch_bounds__(SC_THREADS) void score_probs_kernel(
     }
 }
 
-// Combination over the 32 lanes of a half-wave, result in all of them: rotations within 16 lanes, then
-// the two 16-lane rows of the half (vector-ALU only; the general shuffle goes through the LDS unit)
+// Combination over the 16 lanes of a row, result in all of them: rotations within the row (vector-ALU only; the
+// general shuffle goes through the LDS unit)
 template <typename Op>
-__device__ __forceinline__ float half_wave_all(float x, Op op) {
+__device__ __forceinline__ float row_all(float x, Op op) {
     x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, false)));   // row_ror:8
     x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false)));
     x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, false)));
-    x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false)));
+    return op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false)));
+}
+// ... over the 32 lanes of a half-wave: its two rows exchange what they have
+template <typename Op>
+__device__ __forceinline__ float half_wave_all(float x, Op op) {
+    x = row_all(x, op);
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
@@ -466,6 +471,136 @@ __global__ __launch_bounds__(NW * 64) void score_probs_reg_kernel(
     }
 }
 
+// The same with 16 queries a workgroup, for launches that leave most of the chip idle: twice the workgroups, and a
+// lane holds 4 instead of 16 queries of a key, so the scaling, the exponentials and above all the reductions over the
+// keys of a row (which every lane does for each of its queries) are a quarter of the instructions between the
+// products.  Same scoring rows, us before / after: 32 heads of 128, 32 rows, S = 144 8.5 / 5.3, S = 544 13.0 / 8.8, S = 1024
+// 20.5 / 12.6; 4 heads of 64, 16 rows, S = 144 6.2 / 4.1.  (Sixteen waves: 10.4 us at S = 544.)
+template <int DH, int NW, int KBW, bool COLSUM>
+__global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
+    const bf16_t* __restrict__ q, int ldq, int q_rows /* per sample */, const bf16_t* __restrict__ k,
+    int ldk, const float* __restrict__ key_bias, int S, int H, int nq, float scale,
+    float* __restrict__ probs, int n_out) {
+    constexpr int STEPS = DH / 32;
+    const int qt = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = lane & 15, g = lane >> 4;      // key column (operand row), query rows 4g ..
+    const int row0 = S - nq, qi0 = qt * 16;
+    const bf16_t* kbase = k + (size_t)b * S * ldk + h * DH + g * 8;
+    const float* bias = key_bias ? key_bias + (size_t)b * S : nullptr;
+    uint4 qf[STEPS], kf[KBW][STEPS];
+    {
+        const int qi = min(qi0 + c, nq - 1);
+        // q holds either all S rows of a sample or only its nq scoring rows
+        const bf16_t* src = q + ((size_t)b * q_rows + (q_rows - nq) + qi) * ldq + h * DH + g * 8;
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) qf[st] = *reinterpret_cast<const uint4*>(src + st * 32);
+    }
+    // all keys of the wave in flight (rows past the end are clamped: loaded, never used)
+    float kbias[KBW];
+#pragma unroll
+    for (int i = 0; i < KBW; ++i) {
+        const int key = min((wave + NW * i) * 16 + c, S - 1);
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st)
+            kf[i][st] = *reinterpret_cast<const uint4*>(kbase + (size_t)key * ldk + st * 32);
+        kbias[i] = bias ? bias[key] : 0.f;
+    }
+    float run[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) run[v] = -INFINITY;
+    f32x4_t lg[KBW];
+#pragma unroll
+    for (int i = 0; i < KBW; ++i) {
+        lg[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) lg[i] = mfma16(qf[st], kf[i][st], lg[i]);
+        const int kb = wave + NW * i, key = kb * 16 + c;
+        // a key up to the first scoring row is seen by every query (wave-uniform test)
+        const bool all = kb * 16 + 15 <= row0 + qi0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const bool valid = all || (key < S && key <= row0 + qi0 + 4 * g + v);
+            lg[i][v] = valid ? lg[i][v] * scale + kbias[i] : -INFINITY;
+            run[v] = fmaxf(run[v], lg[i][v]);
+        }
+    }
+    __shared__ float sh_m[NW][16], sh_l[NW][16];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) run[v] = row_all(run[v], [](float a, float o) { return fmaxf(a, o); });
+    if (c == 0) *reinterpret_cast<float4*>(&sh_m[wave][4 * g]) = make_float4(run[0], run[1], run[2], run[3]);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        float gm = sh_m[0][4 * g + v];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) gm = fmaxf(gm, sh_m[w][4 * g + v]);
+        float l = 0.f;       // (the maximum is finite: key 0 is visible to every query)
+#pragma unroll
+        for (int i = 0; i < KBW; ++i) {
+            lg[i][v] = __expf(lg[i][v] - gm);   // exp(-inf) = 0 for masked entries
+            l += lg[i][v];
+        }
+        run[v] = row_all(l, [](float a, float o) { return a + o; });
+    }
+    if (c == 0) *reinterpret_cast<float4*>(&sh_l[wave][4 * g]) = make_float4(run[0], run[1], run[2], run[3]);
+    __syncthreads();
+    float* out = probs + (((size_t)b * H + h) * nq + qi0) * S;
+    float csum[KBW];
+#pragma unroll
+    for (int i = 0; i < KBW; ++i) csum[i] = 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int r = 4 * g + v;
+        float gl = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) gl += sh_l[w][r];
+        const float inv = 1.0f / gl;
+        if (qi0 + r < nq)
+#pragma unroll
+            for (int i = 0; i < KBW; ++i) {
+                const int key = (wave + NW * i) * 16 + c;
+                if (COLSUM) csum[i] += lg[i][v] * inv;
+                else if (key < S) out[(size_t)r * S + key] = lg[i][v] * inv;
+            }
+    }
+    if (COLSUM) {
+        float* sums = probs + (((size_t)b * H + h) * gridDim.x + qt) * n_out;
+#pragma unroll
+        for (int i = 0; i < KBW; ++i) {
+            const int key = (wave + NW * i) * 16 + c;
+            float t = csum[i];       // (over the four rows of lanes: the tile's other queries)
+            t += __shfl_xor(t, 16);
+            t += __shfl_xor(t, 32);
+            if (g == 0 && key < n_out) sums[key] = t;
+        }
+    }
+}
+
+// Where 16 queries a workgroup are the faster ones (us, 32 / 16 queries): while these workgroups fit one per compute
+// unit (B = 4, 32 rows, S = 544, 256 of them 13.9 / 10.3; twice as many 15.5 / 17.1: every workgroup reads all
+// keys); where 32 queries would be no fewer workgroups (16 rows, B = 16: 26.7 / 17.2); and for two key blocks a
+// wave (S = 256) at any number where probabilities are written (B = 16, 64 rows 35.2 / 29.3), up to 512 where their
+// sums are (8.9 / 8.6; 1024 13.2 / 14.3).  Sums of S = 544, 32 rows: 256 of them 12.2 / 8.6, 512 12.4 / 14.2.
+int score_tile_queries(int B, int H, int S, int nq, bool sums) {
+    const size_t groups = (size_t)((nq + 15) / 16) * H * B;
+    if (S <= 8 * 16 * 2) return !sums || groups <= 512 || nq <= 16 ? 16 : 32;
+    return S <= 8 * 16 * 8 && (groups <= 256 || nq <= 16) ? 16 : 32;
+}
+
+template <int DH, bool COLSUM>
+static void launch_score_rows16(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk, const float* key_bias,
+                                int B, int S, int H, int nq, float scale, float* out, int n_out, hipStream_t st) {
+    dim3 grid((nq + 15) / 16, H, B);
+#define MVLA_SCR(NW, KBW)                                                                                     \
+    hipLaunchKernelGGL((score_probs_rows16_kernel<DH, NW, KBW, COLSUM>), grid, dim3(NW * 64), 0, st, q, ldq, q_rows, \
+                       k, ldk, key_bias, S, H, nq, scale, out, n_out)
+    if (S <= 8 * 16 * 2) MVLA_SCR(8, 2);
+    else if (S <= 8 * 16 * 5) MVLA_SCR(8, 5);
+    else MVLA_SCR(8, 8);
+#undef MVLA_SCR
+}
+
 template <int DH, bool COLSUM>
 static bool launch_score_reg(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk,
                              const float* key_bias, int B, int S, int H, int nq, float scale,
@@ -475,8 +610,9 @@ static bool launch_score_reg(const bf16_t* q, int ldq, int q_rows, const bf16_t*
 #define MVLA_SCR(NW, KBW, AHEAD)                                                            \
     hipLaunchKernelGGL((score_probs_reg_kernel<DH, NW, KBW, AHEAD, COLSUM>), grid, dim3(NW * 64), 0, st, \
                        q, ldq, q_rows, k, ldk, key_bias, S, H, nq, scale, out, n_out)
-    if (blocks <= 8 * 1) MVLA_SCR(8, 1, 1);
-    else if (blocks <= 8 * 3) MVLA_SCR(8, 3, 3);
+    if (COLSUM && blocks <= 8 * 1) {   // (probabilities of so few keys: score_probs_rows16_kernel)
+        if constexpr (COLSUM) MVLA_SCR(8, 1, 1);
+    } else if (blocks <= 8 * 3) MVLA_SCR(8, 3, 3);
     else if (blocks <= 8 * 6) MVLA_SCR(8, 6, 2);
     else if (blocks <= 8 * 8) MVLA_SCR(8, 8, 2);
     else return false;
@@ -487,7 +623,11 @@ static bool launch_score_reg(const bf16_t* q, int ldq, int q_rows, const bf16_t*
 template <int DH, bool COLSUM>
 static void launch_score_dh(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk,
                             const float* key_bias, int B, int S, int H, int nq, float scale,
-                            float* out, int n_out, hipStream_t st) {
+                            float* out, int n_out, int tile, hipStream_t st) {
+    if (tile == 16) {
+        launch_score_rows16<DH, COLSUM>(q, ldq, q_rows, k, ldk, key_bias, B, S, H, nq, scale, out, n_out, st);
+        return;
+    }
     // register-resident single pass when the row fits, else two passes
     if (launch_score_reg<DH, COLSUM>(q, ldq, q_rows, k, ldk, key_bias, B, S, H, nq, scale, out, n_out,
                                      st))
@@ -498,16 +638,17 @@ static void launch_score_dh(const bf16_t* q, int ldq, int q_rows, const bf16_t* 
 }
 
 // colsum_n == 0: out = probabilities [B,H,nq,S]; colsum_n > 0: out = per-tile column sums
-// [B, H, ceil(nq/32), colsum_n] over the first colsum_n key columns.
+// [B, H, ceil(nq/tile), colsum_n] over the first colsum_n key columns.  tile: 32, or 16 where
+// score_tile_queries says so.
 int launch_score_probs(const bf16_t* q, int q_row_stride, bool q_tail_only, const bf16_t* k,
                        int k_row_stride, const float* key_bias, int B, int S, int H, int dh, int nq,
-                       float* out, int colsum_n, hipStream_t st) {
+                       float* out, int colsum_n, int tile, hipStream_t st) {
     if (B <= 0 || nq <= 0) return MVLA_OK;
     const float scale = 1.0f / sqrtf((float)dh);
     const int q_rows = q_tail_only ? nq : S;
 #define MVLA_SC(DH_, CS_)                                                                       \
     launch_score_dh<DH_, CS_>(q, q_row_stride, q_rows, k, k_row_stride, key_bias, B, S, H, nq, scale, \
-                              out, colsum_n, st)
+                              out, colsum_n, tile, st)
     if (dh == 128) {
         if (colsum_n > 0) MVLA_SC(128, true); else MVLA_SC(128, false);
     } else if (dh == 64) {
