@@ -30,7 +30,7 @@ template <typename Load>
 __device__ __forceinline__ void finish_sample(Load load, const FusedPrune& f, int b, uint32_t* keys);
 
 constexpr int SAL_THREADS = 256;
-constexpr int SEL_MAX_N = 16384;    // largest segment the selection stages in LDS
+constexpr int SEL_MAX_N = 16384;    // largest segment the selection takes
 constexpr int SEL_FOUR_WAVES = 2048;  // longest segment that four waves select; beyond it sixteen
 constexpr int SAL_LPR = 16;                        // lanes per row-group
 // Attention tensors above this are read past the caches.  344 MB (B = 16, 32 heads x 64 queries x 2624
@@ -429,7 +429,7 @@ int launch_budget(const float* sal, int B, int n2, int n3, int k_total, int min2
 }
 
 // ---------------------------------------------------------------------------
-// Per-modality top-k.  The scores sit in LDS as order-preserving 32-bit keys; a
+// Per-modality top-k.  The scores are held as order-preserving 32-bit keys; a
 // group of waves works on one segment (one workgroup per segment in
 // select_kernel, half a workgroup each in the tail of the fused kernel, both
 // segments in step).  Exact search for the K-th largest key T: a 1024-bin
@@ -448,6 +448,9 @@ int launch_budget(const float* sal, int B, int n2, int n3, int k_total, int min2
 // after the other: 16384 + 16384 tokens
 // (B = 1) 52 -> 17 us, 768 + 1024 (B = 8) 7.8 -> 6.4; the fused step and its gather, 64 rows of two segments of
 // 64 tokens, 13.1 -> 8.0.
+// The kernel of its own keeps each thread's keys in registers (they were read from LDS five times, and laid
+// down there first): calls of 1024 + 1024 (B = 8) 6.2 -> 4.9 us, 2048 + 2048 8.1 -> 6.6, 16384 + 16384 (B = 1)
+// 16.7 -> 14.5.  In the fused tail half a workgroup takes a segment of up to 16384, and the keys stay in LDS.
 // ---------------------------------------------------------------------------
 
 __device__ inline uint32_t sal_key(float x) {
@@ -499,11 +502,12 @@ struct SelShared {
 
 // Every thread of the workgroup calls this with its group's segment (group-uniform arguments;
 // k <= 0 or n <= 0: nothing to do, but the barriers are taken part in; all_short: every group's n is
-// at most 64, the same for the whole workgroup).  The keys were written by
-// this workgroup; the first barrier orders those writes before the reads.
-template <int GW, int NG>
-__device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, int n, int k, int idx_offset,
-                                              int32_t* __restrict__ out, bool all_short,
+// at most 64, the same for the whole workgroup).  KPT == 0: the keys were written to LDS by this workgroup; the
+// first barrier orders those writes before the reads.  KPT > 0: key(i) fetches one, and a thread keeps its up to KPT
+// in registers throughout (those that it places, 64 apart).
+template <int GW, int NG, int KPT = 0, typename Key = const uint32_t*>
+__device__ __forceinline__ void select_groups(Key keys /*LDS [n], or a function of the index*/, int n, int k,
+                                              int idx_offset, int32_t* __restrict__ out, bool all_short,
                                               SelShared<GW, NG>& sh) {
     constexpr int GT = GW * 64, BPT = SEL_BINS / GT;
     static_assert(SEL_BINS % GT == 0, "");
@@ -515,15 +519,46 @@ __device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, 
     bool done = !work;                          // threshold known
     bool rank_now = work && n <= SEL_CAND;      // few enough keys in [lo, hi] to rank directly
 
+    const int per = (n + GT - 1) / GT * 64, i0 = min(n, gw * per), i1 = min(n, i0 + per);   // (this wave's to place)
+    uint32_t own[KPT > 0 ? KPT : 1];
+    if constexpr (KPT > 0)
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) own[j] = keys(min(i0 + j * 64 + lane, n - 1));
+    // all keys of the group, each by one thread
+    auto each = [&](auto take) __attribute__((always_inline)) {
+        if constexpr (KPT > 0) {
+#pragma unroll
+            for (int j = 0; j < KPT; ++j)
+                if (i0 + j * 64 + lane < i1) take(own[j]);
+        } else {
+#pragma unroll 4
+            for (int i = gt; i < n; i += GT) take(keys[i]);
+        }
+    };
+    // the 64 keys at i0 + 64 j of this wave, for every j that it has
+    auto each_run = [&](auto take) __attribute__((always_inline)) {
+        if constexpr (KPT > 0) {
+#pragma unroll
+            for (int j = 0; j < KPT; ++j)
+                if (i0 + j * 64 < i1) take(i0 + j * 64, i0 + j * 64 + lane < i1, own[j]);
+        } else {
+            for (int i = i0; i < i1; i += 64) {
+                const bool in = i + lane < i1;
+                take(i, in, in ? keys[i + lane] : 0u);
+            }
+        }
+    };
     if (gt == 0) sh.n_cand[g] = 0u;
     if (threadIdx.x == 0) sh.open = 0u;
-    lds_barrier();   // the keys are in LDS
+    lds_barrier();   // (the keys are in LDS)
     if (all_short) {
         // (no segment of the workgroup is longer than a wave: one wave each ranks and places its
         // keys, nothing crosses waves)
         if (work && gw == 0) {
             const bool in = lane < n;
-            const uint32_t key = in ? keys[lane] : 0u;
+            uint32_t key;
+            if constexpr (KPT > 0) key = in ? own[0] : 0u;
+            else key = in ? keys[lane] : 0u;
             uint32_t above = 0u, equal = 0u;
             for (int j = 0; j < n; j += 8)       // (lanes beyond n hold 0, below every valid key)
 #pragma unroll
@@ -545,11 +580,10 @@ __device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, 
     }
     if (work && !rank_now) {
         uint32_t mx = 0u, mn_inv = 0u;          // (the minimum as the maximum of the complements)
-        for (int i = gt; i < n; i += GT) {
-            const uint32_t key = keys[i];
+        each([&](uint32_t key) __attribute__((always_inline)) {
             mx = max(mx, key);
             mn_inv = max(mn_inv, ~key);
-        }
+        });
         mx = wave_max(mx);
         mn_inv = wave_max(mn_inv);
         if (lane == 0) {
@@ -580,11 +614,10 @@ __device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, 
         }
         lds_barrier();
         if (narrow) {
-#pragma unroll 4
-            for (int i = gt; i < n; i += GT) {
-                const uint32_t d = keys[i] - lo;
+            each([&](uint32_t key) __attribute__((always_inline)) {
+                const uint32_t d = key - lo;
                 if (d <= range) atomicAdd(&sh.hist[g][d >> shift], 1u);
-            }
+            });
         }
         lds_barrier();
         // counts from the top bin down: thread t looks at bins SEL_BINS-1 - t*BPT ...
@@ -634,10 +667,9 @@ __device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, 
         }
         const bool rank_pass = !done && rank_now;
         if (rank_pass) {
-            for (int i = gt; i < n; i += GT) {
-                const uint32_t key = keys[i];
+            each([&](uint32_t key) __attribute__((always_inline)) {
                 if (key >= lo && key <= hi) sh.cand[g][atomicAdd(&sh.n_cand[g], 1u)] = key;
-            }
+            });
         }
         lds_barrier();
         if (rank_pass) {
@@ -664,15 +696,12 @@ __device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, 
     }
     // placement: wave gw owns `per` consecutive indices
     const uint32_t T = sh.result[g][0], need_eq = sh.result[g][1];
-    const int per = (n + GT - 1) / GT * 64, i0 = min(n, gw * per), i1 = min(n, i0 + per);
     uint32_t n_gt = 0u, n_eq = 0u;
     if (work) {
-        for (int i = i0; i < i1; i += 64) {
-            const bool in = i + lane < i1;
-            const uint32_t key = in ? keys[i + lane] : 0u;
+        each_run([&](int, bool in, uint32_t key) __attribute__((always_inline)) {
             n_gt += (uint32_t)__popcll(__ballot(in && key > T));
             n_eq += (uint32_t)__popcll(__ballot(in && key == T));
-        }
+        });
         if (lane == 0) {
             sh.wave[g][gw][0] = n_gt;
             sh.wave[g][gw][1] = n_eq;
@@ -687,9 +716,7 @@ __device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, 
             eq_before += w < gw ? sh.wave[g][w][1] : 0u;
         }
         const unsigned long long below = (1ull << lane) - 1ull;
-        for (int i = i0; i < i1; i += 64) {
-            const bool in = i + lane < i1;
-            const uint32_t key = in ? keys[i + lane] : 0u;
+        each_run([&](int i, bool in, uint32_t key) __attribute__((always_inline)) {
             const unsigned long long bg = __ballot(in && key > T), be = __ballot(in && key == T);
             const uint32_t eq_rank = eq_before + (uint32_t)__popcll(be & below);
             const bool keep = in && (key > T || (key == T && eq_rank < need_eq));
@@ -697,17 +724,16 @@ __device__ __forceinline__ void select_groups(const uint32_t* keys /*LDS [n]*/, 
             if (keep && slot < (uint32_t)k) out[slot] = idx_offset + i + lane;
             gt_before += (uint32_t)__popcll(bg);
             eq_before += (uint32_t)__popcll(be);
-        }
+        });
     }
 }
 
-// One workgroup of GW waves per (sample, segment).
-template <int GW>
+// One workgroup of GW waves per (sample, segment), up to KPT keys a thread.
+template <int GW, int KPT>
 __global__ __launch_bounds__(GW * 64) void select_kernel(const float* __restrict__ sal,
                                                          const int32_t* __restrict__ k2k3, int n2,
                                                          int n3, int n_text, int k_total,
                                                          int32_t* __restrict__ kept_idx) {
-    extern __shared__ uint32_t keys[];
     __shared__ SelShared<GW, 1> sh;
     const int b = blockIdx.y, which = blockIdx.x;
     int32_t* row = kept_idx + (size_t)b * (k_total + n_text);
@@ -720,9 +746,8 @@ __global__ __launch_bounds__(GW * 64) void select_kernel(const float* __restrict
     }
     const float* seg = sal + (size_t)b * (n2 + n3) + (which ? n2 : 0);
     const int n = which ? n3 : n2;
-#pragma unroll 8
-    for (int i = threadIdx.x; i < n; i += GW * 64) keys[i] = sal_key(seg[i]);
-    select_groups<GW, 1>(keys, n, which ? k_total - k2 : k2, which ? n2 : 0, which ? row + k2 : row,
+    if (n <= 0) return;
+    select_groups<GW, 1, KPT>([&](int i) __attribute__((always_inline)) { return sal_key(seg[i]); }, n, which ? k_total - k2 : k2, which ? n2 : 0, which ? row + k2 : row,
                          n <= SEL_CAND, sh);
 }
 
@@ -777,25 +802,15 @@ __device__ __forceinline__ void finish_sample(Load load, const FusedPrune& f, in
 int launch_select(const float* sal, const int32_t* k2k3, int B, int n2, int n3, int n_text,
                   int k_total, int32_t* kept_idx, hipStream_t st) {
     if (n2 > SEL_MAX_N || n3 > SEL_MAX_N) return MVLA_EUNSUPPORTED;
-    const size_t lds = (size_t)max(max(n2, n3), 1) * 4;
-    // (up to 64 KiB of keys and 5 KiB beside them: above the default limit for the longest segments)
-#define MVLA_SELECT(GW)                                                                         \
-    do {                                                                                        \
-        auto kern = select_kernel<GW>;                                                          \
-        static bool lds_set[kMaxDevices] = {};                                                  \
-        int dev = 0;                                                                            \
-        MVLA_HIP_CHECK(hipGetDevice(&dev));                                                     \
-        if (dev < 0 || dev >= kMaxDevices || !lds_set[dev]) {                                   \
-            MVLA_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),             \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,      \
-                                               SEL_MAX_N * 4));                                 \
-            if (dev >= 0 && dev < kMaxDevices) lds_set[dev] = true;                             \
-        }                                                                                       \
-        hipLaunchKernelGGL(kern, dim3(3, B), dim3(GW * 64), lds, st, sal, k2k3, n2, n3, n_text, \
-                           k_total, kept_idx);                                                  \
-    } while (0)
-    if (max(n2, n3) <= SEL_FOUR_WAVES) MVLA_SELECT(4);
-    else MVLA_SELECT(16);
+    // (four waves up to SEL_FOUR_WAVES, else sixteen, with as many keys a thread as the longer segment needs)
+    const int longest = max(n2, n3);
+#define MVLA_SELECT(GW, KPT)                                                                               \
+    hipLaunchKernelGGL((select_kernel<GW, KPT>), dim3(3, B), dim3(GW * 64), 0, st, sal, k2k3, n2, n3, n_text, k_total, \
+                       kept_idx)
+    if (longest <= 4 * 64 * 4) MVLA_SELECT(4, 4);
+    else if (longest <= SEL_FOUR_WAVES) MVLA_SELECT(4, 8);
+    else if (longest <= 16 * 64 * 8) MVLA_SELECT(16, 8);
+    else MVLA_SELECT(16, 16);
 #undef MVLA_SELECT
     MVLA_HIP_CHECK(hipGetLastError());
     return MVLA_OK;
