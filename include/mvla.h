@@ -314,12 +314,12 @@ int mvla_prefill_layer_prune(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvl
                              float* sal, int32_t* k2k3, int32_t* kept_idx, void* h_out,
                              int32_t* pos_out);
 
-/* Optional set-up step: times every recordable tile configuration / K-split policy of
+/* Optional set-up step: times tile configurations 0 .. 6 with every K-split policy, and the
+ * built-in choice by size where that is a tile shape of its own, for
  * the four projections of a layer at M = B*S rows on this device, cycling
  * through the n_layers weight sets so that weights come from HBM as in real
- * use, and records the fastest per shape in the context; later layer calls at
- * that shape use it instead of the built-in cost model (which also has a few smaller
- * tiles that are not recorded: at a few hundred rows it can be the faster of the two).  Results of the layer
+ * use, and records the fastest per shape in the context (7: the choice by size); later layer
+ * calls at that shape use it.  Results of the layer
  * calls change only in fp32 summation order.  Uses the context's workspace,
  * runs on and SYNCHRONISES the context's stream (not for use under graph
  * capture); takes a few tens of milliseconds.
@@ -327,13 +327,14 @@ int mvla_prefill_layer_prune(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvl
 int mvla_tune_layers(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_weights* layers,
                      int n_layers, int B, int S);
 /* Record a choice by hand (e.g. one measured in an earlier run, for identical
- * summation order across runs): configuration index 0 .. 6 (256x256 on eight waves,
+ * summation order across runs): configuration index 0 .. 7 (256x256 on eight waves,
  * 256x128, 128x128 two per CU, 128x128 on eight waves, 256x256 on four waves, 192x128,
  * 288x192 on four waves; the 288x192 shape runs whole tiles only and ignores the K-split
  * threshold, the four-wave 256x256 shape hands a last round that is to be cut to a second
  * launch: in quarters to the 128x128 eight-wave kernel or along K to the 256x256 eight-wave
  * one, whichever is predicted faster; a shape whose tiles do not hold whole heads is not used for the
- * q/k/v projection, whatever is recorded) and the K-split
+ * q/k/v projection, whatever is recorded; 7: the built-in choice by size, as without a
+ * record, the threshold ignored) and the K-split
  * threshold in percent (0 never, 101 whenever the last round of tiles is not
  * full); cfg < 0 removes the record.  Host-side only, nothing is launched. */
 int mvla_set_gemm_choice(mvla_ctx* ctx, int M, int N, int K, int epilogue, int cfg, int split_pct);

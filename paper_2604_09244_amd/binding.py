@@ -461,8 +461,8 @@ class Context:
         return out
 
     def tune_layers(self, cfg: LayerCfg, structs: Sequence[LayerWeightsC], B: int, S: int):
-        """Measure the projection kernels' tile configurations at M = B*S rows and keep the
-        fastest per shape in this context (synchronises the stream)."""
+        """Measure the projection kernels' tile configurations, and the choice by size, at M = B*S rows
+        and keep the fastest per shape in this context (synchronises the stream)."""
         arr = (LayerWeightsC * len(structs))(*structs)
         _check(load().mvla_tune_layers(self._h, C.byref(cfg), arr, len(structs), B, S),
                "mvla_tune_layers")

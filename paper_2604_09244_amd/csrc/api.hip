@@ -64,14 +64,19 @@ int check_layer_args(const mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_
 
 #define GEMM_WS(ctx) (ctx)->gemm_partial, (ctx)->gemm_partial_bytes, (ctx)->counters + kCounterWords / 2, kCounterWords / 2
 
-// measured choice for this shape, or (-1, 0): let the cost model decide
+// recorded choice for this shape, or (-1, 0)
 struct GemmPick {
     int cfg, split_pct;
 };
-GemmPick gemm_pick(const mvla_ctx* ctx, int M, int N, int K, int epi) {
+GemmPick gemm_record(const mvla_ctx* ctx, int M, int N, int K, int epi) {
     for (const auto& t : ctx->tuned)
         if (t.M == M && t.N == N && t.K == K && t.epi == epi) return {t.cfg, t.split_pct};
     return {-1, 0};
+}
+// ... that its launches are to use; (-1, 0): let the cost model decide (also where that is what was recorded)
+GemmPick gemm_pick(const mvla_ctx* ctx, int M, int N, int K, int epi) {
+    const GemmPick p = gemm_record(ctx, M, N, K, epi);
+    return p.cfg < gemm_num_configs() ? p : GemmPick{-1, 0};
 }
 #define GEMM_PICK(ctx, M, N, K, epi) gemm_pick(ctx, M, N, K, epi).cfg, gemm_pick(ctx, M, N, K, epi).split_pct
 
@@ -813,13 +818,16 @@ int mvla_tune_layers(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_
     for (const Job& j : jobs) {
         float best_ms = 0.f;
         int best_cfg = -1, best_pct = 0;
-        for (int c = 0; c < gemm_num_configs() && rc == MVLA_OK; ++c)
+        // position ids of the timed q/k/v launches: the zeros of the attention buffer
+        const RopeEpilogue rope = {reinterpret_cast<const int32_t*>(lb.attn), layers[0].rope_cos,
+                                   layers[0].rope_sin, lb.vt, layers[0].rope_len, S, lb.S_pad,
+                                   D, cfg->dh};
+        // ... the configurations, and behind them the choice by size where that is none of them
+        const int by_size = gemm_num_configs();
+        const int last = gemm_choice_by_size(M, j.N, j.K, j.epi, &rope) >= by_size ? by_size : by_size - 1;
+        for (int c = 0; c <= last && rc == MVLA_OK; ++c)
             for (int sp = 0; sp < 3 && rc == MVLA_OK; ++sp) {
-                // position ids of the timed q/k/v launches: the zeros of the attention buffer
-                const RopeEpilogue rope = {reinterpret_cast<const int32_t*>(lb.attn), layers[0].rope_cos,
-                                           layers[0].rope_sin, lb.vt, layers[0].rope_len, S, lb.S_pad,
-                                           D, cfg->dh};
-                if (!gemm_config_runs(c, j.epi, &rope)) continue;
+                if (c == by_size ? sp > 0 : !gemm_config_runs(c, j.epi, &rope)) continue;
                 float ms = 0.f;
                 for (int pass = 0; pass < 2 && rc == MVLA_OK; ++pass) {   // the better of two timings
                     for (int r = (pass == 0 ? -1 : 0); r < reps; ++r) {   // r == -1: untimed first launch
@@ -862,7 +870,7 @@ int mvla_tune_layers(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_
 
 int mvla_set_gemm_choice(mvla_ctx* ctx, int M, int N, int K, int epilogue, int cfg, int split_pct) {
     if (!ctx || M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > 3) return MVLA_EINVAL;
-    if (cfg >= gemm_num_configs() || split_pct < 0 || split_pct > 101) return MVLA_EINVAL;
+    if (cfg > gemm_num_configs() || split_pct < 0 || split_pct > 101) return MVLA_EINVAL;
     for (size_t i = 0; i < ctx->tuned.size(); ++i) {
         auto& t = ctx->tuned[i];
         if (t.M == M && t.N == N && t.K == K && t.epi == epilogue) {
@@ -882,7 +890,7 @@ int mvla_set_gemm_choice(mvla_ctx* ctx, int M, int N, int K, int epilogue, int c
 int mvla_tuned_choice(mvla_ctx* ctx, int M, int N, int K, int epilogue, int* cfg_out,
                       int* split_pct_out) {
     if (!ctx || !cfg_out || !split_pct_out) return MVLA_EINVAL;
-    const GemmPick p = gemm_pick(ctx, M, N, K, epilogue);
+    const GemmPick p = gemm_record(ctx, M, N, K, epilogue);
     *cfg_out = p.cfg;
     *split_pct_out = p.split_pct;
     return MVLA_OK;

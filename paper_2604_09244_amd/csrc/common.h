@@ -145,7 +145,10 @@ int rope_pair_config(int M1, const RopeEpilogue& rope1, int M2, const RopeEpilog
 int launch_rope_pair(int cfg, const bf16_t* A1, const bf16_t* W1, int M1, void* C1, const RopeEpilogue& rope1,
                      const bf16_t* A2, const bf16_t* W2, int M2, void* C2, const RopeEpilogue& rope2, int D,
                      hipStream_t st);
+// configurations that a caller can record: 0 .. gemm_num_configs() - 1 (the number itself: the choice by size)
 int gemm_num_configs();
+// what the choice by size takes for a projection (-1: nothing runs it); others than the recordable ones too
+int gemm_choice_by_size(int M, int N, int K, int epilogue, const RopeEpilogue* rope);
 // whether tile configuration cfg can run this epilogue (the rotating one needs whole heads per tile)
 bool gemm_config_runs(int cfg, int epilogue, const RopeEpilogue* rope);
 

@@ -1676,6 +1676,12 @@ static int predict(int M, int N, int K, int epilogue, const RopeEpilogue* rope, 
     return best;
 }
 
+int gemm_choice_by_size(int M, int N, int K, int epilogue, const RopeEpilogue* rope) {
+    int split_pct = 0;
+    float us = 0.f;
+    return predict(M, N, K, epilogue, rope, &split_pct, &us);
+}
+
 // force_cfg >= 0 picks that tile configuration and force_split_pct the K-split threshold
 // (0 = never, 101 = whenever the last round is not full); force_cfg < 0, or a configuration
 // that cannot run this epilogue, leaves the choice to the cost model.

@@ -1,0 +1,61 @@
+"""Set-up measurement at row counts where the choice by size takes a tile that cannot be recorded by its own index: the
+measurement may keep that choice, launches then run its kernel, and the record can be replayed by hand."""
+import re
+from dataclasses import replace
+
+import pytest
+import torch
+
+from helpers import EPI_GATEUP, EPI_QKV, device_layer, layer_cfg
+from paper_2604_09244_amd import binding as mv
+from paper_2604_09244_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+BY_SIZE = 7
+
+
+def _fitted_epilogues(fn):
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    names = [re.search(r"fitted_tile_kernel<\d+, \d+, 64, 2, 2, \d, (\d)>", e.name) for e in prof.events()]
+    return {int(m.group(1)) for m in names if m}
+
+
+# gate/up on the best recordable configuration and on the fitted tile: 76 and 58 us, 158 and 136 us
+@pytest.mark.parametrize("B,S", [(1, 288), (4, 237)])
+def test_measurement_keeps_the_choice_by_size_where_it_is_faster(B, S):
+    wl = replace(W.WORKLOADS["single_view"], n2=S // 2, n3=S - S // 2, nt=0, B=B)
+    M, N, K = B * S, 2 * wl.F, wl.D
+    ctx = mv.Context(B, S, wl.D, wl.H, wl.F, 1)
+    packed, ws = device_layer(ctx, wl, W.layer_weights(wl, 0))
+    x, pos = W.hidden_states(wl, device="cuda")
+    cfg = layer_cfg(wl)
+    y = torch.empty_like(x)
+    assert EPI_GATEUP in _fitted_epilogues(lambda: ctx.prefill_layer(cfg, ws, x, pos, y))
+    ctx.tune_layers(cfg, [ws], B, S)
+    assert ctx.tuned_choice(M, N, K, EPI_GATEUP) == (BY_SIZE, 0)
+    assert EPI_GATEUP in _fitted_epilogues(lambda: ctx.prefill_layer(cfg, ws, x, pos, y))
+    ctx.close()
+
+
+def test_choice_by_size_recorded_by_hand():
+    wl = W.WORKLOADS["single_view"]
+    ctx = mv.Context(wl.B, wl.S, wl.D, wl.H, wl.F, wl.nt)
+    packed, ws = device_layer(ctx, wl, W.layer_weights(wl, 0))
+    x, pos = W.hidden_states(wl, device="cuda")
+    cfg, M = layer_cfg(wl), wl.B * wl.S
+    shapes = [(3 * wl.D, wl.D, 0), (wl.D, wl.D, 1), (wl.D, wl.F, 2), (2 * wl.F, wl.D, 3), (wl.D, wl.D, EPI_QKV)]
+    y, probs = ctx.prefill_layer(cfg, ws, x, pos), ctx.score_only(cfg, ws, x, pos, wl.nt)
+    for N, K, epi in shapes:
+        ctx.set_gemm_choice(M, N, K, epi, BY_SIZE, 50)
+        assert ctx.tuned_choice(M, N, K, epi) == (BY_SIZE, 50)
+        with pytest.raises(RuntimeError):
+            ctx.set_gemm_choice(M, N, K, epi, BY_SIZE + 1, 50)
+    assert torch.equal(ctx.prefill_layer(cfg, ws, x, pos), y)
+    ctx.profile_enable(None)
+    again = ctx.score_only(cfg, ws, x, pos, wl.nt)
+    launches = [name for name, _, _ in ctx.profile_read()]
+    assert torch.equal(again, probs) and launches.count("gemm_qkv") == 1, launches     # (key and query in one launch)
+    ctx.close()
