@@ -339,6 +339,86 @@ __device__ __forceinline__ int nearest_centre(double x, double c0, double c1, do
     return d2 < (one ? d1 : d0) ? 2 : (one ? 1 : 0);
 }
 
+// The clustering score by score, as in candidate_kernel, on scores that are not all finite: those of a run are no
+// difference of prefix sums (one score of -inf would make all centres NaN; here the finite ones stay objects).
+// Nothing is kept in registers for it: scores are read again, a patch's previous label is worked out again from the
+// previous centres.  The centres of the last assignment are left in c.
+template <int NT>
+__device__ __forceinline__ void cluster_scores(const float* sal_b, int P, int max_iter, double (&c)[3],
+                                               double (&sums)[3][NT / 64], uint32_t (&counts)[NT / 64]) {
+    constexpr int NW = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float lo = INFINITY, hi = -INFINITY;         // (NaN is left out)
+#pragma unroll 1
+    for (int p = tid; p < P; p += NT) {
+        const float x = sal_b[p] + sal_b[P + p];
+        lo = fminf(lo, x);
+        hi = fmaxf(hi, x);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, o));
+        hi = fmaxf(hi, __shfl_xor(hi, o));
+    }
+    if (lane == 0) {
+        sums[0][wave] = (double)lo;
+        sums[1][wave] = (double)hi;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int w = 0; w < NW; ++w) {
+        lo = fminf(lo, (float)sums[0][w]);
+        hi = fmaxf(hi, (float)sums[1][w]);
+    }
+    __syncthreads();
+    double next[3] = {(double)lo, 0.5 * ((double)lo + (double)hi), (double)hi};
+#pragma unroll 1
+    for (int it = 0; it < max_iter; ++it) {
+        double s[3] = {0.0, 0.0, 0.0};
+        uint32_t n01 = 0u;                       // patches of labels 0 and 1, 15 bits each
+        bool changed = it == 0;
+#pragma unroll 1
+        for (int p = tid; p < P; p += NT) {
+            const double x = (double)(sal_b[p] + sal_b[P + p]);
+            const int l = nearest_centre(x, next[0], next[1], next[2]);
+            if (it > 0) changed |= l != nearest_centre(x, c[0], c[1], c[2]);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) s[j] += l == j ? x : 0.0;
+            n01 += l == 0 ? 1u : (l == 1 ? 0x8000u : 0u);
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            c[j] = next[j];
+            s[j] = wave_sum_f64(s[j]);
+        }
+        n01 = wave_sum_u32(n01);
+        const bool any = __ballot(changed) != 0ull;
+        if (lane == 0) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) sums[j][wave] = s[j];
+            counts[wave] = n01 | (any ? 0x80000000u : 0u);
+        }
+        __syncthreads();
+        uint32_t n[3] = {0u, 0u, 0u}, moved = 0u;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) s[j] = 0.0;
+#pragma unroll 1
+        for (int w = 0; w < NW; ++w) {
+            const uint32_t v = counts[w];
+            n[0] += v & 0x7FFFu;
+            n[1] += (v >> 15) & 0x7FFFu;
+            moved |= v >> 31;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) s[j] += sums[j][w];
+        }
+        __syncthreads();                         // (read before the next assignment writes)
+        if (!moved) break;
+        n[2] = (uint32_t)P - n[0] - n[1];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if (n[j] > 0u) next[j] = s[j] / (double)n[j];
+    }
+}
+
 template <int NT, int E>
 __global__ __launch_bounds__(NT) void sorted_candidate_kernel(
     const float* __restrict__ x_hat /* [4,B,P] */, const float* __restrict__ sal /* [B,2P] */,
@@ -427,7 +507,13 @@ __global__ __launch_bounds__(NT) void sorted_candidate_kernel(
 
     // Lloyd iterations (Sec. 4.2), as in candidate_kernel: centres start at min, mid-range, max; stop when an
     // assignment repeats the previous one or after kmeans_max_iter assignments
-    if (wave == 0) {
+    if (!__builtin_isfinite(__uint_as_float(sorted[0])) || !__builtin_isfinite(__uint_as_float(sorted[P - 1]))) {
+        double c[3];
+        cluster_scores<NT>(sal_b, P, rules.kmeans_max_iter, c, wave_sums, counts);
+        if (tid == 0)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) centres[j] = c[j];
+    } else if (wave == 0) {
         const float* x = reinterpret_cast<const float*>(sorted);
         double c0 = (double)x[0], c2 = (double)x[P - 1], c1 = 0.5 * (c0 + c2);
         double l0 = c0, l1 = c1, l2 = c2;        // centres of the last assignment

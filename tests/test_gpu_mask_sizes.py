@@ -46,6 +46,41 @@ def test_candidate_masks_at_every_size(P, kind):
     ctx.close()
 
 
+def _labels(score, max_iter):
+    """Lloyd's iteration as the header states it, on scores that may be infinite or NaN: a patch changes centre only
+    for a smaller distance, NaN is left out of the range."""
+    x = score.astype(np.float64)
+    lo, hi = np.fmin.reduce(x, initial=np.inf), np.fmax.reduce(x, initial=-np.inf)
+    c, label = [lo, 0.5 * (lo + hi), hi], None
+    for _ in range(max_iter):
+        d = [np.abs(x - v) for v in c]
+        one = d[1] < d[0]
+        new = np.where(d[2] < np.where(one, d[1], d[0]), 2, one.astype(np.int64))
+        if label is not None and np.array_equal(new, label):
+            break
+        label = new
+        c = [x[label == j].sum() / (label == j).sum() if (label == j).any() else c[j] for j in range(3)]
+    return label
+
+
+@pytest.mark.parametrize("P", [2, 64, 65, 256, 257, 512, 1024, 2048, 4096, 8192, 8193])
+@pytest.mark.parametrize("values", [(-np.inf,), (np.inf,), (-np.inf, np.inf), (np.nan,), (-np.inf, np.nan)])
+@np.errstate(invalid="ignore")
+def test_labels_of_scores_that_are_not_finite(P, values):
+    """The header calls them invalid input; the labels are the same on both sides of the largest sorted variant."""
+    ctx = mv.Context(2, 8, 64, 4, 64, 8)
+    x_hat = W.synthetic_indicators(W.WORKLOADS["single_view"], B=2, n_patch=P, seed=P)
+    u = W.uniform_draws(replace(W.WORKLOADS["single_view"], n2=P), B=2, step=P)
+    sal = _scores("heavy", 2, P, P + 3)
+    for i, v in enumerate(values):
+        sal[0, (P // 2 + i) % P] = v             # (the second sample stays finite)
+    for n in (1, 2, 32):
+        sem = ctx.candidate_masks(x_hat.cuda(), sal.cuda(), u.cuda(), 5, mv.MaskRules.default(kmeans_max_iter=n))[2]
+        for b in range(2):
+            assert np.array_equal(sem[b].cpu().numpy(), _labels(O.patch_score(sal.numpy(), P)[b], n)), (n, b)
+    ctx.close()
+
+
 @pytest.mark.parametrize("P", [1, 32, 33, 127, 128, 129, 255, 256, 257, 511, 1023, 1024, 1025, 4095, 4096, 4097, 16384])
 def test_mask_indices_at_every_size(P):
     ctx = mv.Context(3, 8, 64, 4, 64, 8)
