@@ -525,7 +525,7 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
             run[v] = fmaxf(run[v], lg[i][v]);
         }
     }
-    __shared__ float sh_m[NW][16], sh_l[NW][16];
+    __shared__ alignas(16) float sh_m[NW][16], sh_l[NW][16];   // (written four values at a time)
 #pragma unroll
     for (int v = 0; v < 4; ++v) run[v] = row_all(run[v], [](float a, float o) { return fmaxf(a, o); });
     if (c == 0) *reinterpret_cast<float4*>(&sh_m[wave][4 * g]) = make_float4(run[0], run[1], run[2], run[3]);
