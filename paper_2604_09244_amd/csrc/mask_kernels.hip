@@ -514,8 +514,8 @@ __global__ __launch_bounds__(NT) void sorted_candidate_kernel(
 #pragma unroll
             for (int j = 0; j < 3; ++j) centres[j] = c[j];
     } else if (wave == 0) {
-        const float* x = reinterpret_cast<const float*>(sorted);
-        double c0 = (double)x[0], c2 = (double)x[P - 1], c1 = 0.5 * (c0 + c2);
+        auto x = [&](int i) __attribute__((always_inline)) { return __uint_as_float(sorted[i]); };
+        double c0 = (double)x(0), c2 = (double)x(P - 1), c1 = 0.5 * (c0 + c2);
         double l0 = c0, l1 = c1, l2 = c2;        // centres of the last assignment
         int was0 = -1, was01 = -1;               // its runs: labels 0, and 0 or 1
         for (int it = 0; it < rules.kmeans_max_iter; ++it) {
@@ -538,7 +538,7 @@ __global__ __launch_bounds__(NT) void sorted_candidate_kernel(
                 int len = (P + 63) >> 6, r0, r1;
                 {
                     const int at = min((lane + 1) * len, P) - 1;
-                    const int l = nearest_centre((double)x[at], c0, c1, c2);
+                    const int l = nearest_centre((double)x(at), c0, c1, c2);
                     const unsigned long long m0 = __ballot(l >= 1), m1 = __ballot(l == 2);
                     r0 = m0 ? (__ffsll((long long)m0) - 1) * len : P;
                     r1 = m1 ? (__ffsll((long long)m1) - 1) * len : P;
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(NT) void sorted_candidate_kernel(
                 while (len > 1) {
                     const int step = (len + 31) >> 5, from = lane < 32 ? r0 : r1;
                     const int at = min(min(from + ((lane & 31) + 1) * step, from + len), P) - 1;
-                    const int l = nearest_centre((double)x[at], c0, c1, c2);
+                    const int l = nearest_centre((double)x(at), c0, c1, c2);
                     const unsigned long long m = __ballot(lane < 32 ? l >= 1 : l == 2);
                     const uint32_t m0 = (uint32_t)m, m1 = (uint32_t)(m >> 32);
                     if (r0 < P) r0 += m0 ? (__ffs((int)m0) - 1) * step : 0;
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(NT) void sorted_candidate_kernel(
                 if (RUN > 1) {
                     float v[RUN];
 #pragma unroll
-                    for (int e = 0; e < RUN; ++e) v[e] = x[min(t * RUN + e, NT * E - 1)];
+                    for (int e = 0; e < RUN; ++e) v[e] = x(min(t * RUN + e, NT * E - 1));
 #pragma unroll
                     for (int e = 0; e < RUN; ++e) sum += t * RUN + e < end ? (double)v[e] : 0.0;
                 }

@@ -1,5 +1,6 @@
 """How the kernels' sources read and write LDS arrays (no GPU needed): one that is accessed several values at a time says
-so in its alignment.  (Dynamic LDS, declared as 16-byte words, is raw storage and left out.)"""
+so in its alignment, and none is read as another type than it was written as (the compiler may take two such
+accesses for unrelated ones).  (Dynamic LDS, declared as 16-byte words, is raw storage and left out.)"""
 import glob
 import os
 import re
@@ -35,3 +36,12 @@ def test_wide_accesses_are_aligned(path):
             element, aligned = arrays[name]
             assert WORD.get(element, element) == wide.group(1), (name, element, as_type)
             assert aligned >= int(wide.group(2)) * (8 if element == "double" else 4), (name, as_type)
+
+
+@pytest.mark.parametrize("path", sorted(glob.glob(os.path.join(CSRC, "*.hip"))), ids=os.path.basename)
+def test_no_array_is_accessed_as_another_type(path):
+    src = open(path).read()
+    arrays = lds_arrays(src)
+    for as_type, name in lds_casts(src):
+        if name in arrays and as_type not in ("uint8_t", "char"):
+            assert VECTOR.match(as_type) or as_type == arrays[name][0], (name, arrays[name][0], as_type)
