@@ -76,6 +76,20 @@ def hbm_roofline(bytes_, seconds, measured=None):
     return r
 
 
+def score_tile(B, H, S, nq, sums):
+    """Scoring queries a workgroup, by the library's own rule (score_tile_queries): column sums are written once per
+    this many rows."""
+    groups = -(-nq // 16) * H * B
+    if S <= 256:
+        return 16 if not sums or groups <= 512 or nq <= 16 else 32
+    return 16 if S <= 1024 and (groups <= 256 or nq <= 16) else 32
+
+
+def gather_writes_norm(rows, D):
+    """Whether the gather of the kept rows writes the next layer's first norm too (kGatherNormValues in api.hip)."""
+    return rows * D <= 1 << 22
+
+
 def gemm_source_hash():
     """Hash of the GEMM source without comments and layout, so that only code changes void a
     stored traffic figure."""
@@ -247,6 +261,7 @@ def main():
     prune_us = {n: 1e3 * sum(sum(v) for (nn, t), v in acc.items() if nn == n) / K for n in prune_names}
     prune_us = {n: v for n, v in prune_us.items() if v > 0}
     prune_total_us = sum(prune_us.values())
+    gather_norm = wl.L > wl.p and gather_writes_norm(M_kept, wl.D)   # (then "compact" is both)
     prune_launches = sum(len(v) for (nn, t), v in acc.items() if nn in prune_names) / K
 
     # the pruning kernels are reported against what bounds them: the bandwidth-bound ones
@@ -259,19 +274,22 @@ def main():
         return dict(bound="latency", avg_us=avg_s * 1e6, algorithmic_bytes=bytes_,
                     empty_launch_us=None if not measured else measured["empty_launch_us"])
 
+    sum_rows = -(-wl.nt // score_tile(wl.B, wl.H, wl.S, wl.nt, True))
     for sal_key in (("salience", wl.B), ("prune_fused", wl.B)):   # fused: + budget and selection
         if sal_key in acc:
-            rows = (wl.nt + 31) // 32 if otf else wl.nt     # on the fly: one row per 32-query tile
+            rows = sum_rows if otf else wl.nt     # on the fly: one row per tile of queries
             b = 4.0 * wl.B * wl.H * rows * wl.n_vis + 4.0 * wl.B * wl.n_vis
             extra[sal_key[0]] = by_size(1e-3 * sum(acc[sal_key]) / len(acc[sal_key]), b)
     sc_key = ("score_probs", M_full)
     if sc_key in acc:   # reads every key row once and the query rows, writes sums or probabilities
-        out_b = 4.0 * wl.B * wl.H * (((wl.nt + 31) // 32) * wl.n_vis if otf else wl.nt * wl.S)
+        out_b = 4.0 * wl.B * wl.H * (sum_rows * wl.n_vis if otf else wl.nt * wl.S)
         b = 2.0 * wl.B * wl.S * wl.D + 2.0 * wl.B * wl.nt * wl.D + out_b
         extra["score_probs"] = by_size(1e-3 * sum(acc[sc_key]) / len(acc[sc_key]), b)
     cmp_key = ("compact", M_kept)
     if cmp_key in acc:
         b = 2.0 * M_kept * wl.D * 2 + 12.0 * M_kept
+        if gather_norm:
+            b += 2.0 * M_kept * wl.D + 2.0 * wl.D
         extra["compact"] = by_size(1e-3 * sum(acc[cmp_key]) / len(acc[cmp_key]), b)
     for (n, t), v in acc.items():
         if n.startswith("gemm_"):
@@ -422,6 +440,7 @@ def main():
         "prune_step_us": prune_total_us,
         "prune_step_us_by_kernel": prune_us,
         "prune_step_launches": prune_launches,
+        "prune_step_includes_next_norm": gather_norm,     # in one launch with the gather, under "compact"
         "prune_step_vs_empty_launches": (None if not measured else
                                          prune_total_us / (prune_launches * measured["empty_launch_us"])),
         "prune_pct_of_pruned_prefill": 100.0 * prune_total_us * 1e-6 / sec_instr,
