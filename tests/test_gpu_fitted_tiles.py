@@ -46,6 +46,9 @@ def fitted_launches(fn):
     (1152, 18, 64, 11, 595, {EPI_OUT: 14}),
     (1792, 28, 4160, 7, 227, {EPI_QKV: 18, EPI_GATEUP: 23}),
     (1152, 18, 2816, 11, 744, {EPI_QKV: 23, EPI_OUT: 19, EPI_DOWN: 19}),
+    (1344, 21, 1600, 11, 900, {EPI_OUT: 21}),
+    (4096, 32, 1024, 8, 394, {EPI_OUT: 21}),
+    (1152, 18, 2816, 11, 1205, {EPI_OUT: 23, EPI_DOWN: 23}),
     (1344, 21, 2816, 11, 739, {EPI_OUT: 13, EPI_DOWN: 21})])
 def test_fitted_tiles(D, H, F, B, S, expect):
     wl = replace(W.WORKLOADS["tiny"], D=D, H=H, dh=D // H, F=F, n2=S // 2, n3=S - S // 2, nt=0, B=B, seed=D + S)

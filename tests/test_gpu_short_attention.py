@@ -45,6 +45,27 @@ def test_layer_with_short_attention(dh, S, limit):
     ctx.close()
 
 
+@pytest.mark.parametrize("dh,H,S", [(128, 4, 1024), (128, 4, 1025), (128, 4, 1344), (128, 4, 2047), (128, 4, 4096),
+                                    (128, 1, 8191), (64, 4, 1024), (64, 4, 1344), (64, 4, 2047), (64, 2, 4097),
+                                    (64, 1, 8191)])
+def test_long_sequences_with_few_heads(dh, H, S):
+    """Up to 64 key tiles a wave: its one stage of LDS is written and read again for each."""
+    wl = replace(W.WORKLOADS["tiny"], D=H * dh, H=H, dh=dh, F=256, n2=S // 2, n3=S - S // 2, nt=0, B=1, L=1, p=0,
+                 seed=S + dh)
+    ctx = mv.Context(1, S, wl.D, H, wl.F, 1)
+    w_cpu = W.layer_weights(wl, 0)
+    packed, ws = device_layer(ctx, wl, w_cpu)
+    x, pos = W.hidden_states(wl)
+    xd, pd = x.cuda(), pos.cuda()
+    y = ctx.prefill_layer(layer_cfg(wl), ws, xd, pd)
+    again = torch.empty_like(y)
+    names = _attention_kernels(lambda: ctx.prefill_layer(layer_cfg(wl), ws, xd, pd, again))
+    assert len(names) == 1 and "short_attention" in names[0], names
+    assert torch.equal(y, again)
+    check_layer(y[0], to64(x[0]), pos[0].numpy(), oracle_weights(w_cpu), wl, f"dh={dh} H={H} S={S}")
+    ctx.close()
+
+
 def test_up_to_one_tile_stays_with_the_long_kernel():
     wl = replace(W.WORKLOADS["tiny"], n2=32, n3=32, nt=0, seed=5)
     ctx = mv.Context(1, 64, wl.D, wl.H, wl.F, 1)
