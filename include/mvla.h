@@ -119,7 +119,7 @@ int mvla_modality_budget(mvla_ctx* ctx, const float* sal, int B, int n2, int n3,
  *           0 <= K2 <= n2, 0 <= K3 <= n3 (as mvla_modality_budget writes);
  *           rows violating this are clamped on the device.
  * kept_idx: device, int32 [B, k_total + n_text], strictly increasing per row.
- * n2, n3 <= 16384 each (segment staged in LDS), else MVLA_EUNSUPPORTED. */
+ * n2, n3 <= 16384 each, else MVLA_EUNSUPPORTED. */
 int mvla_select_topk(mvla_ctx* ctx, const float* sal, const int32_t* k2k3, int B, int n2, int n3,
                      int n_text, int k_total, int32_t* kept_idx);
 
@@ -291,7 +291,7 @@ int mvla_prefill_layer(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_laye
 /* The same layer with the scoring rows reduced on the fly (Sec. 3.2, Eq. 3):
  * instead of the probabilities it writes sal[b, j], j < n_vis, as
  * mvla_salience would from them; the [B, H, n_query_tail, S] tensor is never
- * materialised (column sums are formed per 32-query tile in registers, then
+ * materialised (column sums are formed per 16 or 32 queries in registers, then
  * reduced over heads and tiles in a fixed order).  Differs from the two-call
  * route only in summation order.  n_query_tail >= 1, 1 <= n_vis <= S.
  * sal: device fp32 [B, n_vis].  Other arguments as mvla_prefill_layer. */
@@ -483,7 +483,8 @@ int mvla_profile_read(mvla_ctx* ctx, int capacity, int32_t* ids, int32_t* tags, 
  * "attention", "gemm_o", "rmsnorm_mlp", "gemm_gateup", "gemm_down", "salience",
  * "budget", "select", "compact", "rope_table", "prune_fused", "smooth",
  * "decompose", "feature_share", "candidate_masks", "mask_indices"), "?"
- * otherwise. */
+ * otherwise.  In mvla_prefill and mvla_masked_prefill_step a "compact" of up to
+ * 4 Mi kept values writes the next layer's first norm too; no "rmsnorm" follows. */
 const char* mvla_kernel_name(int id);
 
 /* Rates the device sustains on the simplest kernels, so that a kernel's time

@@ -259,8 +259,10 @@ struct NextNorm {
     bf16_t* u;
     bool done = false;
 };
-// A short gather and the norm behind it are one launch (at 288 rows of 4096 values 2.9 + 3.0 us -> 3.1 us, 80 of 256
-// 2.4 + 2.4 -> 2.4); of a long one the copy rate is what counts, and is reported.
+// A short gather and the norm behind it are one launch, recorded as "compact" (us, two launches / one: 256 rows of 4096
+// values 5.3 / 3.4, 1024 of 4096 9.9 / 7.2, 4096 of 1024 10.1 / 6.8, 16384 of 256 14.3 / 8.0).  Above the limit, where
+// a launch is no longer most of it, the gather keeps a record of its own and its copy rate can be read off it; one
+// launch would be the faster one there too (2048 rows of 4096 16.1 / 13.0, 21504 of 4096 120.6 / 87.9).
 constexpr size_t kGatherNormValues = size_t(1) << 22;
 
 static int compact_rows(mvla_ctx* ctx, const void* h, const int32_t* pos, const int32_t* kept_idx, int B,

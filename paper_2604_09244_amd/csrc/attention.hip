@@ -524,10 +524,11 @@ static int launch_short(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_
 // (us, long chain / short chains): one per compute unit for a few tiles (S = 80: 240 6.3 / 5.5, 288 6.4 / 6.9; up to 64
 // keys there is no chain to cut, 5.0 / 5.2), from four long tiles on what is resident at once, two per compute unit
 // at dh = 128 (S = 237: 512 9.7 / 9.1, 640 10.1 / 11.6) and, once the chain is long, four at dh = 64, whose
-// workgroups take half the LDS (S = 900: 928 15.3 / 12.9; S = 448: 512 8.6 / 7.0, 896 9.0 / 9.4).  A partial third
-// round would pay too at S >= 512 (544 15.0 / 12.2, 704 17.9 / 16.8), but those are the full-sequence layers in
-// front of the scoring, whose saliences hang on a few keys: on single inputs another order of sums put them up to 1.5
-// times as far from their 64-bit values, and as often nearer (mean over 12 inputs 0.96), so these keep the long chain.
+// workgroups take half the LDS (S = 900: 928 15.3 / 12.9; S = 448: 512 8.6 / 7.0, 896 9.0 / 9.4).  From S = 512 on
+// a partial third round is faster still at dh = 128 (544 workgroups 15.0 / 12.2, 704 17.9 / 16.8): how far up has not been
+// measured, and the line stays at what is resident.  (The sums' order is no reason: over 12 inputs of a one-sample
+// call, saliences behind short chains were 0.96 times as far from their 64-bit values on average, single ones up to
+// 1.5 times either way.)
 static int short_limit(int S, int dh) {
     if (S <= ATT_KT) return 0;
     if (S <= 3 * ATT_KT) return 256;

@@ -142,9 +142,9 @@ __global__ __launch_bounds__(CM_THREADS) void candidate_kernel(
     // lower-numbered one on equal distance; a centre without points stays; stop when an
     // assignment repeats the previous one or after kmeans_max_iter assignments.
     // (One barrier an iteration.  A patch costs one LDS round trip: its score and label are asked for
-    // together, nothing in the loop is conditional, and the counts stay with the thread.  256 patches
-    // 15.0 us, 1024 28, 4096 88, 16384 253; with ballots for the counts and a branch around the label in
-    // here 18.6, 42, 158 and 490; with shuffles and four barriers an iteration 22.9, 39, 106 and 270.)
+    // together, nothing in the loop is conditional, and the counts stay with the thread.  16384 patches
+    // 253 us; with ballots for the counts and a branch around the label in here 490; with shuffles and four
+    // barriers an iteration 270.  Up to 8192 patches sorted_candidate_kernel takes the call.)
     double c0 = (double)lo, c2 = (double)hi, c1 = 0.5 * (c0 + c2);
     for (int it = 0; it < rules.kmeans_max_iter; ++it) {
         double s[3] = {0.0, 0.0, 0.0};
