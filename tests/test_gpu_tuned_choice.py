@@ -40,6 +40,21 @@ def test_measurement_keeps_the_choice_by_size_where_it_is_faster(B, S):
     ctx.close()
 
 
+def test_measurement_where_no_recordable_tile_holds_whole_heads():
+    """Five heads of 64: none of the recordable tile widths divides a q/k/v section."""
+    wl = replace(W.WORKLOADS["tiny"], D=320, H=5, dh=64, F=256, n2=50, n3=50, nt=0)
+    ctx = mv.Context(1, 100, wl.D, wl.H, wl.F, 1)
+    packed, ws = device_layer(ctx, wl, W.layer_weights(wl, 0))
+    x, pos = W.hidden_states(wl, device="cuda")
+    y = ctx.prefill_layer(layer_cfg(wl), ws, x, pos).clone()
+    ctx.tune_layers(layer_cfg(wl), [ws], 1, 100)
+    assert ctx.tuned_choice(100, 3 * wl.D, wl.D, EPI_QKV) == (BY_SIZE, 0)
+    again = ctx.prefill_layer(layer_cfg(wl), ws, x, pos)
+    # (another order of fp32 sums in the other projections: a bf16 rounding step, a little more next to zero)
+    assert torch.all((again.float() - y.float()).abs() <= 2.0 ** -7 * y.float().abs() + 4e-3 * y.float().std())
+    ctx.close()
+
+
 def test_choice_by_size_recorded_by_hand():
     wl = W.WORKLOADS["single_view"]
     ctx = mv.Context(wl.B, wl.S, wl.D, wl.H, wl.F, wl.nt)
