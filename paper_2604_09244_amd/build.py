@@ -13,6 +13,8 @@ SOURCES = ["api.hip", "prune_kernels.hip", "mask_kernels.hip", "layer_kernels.hi
            "probe_kernels.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # a wave starts with its first kernel arguments in scalar registers instead of loading them
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wno-unused-command-line-argument"]
 
 
