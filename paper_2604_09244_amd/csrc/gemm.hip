@@ -127,6 +127,11 @@ __device__ __forceinline__ int xcd_chunked(int id, int total) {
     return (id & 7) * ((total + 7) >> 3) + (id >> 3);  // may be >= total for padded ids
 }
 __device__ __forceinline__ void tile_of(int lin, int tiles_m, int tiles_n, int* tm, int* tn) {
+    if (tiles_m <= GROUP_M) {   // (one group: a division less before a short projection's first load)
+        *tn = lin / tiles_m;
+        *tm = lin - *tn * tiles_m;
+        return;
+    }
     const int group_tiles = GROUP_M * tiles_n;
     const int g = lin / group_tiles, r = lin % group_tiles;
     const int gm = min(GROUP_M, tiles_m - g * GROUP_M);
@@ -649,7 +654,7 @@ __device__ __forceinline__ void tile_body(
     // ---- which part of which tile is ours --------------------------------------------------
     int n_seg_work;   // 1 for a whole tile, up to 2 for a K-range that straddles two tiles
     int it_begin = 0, it_end = 0, sk_id = 0;
-    const bool is_dp = bid < plan.dp_grid;
+    const bool is_dp = KIND != SPLITTING || bid < plan.dp_grid;
     if (is_dp) {
         n_seg_work = xcd_chunked(bid, plan.dp_tiles) < plan.dp_tiles ? 1 : 0;
     } else {
@@ -738,6 +743,83 @@ __device__ __forceinline__ void tile_body(
 #pragma unroll
             for (int j = 0; j < GN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+        // ---- epilogue: its geometry, and what of its operands is asked for ahead of the slabs -------
+        using EG = EpiGeom<BM, BN, WM, NS, RU>;
+        constexpr int LDT = EG::LDT, PASSES = EG::PASSES, RP = EG::RP;
+        constexpr int OUT_COLS = EPI == EPI_SILU_MUL ? BN / 2 : BN;   // output columns per tile
+        const int out_n0 = EPI == EPI_SILU_MUL ? n0 / 2 : n0;
+        const int out_N = EPI == EPI_SILU_MUL ? N / 2 : N;
+        // (whole tiles that leave the LDS in one pass: position ids and the first residual rows arrive with the first slab)
+        constexpr bool EARLY = KIND != SPLITTING && PASSES == 1;
+        // q/k rotation: an item is 8 columns of a half head and their partners, BN/16 per row; QB items' table rows
+        // fly together
+        constexpr int PER_ROW = BN / 16, PER_THREAD = (RP * PER_ROW + NT - 1) / NT;
+        constexpr int QB_MAX = (GM * GN >= 32 && WM * WN >= 8) ? 2 : 4;
+        constexpr int QB = PER_THREAD < QB_MAX ? PER_THREAD : QB_MAX;
+        constexpr int NB = (RP * PER_ROW + QB * NT - 1) / (QB * NT);
+        constexpr bool PREFETCH = EPI == EPI_QKV_ROPE && QB_MAX == 4;   // (registers to spare)
+        int pos_pre[PREFETCH ? NB * QB : 1];
+        auto pos_request = [&](int t, int prow0) __attribute__((always_inline)) {
+            if (PREFETCH && (EARLY || n0 < 2 * rope.D)) {   // (early: no branch to wait behind; v tiles load them for nothing)
+#pragma unroll
+                for (int q = 0; q < NB * QB; ++q) {
+                    const int row = m0 + prow0 + min((t + q * NT) / PER_ROW, RP - 1);
+                    pos_pre[q] = rope.pos[min(row, M - 1)];
+                }
+            }
+        };
+        // Residual epilogues: an item is 4 columns of a row (16 bytes of fp32: a wave's load
+        // or store covers consecutive whole cache lines; with 8-column items a lane's two
+        // 16-byte fp32 accesses lay 32 bytes apart and a store burst of that form takes 1.4-1.8
+        // times as long).  Items go in batches of RB whose residual reads are in flight
+        // together, the first batch requested before the tile is laid down; reads and stores
+        // are unconditional buffer accesses (behind a per-item branch the compiler made each
+        // read wait for the one before it -- a memory round trip per item -- and behind
+        // conditional stores for the stores before it).
+        constexpr bool RES = EPI == EPI_RES_BF16_TO_F32 || EPI == EPI_RES_F32_TO_BF16;
+        // (register room: shapes with none to spare request after the lay-down, and fewer at a time)
+        constexpr bool TIGHT = !EARLY && ((WM * WN == 8 && BM == 256 && BN == 256) || BM == 288 ||
+                                          (WM * WN == 4 && BM == 128));
+        constexpr int IPR = OUT_COLS / 4;                                 // items per tile row
+        constexpr int RPT = (RP * IPR + NT - 1) / NT;                     // items per thread and pass
+        constexpr int RREG = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;          // registers per item
+        constexpr int RES_ES = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;        // bytes per residual element
+        constexpr int RES_MAX = (WM * WN == 8 && BM == 256 && BN == 256 ? 8 : 16) / RREG;
+        constexpr int RB = RPT < RES_MAX ? RPT : RES_MAX, RNB = (RPT + RB - 1) / RB;
+        // item k of thread t: row r of the pass and first column c4 of the tile.  Where the
+        // threads of the workgroup cover whole rows, the column is the same for every item
+        // and the row advances by a constant: no divisions, offsets by one addition.
+        constexpr bool WHOLE_ROWS = NT % IPR == 0;
+        constexpr int RSTEP = WHOLE_ROWS ? NT / IPR : 0;
+        auto item_rc = [&](int t, int k, int& r, int& c4) __attribute__((always_inline)) {
+            if (WHOLE_ROWS) {
+                r = t / IPR + k * RSTEP;
+                c4 = (t % IPR) * 4;
+            } else {
+                const int it = t + k * NT;
+                r = it / IPR;
+                c4 = (it % IPR) * 4;
+            }
+        };
+        u32x2_t rh_[RES ? RB : 1];    // bf16 residual (4 values)
+        u32x4_t rf_[RES ? RB : 1];    // fp32 residual
+        auto res_request = [&](int t, int b, int prow0) __attribute__((always_inline)) {
+            const int rows_here = min(RP, M - m0 - prow0), cols_here = min(OUT_COLS, out_N - out_n0);
+            const __amdgpu_buffer_rsrc_t r_buf = buffer_of(
+                RES ? static_cast<const char*>(Rv) + ((size_t)(m0 + prow0) * ldr + out_n0) * RES_ES : nullptr,
+                RES && rows_here > 0 ? ((rows_here - 1) * ldr + cols_here) * RES_ES : 0);
+#pragma unroll
+            for (int u = 0; u < RB; ++u) {
+                int r, c4;
+                item_rc(t, b * RB + u, r, c4);
+                const int off = (min(r, RP - 1) * ldr + c4) * RES_ES;   // (beyond the records: zeros)
+                if (EPI == EPI_RES_BF16_TO_F32)
+                    rh_[u] = __builtin_amdgcn_raw_buffer_load_b64(r_buf, off, 0, 0);
+                else
+                    rf_[u] = __builtin_amdgcn_raw_buffer_load_b128(r_buf, off, 0, 0);
+            }
+        };
+
 #define MVLA_ISSUE(KT, STG)                                                                    \
     {                                                                                          \
         const size_t koff = (size_t)min((KT), k1 - 1) * (BK * 2);                              \
@@ -788,6 +870,10 @@ __device__ __forceinline__ void tile_body(
         // stores) is outstanding any more: a wait it placed for those inside the main loop would
         // also wait for the loop's direct loads, which it does not see
         __builtin_amdgcn_s_waitcnt(0);
+        if constexpr (EARLY) {
+            pos_request(stid, 0);
+            if constexpr (RES) res_request(stid, 0, 0);
+        }
         // ---- prologue: NS-1 slabs in flight, then one more behind the first barrier ---------
 #pragma unroll
         for (int s = 0; s < NS - 1; ++s) MVLA_ISSUE(k0 + s, s)
@@ -991,9 +1077,6 @@ __device__ __forceinline__ void tile_body(
         // written), so the residual is read and the result written with one access per lane on
         // whole consecutive cache lines.  A pass covers as many tile rows as the LDS holds (a whole
         // number of wave rows); only the waves owning them write.
-        using EG = EpiGeom<BM, BN, WM, NS, RU>;
-        constexpr int LDT = EG::LDT, PASSES = EG::PASSES, RP = EG::RP;
-        constexpr int OUT_COLS = EPI == EPI_SILU_MUL ? BN / 2 : BN;   // output columns per tile
         static_assert(RP % 16 == 0, "row groups of 8 come in pairs");
         constexpr int ITEMS = RP * OUT_COLS / 8;                      // 8-column items per pass
         float* tile = reinterpret_cast<float*>(lds);
@@ -1001,25 +1084,11 @@ __device__ __forceinline__ void tile_body(
         // the compiler would otherwise put them and keep them in registers the loop needs)
         int etid = tid;
         asm volatile("" : "+v"(etid));
-        const int out_n0 = EPI == EPI_SILU_MUL ? n0 / 2 : n0;
-        const int out_N = EPI == EPI_SILU_MUL ? N / 2 : N;
         auto epilogue_pass = [&](int pass) __attribute__((always_inline)) {
             // first tile row of the pass (with overlapping wave rows the last pass starts early)
             const int prow0 = PASSES == 1 ? 0 : min(pass * TM, BM - TM);
-            // q/k rotation: the position ids of this thread's items of the pass, fetched while
-            // the tile is laid down (items: 8 columns of a half head, BN/16 per row)
-            constexpr int PER_ROW = BN / 16;
-            constexpr int QB = (GM * GN >= 32 && WM * WN >= 8) ? 2 : 4;   // items whose table rows fly together
-            constexpr int NB = (RP * PER_ROW + QB * NT - 1) / (QB * NT);
-            constexpr bool PREFETCH = EPI == EPI_QKV_ROPE && QB == 4;   // (registers to spare)
-            int pos_pre[PREFETCH ? NB * QB : 1];
-            if (PREFETCH && n0 < 2 * rope.D) {
-#pragma unroll
-                for (int q = 0; q < NB * QB; ++q) {
-                    const int row = m0 + prow0 + min((etid + q * NT) / PER_ROW, RP - 1);
-                    pos_pre[q] = rope.pos[min(row, M - 1)];
-                }
-            }
+            // (q/k rotation: the position ids of this thread's items of the pass, fetched while the tile is laid down)
+            if constexpr (!EARLY) pos_request(etid, prow0);
             // This pass's part of the output as a bounds-checked buffer (rows of the pass that
             // exist, the tile's columns that exist); offsets are relative to its first element.
             constexpr int ES = EPI == EPI_RES_BF16_TO_F32 ? 4 : 2;           // bytes per output element
@@ -1029,57 +1098,7 @@ __device__ __forceinline__ void tile_body(
             const __amdgpu_buffer_rsrc_t c_buf = buffer_of(
                 static_cast<char*>(Cv) + ((size_t)(m0 + prow0) * ldc + out_n0) * ES,
                 rows_here > 0 ? ((rows_here - 1) * ldc + cols_here) * ES : 0);
-            // Residual epilogues: an item is 4 columns of a row (16 bytes of fp32: a wave's load
-            // or store covers consecutive whole cache lines; with 8-column items a lane's two
-            // 16-byte fp32 accesses lay 32 bytes apart and a store burst of that form takes 1.4-1.8
-            // times as long).  Items go in batches of RB whose residual reads are in flight
-            // together, the first batch requested before the tile is laid down; reads and stores
-            // are unconditional buffer accesses (behind a per-item branch the compiler made each
-            // read wait for the one before it -- a memory round trip per item -- and behind
-            // conditional stores for the stores before it).
-            constexpr bool RES = EPI == EPI_RES_BF16_TO_F32 || EPI == EPI_RES_F32_TO_BF16;
-            // (register room: shapes with none to spare request after the lay-down, and fewer at a time)
-            constexpr bool TIGHT = (WM * WN == 8 && BM == 256 && BN == 256) || BM == 288 ||
-                                   (WM * WN == 4 && BM == 128);
-            constexpr int IPR = OUT_COLS / 4;                                 // items per tile row
-            constexpr int RPT = (RP * IPR + NT - 1) / NT;                     // items per thread and pass
-            constexpr int RREG = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;          // registers per item
-            constexpr int RES_ES = EPI == EPI_RES_BF16_TO_F32 ? 2 : 4;        // bytes per residual element
-            constexpr int RES_MAX = (WM * WN == 8 && BM == 256 && BN == 256 ? 8 : 16) / RREG;
-            constexpr int RB = RPT < RES_MAX ? RPT : RES_MAX, RNB = (RPT + RB - 1) / RB;
-            // item k of this thread: row r of the pass and first column c4 of the tile.  Where the
-            // threads of the workgroup cover whole rows, the column is the same for every item
-            // and the row advances by a constant: no divisions, offsets by one addition.
-            constexpr bool WHOLE_ROWS = NT % IPR == 0;
-            constexpr int RSTEP = WHOLE_ROWS ? NT / IPR : 0;
             int ftid = etid;   // (thread index as the items' second half sees it: set after the lay-down)
-            auto item_rc = [&](int t, int k, int& r, int& c4) __attribute__((always_inline)) {
-                if (WHOLE_ROWS) {
-                    r = t / IPR + k * RSTEP;
-                    c4 = (t % IPR) * 4;
-                } else {
-                    const int it = t + k * NT;
-                    r = it / IPR;
-                    c4 = (it % IPR) * 4;
-                }
-            };
-            const __amdgpu_buffer_rsrc_t r_buf = buffer_of(
-                RES ? static_cast<const char*>(Rv) + ((size_t)(m0 + prow0) * ldr + out_n0) * RES_ES : nullptr,
-                RES && rows_here > 0 ? ((rows_here - 1) * ldr + cols_here) * RES_ES : 0);
-            u32x2_t rh_[RES ? RB : 1];    // bf16 residual (4 values)
-            u32x4_t rf_[RES ? RB : 1];    // fp32 residual
-            auto res_request = [&](int b) __attribute__((always_inline)) {
-#pragma unroll
-                for (int u = 0; u < RB; ++u) {
-                    int r, c4;
-                    item_rc(etid, b * RB + u, r, c4);
-                    const int off = (min(r, RP - 1) * ldr + c4) * RES_ES;   // (beyond the records: zeros)
-                    if (EPI == EPI_RES_BF16_TO_F32)
-                        rh_[u] = __builtin_amdgcn_raw_buffer_load_b64(r_buf, off, 0, 0);
-                    else
-                        rf_[u] = __builtin_amdgcn_raw_buffer_load_b128(r_buf, off, 0, 0);
-                }
-            };
             auto res_finish = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
                 for (int u = 0; u < RB; ++u) {
@@ -1106,7 +1125,7 @@ __device__ __forceinline__ void tile_body(
                     if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                 }
             };
-            if constexpr (RES && !TIGHT) res_request(0);
+            if constexpr (RES && !TIGHT && !EARLY) res_request(etid, 0, prow0);
             __syncthreads();   // previous readers of the LDS (fragments or the last pass) are done
             if constexpr (WM * WN == 4 && GM * GN >= 54) {
                 // Accumulators in the second register file: fetched one by one (pinned there until then),
@@ -1265,11 +1284,11 @@ __device__ __forceinline__ void tile_body(
                 return;
             }
             if constexpr (RES) {
-                if constexpr (TIGHT) res_request(0);
+                if constexpr (TIGHT) res_request(etid, 0, prow0);
 #pragma unroll 1
                 for (int b = 0; b < RNB; ++b) {
                     res_finish(b);
-                    if (b + 1 < RNB) res_request(b + 1);
+                    if (b + 1 < RNB) res_request(etid, b + 1, prow0);
                 }
                 return;
             }
@@ -1318,11 +1337,30 @@ __device__ __forceinline__ void tile_body(
 // The four-wave 256x256 shape is the persistent kernel, every other one takes a workgroup per tile.
 constexpr bool is_persistent(int BM, int BN, int WM, int WN) { return BM == 256 && BN == 256 && WM * WN == 4; }
 
+// A wave starts with the first 14 words of a kernel's arguments in scalar registers.  What a tile's first loads
+// depend on stands there a second time (Rv: the residual, or the position ids of a projection that rotates): anything
+// else comes by a load of its own, and the wave waits for it.
+// Short projections are mostly this start and their end: with these arguments in front, no plan of K ranges in whole
+// tiles, the epilogue's first operands asked for ahead of the slabs and no more table rows than a thread has items,
+// the small model's pruned prefill takes 45.2 -> 44.7 us (calls of other sizes up to 5 % less),
+// one 7B layer of 237 rows 177.8 -> 174.1, the 4-layer call of 544 tokens 938 -> 926.
+template <int EPI, KernelKind KIND>
+__device__ __forceinline__ void leading_arguments(GemmPlan& plan, RopeEpilogue& rope, PairedGemm& pair, int k_tiles,
+                                                  int tiles_m, int tiles_n, int pair_block, const void* Rv) {
+    plan.tiles_m = tiles_m;
+    plan.tiles_n = tiles_n;
+    plan.k_tiles = k_tiles;
+    if (KIND != SPLITTING) plan.dp_tiles = tiles_m * tiles_n;
+    if (EPI == EPI_QKV_ROPE) rope.pos = static_cast<const int32_t*>(Rv);
+    pair.first_block = pair_block;
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
-    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
-    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int lda, int M, int N, int K, int tiles_m, int tiles_n,
+    int ldr, int pair_block, const void* __restrict__ Rv, void* __restrict__ Cv, int ldc, GemmPlan plan,
     float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, PairedGemm pair) {
+    leading_arguments<EPI, SPLITTING>(plan, rope, pair, K / BK, tiles_m, tiles_n, pair_block, Rv);
     if constexpr (is_persistent(BM, BN, WM, WN))
         persistent_body<EPI>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, rope);
     else
@@ -1335,9 +1373,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_kernel(
 // compiler moves them to the second file and back in every slab)
 template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(WM * WN * 64, 2) void small_tile_kernel(
-    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
-    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int lda, int M, int N, int K, int tiles_m, int tiles_n,
+    int ldr, int pair_block, const void* __restrict__ Rv, void* __restrict__ Cv, int ldc, GemmPlan plan,
     float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, PairedGemm pair) {
+    leading_arguments<EPI, SMALL>(plan, rope, pair, K / BK, tiles_m, tiles_n, pair_block, Rv);
     tile_body<BM, BN, BK, WM, WN, NS, EPI, SMALL>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
                                                   pair);
 }
@@ -1346,9 +1385,10 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void small_tile_kernel(
 // register file.
 template <int BM, int BN, int BK, int WM, int WN, int NS, int EPI>
 __global__ __launch_bounds__(WM * WN * 64) void fitted_tile_kernel(
-    const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ W, int M, int N, int K,
-    void* __restrict__ Cv, int ldc, const void* __restrict__ Rv, int ldr, GemmPlan plan,
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int lda, int M, int N, int K, int tiles_m, int tiles_n,
+    int ldr, int pair_block, const void* __restrict__ Rv, void* __restrict__ Cv, int ldc, GemmPlan plan,
     float* __restrict__ partial, uint32_t* __restrict__ counters, RopeEpilogue rope, PairedGemm pair) {
+    leading_arguments<EPI, FITTED>(plan, rope, pair, K / BK, tiles_m, tiles_n, pair_block, Rv);
     tile_body<BM, BN, BK, WM, WN, NS, EPI, FITTED>(A, lda, W, M, N, K, Cv, ldc, Rv, ldr, plan, partial, counters, rope,
                                                   pair);
 }
@@ -1482,8 +1522,9 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
                                                (int)lds));                                    \
             if (dev >= 0 && dev < kMaxDevices) lds_set[dev] = true;                           \
         }                                                                                     \
-        hipLaunchKernelGGL(kern, dim3(grid), block, lds, st, A, lda, W, M, N, K, C, ldc, R,   \
-                           ldr, plan, partial, counters, rope, pair);                         \
+        hipLaunchKernelGGL(kern, dim3(grid), block, lds, st, A, W, lda, M, N, K, plan.tiles_m, \
+                           plan.tiles_n, ldr, pair.first_block, epi == EPI_QKV_ROPE ? rope.pos : R, C, \
+                           ldc, plan, partial, counters, rope, pair);                         \
     } while (0)
     if (epi == EPI_QKV_ROPE) MVLA_GEMM_LAUNCH(EPI_QKV_ROPE);
     else if (epi == EPI_RES_BF16_TO_F32) MVLA_GEMM_LAUNCH(EPI_RES_BF16_TO_F32);
