@@ -324,13 +324,14 @@ __device__ __forceinline__ float half_wave_all(float x, Op op) {
     return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+constexpr int SC32_MAX = 8 * 8 * 32;       // keys that score_probs_reg_kernel holds
 // Single-pass variant for S <= NW waves * KBW key blocks * 32 keys: every wave keeps the logits
 // of its KBW key blocks in registers, so Q*K^T is computed once and the keys are read once.  AHEAD key
 // blocks are in flight (all of them for short rows: one memory round trip).
 // Bound by latency at batch 1 (one workgroup per head), by the key reads at large batches.  With two key
 // blocks in flight and row reductions through the LDS unit: S = 144 10.5 us, S = 544 17.1 us; now
 // 6.4 and 13.1 us.  (Eleven blocks a wave, for S up to 2816, spill: 868 us at B = 16, S = 2624
-// against 279 us of the two-pass kernel.)
+// against 279 us of the two-pass kernel; such rows take 16 queries a workgroup.)
 template <int DH, int NW, int KBW, int AHEAD, bool COLSUM>
 __global__ __launch_bounds__(NW * 64) void score_probs_reg_kernel(
     const bf16_t* __restrict__ q, int ldq, int q_rows /* per sample */, const bf16_t* __restrict__ k,
@@ -476,19 +477,48 @@ __global__ __launch_bounds__(NW * 64) void score_probs_reg_kernel(
 // keys of a row (which every lane does for each of its queries) are a quarter of the instructions between the
 // products.  Same scoring rows, us before / after: 32 heads of 128, 32 rows, S = 144 8.5 / 5.3, S = 544 13.0 / 8.8, S = 1024
 // 20.5 / 12.6; 4 heads of 64, 16 rows, S = 144 6.2 / 4.1.  (Sixteen waves: 10.4 us at S = 544.)
-template <int DH, int NW, int KBW, bool COLSUM>
+// Direct global -> LDS copy of 16 bytes a lane: the wave's 64 lanes land on 1 KiB from the wave-uniform LDS address.
+// (The compiler does not count it among its loads: wait_loads.)
+__device__ __forceinline__ void load_to_lds16(const void* base, uint32_t off, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base)
+                 : "memory", "m0");
+}
+// All but the last n of this wave's loads have returned (n: a constant once the loop around it is unrolled).
+__device__ __forceinline__ void wait_loads(int n) {
+    switch (n) {
+#define MVLA_WAIT(N) case N: asm volatile("s_waitcnt vmcnt(" #N ")" ::: "memory"); break;
+        MVLA_WAIT(12) MVLA_WAIT(8) MVLA_WAIT(6) MVLA_WAIT(4) MVLA_WAIT(2)
+        default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#undef MVLA_WAIT
+    }
+}
+
+// The same with 16 queries a workgroup: twice the workgroups, and a lane holds 4 instead of 16 queries of a key, so the
+// scaling, the exponentials and above all the reductions over the keys of a row (which every lane does for each of its
+// queries) are a quarter of the instructions between the products, and rows of up to 2688 keys fit the registers.
+// Bound by the key reads and the two reductions.  A key fragment that a wave takes from memory itself is 64 pieces of
+// 16 bytes on 64 different cache lines as the load path counts them; keys come to LDS as whole rows instead, every
+// wave's into a ring of its own, four blocks of 16 in flight.  us, a tile of 32 queries with the keys in two passes or
+// in registers / 16 with fragments from memory / now (32 heads of 128): S = 544, 32 rows 13.0 / 8.9 / 7.3; S = 1400 23.7 / -
+// / 16.5; S = 2500, 64 rows 103 / - / 18.6; B = 16, S = 2624, 64 rows 278 / 221 / 163.
+template <int DH, int NW, int KBW, int AHEAD, bool COLSUM>
 __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
     const bf16_t* __restrict__ q, int ldq, int q_rows /* per sample */, const bf16_t* __restrict__ k,
     int ldk, const float* __restrict__ key_bias, int S, int H, int nq, float scale,
     float* __restrict__ probs, int n_out) {
     constexpr int STEPS = DH / 32;
-    const int qt = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    extern __shared__ uint4 key_rows[];          // ring of AHEAD blocks of 16 key rows per wave
+    // (one grid axis: the tiles of a head are eight apart, on one XCD side by side, and read its keys once)
+    const int tiles = (nq + 15) / 16, pack = gridDim.x % (8 * tiles) == 0 ? 8 : 1;
+    const int qt = (int)blockIdx.x / pack % tiles;
+    const int hb = (int)blockIdx.x % pack * ((int)gridDim.x / (pack * tiles)) + (int)blockIdx.x / (pack * tiles);
+    const int b = hb / H, h = hb - b * H;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;      // key column (operand row), query rows 4g ..
     const int row0 = S - nq, qi0 = qt * 16;
-    const bf16_t* kbase = k + (size_t)b * S * ldk + h * DH + g * 8;
+    const bf16_t* kbase = k + (size_t)b * S * ldk + h * DH;
     const float* bias = key_bias ? key_bias + (size_t)b * S : nullptr;
-    uint4 qf[STEPS], kf[KBW][STEPS];
+    uint4 qf[STEPS];
     {
         const int qi = min(qi0 + c, nq - 1);
         // q holds either all S rows of a sample or only its nq scoring rows
@@ -496,16 +526,26 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) qf[st] = *reinterpret_cast<const uint4*>(src + st * 32);
     }
-    // all keys of the wave in flight (rows past the end are clamped: loaded, never used)
     float kbias[KBW];
 #pragma unroll
-    for (int i = 0; i < KBW; ++i) {
-        const int key = min((wave + NW * i) * 16 + c, S - 1);
+    for (int i = 0; i < KBW; ++i) kbias[i] = bias ? bias[min((wave + NW * i) * 16 + c, S - 1)] : 0.f;
+    // Direct loads of whole key rows: chunk ch of row r of a block lies at place ch ^ (r & 15) of the row, or, of the
+    // eight of a short row, ch ^ (r >> 1): fragment reads without bank conflicts.  (Rows past the end are clamped:
+    // loaded, never used.)
+    constexpr int CPR = DH / 8, LOADS = 16 * CPR / 64;
+    const auto place = [](int row) { return DH == 128 ? row & 15 : (row >> 1) & 7; };
+    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)key_rows) + (uint32_t)wave * (AHEAD * 16 * CPR * 16);
+    auto fetch = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-        for (int st = 0; st < STEPS; ++st)
-            kf[i][st] = *reinterpret_cast<const uint4*>(kbase + (size_t)key * ldk + st * 32);
-        kbias[i] = bias ? bias[key] : 0.f;
-    }
+        for (int l = 0; l < LOADS; ++l) {
+            const int row = (l * 64 + lane) / CPR, ch = lane % CPR ^ place(row);
+            const int key = min((wave + NW * i) * 16 + row, S - 1);
+            load_to_lds16(kbase, ((uint32_t)key * (uint32_t)ldk + (uint32_t)ch * 8u) * 2u,
+                          lds_wave + (uint32_t)((i % AHEAD) * 16 * CPR + l * 64) * 16u);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD && i < KBW; ++i) fetch(i);
     float run[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) run[v] = -INFINITY;
@@ -513,8 +553,17 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
 #pragma unroll
     for (int i = 0; i < KBW; ++i) {
         lg[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        wait_loads(min(AHEAD - 1, KBW - 1 - i) * LOADS);     // block i has landed (a wave's loads return in order)
+        uint4 kf[STEPS];
+        const uint4* rows = key_rows + ((size_t)wave * AHEAD + i % AHEAD) * 16 * CPR + c * CPR;
 #pragma unroll
-        for (int st = 0; st < STEPS; ++st) lg[i] = mfma16(qf[st], kf[i][st], lg[i]);
+        for (int st = 0; st < STEPS; ++st) kf[st] = rows[(st * 4 + g) ^ place(c)];
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) lg[i] = mfma16(qf[st], kf[st], lg[i]);
+        if (i + AHEAD < KBW) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // ... and has been read: its place is free
+            fetch(i + AHEAD);
+        }
         const int kb = wave + NW * i, key = kb * 16 + c;
         // a key up to the first scoring row is seen by every query (wave-uniform test)
         const bool all = kb * 16 + 15 <= row0 + qi0;
@@ -565,7 +614,7 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
             }
     }
     if (COLSUM) {
-        float* sums = probs + (((size_t)b * H + h) * gridDim.x + qt) * n_out;
+        float* sums = probs + ((size_t)hb * tiles + qt) * n_out;
 #pragma unroll
         for (int i = 0; i < KBW; ++i) {
             const int key = (wave + NW * i) * 16 + c;
@@ -577,28 +626,45 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
     }
 }
 
-// Where 16 queries a workgroup are the faster ones (us, 32 / 16 queries): while these workgroups fit one per compute
-// unit (B = 4, 32 rows, S = 544, 256 of them 13.9 / 10.3; twice as many 15.5 / 17.1: every workgroup reads all
-// keys); where 32 queries would be no fewer workgroups (16 rows, B = 16: 26.7 / 17.2); and for two key blocks a
-// wave (S = 256) at any number where probabilities are written (B = 16, 64 rows 35.2 / 29.3), up to 512 where their
-// sums are (8.9 / 8.6; 1024 13.2 / 14.3).  Sums of S = 544, 32 rows: 256 of them 12.2 / 8.6, 512 12.4 / 14.2.
+// Where 16 queries a workgroup are the faster ones (us, 32 / 16 queries; every workgroup reads all keys): while these
+// workgroups fit one per compute unit (S = 544, B = 4, 32 rows, 256 of them 14.1 / 9.6, S = 1000 21.6 / 10.4, S = 1840, 96
+// of them 30.0 / 19.0; S = 544, 1024 of them 27.9 / 30.3, S = 1500, 512 of them 30.7 / 41.6); where 32 queries would be no
+// fewer workgroups (16 rows, B = 16: 26.7 / 17.2); for two key blocks a wave (S = 256) at any number where probabilities
+// are written (B = 16, 64 rows 35.2 / 29.3), up to 512 where their sums are (8.9 / 8.6; 1024 13.2 / 14.3); and wherever
+// 32 queries take two passes over the keys (S > 2048: S = 2600, 512 of them 120 / 50).
+constexpr int SC16_MAX = 8 * 16 * 21;      // keys that eight waves hold
 int score_tile_queries(int B, int H, int S, int nq, bool sums) {
     const size_t groups = (size_t)((nq + 15) / 16) * H * B;
     if (S <= 8 * 16 * 2) return !sums || groups <= 512 || nq <= 16 ? 16 : 32;
-    return S <= 8 * 16 * 8 && (groups <= 256 || nq <= 16) ? 16 : 32;
+    return S <= SC16_MAX && (groups <= 256 || nq <= 16 || S > SC32_MAX) ? 16 : 32;
 }
 
 template <int DH, bool COLSUM>
-static void launch_score_rows16(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk, const float* key_bias,
+static int launch_score_rows16(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk, const float* key_bias,
                                 int B, int S, int H, int nq, float scale, float* out, int n_out, hipStream_t st) {
-    dim3 grid((nq + 15) / 16, H, B);
-#define MVLA_SCR(NW, KBW)                                                                                     \
-    hipLaunchKernelGGL((score_probs_rows16_kernel<DH, NW, KBW, COLSUM>), grid, dim3(NW * 64), 0, st, q, ldq, q_rows, \
-                       k, ldk, key_bias, S, H, nq, scale, out, n_out)
-    if (S <= 8 * 16 * 2) MVLA_SCR(8, 2);
-    else if (S <= 8 * 16 * 5) MVLA_SCR(8, 5);
-    else MVLA_SCR(8, 8);
+    dim3 grid((nq + 15) / 16 * H * B);
+    // (the limit of a kernel's LDS is raised once per device)
+#define MVLA_SCR(NW, KBW, AHEAD)                                                                              \
+    do {                                                                                                      \
+        constexpr int lds = NW * AHEAD * 16 * DH * 2;                                                         \
+        auto kern = score_probs_rows16_kernel<DH, NW, KBW, AHEAD, COLSUM>;                                    \
+        static bool lds_set[kMaxDevices] = {};                                                                \
+        int dev = 0;                                                                                          \
+        MVLA_HIP_CHECK(hipGetDevice(&dev));                                                                   \
+        if (dev < 0 || dev >= kMaxDevices || !lds_set[dev]) {                                                 \
+            MVLA_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                           \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds));             \
+            if (dev >= 0 && dev < kMaxDevices) lds_set[dev] = true;                                           \
+        }                                                                                                     \
+        hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, st, q, ldq, q_rows, k, ldk, key_bias, S, H, nq, scale, \
+                           out, n_out);                                                                       \
+    } while (0)
+    if (S <= 8 * 16 * 2) MVLA_SCR(8, 2, 2);
+    else if (S <= 8 * 16 * 5) MVLA_SCR(8, 5, 4);
+    else if (S <= 8 * 16 * 8) MVLA_SCR(8, 8, 4);
+    else MVLA_SCR(8, 21, 4);
 #undef MVLA_SCR
+    return MVLA_OK;
 }
 
 template <int DH, bool COLSUM>
@@ -621,20 +687,19 @@ static bool launch_score_reg(const bf16_t* q, int ldq, int q_rows, const bf16_t*
 }
 
 template <int DH, bool COLSUM>
-static void launch_score_dh(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk,
+static int launch_score_dh(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk,
                             const float* key_bias, int B, int S, int H, int nq, float scale,
                             float* out, int n_out, int tile, hipStream_t st) {
-    if (tile == 16) {
-        launch_score_rows16<DH, COLSUM>(q, ldq, q_rows, k, ldk, key_bias, B, S, H, nq, scale, out, n_out, st);
-        return;
-    }
+    if (tile == 16)
+        return launch_score_rows16<DH, COLSUM>(q, ldq, q_rows, k, ldk, key_bias, B, S, H, nq, scale, out, n_out, st);
     // register-resident single pass when the row fits, else two passes
     if (launch_score_reg<DH, COLSUM>(q, ldq, q_rows, k, ldk, key_bias, B, S, H, nq, scale, out, n_out,
                                      st))
-        return;
+        return MVLA_OK;
     dim3 grid((nq + 31) / 32, H, B);
     hipLaunchKernelGGL((score_probs_kernel<DH, COLSUM>), grid, dim3(SC_THREADS), 0, st, q, ldq, q_rows,
                        k, ldk, key_bias, S, H, nq, scale, out, n_out);
+    return MVLA_OK;
 }
 
 // colsum_n == 0: out = probabilities [B,H,nq,S]; colsum_n > 0: out = per-tile column sums
@@ -649,14 +714,16 @@ int launch_score_probs(const bf16_t* q, int q_row_stride, bool q_tail_only, cons
 #define MVLA_SC(DH_, CS_)                                                                       \
     launch_score_dh<DH_, CS_>(q, q_row_stride, q_rows, k, k_row_stride, key_bias, B, S, H, nq, scale, \
                               out, colsum_n, tile, st)
+    int rc;
     if (dh == 128) {
-        if (colsum_n > 0) MVLA_SC(128, true); else MVLA_SC(128, false);
+        rc = colsum_n > 0 ? MVLA_SC(128, true) : MVLA_SC(128, false);
     } else if (dh == 64) {
-        if (colsum_n > 0) MVLA_SC(64, true); else MVLA_SC(64, false);
+        rc = colsum_n > 0 ? MVLA_SC(64, true) : MVLA_SC(64, false);
     } else {
         return MVLA_EUNSUPPORTED;
     }
 #undef MVLA_SC
+    if (rc) return rc;
     MVLA_HIP_CHECK(hipGetLastError());
     return MVLA_OK;
 }

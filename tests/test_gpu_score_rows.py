@@ -47,3 +47,10 @@ def test_scoring_rows(dh, H, S, nq, B):
     mean = full[:, :, :, :S - nq].sum((1, 2)) / (H * nq)
     assert np.all(np.abs(sal - mean) <= 1.6e-5 * mean), np.max(np.abs(sal - mean) / mean)
     ctx.close()
+
+
+@pytest.mark.parametrize("dh,H", [(64, 4), (128, 2)])
+@pytest.mark.parametrize("S,nq,B", [(1027, 33, 1), (2047, 17, 2), (2049, 16, 1), (2559, 32, 1), (2688, 33, 3), (2689, 17, 1)])
+def test_long_scoring_rows(dh, H, S, nq, B):
+    """Around the last key block of the longest rows that 16 queries a workgroup take, and just beyond them."""
+    test_scoring_rows(dh, H, S, nq, B)
