@@ -82,7 +82,7 @@ def score_tile(B, H, S, nq, sums):
     groups = -(-nq // 16) * H * B
     if S <= 256:
         return 16 if not sums or groups <= 512 or nq <= 16 else 32
-    return 16 if S <= 1024 and (groups <= 256 or nq <= 16) else 32
+    return 16 if S <= 2688 and (groups <= 256 or nq <= 16 or S > 2048) else 32
 
 
 def gather_writes_norm(rows, D):
