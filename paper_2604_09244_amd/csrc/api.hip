@@ -485,13 +485,17 @@ static int run_layer(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_
           launch_gemm(lb.attn, D, static_cast<const bf16_t*>(w->wo), M, D, D, lb.x1, D, xin, D,
                       EPI_RES_BF16_TO_F32, GEMM_WS(ctx), GEMM_PICK(ctx, M, D, D, EPI_RES_BF16_TO_F32),
                       nullptr, st));
-    TIMED(ctx, KID_RMSNORM_MLP, M,
-          launch_rmsnorm_f32(lb.x1, static_cast<const bf16_t*>(w->g_mlp), M, D, cfg->rms_eps, lb.u,
-                             st));
+    // (short rows are normalised by the projection that reads them, unless a choice is recorded for it)
+    const NormedRows normed_x1 = {lb.x1, static_cast<const bf16_t*>(w->g_mlp), cfg->rms_eps};
+    const bool own_norm = gemm_pick(ctx, M, 2 * F, D, EPI_SILU_MUL).cfg < 0 && gemm_norms_rows(M, 2 * F, D, EPI_SILU_MUL);
+    if (!own_norm) {
+        TIMED(ctx, KID_RMSNORM_MLP, M,
+              launch_rmsnorm_f32(lb.x1, normed_x1.gain, M, D, cfg->rms_eps, lb.u, st));
+    }
     TIMED(ctx, KID_GEMM_GATEUP, M,
           launch_gemm(lb.u, D, static_cast<const bf16_t*>(w->w_gateup), M, 2 * F, D, lb.act, F,
                       nullptr, 0, EPI_SILU_MUL, GEMM_WS(ctx), GEMM_PICK(ctx, M, 2 * F, D, EPI_SILU_MUL),
-                      nullptr, st));
+                      nullptr, st, own_norm ? &normed_x1 : nullptr));
     TIMED(ctx, KID_GEMM_DOWN, M,
           launch_gemm(lb.act, F, static_cast<const bf16_t*>(w->w_down), M, D, F, y, D, lb.x1, D,
                       EPI_RES_F32_TO_BF16, GEMM_WS(ctx), GEMM_PICK(ctx, M, D, F, EPI_RES_F32_TO_BF16),

@@ -135,10 +135,17 @@ struct RopeEpilogue {
 size_t gemm_partial_bytes();
 // compute units of the current device (256 when it cannot be asked, e.g. no device present)
 int device_cu_count();
+// Rows of the fp32 residual stream [M, K] that a projection normalises itself (A is not read then).
+struct NormedRows {
+    const float* x;
+    const bf16_t* gain;
+    float eps;
+};
+bool gemm_norms_rows(int M, int N, int K, int epilogue);
 int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, void* C, int ldc,
                 const void* R, int ldr, int epilogue, float* partial, size_t partial_bytes,
                 uint32_t* counters, int n_counters, int force_cfg, int force_split_pct,
-                const RopeEpilogue* rope, hipStream_t st);
+                const RopeEpilogue* rope, hipStream_t st, const NormedRows* norm = nullptr);
 // Two projections onto D columns of the rotating kind (no V), K = D, in one launch: the configuration that does so
 // where it is predicted to be faster than one launch after the other (-1: it is not), and the launch.
 int rope_pair_config(int M1, const RopeEpilogue& rope1, int M2, const RopeEpilogue& rope2, int D);

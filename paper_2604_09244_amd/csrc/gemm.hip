@@ -108,6 +108,7 @@ struct GemmPlan {
     int sk_tiles;     // tiles of the last partial round, split along K
     int sk_blocks;    // workgroups sharing the sk_tiles * k_tiles iterations
     int quarter_of;   // >= 0: the dp_tiles are quarters (128x128) of the 256x256 tiles from this one on
+    float norm_eps;   // of rows that are normalised on their way in (see norms_rows)
 };
 
 // A second q/k/v-type projection in the same launch, with the same N, K and row pitches: the workgroups from
@@ -137,6 +138,17 @@ __device__ __forceinline__ void tile_of(int lin, int tiles_m, int tiles_n, int* 
     const int gm = min(GROUP_M, tiles_m - g * GROUP_M);
     *tm = g * GROUP_M + r % gm;
     *tn = r / gm;
+}
+
+// Gate/up projections of short rows on 64x64 tiles take the fp32 residual stream and normalise it themselves: a
+// workgroup's rows fit the A places of its LDS stages whole, and the launch of the norm, its output's way through
+// memory and the wait in between are gone.  Told by a negative row pitch; A is the residual, Rv the gain.
+// Bound by the chain of one row read, its sum and one slab after the other.  80 rows, D = 256, F = 1024: 4.9 us and the
+// norm's 2.5 before it -> 5.9 us; the small model's pruned prefill 44.7 -> 42.4.  Longer rows do not fit beside the
+// weights, and larger tiles have their rows from a norm of their own.
+constexpr int NORM_MAX_K = 384;   // six stages of 64
+constexpr bool norms_rows(int BM, int BN, int NS, int EPI) {
+    return EPI == EPI_SILU_MUL && BM == 64 && BN == 64 && NS * 64 >= NORM_MAX_K;
 }
 
 // The three families of tile kernels: shapes with the K-split path (recordable choices), small whole tiles, and
@@ -874,10 +886,68 @@ __device__ __forceinline__ void tile_body(
             pos_request(stid, 0);
             if constexpr (RES) res_request(stid, 0, 0);
         }
+        uint4 af0[GM], bf0[GN], af1[GM], bf1[GN];   // the two k-steps of a slab
+        const bool normed = norms_rows(BM, BN, NS, EPI) && lda < 0;
+        if constexpr (norms_rows(BM, BN, NS, EPI)) if (__builtin_expect(normed, 1)) {   // (laid out in front)
+            // ---- every slab of the tile at once: weights by direct loads, rows through the norm ------
+            // (four threads a row, every fourth chunk of 8 values each; the sum of squares over the quad)
+            constexpr int CH = NORM_MAX_K / 8 / 4;
+            const int row = stid >> 2, quad = stid & 3;
+            const float4* xr = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(A) +
+                                                               (size_t)min(m0 + row, M - 1) * K) + quad * 2;
+            const uint4* gr = static_cast<const uint4*>(Rv) + quad;
+            float4 x[CH][2];
+            uint4 gain[CH];
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (j * 32 < K) {                    // (K is a multiple of 64: all threads alike)
+                    x[j][0] = xr[j * 8];
+                    x[j][1] = xr[j * 8 + 1];
+                    gain[j] = gr[j * 4];
+                }
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (s < k1)
+#pragma unroll
+                    for (int l = A_LD; l < P; ++l) load_one(l, (size_t)s * (BK * 2), (uint32_t)s * STAGE * 16u);
+            float ss = 0.f;
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (j * 32 < K)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        ss += x[j][h].x * x[j][h].x + x[j][h].y * x[j][h].y + x[j][h].z * x[j][h].z + x[j][h].w * x[j][h].w;
+            ss += __shfl_xor(ss, 1);
+            ss += __shfl_xor(ss, 2);
+            const float scale = 1.0f / sqrtf(ss * (1.0f / (float)K) + plan.norm_eps);
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (j * 32 < K) {
+                    const float v[8] = {x[j][0].x, x[j][0].y, x[j][0].z, x[j][0].w,
+                                        x[j][1].x, x[j][1].y, x[j][1].z, x[j][1].w};
+                    const uint32_t g[4] = {gain[j].x, gain[j].y, gain[j].z, gain[j].w};
+                    uint32_t u[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        u[i] = pack_bf16x2(v[2 * i] * scale * __uint_as_float(g[i] << 16),
+                                           v[2 * i + 1] * scale * __uint_as_float(g[i] & 0xFFFF0000u));
+                    const int ch = j * 4 + quad;     // chunk of the row: slab ch / 8
+                    lds[(ch >> 3) * STAGE + row * CPR + ((ch & 7) ^ swz<CPR>(row))] = make_uint4(u[0], u[1], u[2], u[3]);
+                }
+            wait_vm<0>();
+            __syncthreads();
+            MVLA_READ_FRAGS(af0, bf0, 0, 0)
+#pragma unroll 1
+            for (int kt = 0; kt < k1; ++kt) {
+                const int next = min(kt + 1, k1 - 1);
+                MVLA_STEP(af0, bf0, 0, GM, GM + GN, af1, bf1, kt, 1, kt, kt, 0, 0)
+                MVLA_STEP(af1, bf1, 0, GM, GM + GN, af0, bf0, next, 0, kt, kt, 0, 0)
+            }
+        }
+        if (!normed) {
         // ---- prologue: NS-1 slabs in flight, then one more behind the first barrier ---------
 #pragma unroll
         for (int s = 0; s < NS - 1; ++s) MVLA_ISSUE(k0 + s, s)
-        uint4 af0[GM], bf0[GN], af1[GM], bf1[GN];   // the two k-steps of a slab
         wait_vm<(NS - 2) * P>();
         __syncthreads();
         // Three or more stages: there is always a free one, and the loads of a slab go out half in the
@@ -947,6 +1017,7 @@ __device__ __forceinline__ void tile_body(
             }
         }
         wait_vm<0>();
+        }
 #undef MVLA_ISSUE
 #undef MVLA_READ_FRAGS
 #undef MVLA_READ_ONE
@@ -1472,7 +1543,7 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
                       int ldc, const void* R, int ldr, int epi, int slots_per_cu, int sk_pct,
                       float* partial, size_t partial_bytes, uint32_t* counters, int n_counters,
                       const RopeEpilogue& rope, hipStream_t st, PlanPart part = PLAN_ALL,
-                      const PairedGemm* second = nullptr) {
+                      const PairedGemm* second = nullptr, float norm_eps = 0.f) {
     constexpr bool has_sk = KIND == SPLITTING && !(WM * WN == 4 && ((BM / 32 + WM - 1) / WM) * (BN / WN / 32) >= 15);
     const int pb = part == PLAN_QUARTERS ? 2 : 1;   // (planned on the tiles that are quartered)
     GemmPlan plan = plan_for(M, N, K, BM * pb, BN * pb, BK, device_cu_count() * slots_per_cu,
@@ -1489,6 +1560,7 @@ static int launch_cfg(const bf16_t* A, int lda, const bf16_t* W, int M, int N, i
         plan.sk_tiles = plan.sk_blocks = 0;
     }
     if (!has_sk && plan.sk_blocks > 0) return MVLA_EINVAL;
+    plan.norm_eps = norm_eps;
     int grid = plan.dp_grid + plan.sk_blocks;
     PairedGemm pair{};
     if (second) {
@@ -1723,15 +1795,21 @@ int gemm_choice_by_size(int M, int N, int K, int epilogue, const RopeEpilogue* r
     return predict(M, N, K, epilogue, rope, &split_pct, &us);
 }
 
+// Whether the choice by size normalises the rows of a gate/up projection itself (rows shorter than the limit, and the
+// tile that can is the one it takes).
+bool gemm_norms_rows(int M, int N, int K, int epilogue) {
+    return epilogue == EPI_SILU_MUL && K <= NORM_MAX_K && gemm_choice_by_size(M, N, K, epilogue, nullptr) == 8;
+}
+
 // force_cfg >= 0 picks that tile configuration and force_split_pct the K-split threshold
 // (0 = never, 101 = whenever the last round is not full); force_cfg < 0, or a configuration
 // that cannot run this epilogue, leaves the choice to the cost model.
 int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, void* C, int ldc,
                 const void* R, int ldr, int epilogue, float* partial, size_t partial_bytes,
                 uint32_t* counters, int n_counters, int force_cfg, int force_split_pct,
-                const RopeEpilogue* rope, hipStream_t st) {
+                const RopeEpilogue* rope, hipStream_t st, const NormedRows* norm) {
     if (M <= 0 || N <= 0) return MVLA_OK;
-    if (K < 64 || K % 64 != 0 || lda % 8 != 0) return MVLA_EUNSUPPORTED;
+    if (K < 64 || K % 64 != 0 || lda % 8 != 0 || (norm && !gemm_norms_rows(M, N, K, epilogue))) return MVLA_EUNSUPPORTED;
     if (epilogue == EPI_SILU_MUL && N % 64 != 0) return MVLA_EUNSUPPORTED;
     if (N % 8 != 0 || ldc % 8 != 0 || (R && ldr % 8 != 0)) return MVLA_EUNSUPPORTED;
     if (ldc > (1 << 20) || ldr > (1 << 20)) return MVLA_EUNSUPPORTED;   // (32-bit byte offsets inside a tile)
@@ -1744,6 +1822,10 @@ int launch_gemm(const bf16_t* A, int lda, const bf16_t* W, int M, int N, int K, 
         if ((N == 3 * rope->D) != (rope->vt != nullptr)) return MVLA_EINVAL;
         if (M % rope->S != 0 || rope->S_pad < rope->S || rope->S_pad % 8 != 0) return MVLA_EINVAL;
     }
+    if (norm)    // (chosen by size: see gemm_norms_rows)
+        return launch_cfg<64, 64, 64, 2, 2, 6, SMALL>(reinterpret_cast<const bf16_t*>(norm->x), -1, W, M, N, K, C, ldc,
+                                                      norm->gain, 0, epilogue, 1, 0, partial, partial_bytes, counters,
+                                                      n_counters, RopeEpilogue{}, st, PLAN_ALL, nullptr, norm->eps);
     int best = -1, split_pct = 0;
     if (force_cfg >= 0 && force_cfg < kNumCfgs && cfg_runs(kCfgs[force_cfg], epilogue, rope)) {
         best = force_cfg;

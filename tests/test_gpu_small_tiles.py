@@ -118,3 +118,24 @@ def test_every_configuration_of_the_paired_projections(D, H, B, S, nt, config):
         ref = O.score_only(to64(x[b]), pos[b].cpu().numpy(), ow, H, nt, wl.rms_eps, wl.rope_base)
         assert (abs(to64(probs[b]) - ref) <= PROBS_RTOL * abs(ref) + PROBS_ATOL).all(), f"sample {b}"
     ctx.close()
+
+
+@pytest.mark.parametrize("D,H,norms", [(64, 1, 1), (320, 5, 1), (384, 3, 1), (448, 7, 2)])
+@pytest.mark.parametrize("B,S", [(1, 1), (1, 63), (2, 33)])
+def test_rows_normalised_by_the_projection(D, H, norms, B, S):
+    """Gate/up rows of up to 384 values: one to six slabs, rows that end inside the tile, and the first length beyond."""
+    wl = replace(W.WORKLOADS["tiny"], D=D, H=H, dh=D // H, F=192, n2=S // 2, n3=S - S // 2, nt=0, B=B, seed=D + S)
+    ctx = mv.Context(B, S, D, H, 192, 0)
+    w_cpu = W.layer_weights(wl, 0)
+    packed, struct = device_layer(ctx, wl, w_cpu)
+    x, pos = W.hidden_states(wl, device="cuda")
+    y = ctx.prefill_layer(layer_cfg(wl), struct, x, pos)
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        ctx.prefill_layer(layer_cfg(wl), struct, x, pos)
+        torch.cuda.synchronize()
+    assert sum("rmsnorm" in e.name for e in prof.events()) == norms
+    for b in range(B):
+        ref = O.decoder_layer(to64(x[b]), pos[b].cpu().numpy(), oracle_weights(w_cpu), H, wl.rms_eps, wl.rope_base)[0]
+        assert_layer_close(y[b], ref, f"D={D} B={B} S={S} sample {b}", D)
+    ctx.close()
