@@ -524,15 +524,18 @@ static int launch_short(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_
 // (us, long chain / short chains): one per compute unit for a few tiles (S = 80: 240 6.3 / 5.5, 288 6.4 / 6.9; up to 64
 // keys there is no chain to cut, 5.0 / 5.2), from four long tiles on what is resident at once, two per compute unit
 // at dh = 128 (S = 237: 512 9.7 / 9.1, 640 10.1 / 11.6) and, once the chain is long, four at dh = 64, whose
-// workgroups take half the LDS (S = 900: 928 15.3 / 12.9; S = 448: 512 8.6 / 7.0, 896 9.0 / 9.4).  From S = 512 on
-// a partial third round is faster still at dh = 128 (544 workgroups 15.0 / 12.2, 704 17.9 / 16.8): how far up has not been
-// measured, and the line stays at what is resident.  (The sums' order is no reason: over 12 inputs of a one-sample
-// call, saliences behind short chains were 0.96 times as far from their 64-bit values on average, single ones up to
-// 1.5 times either way.)
+// workgroups take half the LDS (S = 900: 928 15.3 / 12.9; S = 448: 512 8.6 / 7.0, 896 9.0 / 9.4).  Longer chains pay
+// for a partial third round of short ones too: dh = 128, 544 workgroups at S = 544 15.5 / 13.3, 608 at S = 600 18.0 / 15.9, 704
+// at S = 704 21.5 / 18.3 (but 832 at S = 400 15.2 / 17.2, and 832 of eight heads at S = 832 21.9 / 24.4), 704 at S = 1400
+// 33.1 / 23.1, 912 at S = 1800 42.0 / 34.6; dh = 64, 1280 at S = 640 17.2 / 16.2, at S = 1000 24.6 / 20.2.  (The sums'
+// order is no reason: over 12 inputs of a one-sample call, saliences behind short chains were 0.96 times as far from
+// their 64-bit values on average, single ones up to 1.5 times either way.)
 static int short_limit(int S, int dh) {
     if (S <= ATT_KT) return 0;
     if (S <= 3 * ATT_KT) return 256;
-    return dh == 64 && S >= 512 ? 1024 : 512;
+    if (S < 512) return 512;
+    if (dh == 64) return S < 640 ? 1024 : 1280;
+    return S >= 1400 ? 912 : S < 704 ? S : 704;
 }
 
 int launch_attention(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad,

@@ -74,3 +74,23 @@ def test_up_to_one_tile_stays_with_the_long_kernel():
     names = _attention_kernels(lambda: ctx.prefill_layer(layer_cfg(wl), ws, x, pos))
     assert len(names) == 1 and "short_attention" not in names[0], names
     ctx.close()
+
+
+@pytest.mark.parametrize("dh,H,S,limit", [(128, 4, 544, 544), (128, 8, 703, 703), (128, 4, 900, 704), (128, 4, 1400, 912),
+                                          (64, 4, 639, 1024), (64, 4, 640, 1280)])
+def test_limit_of_long_chains(dh, H, S, limit):
+    """The last batch that takes short chains and the first that does not, where the limit grows with the length."""
+    most = limit // (H * ((S + 31) // 32))
+    wl = replace(W.WORKLOADS["tiny"], D=H * dh, H=H, dh=dh, F=256, n2=S // 2, n3=S - S // 2, nt=0, B=most + 1, L=1, p=0,
+                 seed=S + dh)
+    ctx = mv.Context(wl.B, S, wl.D, H, wl.F, 1)
+    w_cpu = W.layer_weights(wl, 0)
+    packed, ws = device_layer(ctx, wl, w_cpu)
+    x, pos = W.hidden_states(wl)
+    for B in (most, most + 1):
+        xb, pb = x[:B].contiguous().cuda(), pos[:B].contiguous().cuda()
+        y = ctx.prefill_layer(layer_cfg(wl), ws, xb, pb)
+        names = _attention_kernels(lambda: ctx.prefill_layer(layer_cfg(wl), ws, xb, pb, y))
+        assert len(names) == 1 and ("short_attention" in names[0]) == (B <= most), names
+        check_layer(y[B - 1], to64(x[B - 1]), pos[B - 1].numpy(), oracle_weights(w_cpu), wl, f"dh={dh} B={B} S={S}")
+    ctx.close()
