@@ -38,7 +38,17 @@ __global__ __launch_bounds__(FS_THREADS) void feature_share_kernel(
     const int half = threadIdx.x >> 7, t = threadIdx.x & 127;
     const uint4* row = feat + ((size_t)b * S + (half ? n_patch + p : p)) * row_vec;
     float s = 0.f;
-    for (int c = t; c < row_vec; c += FS_THREADS / 2) s += abs_sum8(row[c]);
+    // (four chunks in flight together: one by one, each was a memory round trip; 2 x 256 rows of 4096 values, B = 4,
+    // 4.7 -> 4.1 us)
+    int c = t;
+    for (; c + 3 * (FS_THREADS / 2) < row_vec; c += 4 * (FS_THREADS / 2)) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = row[c + u * (FS_THREADS / 2)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += abs_sum8(v[u]);
+    }
+    for (; c < row_vec; c += FS_THREADS / 2) s += abs_sum8(row[c]);
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
