@@ -498,9 +498,13 @@ __device__ __forceinline__ void wait_loads(int n) {
 // queries) are a quarter of the instructions between the products, and rows of up to 2688 keys fit the registers.
 // Bound by the key reads and the two reductions.  A key fragment that a wave takes from memory itself is 64 pieces of
 // 16 bytes on 64 different cache lines as the load path counts them; keys come to LDS as whole rows instead, every
-// wave's into a ring of its own, four blocks of 16 in flight.  us, a tile of 32 queries with the keys in two passes or
-// in registers / 16 with fragments from memory / now (32 heads of 128): S = 544, 32 rows 13.0 / 8.9 / 7.3; S = 1400 23.7 / -
+// wave's into a ring of its own of AHEAD blocks of 16.  us, a tile of 32 queries with the keys in two passes or
+// in registers / 16 with fragments from memory / now (32 heads of 128): S = 544, 32 rows 13.0 / 8.9 / 6.6; S = 1400 23.7 / -
 // / 16.5; S = 2500, 64 rows 103 / - / 18.6; B = 16, S = 2624, 64 rows 278 / 221 / 163.
+// A ring leaves room for a second workgroup per compute unit: with four blocks (128 KiB at DH = 128) one scoring tile of 16
+// rows took, us, fragments / four blocks / two, S = 300, 512 workgroups 12.0 / 15.3 / 11.8, S = 544, 1024 of them
+// 25.0 / 35.3 / 26.9, and fewer workgroups lose nothing (S = 1000, 64 of them 11.9 / 8.0 / 7.6).  (At 64-wide heads the
+// keys of 256 tokens fit whole.)
 template <int DH, int NW, int KBW, int AHEAD, bool COLSUM>
 __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
     const bf16_t* __restrict__ q, int ldq, int q_rows /* per sample */, const bf16_t* __restrict__ k,
@@ -659,9 +663,10 @@ static int launch_score_rows16(const bf16_t* q, int ldq, int q_rows, const bf16_
         hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, st, q, ldq, q_rows, k, ldk, key_bias, S, H, nq, scale, \
                            out, n_out);                                                                       \
     } while (0)
-    if (S <= 8 * 16 * 2) MVLA_SCR(8, 2, 2);
-    else if (S <= 8 * 16 * 5) MVLA_SCR(8, 5, 4);
-    else if (S <= 8 * 16 * 8) MVLA_SCR(8, 8, 4);
+    // (rings of up to 64 KiB, two workgroups per compute unit; the longest rows hold the registers of one)
+    if (S <= 8 * 16 * 2) MVLA_SCR(8, 2, (DH == 128 ? 1 : 2));
+    else if (S <= 8 * 16 * 5) MVLA_SCR(8, 5, 2);
+    else if (S <= 8 * 16 * 8) MVLA_SCR(8, 8, 2);
     else MVLA_SCR(8, 21, 4);
 #undef MVLA_SCR
     return MVLA_OK;

@@ -203,3 +203,18 @@ def test_decomposition_workgroups_fit_their_rows(tmp_path):
     assert {int(re.search(r"decompose_kernelILi(\d+)E", n).group(1)) for n in k} == {256, 512, 1024}
     for name, v in k.items():
         assert v["ScratchSize"] == 0, (name, v)
+
+
+def test_scoring_rings_leave_room_for_a_second_workgroup():
+    """Key rings of score_probs_rows16_kernel (waves x blocks ahead x 16 rows of 128 values, as its launch spells them) for
+    rows of up to 1024 keys: one that takes most of a compute unit's 160 KiB of LDS halves what is resident, and a
+    launch of more workgroups than compute units takes up to 1.5 times as long."""
+    src = open(os.path.join(CSRC, "layer_kernels.hip")).read()
+    src = src[src.index("static int launch_score_rows16("):]
+    src = src[:src.index("#undef MVLA_SCR")]
+    assert "lds = NW * AHEAD * 16 * DH * 2;" in src
+    rings = re.findall(r"MVLA_SCR\((\d+), (\d+), \(?(?:DH == 128 \? )?(\d+)(?: : \d+\))?\);", src)
+    assert len(rings) == src.count("MVLA_SCR(") - 1
+    for waves, blocks, ahead in ((int(a), int(b), int(c)) for a, b, c in rings):
+        if waves * blocks * 16 <= 1024:
+            assert 2 * waves * ahead * 16 * 128 * 2 <= 160 * 1024 - 2 * 4096, (waves, blocks, ahead)
