@@ -512,11 +512,17 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
     float* __restrict__ probs, int n_out) {
     constexpr int STEPS = DH / 32;
     extern __shared__ uint4 key_rows[];          // ring of AHEAD blocks of 16 key rows per wave
-    // (one grid axis: the tiles of a head are eight apart, on one XCD side by side, and read its keys once)
-    const int tiles = (nq + 15) / 16, pack = gridDim.x % (8 * tiles) == 0 ? 8 : 1;
-    const int qt = (int)blockIdx.x / pack % tiles;
-    const int hb = (int)blockIdx.x % pack * ((int)gridDim.x / (pack * tiles)) + (int)blockIdx.x / (pack * tiles);
-    const int b = hb / H, h = hb - b * H;
+    // (heads and samples are the grid's axes, or there is one axis: the tiles of a head are eight apart, on one XCD side by
+    // side, and read its keys once)
+    const int tiles = (nq + 15) / 16;
+    int qt = 0, b = blockIdx.y, h = blockIdx.x;
+    if ((int)gridDim.x != H) {
+        const int pack = gridDim.x % (8 * tiles) == 0 ? 8 : 1;
+        qt = (int)blockIdx.x / pack % tiles;
+        const int hb = (int)blockIdx.x % pack * ((int)gridDim.x / (pack * tiles)) + (int)blockIdx.x / (pack * tiles);
+        b = hb / H;
+        h = hb - b * H;
+    }
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;      // key column (operand row), query rows 4g ..
     const int row0 = S - nq, qi0 = qt * 16;
@@ -618,7 +624,7 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
             }
     }
     if (COLSUM) {
-        float* sums = probs + ((size_t)hb * tiles + qt) * n_out;
+        float* sums = probs + (((size_t)b * H + h) * tiles + qt) * n_out;
 #pragma unroll
         for (int i = 0; i < KBW; ++i) {
             const int key = (wave + NW * i) * 16 + c;
@@ -637,8 +643,14 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
 // are written (B = 16, 64 rows 35.2 / 29.3), up to 512 where their sums are (8.9 / 8.6; 1024 13.2 / 14.3); and wherever
 // 32 queries take two passes over the keys (S > 2048: S = 2600, 512 of them 120 / 50).
 constexpr int SC16_MAX = 8 * 16 * 21;      // keys that eight waves hold
+constexpr size_t SC16_GROUPS = ((size_t)1 << 32) / 512 - 1;   // workgroups of 512 threads that one grid axis holds
+// One tile of queries has no keys to share: heads and samples are the grid's axes, and the workgroups run in the order of the
+// key rows (us, one axis with its divisions / two: 32 heads of 128, S = 144, 256 workgroups 5.2 / 4.8, S = 544, 1024 of them
+// 26.9 / 25.8; 16 heads of 64, S = 544, 1024 of them 18.1 / 15.9).
+static bool score_axes(int B, int nq) { return nq <= 16 && B <= 65535; }
 int score_tile_queries(int B, int H, int S, int nq, bool sums) {
     const size_t groups = (size_t)((nq + 15) / 16) * H * B;
+    if (!score_axes(B, nq) && groups > SC16_GROUPS) return 32;
     if (S <= 8 * 16 * 2) return !sums || groups <= 512 || nq <= 16 ? 16 : 32;
     return S <= SC16_MAX && (groups <= 256 || nq <= 16 || S > SC32_MAX) ? 16 : 32;
 }
@@ -646,7 +658,7 @@ int score_tile_queries(int B, int H, int S, int nq, bool sums) {
 template <int DH, bool COLSUM>
 static int launch_score_rows16(const bf16_t* q, int ldq, int q_rows, const bf16_t* k, int ldk, const float* key_bias,
                                 int B, int S, int H, int nq, float scale, float* out, int n_out, hipStream_t st) {
-    dim3 grid((nq + 15) / 16 * H * B);
+    const dim3 grid = score_axes(B, nq) ? dim3(H, B) : dim3((nq + 15) / 16 * H * B);
     // (the limit of a kernel's LDS is raised once per device)
 #define MVLA_SCR(NW, KBW, AHEAD)                                                                              \
     do {                                                                                                      \

@@ -1,6 +1,7 @@
 """Compile-time properties the launch configurations rely on (no GPU needed): the projection
 kernels must not spill to scratch, and the shapes that are meant to run two workgroups per CU
 must leave room for them (registers per wave, both register files counted)."""
+import ctypes
 import os
 import re
 import shutil
@@ -218,3 +219,15 @@ def test_scoring_rings_leave_room_for_a_second_workgroup():
     for waves, blocks, ahead in ((int(a), int(b), int(c)) for a, b, c in rings):
         if waves * blocks * 16 <= 1024:
             assert 2 * waves * ahead * 16 * 128 * 2 <= 160 * 1024 - 2 * 4096, (waves, blocks, ahead)
+
+
+def test_scoring_tiles_that_one_grid_axis_cannot_hold():
+    """Workgroups of 512 threads on one grid axis: fewer than 2^32 threads.  Beyond, 32 queries a workgroup take the
+    launch (three axes); one tile of queries has an axis for the heads and one for the samples."""
+    from paper_2604_09244_amd import binding as mv
+    tile = getattr(mv.load(), "_ZN4mvla18score_tile_queriesEiiiib")
+    tile.argtypes, tile.restype = [ctypes.c_int] * 4 + [ctypes.c_bool], ctypes.c_int
+    assert tile(65535, 64, 17, 17, False) == 16              # 2^23 - 128 workgroups
+    assert tile(65535, 65, 17, 17, False) == 32
+    assert tile(1 << 16, 128, 16, 16, False) == 32           # (more samples than the second axis holds)
+    assert tile(65535, 128, 16, 16, False) == tile(65535, 128, 300, 16, True) == 16
