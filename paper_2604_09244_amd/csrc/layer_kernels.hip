@@ -504,7 +504,9 @@ __device__ __forceinline__ void wait_loads(int n) {
 // A ring leaves room for a second workgroup per compute unit: with four blocks (128 KiB at DH = 128) one scoring tile of 16
 // rows took, us, fragments / four blocks / two, S = 300, 512 workgroups 12.0 / 15.3 / 11.8, S = 544, 1024 of them
 // 25.0 / 35.3 / 26.9, and fewer workgroups lose nothing (S = 1000, 64 of them 11.9 / 8.0 / 7.6).  (At 64-wide heads the
-// keys of 256 tokens fit whole.)
+// keys of 256 tokens fit whole.)  A block of clamped rows costs as much as one of keys: rows of up to 128 take one a wave
+// (us, fragments / two blocks / one, S = 80, 64 rows of 4 heads of 64, 1024 workgroups 8.0 / 8.7 / 7.5; 32 heads of 128, 32
+// workgroups 5.0 / 5.0 / 4.1, 2048 of them 18.8 / 18.0 / 15.5).
 template <int DH, int NW, int KBW, int AHEAD, bool COLSUM>
 __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
     const bf16_t* __restrict__ q, int ldq, int q_rows /* per sample */, const bf16_t* __restrict__ k,
@@ -676,7 +678,8 @@ static int launch_score_rows16(const bf16_t* q, int ldq, int q_rows, const bf16_
                            out, n_out);                                                                       \
     } while (0)
     // (rings of up to 64 KiB, two workgroups per compute unit; the longest rows hold the registers of one)
-    if (S <= 8 * 16 * 2) MVLA_SCR(8, 2, (DH == 128 ? 1 : 2));
+    if (S <= 8 * 16) MVLA_SCR(8, 1, 1);
+    else if (S <= 8 * 16 * 2) MVLA_SCR(8, 2, (DH == 128 ? 1 : 2));
     else if (S <= 8 * 16 * 5) MVLA_SCR(8, 5, 2);
     else if (S <= 8 * 16 * 8) MVLA_SCR(8, 8, 2);
     else MVLA_SCR(8, 21, 4);

@@ -1,6 +1,7 @@
 """Scoring with 16 queries a workgroup: probabilities and on-the-fly salience against the oracle at key counts around
 the edges of its three row lengths and of a key block, at query counts around one and two tiles, with and without a
 scoring bias, and at batches on both sides of the number of workgroups up to which it is taken."""
+import re
 from dataclasses import replace
 
 import numpy as np
@@ -54,3 +55,21 @@ def test_scoring_rows(dh, H, S, nq, B):
 def test_long_scoring_rows(dh, H, S, nq, B):
     """Around the last key block of the longest rows that 16 queries a workgroup take, and just beyond them."""
     test_scoring_rows(dh, H, S, nq, B)
+
+
+@pytest.mark.parametrize("dh,H", [(64, 4), (128, 2)])
+@pytest.mark.parametrize("S,nq,B", [(17, 16, 3), (80, 33, 2), (112, 16, 1), (127, 17, 2), (128, 1, 2), (128, 64, 1), (129, 16, 2)])
+def test_short_scoring_rows(dh, H, S, nq, B):
+    """Up to 128 keys a wave has one block of them and no second one to fetch."""
+    test_scoring_rows(dh, H, S, nq, B)
+    wl = replace(W.WORKLOADS["tiny"], D=H * dh, H=H, dh=dh, F=256, n2=S - nq, n3=0, nt=nq, B=B, L=1, p=0)
+    ctx = mv.Context(B, S, wl.D, H, wl.F, nq)
+    packed, ws = device_layer(ctx, wl, W.layer_weights(wl, 0))
+    x, pos = W.hidden_states(wl, device="cuda")
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        ctx.score_only(layer_cfg(wl), ws, x, pos, nq)
+        torch.cuda.synchronize()
+    (blocks,) = [int(m.group(1)) for e in prof.events() for m in [re.search(r"rows16_kernel<\d+, 8, (\d+)", e.name)] if m]
+    assert blocks == (1 if S <= 128 else 2)
+    ctx.close()
