@@ -520,22 +520,34 @@ static int launch_short(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_
                            ldqkv, vt, S_pad, S, H, DH, out, ldo, st);
 }
 
-// Workgroups of 32 queries up to which short_attention_kernel is the faster one, measured on both sides of each line
-// (us, long chain / short chains): one per compute unit for a few tiles (S = 80: 240 6.3 / 5.5, 288 6.4 / 6.9; up to 64
-// keys there is no chain to cut, 5.0 / 5.2), from four long tiles on what is resident at once, two per compute unit
-// at dh = 128 (S = 237: 512 9.7 / 9.1, 640 10.1 / 11.6) and, once the chain is long, four at dh = 64, whose
-// workgroups take half the LDS (S = 900: 928 15.3 / 12.9; S = 448: 512 8.6 / 7.0, 896 9.0 / 9.4).  Longer chains pay
-// for a partial third round of short ones too: dh = 128, 544 workgroups at S = 544 15.5 / 13.3, 608 at S = 600 18.0 / 15.9, 704
-// at S = 704 21.5 / 18.3 (but 832 at S = 400 15.2 / 17.2, and 832 of eight heads at S = 832 21.9 / 24.4), 704 at S = 1400
-// 33.1 / 23.1, 912 at S = 1800 42.0 / 34.6; dh = 64, 1280 at S = 640 17.2 / 16.2, at S = 1000 24.6 / 20.2.  (The sums'
-// order is no reason: over 12 inputs of a one-sample call, saliences behind short chains were 0.96 times as far from
-// their 64-bit values on average, single ones up to 1.5 times either way.)
-static int short_limit(int S, int dh) {
+// Workgroups of 32 queries up to which short_attention_kernel is the faster one (us, long chain / short chains): one per
+// compute unit for a few tiles (S = 80: 240 6.3 / 5.5, 288 6.4 / 6.9; up to 64 keys there is no chain to cut, 5.0 / 5.2),
+// from four long tiles on what is resident at once, two per compute unit at dh = 128 (S = 237: 512 9.7 / 9.1, 640
+// 10.1 / 11.6) and, once the chain is long, four at dh = 64, whose workgroups take half the LDS (S = 900: 928 15.3 / 12.9;
+// S = 448: 512 8.6 / 7.0, 896 9.0 / 9.4).
+// Longer chains pay for a partial third round of short ones too, while it is made of the ends of a sample: a
+// sample's tiles go out longest first, the samples one after the other, so few samples end in short tiles and many
+// in the long tiles of the last ones.  dh = 128, within 32 workgroups a tile of keys (32 heads of one sample, at any length):
+//   up to 3 samples up to 1024: 32 heads S = 545 576 14.9 / 13.7, S = 600 608 16.6 / 14.1, S = 705 736 18.8 / 17.4, S = 1000 1024
+//     24.9 / 23.2, S = 1200 1216 29.5 / 31.3 (16 heads of 3 samples, 48 a tile: S = 700 1056 20.0 / 21.2)
+//   up to 7 up to 700: 6 samples S = 880 672 22.1 / 20.0; 7 samples S = 760 672 19.9 / 19.8, S = 900 812 22.5 / 24.0; 4 samples
+//     S = 760 768 19.8 / 20.4
+//   up to 16 up to 544: 16 samples S = 528 544 15.3 / 14.7, S = 620 640 17.5 / 18.1; 8 samples S = 704 704 18.2 / 19.0
+//   more up to what is resident: 32 samples S = 512 512 15.0 / 15.0, S = 560 576 15.7 / 18.2
+// and from S = 1400 on 912 of up to 8 samples (S = 1800, 4 samples 39.3 / 39.2; 5 samples S = 1600 1000 36.6 / 36.8), 704 of
+// more (S = 1400, 16 samples 704 32.0 / 29.3, 20 samples 880 32.7 / 34.5).  dh = 64 from S = 640 on: 1280 (8 samples S = 640
+// 14.4 / 13.4, S = 704 1408 14.9 / 15.2; 16 samples S = 640 16.5 / 15.2) unless the samples are many (28 of them S = 672 1176
+// 14.8 / 16.1, 56 S = 640 1120 15.3 / 16.5).
+// (The sums' order is no reason: attention outputs behind short chains are 0.96 to 0.99 times as far from their
+// 64-bit values over 24 inputs of 544 to 1400 tokens.)
+static int short_limit(int B, int S, int dh) {
     if (S <= ATT_KT) return 0;
     if (S <= 3 * ATT_KT) return 256;
     if (S < 512) return 512;
-    if (dh == 64) return S < 640 ? 1024 : 1280;
-    return S >= 1400 ? 912 : S < 704 ? S : 704;
+    if (dh == 64) return S < 640 || B > 24 ? 1024 : 1280;
+    if (S >= 1400) return B <= 3 ? 1024 : B <= 8 ? 912 : 704;
+    const int most = B <= 3 ? 1024 : B <= 7 ? 700 : B <= 16 ? 544 : 512, per_tile = 32 * ((S + 31) / 32);
+    return per_tile < most ? per_tile : most;
 }
 
 int launch_attention(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* vt, int S_pad,
@@ -545,7 +557,7 @@ int launch_attention(const bf16_t* q, const bf16_t* k, int ldqkv, const bf16_t* 
     // per-lane byte offsets inside one sample's keys / one head's V^T are 32-bit (kept below 2^31)
     if ((size_t)S * ldqkv * 2 >= ((size_t)1 << 31) || (size_t)dh * S_pad * 2 >= ((size_t)1 << 31))
         return MVLA_EUNSUPPORTED;
-    if ((size_t)B * H * ((S + 31) / 32) <= (size_t)short_limit(S, dh)) {
+    if ((size_t)B * H * ((S + 31) / 32) <= (size_t)short_limit(B, S, dh)) {
         if (dh == 128) return launch_short<128, 4>(q, k, ldqkv, vt, S_pad, B, S, H, out, ldo, st);
         if (dh == 64) return launch_short<64, 4>(q, k, ldqkv, vt, S_pad, B, S, H, out, ldo, st);
     }

@@ -94,3 +94,26 @@ def test_limit_of_long_chains(dh, H, S, limit):
         assert len(names) == 1 and ("short_attention" in names[0]) == (B <= most), names
         check_layer(y[B - 1], to64(x[B - 1]), pos[B - 1].numpy(), oracle_weights(w_cpu), wl, f"dh={dh} B={B} S={S}")
     ctx.close()
+
+
+@pytest.mark.parametrize("dh,H,B,S,short", [
+    (128, 32, 1, 543, True), (128, 32, 1, 545, True), (128, 32, 1, 600, True), (128, 32, 1, 703, True),
+    (128, 32, 1, 705, True), (128, 32, 1, 1024, True), (128, 32, 1, 1025, False), (128, 11, 3, 600, False),
+    (128, 8, 4, 672, True), (128, 8, 4, 673, False), (128, 4, 7, 800, True), (128, 4, 7, 801, False),
+    (128, 2, 16, 543, True), (128, 2, 16, 545, False), (128, 1, 30, 544, True), (128, 1, 32, 544, False),
+    (128, 1, 16, 1408, True), (128, 1, 16, 1409, False), (64, 1, 24, 1696, True), (64, 1, 24, 1697, False),
+    (64, 1, 25, 1280, True), (64, 1, 25, 1281, False)])
+def test_limit_counts_tiles_and_samples(dh, H, B, S, short):
+    """Lengths of one number of tiles go the same way, and the limit falls with the number of samples."""
+    wl = replace(W.WORKLOADS["tiny"], D=H * dh, H=H, dh=dh, F=64, n2=S // 2, n3=S - S // 2, nt=0, B=B, L=1, p=0, seed=S + dh)
+    ctx = mv.Context(B, S, wl.D, H, wl.F, 1)
+    w_cpu = W.layer_weights(wl, 0)
+    packed, ws = device_layer(ctx, wl, w_cpu)
+    x, pos = W.hidden_states(wl)
+    xd, pd = x.cuda(), pos.cuda()
+    y = ctx.prefill_layer(layer_cfg(wl), ws, xd, pd)
+    names = _attention_kernels(lambda: ctx.prefill_layer(layer_cfg(wl), ws, xd, pd, y))
+    assert len(names) == 1 and ("short_attention" in names[0]) == short, names
+    if H <= 4:
+        check_layer(y[B - 1], to64(x[B - 1]), pos[B - 1].numpy(), oracle_weights(w_cpu), wl, f"dh={dh} H={H} B={B} S={S}")
+    ctx.close()
