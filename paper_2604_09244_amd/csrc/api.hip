@@ -831,6 +831,8 @@ int mvla_tune_layers(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_
         // ... the configurations, and behind them the choice by size where that is none of them
         const int by_size = gemm_num_configs();
         const int last = gemm_choice_by_size(M, j.N, j.K, j.epi, &rope) >= by_size ? by_size : by_size - 1;
+        // (where that one normalises its rows itself, the others are timed with the norm that they need in front)
+        const bool own_norm = gemm_norms_rows(M, j.N, j.K, j.epi);
         for (int c = 0; c <= last && rc == MVLA_OK; ++c)
             for (int sp = 0; sp < 3 && rc == MVLA_OK; ++sp) {
                 if (c == by_size ? sp > 0 : !gemm_config_runs(c, j.epi, &rope)) continue;
@@ -841,10 +843,15 @@ int mvla_tune_layers(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvla_layer_
                         const mvla_layer_weights& w = layers[(r + n_layers) % n_layers];
                         const void* wt = j.which == 0 ? w.wqkv : j.which == 1 ? w.wo
                                          : j.which == 2 ? w.w_gateup : w.w_down;
-                        const int lrc = launch_gemm(j.A, j.lda, static_cast<const bf16_t*>(wt), M, j.N,
-                                                    j.K, j.C, j.ldc, j.R, j.ldr, j.epi, GEMM_WS(ctx), c,
-                                                    kSplitChoices[sp],
-                                                    j.epi == EPI_QKV_ROPE ? &rope : nullptr, st);
+                        const NormedRows rows = {lb.x1, static_cast<const bf16_t*>(w.g_mlp), cfg->rms_eps};
+                        int lrc = MVLA_OK;
+                        if (own_norm && c != by_size)
+                            lrc = launch_rmsnorm_f32(rows.x, rows.gain, M, D, rows.eps, lb.u, st);
+                        if (!lrc)
+                            lrc = launch_gemm(j.A, j.lda, static_cast<const bf16_t*>(wt), M, j.N,
+                                              j.K, j.C, j.ldc, j.R, j.ldr, j.epi, GEMM_WS(ctx), c,
+                                              kSplitChoices[sp], j.epi == EPI_QKV_ROPE ? &rope : nullptr, st,
+                                              own_norm && c == by_size ? &rows : nullptr);
                         if (lrc) rc = lrc;   // (configurations that cannot run were skipped above)
                     }
                     float t = 0.f;

@@ -74,3 +74,28 @@ def test_choice_by_size_recorded_by_hand():
     launches = [name for name, _, _ in ctx.profile_read()]
     assert torch.equal(again, probs) and launches.count("gemm_qkv") == 1, launches     # (key and query in one launch)
     ctx.close()
+
+
+@pytest.mark.parametrize("S", [80, 400])
+def test_measurement_counts_the_norm_that_a_choice_needs(S):
+    """Gate/up rows of up to 384 values: the choice by size normalises them itself, any other needs the norm's launch, and
+    is timed with it.  Whatever is kept, the layer's output is the same but for the order of fp32 sums."""
+    wl = replace(W.WORKLOADS["tiny"], n2=S // 2, n3=S - S // 2, nt=0)
+    ctx = mv.Context(1, S, wl.D, wl.H, wl.F, 1)
+    packed, ws = device_layer(ctx, wl, W.layer_weights(wl, 0))
+    x, pos = W.hidden_states(wl, device="cuda")
+    cfg = layer_cfg(wl)
+    y = ctx.prefill_layer(cfg, ws, x, pos).clone()
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        ctx.tune_layers(cfg, [ws], 1, S)
+        torch.cuda.synchronize()
+    names = [e.name for e in sorted(prof.events(), key=lambda e: e.time_range.start) if "mvla::" in e.name]
+    gateup = [i for i, n in enumerate(names) if re.search(r"(gemm_kernel|tile_kernel)<.*, 3>", n)]
+    own = [i for i in gateup if "small_tile_kernel<64, 64," in names[i]]
+    assert own and len(own) < len(gateup)
+    for i in gateup:
+        assert ("rmsnorm" in names[i - 1]) == (i not in own), (names[i - 1], names[i])
+    again = ctx.prefill_layer(cfg, ws, x, pos)
+    assert torch.all((again.float() - y.float()).abs() <= 2.0 ** -7 * y.float().abs() + 4e-3 * y.float().std())
+    ctx.close()
