@@ -39,6 +39,14 @@ def test_score_tile(B, S, nq, sums):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,S,nq", [(17, 2048, 64), (17, 2049, 64), (17, 2688, 64), (17, 2689, 64), (1, 2689, 16)])
+@pytest.mark.parametrize("sums", [True, False])
+def test_score_tile_of_many_workgroups(B, S, nq, sums):
+    """Two lines that a number of workgroups up to one per compute unit does not show: what 32 queries keep in registers
+    (2048 keys), and what 16 do (2688)."""
+    test_score_tile(B, S, nq, sums)
+
+
 @pytest.mark.parametrize("D,K", [(256, 33), (4096, 1021), (4096, 1022)])
 def test_gather_writes_norm(D, K):
     wl = replace(W.WORKLOADS["tiny"], D=D, H=D // 128, dh=128, F=64, n2=600, n3=500, nt=3, B=1, L=1, p=0)

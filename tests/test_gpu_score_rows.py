@@ -1,5 +1,5 @@
 """Scoring with 16 queries a workgroup: probabilities and on-the-fly salience against the oracle at key counts around
-the edges of its three row lengths and of a key block, at query counts around one and two tiles, with and without a
+the edges of its five row lengths and of a key block, at query counts around one and two tiles, with and without a
 scoring bias, and at batches on both sides of the number of workgroups up to which it is taken."""
 import re
 from dataclasses import replace
@@ -72,4 +72,23 @@ def test_short_scoring_rows(dh, H, S, nq, B):
         torch.cuda.synchronize()
     (blocks,) = [int(m.group(1)) for e in prof.events() for m in [re.search(r"rows16_kernel<\d+, 8, (\d+)", e.name)] if m]
     assert blocks == (1 if S <= 128 else 2)
+    ctx.close()
+
+
+@pytest.mark.parametrize("dh,H", [(64, 4), (128, 2)])
+@pytest.mark.parametrize("S,nq,B", [(2689, 33, 3), (2720, 64, 2)])
+def test_two_passes_over_the_keys(dh, H, S, nq, B):
+    """Beyond 2688 keys, with several samples and tiles of 32 queries (the offsets of both)."""
+    test_scoring_rows(dh, H, S, nq, B)
+    wl = replace(W.WORKLOADS["tiny"], D=H * dh, H=H, dh=dh, F=256, n2=S - nq, n3=0, nt=nq, B=B, L=1, p=0)
+    ctx = mv.Context(B, S, wl.D, H, wl.F, nq)
+    packed, ws = device_layer(ctx, wl, W.layer_weights(wl, 0))
+    x, pos = W.hidden_states(wl, device="cuda")
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        ctx.score_only(layer_cfg(wl), ws, x, pos, nq)
+        ctx.prefill_layer_salience(layer_cfg(wl), ws, x, pos, nq, S - nq)
+        torch.cuda.synchronize()
+    names = [e.name for e in prof.events() if "mvla::score_probs" in e.name]
+    assert len(names) == 2 and all("score_probs_kernel<" in n for n in names), names
     ctx.close()

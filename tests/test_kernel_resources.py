@@ -9,6 +9,8 @@ import subprocess
 
 import pytest
 
+from paper_2604_09244_amd.build import FLAGS   # (what ships is what is looked at)
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2604_09244_amd", "csrc")
 PROJECTION_KERNEL = "_ZN4mvla(?:11gemm|17small_tile)_kernelI"
@@ -18,8 +20,7 @@ def _resource_usage(src):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
-    cmd = [hipcc, "-O3", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
-           "-packed-fp32-ops", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-c",
+    cmd = [hipcc, *FLAGS, "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-c",
            os.path.join(CSRC, src), "-o", os.devnull, "-Rpass-analysis=kernel-resource-usage"]
     out = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
     assert out.returncode == 0, out.stderr[-2000:]
@@ -66,8 +67,7 @@ def _device_assembly(src, tmp_path):
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
     out_s = os.path.join(str(tmp_path), src + ".s")
-    cmd = [hipcc, "-O3", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
-           "-packed-fp32-ops", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-S",
+    cmd = [hipcc, *FLAGS, "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-S",
            "--cuda-device-only", os.path.join(CSRC, src), "-o", out_s]
     out = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
     assert out.returncode == 0, out.stderr[-2000:]
@@ -231,3 +231,27 @@ def test_scoring_tiles_that_one_grid_axis_cannot_hold():
     assert tile(65535, 65, 17, 17, False) == 32
     assert tile(1 << 16, 128, 16, 16, False) == 32           # (more samples than the second axis holds)
     assert tile(65535, 128, 16, 16, False) == tile(65535, 128, 300, 16, True) == 16
+
+
+def test_no_compiler_wait_behind_the_first_key_block_of_the_scoring_rings(tmp_path):
+    """score_probs_rows16_kernel: the query fragments are the compiler's own loads, asked for ahead of the ring, so its waits
+    for them (at the first block of keys) count the ring too.  From the second block on a wait of its own would drain the
+    ring once per block: there must be none."""
+    lines = _device_assembly("layer_kernels.hip", tmp_path)
+    starts = [i for i, l in enumerate(lines) if re.match(r"^_ZN4mvla25score_probs_rows16_kernelI.*:", l)]
+    assert len(starts) == 20                                  # 5 row lengths x 2 head sizes x 2 outputs
+    for a, b in zip(starts, starts[1:] + [len(lines)]):
+        dh, blocks = (int(x) for x in re.search(r"ILi(\d+)ELi8ELi(\d+)E", lines[a]).groups())
+        seg = lines[a:b]
+        seg = seg[:next(i for i, l in enumerate(seg) if "s_endpgm" in l)]
+        products = [i for i, l in enumerate(seg) if "v_mfma" in l]
+        assert len(products) == blocks * dh // 32 and sum("global_load_lds" in l for l in seg) == blocks * dh // 32
+        in_asm, waits = False, []
+        for l in seg[products[dh // 32 - 1] + 1:products[-1]]:
+            if "ASMSTART" in l:
+                in_asm = True
+            elif "ASMEND" in l:
+                in_asm = False
+            elif not in_asm and "s_waitcnt" in l and "vmcnt" in l:
+                waits.append(l.strip())
+        assert not waits, (lines[a], waits)
