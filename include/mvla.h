@@ -319,7 +319,8 @@ int mvla_prefill_layer_prune(mvla_ctx* ctx, const mvla_layer_cfg* cfg, const mvl
  * the four projections of a layer at M = B*S rows on this device, cycling
  * through the n_layers weight sets so that weights come from HBM as in real
  * use, and records the fastest per shape in the context (7: the choice by size); later layer
- * calls at that shape use it.  Results of the layer
+ * calls at that shape use it.  (Where the choice by size normalises the gate/up
+ * projection's rows itself, the others are timed with the norm that they need.)  Results of the layer
  * calls change only in fp32 summation order.  Uses the context's workspace,
  * runs on and SYNCHRONISES the context's stream (not for use under graph
  * capture); takes a few tens of milliseconds.
@@ -484,7 +485,9 @@ int mvla_profile_read(mvla_ctx* ctx, int capacity, int32_t* ids, int32_t* tags, 
  * "budget", "select", "compact", "rope_table", "prune_fused", "smooth",
  * "decompose", "feature_share", "candidate_masks", "mask_indices"), "?"
  * otherwise.  In mvla_prefill and mvla_masked_prefill_step a "compact" of up to
- * 4 Mi kept values writes the next layer's first norm too; no "rmsnorm" follows. */
+ * 4 Mi kept values writes the next layer's first norm too; no "rmsnorm" follows.
+ * Rows of up to 384 values may be normalised by the gate/up projection itself (as the
+ * choice by size has it): no "rmsnorm_mlp" then, its time is in "gemm_gateup". */
 const char* mvla_kernel_name(int id);
 
 /* Rates the device sustains on the simplest kernels, so that a kernel's time

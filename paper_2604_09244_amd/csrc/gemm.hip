@@ -143,9 +143,11 @@ __device__ __forceinline__ void tile_of(int lin, int tiles_m, int tiles_n, int* 
 // Gate/up projections of short rows on 64x64 tiles take the fp32 residual stream and normalise it themselves: a
 // workgroup's rows fit the A places of its LDS stages whole, and the launch of the norm, its output's way through
 // memory and the wait in between are gone.  Told by a negative row pitch; A is the residual, Rv the gain.
-// Bound by the chain of one row read, its sum and one slab after the other.  80 rows, D = 256, F = 1024: 4.9 us and the
-// norm's 2.5 before it -> 5.9 us; the small model's pruned prefill 44.7 -> 42.4.  Longer rows do not fit beside the
-// weights, and larger tiles have their rows from a norm of their own.
+// Bound by the chain of one row read, its sum and one slab after the other.  us, norm and projection / this, back to
+// back in a graph: D = 256, F = 1024, 80 rows 6.1 / 5.2, 237 6.2 / 5.3, 512 6.4 / 5.6 (where the choice by size leaves the tile);
+// D = 64, F = 256, 2048 rows 6.2 / 4.1; D = 384, F = 1024, 80 rows 6.3 / 6.1, F = 1536, 300 rows 6.6 / 6.7.  The small model's
+// pruned prefill 44.7 -> 42.4.  Longer rows do not fit beside the weights, and larger tiles have their rows from a norm
+// of their own.
 constexpr int NORM_MAX_K = 384;   // six stages of 64
 constexpr bool norms_rows(int BM, int BN, int NS, int EPI) {
     return EPI == EPI_SILU_MUL && BM == 64 && BN == 64 && NS * 64 >= NORM_MAX_K;
@@ -1413,8 +1415,8 @@ constexpr bool is_persistent(int BM, int BN, int WM, int WN) { return BM == 256 
 // else comes by a load of its own, and the wave waits for it.
 // Short projections are mostly this start and their end: with these arguments in front, no plan of K ranges in whole
 // tiles, the epilogue's first operands asked for ahead of the slabs and no more table rows than a thread has items,
-// the small model's pruned prefill takes 45.2 -> 44.7 us (calls of other sizes up to 5 % less),
-// one 7B layer of 237 rows 177.8 -> 174.1, the 4-layer call of 544 tokens 938 -> 926.
+// the small model's pruned prefill takes 45.2 -> 44.7 us, one 7B layer of 237 rows 177.8 -> 174.1, the 4-layer call of
+// 544 tokens 938 -> 926.
 template <int EPI, KernelKind KIND>
 __device__ __forceinline__ void leading_arguments(GemmPlan& plan, RopeEpilogue& rope, PairedGemm& pair, int k_tiles,
                                                   int tiles_m, int tiles_n, int pair_block, const void* Rv) {

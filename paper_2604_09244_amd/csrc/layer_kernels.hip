@@ -472,13 +472,9 @@ __global__ __launch_bounds__(NW * 64) void score_probs_reg_kernel(
     }
 }
 
-// The same with 16 queries a workgroup, for launches that leave most of the chip idle: twice the workgroups, and a
-// lane holds 4 instead of 16 queries of a key, so the scaling, the exponentials and above all the reductions over the
-// keys of a row (which every lane does for each of its queries) are a quarter of the instructions between the
-// products.  Same scoring rows, us before / after: 32 heads of 128, 32 rows, S = 144 8.5 / 5.3, S = 544 13.0 / 8.8, S = 1024
-// 20.5 / 12.6; 4 heads of 64, 16 rows, S = 144 6.2 / 4.1.  (Sixteen waves: 10.4 us at S = 544.)
 // Direct global -> LDS copy of 16 bytes a lane: the wave's 64 lanes land on 1 KiB from the wave-uniform LDS address.
-// (The compiler does not count it among its loads: wait_loads.)
+// (The compiler does not count it among its loads: wait_loads.  A wait of its own, for loads asked for before these,
+// takes them for none and so waits for them too.)
 __device__ __forceinline__ void load_to_lds16(const void* base, uint32_t off, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base)
                  : "memory", "m0");
@@ -493,12 +489,13 @@ __device__ __forceinline__ void wait_loads(int n) {
     }
 }
 
-// The same with 16 queries a workgroup: twice the workgroups, and a lane holds 4 instead of 16 queries of a key, so the
+// As score_probs_reg_kernel with 16 queries a workgroup: twice the workgroups, and a lane holds 4 instead of 16 queries of a key, so the
 // scaling, the exponentials and above all the reductions over the keys of a row (which every lane does for each of its
 // queries) are a quarter of the instructions between the products, and rows of up to 2688 keys fit the registers.
 // Bound by the key reads and the two reductions.  A key fragment that a wave takes from memory itself is 64 pieces of
 // 16 bytes on 64 different cache lines as the load path counts them; keys come to LDS as whole rows instead, every
-// wave's into a ring of its own of AHEAD blocks of 16.  us, a tile of 32 queries with the keys in two passes or
+// wave's into a ring of its own of AHEAD blocks of 16 (the first AHEAD land together: the wait for the queries, asked for in
+// front of them, counts them).  us, a tile of 32 queries with the keys in two passes or
 // in registers / 16 with fragments from memory / now (32 heads of 128): S = 544, 32 rows 13.0 / 8.9 / 6.6; S = 1400 23.7 / -
 // / 16.5; S = 2500, 64 rows 103 / - / 18.6; B = 16, S = 2624, 64 rows 278 / 221 / 163.
 // A ring leaves room for a second workgroup per compute unit: with four blocks (128 KiB at DH = 128) one scoring tile of 16
@@ -638,12 +635,14 @@ __global__ __launch_bounds__(NW * 64) void score_probs_rows16_kernel(
     }
 }
 
-// Where 16 queries a workgroup are the faster ones (us, 32 / 16 queries; every workgroup reads all keys): while these
-// workgroups fit one per compute unit (S = 544, B = 4, 32 rows, 256 of them 14.1 / 9.6, S = 1000 21.6 / 10.4, S = 1840, 96
-// of them 30.0 / 19.0; S = 544, 1024 of them 27.9 / 30.3, S = 1500, 512 of them 30.7 / 41.6); where 32 queries would be no
-// fewer workgroups (16 rows, B = 16: 26.7 / 17.2); for two key blocks a wave (S = 256) at any number where probabilities
-// are written (B = 16, 64 rows 35.2 / 29.3), up to 512 where their sums are (8.9 / 8.6; 1024 13.2 / 14.3); and wherever
-// 32 queries take two passes over the keys (S > 2048: S = 2600, 512 of them 120 / 50).
+// Where 16 queries a workgroup are the faster ones (us, 32 / 16 queries, 32 heads of 128, probabilities; every workgroup
+// reads all keys): while these workgroups fit one per compute unit (S = 544, B = 4, 32 rows, 256 of them 14.0 / 7.8, S = 1000
+// 21.6 / 11.8, S = 1840, 96 of them 28.7 / 16.0; S = 1500, 512 of them 31.2 / 39.8); where 32 queries would be no fewer
+// workgroups (16 rows, B = 16: S = 544 27.1 / 17.0, S = 1025 43.6 / 42.8); for two key blocks a wave
+// (S = 256) at any number where probabilities are written (B = 16, 64 rows 41.4 / 20.0), up to 512 where their sums are
+// (9.2 / 7.1), whose number doubles; and wherever 32 queries take two passes over the keys (S > 2048: S = 2600, 512 of
+// them 101 / 46).  (The lines at 256 and 512 date from rings of four blocks; with two there is room beyond them: S = 544, 512
+// workgroups 15.9 / 13.9, sums of S = 256, 1024 of them 13.1 / 10.8.)
 constexpr int SC16_MAX = 8 * 16 * 21;      // keys that eight waves hold
 constexpr size_t SC16_GROUPS = ((size_t)1 << 32) / 512 - 1;   // workgroups of 512 threads that one grid axis holds
 // One tile of queries has no keys to share: heads and samples are the grid's axes, and the workgroups run in the order of the
