@@ -489,8 +489,8 @@ __device__ __forceinline__ void wait_loads(int n) {
     }
 }
 
-// As score_probs_reg_kernel with 16 queries a workgroup: twice the workgroups, and a lane holds 4 instead of 16 queries of a key, so the
-// scaling, the exponentials and above all the reductions over the keys of a row (which every lane does for each of its
+// As score_probs_reg_kernel with 16 queries a workgroup: twice the workgroups, and a lane holds 4 instead of 16 queries of
+// a key, so the scaling, the exponentials and above all the reductions over the keys of a row (which every lane does for each of its
 // queries) are a quarter of the instructions between the products, and rows of up to 2688 keys fit the registers.
 // Bound by the key reads and the two reductions.  A key fragment that a wave takes from memory itself is 64 pieces of
 // 16 bytes on 64 different cache lines as the load path counts them; keys come to LDS as whole rows instead, every
